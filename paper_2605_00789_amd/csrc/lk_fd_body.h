@@ -166,29 +166,146 @@ __device__ __forceinline__ void fd_partial_body(const FdArgs &g, int block_id, c
   }
 }
 
-// One workgroup per 32 A rows.  Phase 1: squared norms of the block's rows and of its window's columns
-// into LDS.  Phase 2: thread (row group t/32, column lane t%32) sweeps 4 rows x the column tiles; all
-// loads of the partial slices are issued together (the slice loop is unrolled), the sum order is fixed.
 constexpr int FD_MAX_KSPLIT = 16;
 
+// Sum of one partial value over the slices, in slice order (fp64).
 __device__ __forceinline__ double sum_slices(const float *p, int64_t ks_stride, int ksplit) {
   // every load is unconditional (surplus slices re-read the last one and are dropped afterwards): the
   // compiler then issues all of them before the first wait instead of one load per branch
   float v[FD_MAX_KSPLIT];
 #pragma unroll
   for (int ks = 0; ks < FD_MAX_KSPLIT; ++ks) v[ks] = p[(ks < ksplit ? ks : ksplit - 1) * ks_stride];
-#pragma unroll
-  for (int ks = 0; ks < FD_MAX_KSPLIT; ++ks) v[ks] = (ks < ksplit) ? v[ks] : 0.f;
   double s = 0.0;
 #pragma unroll
-  for (int ks = 0; ks < FD_MAX_KSPLIT; ++ks) s += (double)v[ks];
+  for (int ks = 0; ks < FD_MAX_KSPLIT; ++ks) s += (ks < ksplit) ? (double)v[ks] : 0.0;
   return s;
+}
+// The same for four neighbouring values: the loads (16 bytes each, all in flight together) and the sums are separate
+// calls, so that other loads can be issued between them.
+__device__ __forceinline__ void load_slices4(const float *p, int64_t ks_stride, int ksplit, f32x4 (&v)[FD_MAX_KSPLIT]) {
+#pragma unroll
+  for (int ks = 0; ks < FD_MAX_KSPLIT; ++ks) v[ks] = *reinterpret_cast<const f32x4 *>(p + (ks < ksplit ? ks : ksplit - 1) * ks_stride);
+}
+__device__ __forceinline__ void sum_slices4(const f32x4 (&v)[FD_MAX_KSPLIT], int ksplit, double (&dot)[4]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) dot[j] = 0.0;
+#pragma unroll
+  for (int ks = 0; ks < FD_MAX_KSPLIT; ++ks) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) dot[j] += (ks < ksplit) ? (double)v[ks][j] : 0.0;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Windows of more than 64 tokens: best edge of every A node from the partial tiles.  TPR = 8 * min(column tiles, 4)
+// threads share an A row, each takes four neighbouring columns of every TPR/8-th column tile: the slices of up to
+// 128 columns of a row are one round trip (with eight threads a row, 64 to 255 columns were 2 to 8 trips in a row:
+// 16 us for a window of 387 tokens).  A workgroup covers FD_THREADS / TPR rows.  The squared norms of the window's
+// columns go to LDS; their loads and those of the first products are in flight together.
+constexpr int FD_EPILOGUE_LDS = (FD_MAX_COLS + 32) * (int)sizeof(double);
+__host__ __device__ __forceinline__ int fd_epilogue_tpr_shift(int group, int nt) {   // log2 of TPR
+  return group > 1 || nt == 1 ? 3 : (nt == 2 ? 4 : 5);
+}
+__host__ __device__ __forceinline__ int fd_epilogue_blocks(int n_rowblocks, int group, int nt) {
+  return n_rowblocks << (fd_epilogue_tpr_shift(group, nt) - 3);
+}
+
+__device__ __forceinline__ void fd_epilogue_body(const FdArgs &g, int block_id, char *lds) {
+  double *nb2 = reinterpret_cast<double *>(lds);          // [FD_MAX_COLS]
+  double *na2 = nb2 + FD_MAX_COLS;                        // [32]
+  const int64_t ks_stride = (int64_t)g.n_tiles * FD_TILE_FLOATS;
+  const int per = g.mt * g.nt;
+  const int tsh = fd_epilogue_tpr_shift(g.group, g.nt);
+  const int parts = 1 << (tsh - 3);                       // workgroups per 32-row block
+  const int rb = block_id / parts;
+  const int row_in_block = (block_id - rb * parts) * (FD_THREADS >> tsh) + ((int)threadIdx.x >> tsh);   // 0..31
+  const int sub = (int)threadIdx.x & ((1 << tsh) - 1);
+
+  int tile_row0;            // tile holding the dots of (this row block, column tile 0)
+  int tile_col0;            // tile holding |b|^2 of column tile 0
+  int w_single = 0, m_single = 0;
+  if (g.group > 1) {
+    tile_row0 = tile_col0 = rb;
+  } else {
+    w_single = rb / g.mt;
+    m_single = rb - w_single * g.mt;
+    tile_row0 = w_single * per + m_single * g.nt;
+    tile_col0 = w_single * per;
+  }
+  const int ncol_tiles = (g.group > 1) ? 1 : g.nt;
+  const int t_step = parts;                               // column tiles one sweep of a row's threads covers
+  const float *prow = g.partial + (int64_t)tile_row0 * FD_TILE_FLOATS + row_in_block * 32 + (sub & 7) * 4;
+  // (a column tile past the window's: clamped, its values are dropped below)
+  auto tile_at = [&](int t) { return prow + (int64_t)(t < ncol_tiles ? t : ncol_tiles - 1) * FD_TILE_FLOATS; };
+  f32x4 v[FD_MAX_KSPLIT];
+  load_slices4(tile_at(sub >> 3), ks_stride, g.ksplit, v);
+  for (int c = threadIdx.x; c < ncol_tiles * 32 + 32; c += FD_THREADS) {
+    if (c < ncol_tiles * 32)
+      nb2[c] = sum_slices(g.partial + (int64_t)(tile_col0 + (c >> 5)) * FD_TILE_FLOATS + 32 * 32 + 32 + (c & 31),
+                          ks_stride, g.ksplit);
+    else
+      na2[c - ncol_tiles * 32] = sum_slices(g.partial + (int64_t)tile_row0 * FD_TILE_FLOATS + 32 * 32 + (c - ncol_tiles * 32),
+                                            ks_stride, g.ksplit);
+  }
+  const int col_cap = (g.group > 1) ? g.slot : g.nt * 32;   // columns this launch really tiled
+  WinInfo wi;
+  int l, col_base;   // local A position; first tile column of this row's window
+  if (g.group > 1) {
+    const int s = row_in_block / g.slot;
+    l = row_in_block - s * g.slot;
+    wi = win_info(g, rb * g.group + s);
+    col_base = s * g.slot;
+  } else {
+    wi = win_info(g, w_single);
+    l = m_single * 32 + row_in_block;
+    col_base = 0;
+  }
+  const bool a_valid = l < wi.nA;
+  const int nB = wi.nB < col_cap ? wi.nB : col_cap;
+  // the token of this row (and of the B node at the same position): the loads travel with the others
+  const int a_tok = a_valid ? checked_token(g, wi.off + pos_a(l, g.dir)) : -1;
+  const int b_tok = l < wi.nB ? checked_token(g, wi.off + pos_b(l, g.dir)) : -1;
+  __syncthreads();
+  double best = __longlong_as_double(0x7ff0000000000000ll);   // +inf
+  int best_c = 0x7fffffff;
+  const double a2 = na2[row_in_block];
+  for (int t0 = 0; t0 < ncol_tiles; t0 += t_step) {   // uniform
+    const int t = t0 + (sub >> 3);
+    double dot[4];
+    sum_slices4(v, g.ksplit, dot);
+    if (t0 + t_step < ncol_tiles) load_slices4(tile_at(t + t_step), ks_stride, g.ksplit, v);
+    const int tc0 = t * 32 + (sub & 7) * 4;   // first of this thread's columns inside the block's tile row
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int c = tc0 + j - col_base;   // column inside the window
+      if (a_valid && t < ncol_tiles && c >= 0 && c < nB) {
+        const double fd = divergence(g.metric, dot[j], a2, nb2[tc0 + j]);
+        if (fd < best) { best = fd; best_c = c; }   // columns ascend: strict < keeps the first minimum
+      }
+    }
+  }
+  // reduce over the lanes that share this row (at most 32, neighbours)
+  for (int m = 1 << (tsh - 1); m >= 1; m >>= 1) {   // uniform
+    const double ob = __shfl_xor(best, m, 64);
+    const int oc = __shfl_xor(best_c, m, 64);
+    if (ob < best || (ob == best && oc < best_c)) { best = ob; best_c = oc; }
+  }
+  if (sub == 0 && a_tok >= 0) {
+    // no finite score at all (NaN rows): propose the first B node with FD = +inf, so that counts stay exact
+    const bool has = best_c != 0x7fffffff;
+    g.best_fd[a_tok] = has ? (float)best : __uint_as_float(0x7f800000u);
+    g.best_dst[a_tok] = (wi.nB > 0) ? checked_token(g, wi.off + pos_b(has ? best_c : 0, g.dir)) : -1;
+  }
+  if (sub == 1 && b_tok >= 0) {   // B rows carry no proposal
+    g.best_fd[b_tok] = __uint_as_float(0x7f800000u);
+    g.best_dst[b_tok] = -1;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------------------
 // Windows that fit one 32 x 32 tile (at most 64 tokens): the epilogue AND the per-window selection (paper Step 2:
 // the r A nodes with the lowest FD) in one kernel.  fd_partial_kernel leaves the partial tiles; one workgroup per
-// tile sums them in their fixed order and finishes the tile in LDS: cosines, first minimum per row, rank of every
+// tile sums them in their fixed order and finishes the tile: cosines, first minimum per row, rank of every
 // A node among the keys (FD bits, position) of its window, then dst / per-target source counts / rank of each
 // source in its group -- exactly what select_window_kernel derives from best_fd and best_dst.
 // (Handing the tile to "the last workgroup to arrive" inside fd_partial_kernel was tried and dropped: the
@@ -199,7 +316,6 @@ struct SmallSelArgs {
 };
 
 struct SmallTileLds {
-  double tile[32 * 32];
   double n2[2][32];             // |a|^2 per tile row, |b|^2 per tile column
   uint32_t row_key[32];         // order-preserving bits of the row's best FD (as stored in fp32)
   int row_col[32];              // best tile column (-1: none)
@@ -208,50 +324,51 @@ struct SmallTileLds {
   uint32_t col_mask;            // bit c set: tile column c holds a B node
 };
 
-// One workgroup per tile: partial tiles summed in slice order, then the tile is finished in LDS.
-// Every global load of the kernel is independent of the others (the token lists of the tile come from the
-// record fd_partial_kernel left with slice 0), so all of them are in flight together.
+// One workgroup per tile: partial tiles summed in slice order, then the tile is finished in registers and LDS.
+// Latency bound: every global load of the kernel is independent of the others (the token lists of the tile come from
+// the record fd_partial_kernel left with slice 0; a thread's four columns are one 16-byte load per slice), so all of
+// them are one trip to memory -- thread-per-value loads were four trips in a row (10 us a launch).
 __device__ __forceinline__ void fd_tail_select_body(const FdArgs &g, const SmallSelArgs &q, int tile, char *lds) {
   SmallTileLds &L = *reinterpret_cast<SmallTileLds *>(lds);
   const int tid = threadIdx.x;
   const int64_t ks_stride = (int64_t)g.n_tiles * FD_TILE_FLOATS;
   const float *base = g.partial + (int64_t)tile * FD_TILE_FLOATS;
   const int shift = (g.group > 1) ? (g.slot == 8 ? 3 : 4) : 5;   // tile row or column >> shift = its window slot
+  constexpr int TPR = FD_THREADS / 32;   // threads per tile row, four neighbouring columns each
+  const int rr0 = tid / TPR, cl = tid % TPR;
 
-  // ---- metadata (wave 0) and partial sums (everyone)
-  int m_tok = -1, m_off = 0, m_end = 0, m_rem = 0;
+  // ---- products (everyone), metadata and squared norms (wave 0)
+  // a tile without A rows or without B rows has no sums from fd_partial_kernel: they are not used either
+  f32x4 v[FD_MAX_KSPLIT];
+  load_slices4(base + rr0 * 32 + cl * 4, ks_stride, g.ksplit, v);
   if (tid < 64) {
-    m_tok = reinterpret_cast<const int32_t *>(base + FD_TOK_OFFSET)[tid];   // rows 0..31, then columns 0..31
+    const int m_tok = reinterpret_cast<const int32_t *>(base + FD_TOK_OFFSET)[tid];   // rows 0..31, then columns 0..31
     const int rr = tid & 31;
     const int w = tile * g.group + (rr >> shift);
     const int wc = w < g.n_windows ? w : g.n_windows - 1;
-    m_off = g.win_offsets[wc]; m_end = g.win_offsets[wc + 1]; m_rem = q.win_remove[wc];
+    int m_off = g.win_offsets[wc], m_end = g.win_offsets[wc + 1], m_rem = q.win_remove[wc];
     if (w >= g.n_windows) { m_end = m_off; m_rem = 0; }
-  }
-  // a tile without A rows or without B rows has no sums from fd_partial_kernel: they are not used either
-  for (int e = tid; e < 32 * 32; e += FD_THREADS) L.tile[e] = sum_slices(base + e, ks_stride, g.ksplit);
-  if (tid < 64) {
     L.n2[tid >> 5][tid & 31] = sum_slices(base + 32 * 32 + tid, ks_stride, g.ksplit);
     if (tid < 32) L.row_tok[tid] = m_tok; else L.col_tok[tid - 32] = m_tok;
     const unsigned long long cm = __ballot(tid >= 32 && m_tok >= 0);
     if (tid == 0) L.col_mask = (uint32_t)(cm >> 32);
     if (tid < 32 && (tid & ((1 << shift) - 1)) == 0) {   // first row of a window slot: its removal count
-      const int v = m_end - m_off;
+      const int wv = m_end - m_off;
       const int cap = (g.group > 1) ? g.slot : 32;
-      int nA = side_a(v, g.dir);
+      int nA = side_a(wv, g.dir);
       nA = nA < cap ? nA : cap;
-      int rr = m_rem < 0 ? 0 : (m_rem > nA ? nA : m_rem);
-      if (side_b(v, g.dir) == 0) rr = 0;
-      L.slot_r[tid >> shift] = rr;
+      int r = m_rem < 0 ? 0 : (m_rem > nA ? nA : m_rem);
+      if (side_b(wv, g.dir) == 0) r = 0;
+      L.slot_r[tid >> shift] = r;
     }
   }
+  double dots[4];
+  sum_slices4(v, g.ksplit, dots);
   __syncthreads();
 
-  // ---- FD and first minimum per row: 8 threads per row, 4 columns each
-  constexpr int TPR = FD_THREADS / 32;
-  constexpr int CPT = 32 / TPR;
+  // ---- FD and first minimum per row
   {
-    const int rr = tid / TPR, cl = tid % TPR;
+    const int rr = rr0;
     const int ta = L.row_tok[rr];
     const int sw = rr >> shift;
     const uint32_t cols = L.col_mask & ((shift == 5) ? 0xffffffffu : (((1u << (1 << shift)) - 1u) << (sw << shift)));
@@ -259,10 +376,9 @@ __device__ __forceinline__ void fd_tail_select_body(const FdArgs &g, const Small
     int best_c = 0x7fffffff;
     const double a2 = L.n2[0][rr];
 #pragma unroll
-    for (int k = 0; k < CPT; ++k) {
-      const int c = cl + TPR * k;
-      const double dot = L.tile[rr * 32 + c];
-      const double fd = divergence(g.metric, dot, a2, L.n2[1][c]);
+    for (int k = 0; k < 4; ++k) {
+      const int c = cl * 4 + k;
+      const double fd = divergence(g.metric, dots[k], a2, L.n2[1][c]);
       const bool live = ta >= 0 && ((cols >> c) & 1u);
       if (live && fd < best) { best = fd; best_c = c; }   // columns ascend: strict < keeps the first minimum
     }

@@ -28,101 +28,8 @@ __global__ __launch_bounds__(FD_THREADS) void fd_tail_select_kernel(FdArgs g, Sm
 }
 
 __global__ __launch_bounds__(FD_THREADS) void fd_epilogue_kernel(FdArgs g) {
-  __shared__ double nb2[FD_MAX_COLS];
-  __shared__ double na2[32];
-  const int rb = blockIdx.x;
-  const int64_t ks_stride = (int64_t)g.n_tiles * FD_TILE_FLOATS;
-  const int per = g.mt * g.nt;
-
-  int tile_row0;            // tile holding the dots of (this row block, column tile 0)
-  int tile_col0;            // tile holding |b|^2 of column tile 0
-  int w_single = 0, m_single = 0;
-  if (g.group > 1) {
-    tile_row0 = tile_col0 = rb;
-  } else {
-    w_single = rb / g.mt;
-    m_single = rb - w_single * g.mt;
-    tile_row0 = w_single * per + m_single * g.nt;
-    tile_col0 = w_single * per;
-  }
-  const int ncol_tiles = (g.group > 1) ? 1 : g.nt;
-  for (int c = threadIdx.x; c < ncol_tiles * 32 + 32; c += FD_THREADS) {
-    if (c < ncol_tiles * 32)
-      nb2[c] = sum_slices(g.partial + (int64_t)(tile_col0 + (c >> 5)) * FD_TILE_FLOATS + 32 * 32 + 32 + (c & 31),
-                          ks_stride, g.ksplit);
-    else
-      na2[c - ncol_tiles * 32] = sum_slices(g.partial + (int64_t)tile_row0 * FD_TILE_FLOATS + 32 * 32 + (c - ncol_tiles * 32),
-                                            ks_stride, g.ksplit);
-  }
-  __syncthreads();
-
-  const int col_cap = (g.group > 1) ? g.slot : g.nt * 32;   // columns this launch really tiled
-  // Eight threads share a row of the block; a thread takes four neighbouring columns of every column tile, so the
-  // slices of a tile arrive as ksplit 16-byte loads per thread, all in flight together (one round trip per column tile).
-  const int r = threadIdx.x >> 3, sub = threadIdx.x & 7;
-  WinInfo wi;
-  int l, col_base;   // local A position; first tile column of this row's window
-  if (g.group > 1) {
-    const int s = r / g.slot;
-    l = r - s * g.slot;
-    wi = win_info(g, rb * g.group + s);
-    col_base = s * g.slot;
-  } else {
-    wi = win_info(g, w_single);
-    l = m_single * 32 + r;
-    col_base = 0;
-  }
-  const bool a_valid = l < wi.nA;
-  const int nB = wi.nB < col_cap ? wi.nB : col_cap;
-  double best = __longlong_as_double(0x7ff0000000000000ll);   // +inf
-  int best_c = 0x7fffffff;
-  const double a2 = na2[r];
-  for (int t = 0; t < ncol_tiles; ++t) {
-    const int tc0 = t * 32 + sub * 4;   // first of this thread's columns inside the block's tile row
-    if (tc0 + 3 < col_base || tc0 >= col_base + nB) continue;   // none of the four belongs to this row's window
-    const float *p = g.partial + (int64_t)(tile_row0 + t) * FD_TILE_FLOATS + r * 32 + sub * 4;
-    f32x4 v[FD_MAX_KSPLIT];
-#pragma unroll
-    for (int ks = 0; ks < FD_MAX_KSPLIT; ++ks)   // surplus slices re-read the last one and are dropped
-      v[ks] = *reinterpret_cast<const f32x4 *>(p + (ks < g.ksplit ? ks : g.ksplit - 1) * ks_stride);
-    double dot[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int ks = 0; ks < FD_MAX_KSPLIT; ++ks) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) dot[j] += (ks < g.ksplit) ? (double)v[ks][j] : 0.0;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int c = tc0 + j - col_base;   // column inside the window
-      if (a_valid && c >= 0 && c < nB) {
-        const double fd = divergence(g.metric, dot[j], a2, nb2[tc0 + j]);
-        if (fd < best) { best = fd; best_c = c; }   // columns ascend: strict < keeps the first minimum
-      }
-    }
-  }
-  // reduce over the eight lanes that share this row
-#pragma unroll
-  for (int m = 4; m >= 1; m >>= 1) {
-    const double ob = __shfl_xor(best, m, 64);
-    const int oc = __shfl_xor(best_c, m, 64);
-    if (ob < best || (ob == best && oc < best_c)) { best = ob; best_c = oc; }
-  }
-  if (sub == 0 && a_valid) {
-    const int a_tok = checked_token(g, wi.off + pos_a(l, g.dir));
-    if (a_tok >= 0) {
-      // no finite score at all (NaN rows): propose the first B node with FD = +inf, so that counts stay exact
-      const bool has = best_c != 0x7fffffff;
-      g.best_fd[a_tok] = has ? (float)best : __uint_as_float(0x7f800000u);
-      g.best_dst[a_tok] = (wi.nB > 0) ? checked_token(g, wi.off + pos_b(has ? best_c : 0, g.dir)) : -1;
-    }
-  }
-  if (sub == 1 && l < wi.nB) {   // B rows carry no proposal
-    const int b_tok = checked_token(g, wi.off + pos_b(l, g.dir));
-    if (b_tok >= 0) {
-      g.best_fd[b_tok] = __uint_as_float(0x7f800000u);
-      g.best_dst[b_tok] = -1;
-    }
-  }
+  __shared__ __attribute__((aligned(16))) char lds[FD_EPILOGUE_LDS];
+  fd_epilogue_body(g, blockIdx.x, lds);
 }
 
 FdPlan make_fd_small_fused_plan(int n_windows, int max_window_tokens, int d, int dtype_bytes) {
@@ -195,7 +102,8 @@ hipError_t launch_fd(const FdPlan &plan, int dtype, const void *X, int64_t ldx, 
   else hipLaunchKernelGGL(fd_partial_kernel<float>, grid, dim3(FD_THREADS), 0, stream, g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(fd_epilogue_kernel, dim3((unsigned)plan.n_rowblocks), dim3(FD_THREADS), 0, stream, g);
+  hipLaunchKernelGGL(fd_epilogue_kernel, dim3((unsigned)fd_epilogue_blocks(plan.n_rowblocks, plan.group, plan.nt)),
+                     dim3(FD_THREADS), 0, stream, g);
   return hipGetLastError();
 }
 

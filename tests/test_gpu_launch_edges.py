@@ -28,3 +28,16 @@ def test_window_partition_around_its_passes(tiles, gh, gw, w):
     ro, rt = O.build_windows(pos, h_cu, tiles, gh, gw, w)
     np.testing.assert_array_equal(wo.cpu().numpy(), ro)
     np.testing.assert_array_equal(wt.cpu().numpy(), rt)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 96), ("bf16", 1088), ("f32", 128)])
+@pytest.mark.parametrize("gh,gw", [(1, 2), (5, 13), (6, 11), (8, 16), (3, 43), (10, 13), (12, 16), (1, 193), (4, 65), (15, 26)])
+def test_one_window_around_the_column_tiles_of_the_epilogue(gh, gw, dtype, d):
+    """One window of 2, 65, 66, 128, 129, 130, 192, 193, 260 and 390 tokens: one to seven column tiles of 32 B nodes,
+    whole and partial, on the small-tile path; every stage against the oracle at the protocol's tolerances."""
+    from workloads import make_custom
+    from parity import check_workload
+    n = gh * gw
+    wl = make_custom(name="window_%d" % n, seed=n, dtype=dtype, batch=2, grid_h=gh, grid_w=gw, text_lens=(5, 33), d=d,
+                     heads=d // 32, head_dim=32, n_c=12, structure="iid", windows_per_axis=(0,), targets=(n - max(1, n // 5),))
+    check_workload(wl)
