@@ -24,9 +24,9 @@
  *     static device array instead.
  *   - state the library keeps between calls (per device, host-side handles only,
  *     created on first use outside stream capture, default priority, never
- *     destroyed): one helper stream with two events for lightkv_score, two helper
- *     streams with four events for the two schedule calls, and the "large LDS"
- *     attribute of three kernels.  Calls whose `stream` is being captured never
+ *     destroyed): one helper stream with two events for lightkv_score, another such
+ *     set for lightkv_compress_schedule, and the "large LDS" attribute of some
+ *     kernels.  Calls whose `stream` is being captured never
  *     touch the helper streams: they enqueue everything on `stream` in order, so
  *     a capture only ever contains the caller's stream.
  *   - all work is enqueued on `stream` (a hipStream_t passed as void*, NULL = the
@@ -136,8 +136,9 @@ typedef enum {
 #define LIGHTKV_EDGE_MAX_WINDOW_TOKENS 4096 /* tokens in one window with LIGHTKV_MATCH_EDGE_TOPK; windows bounded by more than
                                                256 tokens are ranked through a matrix of all their FD values in the workspace */
 #define LIGHTKV_SELECT_STATIC_MAX_TOKENS 65536  /* vision tokens of a batch in lightkv_select_static */
-/* Steps of at most this many vision tokens whose windows hold at most 64 tokens: lightkv_score_select runs the xi
-   passes inside the launches of the FD chain, on the caller's stream alone (see there). */
+/* Steps of at most this many vision tokens whose windows hold at most 64 tokens are three launches on the caller's stream
+   when lightkv_score_select is asked for xi as well.  (The call shares launches between the two chains on larger steps,
+   too; the constant is for callers that arrange the single calls over streams of their own.) */
 #define LIGHTKV_ONE_STREAM_MAX_TOKENS 1024
 
 /*
@@ -311,8 +312,9 @@ lightkv_status lightkv_select_static(const lightkv_problem *p, const float *best
 /*
  * lightkv_score followed by lightkv_select in one call: same arguments, same outputs (bit for bit).  When every
  * window holds at most 64 tokens, the row arg-min and the per-window selection run in one kernel (one launch less);
- * if in addition xi is computed and the step has at most LIGHTKV_ONE_STREAM_MAX_TOKENS tokens, the xi passes share the
- * launches of the FD kernels and the whole call is three launches on `stream` (no helper stream).  Otherwise the call
+ * if xi is computed as well, the xi passes share the launches of the FD kernels and the whole call runs on `stream`
+ * (three launches, or four to five with larger windows; no helper stream), except on the tiled path of large windows and
+ * for batches of 256 or more (sequence, head) pairs with prompts of at most 256 tokens.  Otherwise the call
  * is the two calls in sequence.  X must not be NULL; xi_mode GIVEN skips the xi half as in lightkv_score.
  *
  * With p->match == LIGHTKV_MATCH_EDGE_TOPK (this call only; lightkv_select alone returns LIGHTKV_ERR_UNSUPPORTED,
@@ -423,13 +425,12 @@ typedef struct lightkv_stage {
  *   Q[sumT, heads, head_dim] (prompt queries, TEXT_QUERY) is the same for all stages; xi of stage s is computed
  *   against the K rows that stage merges.  softmax_scale as in lightkv_score.
  * Per stage the call enqueues what the single calls would -- lightkv_build_windows (stage 0; later stages' windows are
- * built by lightkv_build_windows_next next to the previous stage's merge), lightkv_score (xi) next to
- * lightkv_score_select (FD + selection), lightkv_aggregate_compact -- with the same results, bit for bit.  xi and the
- * next stage's windows run on two internal helper streams that fork from and join `stream` (created per device on the
- * first call outside stream capture, default priority, kept for the life of the process; if they cannot be made, or
- * the first call on a device comes under capture, everything is enqueued on `stream` in order).  Steps of at most
- * LIGHTKV_ONE_STREAM_MAX_TOKENS tokens whose windows hold at most 64 tokens use the one-stream form of
- * lightkv_score_select instead.  One workspace serves all stages: ws_bytes must cover lightkv_workspace_size of every
+ * built by workgroups of the previous stage's merge launch), lightkv_score_select with xi, lightkv_aggregate_compact --
+ * with the same results, bit for bit.  Stages whose lightkv_score_select would fork (see there) run xi on one internal
+ * helper stream beside the feature divergence and the selection; it forks from and joins `stream` (created per device on
+ * the first such call outside stream capture, default priority, kept for the life of the process; if it cannot be made, or
+ * the first call on a device comes under capture, everything is enqueued on `stream` in order).
+ * One workspace serves all stages: ws_bytes must cover lightkv_workspace_size of every
  * stage.  Host threads calling this on one device take turns enqueueing.  Only LIGHTKV_MATCH_BEST_PER_A (fixed token
  * counts) is supported here; lightkv_compress_schedule_ratio below takes the others.
  * Errors: the first failing call's status; stages before it have been enqueued.
@@ -448,8 +449,7 @@ lightkv_status lightkv_compress_schedule(const lightkv_stage *stages, int32_t n_
  * (host) is the ratio of every stage; the per-window counts are computed on the device from the windows as they are
  * (lightkv_window_counts: LIGHTKV_COUNT_EDGES for EDGE_TOPK, LIGHTKV_COUNT_RATIO otherwise) and consumed there.
  * Per stage the call enqueues lightkv_build_windows + lightkv_window_counts (stage 0; later stages' windows and counts
- * are built by lightkv_build_windows_next next to the previous stage's merge, on a helper stream as in
- * lightkv_compress_schedule), lightkv_score_select (xi from Q and the stage's K rows, TEXT_QUERY) and
+ * are built beside the previous stage's merge, as in lightkv_compress_schedule), lightkv_score_select (xi from Q and the stage's K rows, TEXT_QUERY) and
  * lightkv_aggregate_compact -- with the same results as those calls, bit for bit -- then copies the stage's cu_vis_out
  * to h_cu_vis_out[s * (batch+1) ...] (host, [n_stages * (batch+1)], out) and WAITS for `stream`: the next stage's launch
  * plans need those offsets.  One synchronisation per stage; the call cannot be captured into a graph (a capturing

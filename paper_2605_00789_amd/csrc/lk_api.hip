@@ -3,6 +3,7 @@
 #include "../../include/lightkv.h"
 #include "lk_launch.h"
 #include "lk_helpers.h"
+#include "lk_win_body.h"
 
 #include <math.h>
 #include <mutex>
@@ -137,6 +138,14 @@ bool use_big_fd(const lightkv_problem *p, const Checked &c) {
   return (int64_t)p->n_windows * big.mt * big.nt >= FD_BIG_MIN_TILES;
 }
 
+// lightkv_score_select, both halves requested: the k-th kernels of the two chains share launches on the caller's stream.
+// Not for the tiled FD kernel (one workgroup of it fills a CU's LDS) and not for batches whose xi is one workgroup per
+// (sequence, head) pair; there the chains run on two streams.
+bool fused_launches(const lightkv_problem *p, const Checked &c, const FdPlan &fd, const XiPlan &xp, int xi_mode, const float *lse) {
+  return p->match == LIGHTKV_MATCH_BEST_PER_A && p->n_windows > 0 && c.sum_n > 0 && fd.n_tiles > 0 && xp.max_vis_blocks > 0 &&
+         !use_big_fd(p, c) && !xi_seq_applies(xp, xi_mode, lse, p->batch, p->heads);
+}
+
 WsLayout ws_layout(const FdPlan &fd, const FdBigPlan &big, bool use_big, const XiPlan &xi, int sum_n, size_t n_edge_ints) {
   // (full pairwise matching needs at most what the tiled bipartite path lays out: norms and one key plane or more)
   WsLayout l;
@@ -223,34 +232,60 @@ lightkv_status lightkv_workspace_size(const lightkv_problem *p, size_t *bytes) {
   return LIGHTKV_OK;
 }
 
-static lightkv_status build_windows_impl(int32_t batch, const int32_t *h_cu_vis, const int32_t *cu_vis,
-                                         const int32_t *pos, const int32_t *new_index, const int32_t *cu_vis_out,
-                                         int32_t tiles, int32_t grid_h, int32_t grid_w, int32_t w,
-                                         int32_t *win_offsets, int32_t *win_tokens, void *stream,
-                                         const int32_t *cu_target = nullptr, int32_t *win_remove = nullptr,
-                                         int32_t *status = nullptr, int dir = 0, bool *counts_done = nullptr) {
-  if (!h_cu_vis || !cu_vis || !pos || !win_offsets || !win_tokens) return LIGHTKV_ERR_NULL;
-  if (batch < 1 || tiles < 1 || grid_h < 1 || grid_w < 1 || w < 0 || h_cu_vis[0] != 0) return LIGHTKV_ERR_SHAPE;
-  int max_seq = 0;
+// Largest sequence of the batch; validates what every form of the partition needs.
+static lightkv_status check_windows(int32_t batch, const int32_t *h_cu_vis, const int32_t *cu_vis, const int32_t *pos,
+                                    const WinSpec &spec, int &max_seq) {
+  if (!h_cu_vis || !cu_vis || !pos || !spec.win_offsets || !spec.win_tokens) return LIGHTKV_ERR_NULL;
+  if (batch < 1 || spec.tiles < 1 || spec.grid_h < 1 || spec.grid_w < 1 || spec.w < 0 || h_cu_vis[0] != 0) return LIGHTKV_ERR_SHAPE;
+  max_seq = 0;
   for (int b = 0; b < batch; ++b) {
     const int n = h_cu_vis[b + 1] - h_cu_vis[b];
     if (n < 0) return LIGHTKV_ERR_SHAPE;
     max_seq = n > max_seq ? n : max_seq;
   }
   if (max_seq > LIGHTKV_MAX_SEQ_TOKENS) return LIGHTKV_ERR_UNSUPPORTED;
-  if ((int64_t)tiles * w * w > (1 << 17) || (int64_t)tiles * grid_h * grid_w > (1ll << 30)) return LIGHTKV_ERR_UNSUPPORTED;
-  if (launch_build_windows(cu_vis, pos, new_index, cu_vis_out, batch, max_seq, tiles, grid_h, grid_w, w, win_offsets,
-                           win_tokens, cu_target, win_remove, status, dir, counts_done,
+  if ((int64_t)spec.tiles * spec.w * spec.w > (1 << 17) || (int64_t)spec.tiles * spec.grid_h * spec.grid_w > (1ll << 30))
+    return LIGHTKV_ERR_UNSUPPORTED;
+  if (spec.count_mode >= 0) {
+    if (!spec.win_remove || (spec.count_mode == LIGHTKV_COUNT_TARGET && !spec.cu_target)) return LIGHTKV_ERR_NULL;
+    if (spec.dir != LIGHTKV_DIRECTION_A_TO_B && spec.dir != LIGHTKV_DIRECTION_B_TO_A) return LIGHTKV_ERR_UNSUPPORTED;
+    const int32_t wps = lightkv_windows_per_sequence(spec.tiles, spec.w);
+    if (wps < 0 || (int64_t)wps * batch != spec.n_windows) return LIGHTKV_ERR_SHAPE;
+  }
+  return LIGHTKV_OK;
+}
+
+// Windows and, if the spec asks for them, their counts: in ONE launch where the partition kernel allows it (the window
+// sizes are in its LDS), in two otherwise.
+static lightkv_status build_windows_impl(int32_t batch, const int32_t *h_cu_vis, const int32_t *cu_vis,
+                                         const int32_t *pos, const int32_t *new_index, const int32_t *cu_vis_out,
+                                         const WinSpec &spec, void *stream) {
+  if ((new_index == nullptr) != (cu_vis_out == nullptr)) return LIGHTKV_ERR_NULL;
+  int max_seq = 0;
+  const lightkv_status st = check_windows(batch, h_cu_vis, cu_vis, pos, spec, max_seq);
+  if (st != LIGHTKV_OK) return st;
+  bool done = false;
+  if (launch_build_windows(spec, cu_vis, pos, new_index, cu_vis_out, batch, max_seq, &done,
                            static_cast<hipStream_t>(stream)) != hipSuccess)
     return LIGHTKV_ERR_LAUNCH;
-  return LIGHTKV_OK;
+  if (spec.count_mode < 0 || done) return LIGHTKV_OK;
+  // (the current lengths of the sequences: after the previous stage's compaction in the "next" form)
+  return lightkv_window_counts(batch, spec.n_windows, spec.win_offsets, spec.count_mode, spec.dir, spec.rho,
+                               cu_vis_out ? cu_vis_out : cu_vis, spec.cu_target, spec.win_remove, spec.status, stream);
+}
+
+static WinSpec plain_windows(int32_t tiles, int32_t grid_h, int32_t grid_w, int32_t w, int32_t *win_offsets, int32_t *win_tokens) {
+  WinSpec s{};
+  s.tiles = tiles; s.grid_h = grid_h; s.grid_w = grid_w; s.w = w; s.win_offsets = win_offsets; s.win_tokens = win_tokens;
+  s.count_mode = -1;
+  return s;
 }
 
 lightkv_status lightkv_build_windows(int32_t batch, const int32_t *h_cu_vis, const int32_t *cu_vis,
                                      const int32_t *pos, int32_t tiles, int32_t grid_h, int32_t grid_w,
                                      int32_t w, int32_t *win_offsets, int32_t *win_tokens, void *stream) {
-  return build_windows_impl(batch, h_cu_vis, cu_vis, pos, nullptr, nullptr, tiles, grid_h, grid_w, w, win_offsets,
-                            win_tokens, stream);
+  return build_windows_impl(batch, h_cu_vis, cu_vis, pos, nullptr, nullptr,
+                            plain_windows(tiles, grid_h, grid_w, w, win_offsets, win_tokens), stream);
 }
 
 lightkv_status lightkv_build_windows_next(int32_t batch, const int32_t *h_cu_vis, const int32_t *cu_vis,
@@ -258,8 +293,8 @@ lightkv_status lightkv_build_windows_next(int32_t batch, const int32_t *h_cu_vis
                                           int32_t tiles, int32_t grid_h, int32_t grid_w, int32_t w,
                                           int32_t *win_offsets, int32_t *win_tokens, void *stream) {
   if (!new_index || !cu_vis_out) return LIGHTKV_ERR_NULL;
-  return build_windows_impl(batch, h_cu_vis, cu_vis, pos, new_index, cu_vis_out, tiles, grid_h, grid_w, w, win_offsets,
-                            win_tokens, stream);
+  return build_windows_impl(batch, h_cu_vis, cu_vis, pos, new_index, cu_vis_out,
+                            plain_windows(tiles, grid_h, grid_w, w, win_offsets, win_tokens), stream);
 }
 
 int32_t lightkv_windows_per_sequence(int32_t tiles, int32_t w) {
@@ -303,26 +338,17 @@ lightkv_status lightkv_window_counts(int32_t batch, int32_t n_windows, const int
 
 }  // extern "C"
 
-// Windows and their counts for lightkv_compress_schedule: lightkv_build_windows (or _next) followed by
-// lightkv_window_counts(LIGHTKV_COUNT_TARGET) on the windows just built -- in ONE launch where the partition kernel
-// allows it (the window sizes are in its LDS at the end), in two otherwise.  Same validation, same results.
+// The schedules' form: a spec with counts.
 int lk::build_windows_with_counts(int32_t batch, const int32_t *h_cu_vis, const int32_t *cu_vis, const int32_t *pos,
-                                  const int32_t *new_index, const int32_t *cu_vis_out, int32_t tiles, int32_t grid_h,
-                                  int32_t grid_w, int32_t w, int32_t *win_offsets, int32_t *win_tokens, int32_t n_windows,
-                                  int32_t direction, const int32_t *cu_target, int32_t *win_remove, int32_t *status,
-                                  void *stream) {
-  if ((new_index == nullptr) != (cu_vis_out == nullptr)) return LIGHTKV_ERR_NULL;
-  if (!cu_target || !win_remove) return LIGHTKV_ERR_NULL;
-  if (direction != LIGHTKV_DIRECTION_A_TO_B && direction != LIGHTKV_DIRECTION_B_TO_A) return LIGHTKV_ERR_UNSUPPORTED;
-  const int32_t wps = lightkv_windows_per_sequence(tiles, w);
-  if (batch < 1 || wps < 0 || (int64_t)wps * batch != n_windows) return LIGHTKV_ERR_SHAPE;
-  bool done = false;
-  const lightkv_status st = build_windows_impl(batch, h_cu_vis, cu_vis, pos, new_index, cu_vis_out, tiles, grid_h, grid_w, w,
-                                               win_offsets, win_tokens, stream, cu_target, win_remove, status, direction, &done);
-  if (st != LIGHTKV_OK || done) return st;
-  // the current lengths of the sequences: after the previous stage's compaction in the "next" form
-  return lightkv_window_counts(batch, n_windows, win_offsets, LIGHTKV_COUNT_TARGET, direction, 0.0,
-                               cu_vis_out ? cu_vis_out : cu_vis, cu_target, win_remove, status, stream);
+                                  const WinSpec &spec, void *stream) {
+  return build_windows_impl(batch, h_cu_vis, cu_vis, pos, nullptr, nullptr, spec, stream);
+}
+
+bool lk::score_select_one_stream(const lightkv_problem *p) {
+  Checked c;
+  if (check_problem(p, true, true, c) != LIGHTKV_OK) return true;   // (lightkv_score_select reports the error)
+  return fused_launches(p, c, make_fd_plan(p->n_windows, c.max_window, p->d, c.elem_bytes),
+                        make_xi_plan(p->batch, p->h_cu_vis, p->h_cu_txt, p->heads, LIGHTKV_XI_TEXT_QUERY), LIGHTKV_XI_TEXT_QUERY, nullptr);
 }
 
 namespace {
@@ -330,7 +356,8 @@ struct SelectOut {   // outputs of lightkv_select, present when selection is to 
   int32_t *dst, *new_index, *grp_offsets, *grp_src, *cu_vis_out;
 };
 
-// sel == nullptr: plain lightkv_score.  Otherwise the caller guarantees that make_fd_small_fused_plan applies.
+// sel == nullptr: plain lightkv_score.  Otherwise the caller guarantees that make_fd_small_fused_plan or fused_launches
+// applies, or that the matching is one with a selection of its own.
 // keys_only: on the tiled MFMA path, leave the packed keys in the workspace and do not write best_fd / best_dst
 // (the caller's selection reads the keys and writes them).
 lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, const float *x_sqnorm,
@@ -392,13 +419,8 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
   hipStream_t s = static_cast<hipStream_t>(stream);
 
   if (use_big && (uint64_t)c.sum_n * (uint64_t)ldx * 2u >= (1ull << 32)) return LIGHTKV_ERR_UNSUPPORTED;   // 32-bit row offsets
-  // Both halves and the selection, single-tile windows, a small step: three launches on the caller's stream, each
-  // running a step of the xi chain next to a step of the FD chain (no helper stream, no fork/join).  Larger steps fill
-  // the chip with either chain alone; there the shared launches take as long as the two in a row and the helper
-  // stream is the better arrangement (measured: 2880 tokens 248 vs 237 us per three stages, 576 tokens 190 vs 199).
-  // (only layouts of the small-tile path hold the partial tiles these launches write: never with use_big)
-  if (need_xi && need_fd && sel && !edge && !pairwise && !use_big && fd.n_tiles > 0 && c.sum_n > 0 &&
-      c.sum_n <= LIGHTKV_ONE_STREAM_MAX_TOKENS && p->n_windows > 0) {
+  // both halves and the selection: the two chains side by side in the same launches, on the caller's stream
+  if (need_xi && need_fd && sel && fused_launches(p, c, fd, xp, xi_mode, lse)) {
     const float scale = softmax_scale != 0.f ? softmax_scale : 1.0f / sqrtf((float)p->head_dim);
     int32_t *cnt = reinterpret_cast<int32_t *>(wsb + l.sel_cnt), *rank = reinterpret_cast<int32_t *>(wsb + l.sel_rank);
     const hipError_t e = launch_score_select_fused(
@@ -406,7 +428,7 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
         p->cu_txt, Q, q_tok_stride, q_head_stride, K, k_tok_stride, k_head_stride, lse, scale,
         reinterpret_cast<float *>(wsb + l.xi_stats), reinterpret_cast<float *>(wsb + l.xi_part), xi, X, ldx,
         p->win_offsets, p->win_tokens, p->win_remove, reinterpret_cast<float *>(wsb + l.fd_partial), best_fd, best_dst,
-        sel->dst, cnt, rank, sel->new_index, sel->grp_offsets, sel->grp_src, sel->cu_vis_out, s);
+        sel->dst, cnt, rank, sel->new_index, sel->grp_offsets, sel->grp_src, sel->cu_vis_out, c.max_window, s);
     return e == hipSuccess ? LIGHTKV_OK : LIGHTKV_ERR_LAUNCH;
   }
   Fork *fk = nullptr;
@@ -512,7 +534,12 @@ lightkv_status lightkv_score_select(const lightkv_problem *p, const void *X, int
   if (st != LIGHTKV_OK) return st;
   if (!p->win_remove) return LIGHTKV_ERR_NULL;
   const FdPlan small = make_fd_small_fused_plan(p->n_windows, c.max_window, p->d, c.elem_bytes);
-  if ((small.n_tiles > 0 && !use_big_fd(p, c)) || p->n_windows == 0 || edge_topk(p) || full_pairwise(p)) {
+  bool fused = false;
+  if (xi_mode != LIGHTKV_XI_GIVEN && p->h_cu_txt && p->cu_txt) {
+    const FdPlan fd = make_fd_plan(p->n_windows, c.max_window, p->d, c.elem_bytes);
+    fused = fused_launches(p, c, fd, make_xi_plan(p->batch, p->h_cu_vis, p->h_cu_txt, p->heads, xi_mode), xi_mode, lse);
+  }
+  if (fused || (small.n_tiles > 0 && !use_big_fd(p, c)) || p->n_windows == 0 || edge_topk(p) || full_pairwise(p)) {
     const SelectOut sel{dst, new_index, grp_offsets, grp_src, cu_vis_out};
     return score_impl(p, X, ldx, x_sqnorm, Q, q_tok_stride, q_head_stride, K, k_tok_stride, k_head_stride, xi_mode, lse,
                       softmax_scale, xi, best_fd, best_dst, &sel, false, nullptr, 0, ws, ws_bytes, stream);
@@ -539,7 +566,7 @@ static lightkv_status rows_call(int mode, const lightkv_problem *p, const int32_
                                 const void *X, int64_t ldx, const void *K, int64_t ldk, const void *V, int64_t ldv,
                                 const int32_t *pos, void *Xo, void *Ko, void *Vo, int32_t *pos_out,
                                 float *x_sqnorm_out, int64_t out_rows, int64_t tail_rows, const int32_t *cu_vis_out,
-                                void *stream) {
+                                const WinSpec *next, void *stream) {
   Checked c;
   lightkv_status st = check_problem(p, false, false, c);
   if (st != LIGHTKV_OK) return st;
@@ -572,11 +599,22 @@ static lightkv_status rows_call(int mode, const lightkv_problem *p, const int32_
   if (mode != 0 && ((pos == nullptr) != (pos_out == nullptr))) return LIGHTKV_ERR_NULL;
   if (mode != 0 && pos && pos == pos_out) return LIGHTKV_ERR_SHAPE;
   if (x_sqnorm_out && (!X || (reinterpret_cast<uintptr_t>(x_sqnorm_out) & 3))) return LIGHTKV_ERR_NULL;
-  if (launch_rows(mode, p->dtype, p->d, c.sum_n, t, new_index, grp_offsets, grp_src, xi, pos, pos_out, x_sqnorm_out,
-                  out_rows, static_cast<hipStream_t>(stream)) != hipSuccess)
-    return LIGHTKV_ERR_LAUNCH;
-  if (tail_rows > 0 && launch_tail_rows(p->dtype, p->d, c.sum_n, p->batch, t, pos, pos_out, cu_vis_out, tail_rows, out_rows,
-                                        static_cast<hipStream_t>(stream)) != hipSuccess)
+  // the next stage's windows: guests of the row launch, or a launch in front of it
+  WinArgs win;
+  size_t win_lds = 0;
+  if (next) {
+    int max_seq = 0;
+    st = check_windows(p->batch, p->h_cu_vis, p->cu_vis, pos, *next, max_seq);
+    if (st != LIGHTKV_OK) return st;
+    if (!cu_vis_out) return LIGHTKV_ERR_NULL;
+    win_lds = make_win_args(*next, p->cu_vis, pos, new_index, cu_vis_out, p->batch, max_seq, &win);
+    if (win_lds == 0) {
+      st = build_windows_impl(p->batch, p->h_cu_vis, p->cu_vis, pos, new_index, cu_vis_out, *next, stream);
+      if (st != LIGHTKV_OK) return st;
+    }
+  }
+  if (launch_rows(mode, p->dtype, p->d, c.sum_n, p->batch, t, new_index, grp_offsets, grp_src, xi, pos, pos_out, x_sqnorm_out,
+                  out_rows, tail_rows, cu_vis_out, win_lds ? &win : nullptr, win_lds, static_cast<hipStream_t>(stream)) != hipSuccess)
     return LIGHTKV_ERR_LAUNCH;
   return LIGHTKV_OK;
 }
@@ -585,7 +623,7 @@ lightkv_status lightkv_aggregate(const lightkv_problem *p, const int32_t *grp_of
                                  const float *xi, void *X, int64_t ldx, void *K, int64_t ldk,
                                  void *V, int64_t ldv, void *stream) {
   return rows_call(0, p, nullptr, grp_offsets, grp_src, xi, X, ldx, K, ldk, V, ldv, nullptr, nullptr, nullptr,
-                   nullptr, nullptr, nullptr, 0, 0, nullptr, stream);
+                   nullptr, nullptr, nullptr, 0, 0, nullptr, nullptr, stream);
 }
 
 lightkv_status lightkv_compact(const lightkv_problem *p, const int32_t *new_index,
@@ -594,7 +632,7 @@ lightkv_status lightkv_compact(const lightkv_problem *p, const int32_t *new_inde
                                void *X_out, void *K_out, void *V_out, int32_t *pos_out, float *x_sqnorm_out,
                                int64_t out_rows, int64_t tail_rows, const int32_t *cu_vis_out, void *stream) {
   return rows_call(1, p, new_index, nullptr, nullptr, nullptr, X, ldx, K, ldk, V, ldv, pos, X_out, K_out, V_out,
-                   pos_out, x_sqnorm_out, out_rows, tail_rows, cu_vis_out, stream);
+                   pos_out, x_sqnorm_out, out_rows, tail_rows, cu_vis_out, nullptr, stream);
 }
 
 lightkv_status lightkv_aggregate_compact(const lightkv_problem *p, const int32_t *new_index,
@@ -605,10 +643,19 @@ lightkv_status lightkv_aggregate_compact(const lightkv_problem *p, const int32_t
                                          float *x_sqnorm_out, int64_t out_rows, int64_t tail_rows,
                                          const int32_t *cu_vis_out, void *stream) {
   return rows_call(2, p, new_index, grp_offsets, grp_src, xi, X, ldx, K, ldk, V, ldv, pos, X_out, K_out, V_out,
-                   pos_out, x_sqnorm_out, out_rows, tail_rows, cu_vis_out, stream);
+                   pos_out, x_sqnorm_out, out_rows, tail_rows, cu_vis_out, nullptr, stream);
 }
 
 }  // extern "C"
+
+int lk::aggregate_compact_with_windows(const lightkv_problem *p, const int32_t *new_index, const int32_t *grp_offsets,
+                                       const int32_t *grp_src, const float *xi, const void *X, int64_t ldx, const void *K,
+                                       int64_t ldk, const void *V, int64_t ldv, const int32_t *pos, void *X_out, void *K_out,
+                                       void *V_out, int32_t *pos_out, float *x_sqnorm_out, int64_t out_rows,
+                                       const int32_t *cu_vis_out, const WinSpec *next, void *stream) {
+  return rows_call(2, p, new_index, grp_offsets, grp_src, xi, X, ldx, K, ldk, V, ldv, pos, X_out, K_out, V_out, pos_out,
+                   x_sqnorm_out, out_rows, 0, cu_vis_out, next, stream);
+}
 
 // ---- lightkv_select without a workspace argument ---------------------------------------------------------------
 // For callers that can neither allocate nor carry a workspace (code under graph capture, serving loops with a fixed

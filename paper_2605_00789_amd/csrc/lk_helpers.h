@@ -17,7 +17,8 @@ namespace lk {
 constexpr int HELPER_SETS_PER_DEVICE = 4;
 constexpr int HELPER_MAX_DEVICES = 64;
 
-template <int N_STREAMS, int N_EVENTS>
+// TAG: a pool of its own (a call that holds a set of one pool may call into another that takes a set of a second one)
+template <int N_STREAMS, int N_EVENTS, int TAG = 0>
 struct HelperSet {
   hipStream_t stream[N_STREAMS] = {};
   hipEvent_t event[N_EVENTS] = {};
@@ -26,9 +27,9 @@ struct HelperSet {
 };
 
 // Returns a usable set for a call on `main` with `guard` holding its in_use mutex, or nullptr (then: no helpers).
-template <int N_STREAMS, int N_EVENTS>
-HelperSet<N_STREAMS, N_EVENTS> *acquire_helpers(hipStream_t main, std::unique_lock<std::mutex> &guard) {
-  using Set = HelperSet<N_STREAMS, N_EVENTS>;
+template <int N_STREAMS, int N_EVENTS, int TAG = 0>
+HelperSet<N_STREAMS, N_EVENTS, TAG> *acquire_helpers(hipStream_t main, std::unique_lock<std::mutex> &guard) {
+  using Set = HelperSet<N_STREAMS, N_EVENTS, TAG>;
   static Set pool[HELPER_MAX_DEVICES][HELPER_SETS_PER_DEVICE];
   static std::mutex mu[HELPER_MAX_DEVICES];
   int dev = 0;

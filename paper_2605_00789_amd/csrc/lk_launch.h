@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+struct lightkv_problem;
+
 namespace lk {
 
 // The bipartite split of a window's list (Sec. 3.2.1 Step 1) and the direction of the merge (message-passing
@@ -38,20 +40,33 @@ constexpr int FD_MAX_COLS = 2048;                   // |B| of the largest suppor
 
 FdPlan make_fd_plan(int n_windows, int max_window_tokens, int d, int dtype_bytes);
 
-// cu_target / win_remove / status / dir / counts_done (all optional): the per-window counts of a token budget
-// (launch_window_counts, mode 2) in the same launch where the kernel allows it; *counts_done says whether it did.
-hipError_t launch_build_windows(const int32_t *cu_vis, const int32_t *pos, const int32_t *new_index,
-                                const int32_t *cu_out, int batch, int max_seq, int tiles,
-                                int grid_h, int grid_w, int w, int32_t *win_offsets, int32_t *win_tokens,
-                                const int32_t *cu_target, int32_t *win_remove, int32_t *status, int dir, bool *counts_done,
-                                hipStream_t stream);
+// The partition of one stage's tokens and, optionally, the per-window counts that go with it (host struct).
+struct WinArgs;
+struct WinSpec {
+  int tiles, grid_h, grid_w, w;
+  int32_t *win_offsets, *win_tokens;
+  int count_mode;             // -1: no counts; otherwise a mode of launch_window_counts
+  double rho;
+  int dir, n_windows;         // (with counts)
+  const int32_t *cu_target;
+  int32_t *win_remove, *status;
+};
+// new_index / cu_out: the "next stage" form.  *counts_done says whether the counts were part of the launch (the kernel
+// that sorts leaves them to the caller).
+hipError_t launch_build_windows(const WinSpec &spec, const int32_t *cu_vis, const int32_t *pos, const int32_t *new_index,
+                                const int32_t *cu_out, int batch, int max_seq, bool *counts_done, hipStream_t stream);
+// arguments and LDS bytes of the same partition as a guest of another launch; 0 bytes: not possible
+size_t make_win_args(const WinSpec &spec, const int32_t *cu_vis, const int32_t *pos, const int32_t *new_index,
+                     const int32_t *cu_out, int batch, int max_seq, WinArgs *out);
 
-// windows + their counts from per-sequence target lengths, in one launch where possible (lk_api.hip); a lightkv_status
+// Windows + their counts (lk_api.hip), and the fused merge with the next stage's windows beside it; a lightkv_status
 int build_windows_with_counts(int32_t batch, const int32_t *h_cu_vis, const int32_t *cu_vis, const int32_t *pos,
-                              const int32_t *new_index, const int32_t *cu_vis_out, int32_t tiles, int32_t grid_h,
-                              int32_t grid_w, int32_t w, int32_t *win_offsets, int32_t *win_tokens, int32_t n_windows,
-                              int32_t direction, const int32_t *cu_target, int32_t *win_remove, int32_t *status,
-                              void *stream);
+                              const WinSpec &spec, void *stream);
+int aggregate_compact_with_windows(const lightkv_problem *p, const int32_t *new_index, const int32_t *grp_offsets,
+                                   const int32_t *grp_src, const float *xi, const void *X, int64_t ldx, const void *K,
+                                   int64_t ldk, const void *V, int64_t ldv, const int32_t *pos, void *X_out, void *K_out,
+                                   void *V_out, int32_t *pos_out, float *x_sqnorm_out, int64_t out_rows,
+                                   const int32_t *cu_vis_out, const WinSpec *next, void *stream);
 
 // per-window counts from a ratio (mode 0: tokens, 1: edges) or from per-sequence target lengths (mode 2)
 hipError_t launch_window_counts(int batch, int win_per_seq, const int32_t *win_offsets, int mode, int dir, double rho,
@@ -125,7 +140,12 @@ hipError_t launch_pair_select(int n_windows, int max_window, int sum_n, const in
                               float *best_fd, int32_t *best_dst, int32_t *dst, int32_t *cnt, int32_t *src_rank,
                               hipStream_t stream);
 
-// ---- scores + selection in three launches on one stream (lk_fused.hip); windows of at most 64 tokens
+// Whether lightkv_score_select with xi requested runs this step on the caller's stream alone (lk_api.hip).
+bool score_select_one_stream(const lightkv_problem *p);
+
+// ---- scores + selection on one stream, the k-th kernels of the xi chain and of the FD chain sharing a launch
+// (lk_fused.hip): three launches for windows of at most 64 tokens, the window selection as a fourth (or fourth and
+// fifth) for larger ones
 struct XiArgs;
 struct XiPlan;
 hipError_t launch_score_select_fused(const XiPlan &xp, const FdPlan &fp, int dtype, int xi_mode, int batch, int heads,
@@ -136,7 +156,7 @@ hipError_t launch_score_select_fused(const XiPlan &xp, const FdPlan &fp, int dty
                                      const int32_t *win_offsets, const int32_t *win_tokens, const int32_t *win_remove,
                                      float *partial, float *best_fd, int32_t *best_dst, int32_t *dst, int32_t *cnt,
                                      int32_t *src_rank, int32_t *new_index, int32_t *grp_offsets, int32_t *grp_src,
-                                     int32_t *cu_vis_out, hipStream_t stream);
+                                     int32_t *cu_vis_out, int max_window, hipStream_t stream);
 // index scan with the head sum of xi in the same launch (x: arguments of the xi passes)
 hipError_t launch_select_scan_heads(int batch, int sum_n, const int32_t *cu_vis, const int32_t *dst, int32_t *new_index,
                                     int32_t *grp_offsets, int32_t *grp_src, int32_t *cu_vis_out, const int32_t *cnt,
@@ -172,6 +192,12 @@ hipError_t launch_select(int n_windows, int max_window_tokens, int batch, int su
                          int32_t *new_index, int32_t *grp_offsets, int32_t *grp_src, int32_t *cu_vis_out, int32_t *cnt,
                          int32_t *src_rank, int dir, hipStream_t stream);
 
+// the window half of lightkv_select alone: dst, cnt, src_rank from the scores
+hipError_t launch_select_windows(int n_windows, int max_window_tokens, int sum_n, const int32_t *win_offsets,
+                                 const int32_t *win_tokens, const int32_t *win_remove, const unsigned long long *keys,
+                                 int key_mt, int key_nt, float *best_fd, int32_t *best_dst, int32_t *dst, int32_t *cnt,
+                                 int32_t *src_rank, int dir, hipStream_t stream);
+
 // the scan half of lightkv_select alone (dst, cnt, src_rank already written)
 hipError_t launch_select_scan(int batch, int sum_n, const int32_t *cu_vis, const int32_t *dst, int32_t *new_index,
                               int32_t *grp_offsets, int32_t *grp_src, int32_t *cu_vis_out, const int32_t *cnt,
@@ -187,13 +213,13 @@ struct RowTensors {
 // mode 0: aggregate in place (out == in, only rows with sources are written)
 // mode 1: compact (copy staying rows to new_index)      mode 2: aggregate + compact
 // x_sqnorm_out (optional, modes 1 and 2): |x|^2 of every output row of the first tensor, fp32
-hipError_t launch_rows(int mode, int dtype, int d, int sum_n, const RowTensors &t, const int32_t *new_index,
+// tail_rows (modes 1 and 2): rows behind the vision span, input row sum_n + j -> output row cu_vis_out[batch] + j
+// win (mode 2, optional): the next stage's windows, built by `batch` workgroups of the same launch with win_lds bytes of
+// LDS each (at most ROWS_WIN_LDS_MAX: the row workgroups of the launch reserve them too)
+constexpr size_t ROWS_WIN_LDS_MAX = 32 * 1024;
+hipError_t launch_rows(int mode, int dtype, int d, int sum_n, int batch, const RowTensors &t, const int32_t *new_index,
                        const int32_t *grp_offsets, const int32_t *grp_src, const float *xi, const int32_t *pos,
-                       int32_t *pos_out, float *x_sqnorm_out, int64_t out_rows, hipStream_t stream);
-
-// rows behind the vision span (modes 1 and 2): input row sum_n + j -> output row cu_vis_out[batch] + j
-hipError_t launch_tail_rows(int dtype, int d, int sum_n, int batch, const RowTensors &t, const int32_t *pos,
-                            int32_t *pos_out, const int32_t *cu_vis_out, int64_t tail_rows, int64_t out_rows,
-                            hipStream_t stream);
+                       int32_t *pos_out, float *x_sqnorm_out, int64_t out_rows, int64_t tail_rows,
+                       const int32_t *cu_vis_out, const WinArgs *win, size_t win_lds, hipStream_t stream);
 
 }  // namespace lk

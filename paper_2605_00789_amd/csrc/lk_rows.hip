@@ -5,8 +5,7 @@
 // A token b with sources a_1..a_m becomes  y_b + sum_a w_a (y_a - y_b),  w_a = xi_a / (xi_b + sum xi_a),
 // which equals the xi-weighted mean of the equation and returns y_b bit for bit when all rows are equal.
 // Sources are visited in ascending token order (grp_src), so results are reproducible run to run.
-#include "lk_common.h"
-#include "lk_launch.h"
+#include "lk_win_body.h"
 
 namespace lk {
 
@@ -18,8 +17,12 @@ struct RowArgs {
   int32_t *pos_out;
   float *x_sqnorm_out;   // optional: |x|^2 of every output row of tensor 0 (as stored), fp32
   const float *xi;
-  int d, sum_n, mode;
+  int d, sum_n, batch;
   int64_t out_rows;   // capacity of the compacted outputs; rows beyond it are dropped
+  int64_t tail_rows;  // rows behind the vision span (modes 1 and 2)
+  const int32_t *cu_vis_out;   // with tail_rows: cu_vis_out[batch] vision rows stay
+  int n_win_blocks;   // workgroups in front of the row workgroups that build the next stage's windows
+  int segs;           // segments per row
 };
 
 template <typename T> struct RowIO;
@@ -50,12 +53,18 @@ template <> struct RowIO<float> {
   }
 };
 
-// One wave = one row of one tensor (4 rows per workgroup).  Index loads go out together, then the whole row
-// (8 x 16 bytes per lane for an 8 KB row) is in flight before anything is consumed; all loads are
-// unconditional (clamped addresses) so that the compiler never has to wait inside a branch.
+// One wave = one segment of one row of one tensor (4 rows per workgroup): U chunks of 16 bytes per lane, so that the
+// whole segment is in flight before anything is consumed.  A row of more than 8 chunks per lane (8 KB) is cut into
+// equal segments for as many waves: two passes of one wave over a 10 KB row are two trips to memory in a row (2304 rows
+// of 5120 bf16 and 200 text rows: 52 + 6 us in two launches -> 41 us).  All loads are unconditional (clamped addresses) so that the
+// compiler never has to wait inside a branch.
 constexpr int ROWS_PER_WG = ROW_THREADS / WAVE;
-constexpr int ROW_UNROLL = 8;   // 16-byte chunks per lane and pass
+// 16-byte chunks per lane and segment, at most.  Streaming sizes (HBM bound) want few long segments: 21312 rows of
+// 8 KB and 5352 behind them 199 us against 204 us with rows cut in two; cache-resident ones want more waves with shorter lives:
+// three stages of 2880 tokens 238 us a step with whole rows, 234 us with rows cut in two.
+constexpr int ROW_MAX_U_STREAM = 8, ROW_MAX_U = 5;
 constexpr int64_t ROWS_STREAM_OUT_BYTES = 128ll << 20;   // inputs beyond this: nontemporal output stores
+constexpr int ROWS_WIN_KEEP = 12;   // passes of 256 tokens the window partition keeps in registers (3072 tokens)
 
 // MODE 0: aggregate in place   1: compact   2: aggregate + compact
 //
@@ -64,29 +73,57 @@ constexpr int64_t ROWS_STREAM_OUT_BYTES = 128ll << 20;   // inputs beyond this: 
 //   round 2  the source list of the group
 //   round 3  xi of the sources and the rows of the first two sources, together
 // A row without sources is stored after round 1.  Third and later sources of a group (rare) are fetched one by one.
+//
+// Two guests share the launch, because a launch or a stream fork of their own costs as much as they do:
+//   rows behind the vision span (the prompt's text, Steps 4-5): rows sum_n .. sum_n + tail_rows of the inputs move to
+//   output row n' + j, n' = cu_vis_out[batch] being read from the device;
+//   the next stage's windows: the first n_win_blocks workgroups build them (they need pos and new_index only).
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+template <bool STREAM>
+__device__ __forceinline__ void store16(char *p, const uint4 &v) {
+  const u32x4 t4 = {v.x, v.y, v.z, v.w};
+  if (STREAM) __builtin_nontemporal_store(t4, reinterpret_cast<u32x4 *>(p));
+  else *reinterpret_cast<u32x4 *>(p) = t4;
+}
+
+// Registers: 8 chunks a lane fit three waves per SIMD (167; left alone the compiler takes 179 = two waves, merge of 21312
+// rows 230 us against 199), 4 need 140 and spill when held to four waves (2880 tokens 234 against 229 us a step).
+//
 // STREAM: the output rows are stored nontemporally (a template parameter: as a run-time choice between two stores of
 // the same value the compiler merges them into one plain store)
-template <typename T, int MODE, bool STREAM>
-__global__ __launch_bounds__(ROW_THREADS) void rows_kernel(RowArgs g) {
+template <typename T, int MODE, bool STREAM, int U>
+__global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 : 4)) void rows_kernel(RowArgs g, WinArgs wn) {
   using IO = RowIO<T>;
   constexpr int N = IO::N;
   constexpr int BYTES = Elem<T>::BYTES;
-  constexpr int HU = ROW_UNROLL / 2;
+  constexpr int HU = U > 4 ? (U + 1) / 2 : U;   // chunks of a merge in flight per source
+  if constexpr (MODE == 2) {
+    if ((int)blockIdx.x < g.n_win_blocks) {
+      if (blockIdx.y > 0) return;
+      extern __shared__ __attribute__((aligned(16))) char win_lds[];
+      build_windows_body<ROW_THREADS, ROWS_WIN_KEEP>(wn, blockIdx.x, win_lds);
+      return;
+    }
+  }
   const int lane = threadIdx.x & 63;
-  const int b = blockIdx.x * ROWS_PER_WG + (threadIdx.x >> 6);
-  const int which = blockIdx.y;
-  if (b >= g.sum_n) return;
+  const int64_t b = (int64_t)((int)blockIdx.x - g.n_win_blocks) * ROWS_PER_WG + (threadIdx.x >> 6);
+  const int which = blockIdx.y / g.segs;                   // grid y: tensor and segment
+  int seg = blockIdx.y - which * g.segs;
+  if (b >= g.sum_n + g.tail_rows) return;
   const char *in = static_cast<const char *>(g.t.in[which]);
   char *out = static_cast<char *>(g.t.out[which]);
   const int64_t ld_in = g.t.ld_in[which] * BYTES;
   const int n_chunks = g.d / N;
-  const bool single_pass = n_chunks <= WAVE * ROW_UNROLL;
+  const char *row_in = in ? in + b * ld_in : nullptr;
+  // |x|^2 of the row as it is stored (tensor 0 only, on request): the next stage's feature divergence wants it, and
+  // here the row is in registers anyway.  Same order of summation as the stand-alone pass over X, so one wave takes all
+  // segments of such a row in turn.
+  const bool want_sq = MODE != 0 && which == 0 && g.x_sqnorm_out != nullptr && b < g.sum_n;
+  if (want_sq && seg > 0) return;
+  const int seg_end = want_sq ? g.segs : seg + 1;
 
   // round 1 (the in-place mode touches few rows: it looks at the group bounds first instead of fetching every row)
-  uint4 v[ROW_UNROLL];
-  const char *row_in = in ? in + (int64_t)b * ld_in : nullptr;
   if (MODE == 0 && g.grp_offsets[b + 1] == g.grp_offsets[b]) return;
   // A row that is merged away is fetched by its own wave as well as by its target's (8-11 % more bytes read): looking
   // at new_index first would save those bytes but puts one more dependent load in front of every row, and the longer
@@ -94,28 +131,45 @@ __global__ __launch_bounds__(ROW_THREADS) void rows_kernel(RowArgs g) {
   // Large outputs are stored nontemporally: they cannot stay cached until the next stage reads them, and kept out of
   // the caches they leave them to the kernels that run next (batch of 16: step -3.6 %; on the cache-resident sizes the
   // same stores cost +2.4 %: the next stage's kernels then find their inputs in HBM).
-  if (in != nullptr) {
+  uint4 v[U];
+  auto load_row = [&](const char *row, int sg, uint4 (&dst)[U]) {
 #pragma unroll
-    for (int u = 0; u < ROW_UNROLL; ++u) {
-      const int c = u * WAVE + lane;
-      v[u] = ld16(row_in + (int64_t)(c < n_chunks ? c : n_chunks - 1) * 16);
+    for (int u = 0; u < U; ++u) {
+      const int c = (sg * U + u) * WAVE + lane;
+      dst[u] = ld16(row + (int64_t)(c < n_chunks ? c : n_chunks - 1) * 16);
     }
+  };
+  if (in != nullptr) load_row(row_in, seg, v);
+  if (MODE != 0 && b >= g.sum_n) {   // a row behind the vision span
+    int n_keep = g.cu_vis_out[g.batch];
+    n_keep = n_keep < 0 ? 0 : (n_keep > g.sum_n ? g.sum_n : n_keep);
+    const int64_t out_row = n_keep + (b - g.sum_n);
+    if (out_row >= g.out_rows) return;   // no room in the output: dropped, never written out of bounds
+    if (which == 0 && seg == 0 && lane == 0 && g.pos && g.pos_out) g.pos_out[out_row] = g.pos[b];
+    if (in == nullptr) return;
+    char *row_out = out + out_row * g.t.ld_out[which] * BYTES;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = (seg * U + u) * WAVE + lane;
+      if (c < n_chunks) store16<STREAM>(row_out + (int64_t)c * 16, v[u]);
+    }
+    return;
   }
   float xb = 0.f;
   if (MODE != 1) xb = g.xi[b];
-  int out_row = b, s0 = 0, s1 = 0;
+  int out_row = (int)b, s0 = 0, s1 = 0;
   if (MODE != 0) out_row = g.new_index[b];
   if (MODE != 1) { s0 = g.grp_offsets[b]; s1 = g.grp_offsets[b + 1]; }
   const int m = s1 - s0;
   if (MODE != 0 && (out_row < 0 || out_row >= g.out_rows)) return;   // merged away, or no room in the output
   if (MODE == 0 && m == 0) return;                                    // in place: nothing to do for this row
-  if (MODE != 0 && which == 0 && lane == 0 && g.pos && g.pos_out) g.pos_out[out_row] = g.pos[b];
+  if (MODE != 0 && which == 0 && seg == 0 && lane == 0 && g.pos && g.pos_out) g.pos_out[out_row] = g.pos[b];
   if (in == nullptr) return;
   char *row_out = out + (int64_t)out_row * g.t.ld_out[which] * BYTES;
 
   // rounds 2 and 3: lane s holds source s and its weight (groups beyond 64 sources take the slow loop)
-  int a_l = b;
-  float w_l = 0.f;
+  int a_l = (int)b;
+  float w_l = 0.f, w0 = 0.f, w1 = 0.f;
   const char *row_a0 = row_in, *row_a1 = row_in;
   if (MODE != 1 && m > 0) {
     const int mm = m < WAVE ? m : WAVE;
@@ -124,29 +178,21 @@ __global__ __launch_bounds__(ROW_THREADS) void rows_kernel(RowArgs g) {
     row_a1 = in + (int64_t)__shfl(a_l, mm > 1 ? 1 : 0, 64) * ld_in;
   }
 
-  // |x|^2 of the row as it is stored (tensor 0 only, on request): the next stage's feature divergence wants it, and
-  // here the row is in registers anyway.  Same order of summation as the stand-alone pass over X.
-  const bool want_sq = MODE != 0 && which == 0 && g.x_sqnorm_out != nullptr;
   float sq = 0.f;
-  for (int c0 = 0; c0 < n_chunks; c0 += WAVE * ROW_UNROLL) {
-    if (c0 > 0) {   // rows longer than one pass: later passes reload
-#pragma unroll
-      for (int u = 0; u < ROW_UNROLL; ++u) {
-        const int c = c0 + u * WAVE + lane;
-        v[u] = ld16(row_in + (int64_t)(c < n_chunks ? c : n_chunks - 1) * 16);
-      }
-    }
+  bool first = true;
+  for (; seg < seg_end; ++seg) {
+    if (!first) load_row(row_in, seg, v);
     if (MODE != 1 && m > 0) {
-      // first half of the pass: its source chunks go out together with the xi loads below
+      // first half of the segment: its source chunks go out together with the xi loads below
       uint4 va0[HU], va1[HU];
 #pragma unroll
       for (int u = 0; u < HU; ++u) {
-        const int c = c0 + u * WAVE + lane;
+        const int c = (seg * U + u) * WAVE + lane;
         const int64_t o = (int64_t)(c < n_chunks ? c : n_chunks - 1) * 16;
         va0[u] = ld16(row_a0 + o);
         va1[u] = ld16(row_a1 + o);
       }
-      if (c0 == 0) {
+      if (first) {
         const int mm = m < WAVE ? m : WAVE;
         float x_l = g.xi[a_l];
         x_l = lane < mm ? x_l : 0.f;
@@ -157,29 +203,33 @@ __global__ __launch_bounds__(ROW_THREADS) void rows_kernel(RowArgs g) {
         for (int s = s0 + WAVE; s < s1; ++s) den += g.xi[g.grp_src[s]];
         w_l = x_l / den;
         if (m > WAVE) w_l = 1.f / den;   // slow path keeps 1/den instead
+        w0 = (m <= WAVE) ? __shfl(w_l, 0, 64) : g.xi[__shfl(a_l, 0, 64)] * __shfl(w_l, 0, 64);
+        w1 = (m <= 1) ? 0.f : ((m <= WAVE) ? __shfl(w_l, 1, 64) : g.xi[g.grp_src[s0 + 1]] * __shfl(w_l, 0, 64));
       }
-      const float w0 = (m <= WAVE) ? __shfl(w_l, 0, 64) : g.xi[__shfl(a_l, 0, 64)] * __shfl(w_l, 0, 64);
-      const float w1 = (m <= 1) ? 0.f : ((m <= WAVE) ? __shfl(w_l, 1, 64) : g.xi[g.grp_src[s0 + 1]] * __shfl(w_l, 0, 64));
 #pragma unroll
-      for (int hb = 0; hb < ROW_UNROLL; hb += HU) {
+      for (int hb = 0; hb < U; hb += HU) {
         if (hb > 0) {
 #pragma unroll
           for (int u = 0; u < HU; ++u) {
-            const int c = c0 + (hb + u) * WAVE + lane;
-            const int64_t o = (int64_t)(c < n_chunks ? c : n_chunks - 1) * 16;
-            va0[u] = ld16(row_a0 + o);
-            va1[u] = ld16(row_a1 + o);
+            if (hb + u < U) {
+              const int c = (seg * U + hb + u) * WAVE + lane;
+              const int64_t o = (int64_t)(c < n_chunks ? c : n_chunks - 1) * 16;
+              va0[u] = ld16(row_a0 + o);
+              va1[u] = ld16(row_a1 + o);
+            }
           }
         }
         float acc[HU][N];   // y_b stays packed in v[] and is unpacked where it is used
 #pragma unroll
         for (int u = 0; u < HU; ++u) {
-          float y0[N], y1[N], yb[N];
-          IO::unpack(v[hb + u], yb);
-          IO::unpack(va0[u], y0);
-          IO::unpack(va1[u], y1);
+          if (hb + u < U) {
+            float y0[N], y1[N], yb[N];
+            IO::unpack(v[hb + u], yb);
+            IO::unpack(va0[u], y0);
+            IO::unpack(va1[u], y1);
 #pragma unroll
-          for (int e = 0; e < N; ++e) acc[u][e] = fmaf(w1, y1[e] - yb[e], fmaf(w0, y0[e] - yb[e], yb[e]));
+            for (int e = 0; e < N; ++e) acc[u][e] = fmaf(w1, y1[e] - yb[e], fmaf(w0, y0[e] - yb[e], yb[e]));
+          }
         }
         for (int s = 2; s < m; ++s) {   // third and later sources
           int a;
@@ -195,122 +245,90 @@ __global__ __launch_bounds__(ROW_THREADS) void rows_kernel(RowArgs g) {
           uint4 va[HU];
 #pragma unroll
           for (int u = 0; u < HU; ++u) {
-            const int c = c0 + (hb + u) * WAVE + lane;
-            va[u] = ld16(row_a + (int64_t)(c < n_chunks ? c : n_chunks - 1) * 16);
+            if (hb + u < U) {
+              const int c = (seg * U + hb + u) * WAVE + lane;
+              va[u] = ld16(row_a + (int64_t)(c < n_chunks ? c : n_chunks - 1) * 16);
+            }
           }
 #pragma unroll
           for (int u = 0; u < HU; ++u) {
-            float ya[N], yb[N];
-            IO::unpack(va[u], ya);
-            IO::unpack(v[hb + u], yb);
+            if (hb + u < U) {
+              float ya[N], yb[N];
+              IO::unpack(va[u], ya);
+              IO::unpack(v[hb + u], yb);
 #pragma unroll
-            for (int e = 0; e < N; ++e) acc[u][e] = fmaf(w, ya[e] - yb[e], acc[u][e]);
+              for (int e = 0; e < N; ++e) acc[u][e] = fmaf(w, ya[e] - yb[e], acc[u][e]);
+            }
           }
         }
 #pragma unroll
-        for (int u = 0; u < HU; ++u) v[hb + u] = IO::pack(acc[u]);
+        for (int u = 0; u < HU; ++u)
+          if (hb + u < U) v[hb + u] = IO::pack(acc[u]);
       }
     }
 #pragma unroll
-    for (int u = 0; u < ROW_UNROLL; ++u) {
-      const int c = c0 + u * WAVE + lane;
-      if (c < n_chunks) {
-        u32x4 *dst = reinterpret_cast<u32x4 *>(row_out + (int64_t)c * 16);
-        const u32x4 t4 = {v[u].x, v[u].y, v[u].z, v[u].w};
-        if (STREAM) __builtin_nontemporal_store(t4, dst);
-        else *dst = t4;
-      }
+    for (int u = 0; u < U; ++u) {
+      const int c = (seg * U + u) * WAVE + lane;
+      if (c < n_chunks) store16<STREAM>(row_out + (int64_t)c * 16, v[u]);
     }
     if (want_sq) {
 #pragma unroll
-      for (int u = 0; u < ROW_UNROLL; ++u) {
-        const int c = c0 + u * WAVE + lane;
+      for (int u = 0; u < U; ++u) {
+        const int c = (seg * U + u) * WAVE + lane;
         const float t = BYTES == 2 ? sumsq_chunk_bf16(v[u]) : sumsq_chunk_f32(v[u]);
         sq += (c < n_chunks) ? t : 0.f;
       }
     }
+    first = false;
   }
   if (want_sq) {
     sq = wave_sum_butterfly(sq);
     if (lane == 0) g.x_sqnorm_out[out_row] = sq;
   }
-  (void)single_pass;
 }
 
-// Rows that trail the vision span in the caller's tensors (the prompt's text behind the image, Steps 4-5: the sequence
-// is rebuilt behind the shorter vision span): row sum_n + j of the input moves to row n' + j of the output, n' being
-// the number of vision rows that stay, read from the device (cu_vis_out[batch]).  One wave per (row, tensor).
-struct TailArgs {
-  RowTensors t;
-  const int32_t *pos, *cu_vis_out;
-  int32_t *pos_out;
-  int d, sum_n, batch, elem_bytes;
-  int64_t tail_rows, out_rows;
-};
-
-__global__ __launch_bounds__(ROW_THREADS) void tail_rows_kernel(TailArgs g) {
-  const int lane = threadIdx.x & 63;
-  const int64_t j = (int64_t)blockIdx.x * ROWS_PER_WG + (threadIdx.x >> 6);
-  const int which = blockIdx.y;
-  if (j >= g.tail_rows) return;
-  int n_keep = g.cu_vis_out[g.batch];
-  n_keep = n_keep < 0 ? 0 : (n_keep > g.sum_n ? g.sum_n : n_keep);
-  const int64_t out_row = (int64_t)n_keep + j;
-  if (out_row >= g.out_rows) return;   // no room in the output: dropped, never written out of bounds
-  if (which == 0 && lane == 0 && g.pos && g.pos_out) g.pos_out[out_row] = g.pos[g.sum_n + j];
-  const char *in = static_cast<const char *>(g.t.in[which]);
-  char *out = static_cast<char *>(g.t.out[which]);
-  if (!in) return;
-  const char *row_in = in + ((int64_t)g.sum_n + j) * g.t.ld_in[which] * g.elem_bytes;
-  char *row_out = out + out_row * g.t.ld_out[which] * g.elem_bytes;
-  const int n_chunks = g.d * g.elem_bytes / 16;
-  for (int c0 = 0; c0 < n_chunks; c0 += WAVE * ROW_UNROLL) {
-    uint4 v[ROW_UNROLL];
-#pragma unroll
-    for (int u = 0; u < ROW_UNROLL; ++u) {
-      const int c = c0 + u * WAVE + lane;
-      v[u] = ld16(row_in + (int64_t)(c < n_chunks ? c : n_chunks - 1) * 16);
-    }
-#pragma unroll
-    for (int u = 0; u < ROW_UNROLL; ++u) {
-      const int c = c0 + u * WAVE + lane;
-      if (c < n_chunks) *reinterpret_cast<uint4 *>(row_out + (int64_t)c * 16) = v[u];
-    }
-  }
+template <typename T, int U>
+static void launch_rows_u(int mode, bool stream_out, const dim3 &grid, size_t lds, hipStream_t stream, const RowArgs &g,
+                          const WinArgs &wn) {
+  const dim3 block(ROW_THREADS);
+  if (mode == 0) hipLaunchKernelGGL((rows_kernel<T, 0, false, U>), grid, block, lds, stream, g, wn);
+  else if (mode == 1 && stream_out) hipLaunchKernelGGL((rows_kernel<T, 1, true, U>), grid, block, lds, stream, g, wn);
+  else if (mode == 1) hipLaunchKernelGGL((rows_kernel<T, 1, false, U>), grid, block, lds, stream, g, wn);
+  else if (stream_out) hipLaunchKernelGGL((rows_kernel<T, 2, true, U>), grid, block, lds, stream, g, wn);
+  else hipLaunchKernelGGL((rows_kernel<T, 2, false, U>), grid, block, lds, stream, g, wn);
 }
 
-hipError_t launch_tail_rows(int dtype, int d, int sum_n, int batch, const RowTensors &t, const int32_t *pos,
-                            int32_t *pos_out, const int32_t *cu_vis_out, int64_t tail_rows, int64_t out_rows,
-                            hipStream_t stream) {
-  if (tail_rows <= 0) return hipSuccess;
-  TailArgs g{};
-  g.t = t; g.pos = pos; g.pos_out = pos_out; g.cu_vis_out = cu_vis_out; g.d = d; g.sum_n = sum_n; g.batch = batch;
-  g.elem_bytes = dtype == 1 ? 2 : 4; g.tail_rows = tail_rows; g.out_rows = out_rows;
-  const dim3 grid((unsigned)((tail_rows + ROWS_PER_WG - 1) / ROWS_PER_WG), 3);
-  hipLaunchKernelGGL(tail_rows_kernel, grid, dim3(ROW_THREADS), 0, stream, g);
-  return hipGetLastError();
-}
-
-hipError_t launch_rows(int mode, int dtype, int d, int sum_n, const RowTensors &t, const int32_t *new_index,
+hipError_t launch_rows(int mode, int dtype, int d, int sum_n, int batch, const RowTensors &t, const int32_t *new_index,
                        const int32_t *grp_offsets, const int32_t *grp_src, const float *xi, const int32_t *pos,
-                       int32_t *pos_out, float *x_sqnorm_out, int64_t out_rows, hipStream_t stream) {
-  if (sum_n == 0) return hipSuccess;
+                       int32_t *pos_out, float *x_sqnorm_out, int64_t out_rows, int64_t tail_rows,
+                       const int32_t *cu_vis_out, const WinArgs *win, size_t win_lds, hipStream_t stream) {
+  if (mode == 0) tail_rows = 0;
+  if (sum_n + tail_rows == 0 && !win) return hipSuccess;
   RowArgs g{};
   g.x_sqnorm_out = x_sqnorm_out;
   g.t = t; g.new_index = new_index; g.grp_offsets = grp_offsets; g.grp_src = grp_src; g.pos = pos;
-  g.pos_out = pos_out; g.xi = xi; g.d = d; g.sum_n = sum_n; g.mode = mode; g.out_rows = out_rows;
+  g.pos_out = pos_out; g.xi = xi; g.d = d; g.sum_n = sum_n; g.out_rows = out_rows;
+  g.tail_rows = tail_rows; g.cu_vis_out = cu_vis_out; g.batch = batch;
+  g.n_win_blocks = win ? batch : 0;
   int n_tensors = 0;
   for (int i = 0; i < 3; ++i) n_tensors += t.in[i] != nullptr;
   // nontemporal output stores once the tensors are far beyond what stays cached until the next stage reads them
   const bool stream_out = mode != 0 && (int64_t)sum_n * d * (dtype == 1 ? 2 : 4) * n_tensors > ROWS_STREAM_OUT_BYTES;
-  const dim3 grid((unsigned)((sum_n + ROWS_PER_WG - 1) / ROWS_PER_WG), 3);
-#define LK_ROWS(TT)                                                                                                \
-  do {                                                                                                             \
-    if (mode == 0) hipLaunchKernelGGL((rows_kernel<TT, 0, false>), grid, dim3(ROW_THREADS), 0, stream, g);        \
-    else if (mode == 1 && stream_out) hipLaunchKernelGGL((rows_kernel<TT, 1, true>), grid, dim3(ROW_THREADS), 0, stream, g);  \
-    else if (mode == 1) hipLaunchKernelGGL((rows_kernel<TT, 1, false>), grid, dim3(ROW_THREADS), 0, stream, g);   \
-    else if (stream_out) hipLaunchKernelGGL((rows_kernel<TT, 2, true>), grid, dim3(ROW_THREADS), 0, stream, g);   \
-    else hipLaunchKernelGGL((rows_kernel<TT, 2, false>), grid, dim3(ROW_THREADS), 0, stream, g);                  \
+  // chunks per lane of a whole row; rows beyond max_u are cut into equal segments, rounded up to a size there is
+  const int per_lane = (d * (dtype == 1 ? 2 : 4) / 16 + WAVE - 1) / WAVE;
+  const int max_u = stream_out ? ROW_MAX_U_STREAM : ROW_MAX_U;
+  g.segs = (per_lane + max_u - 1) / max_u;
+  const int u = (per_lane + g.segs - 1) / g.segs;
+  const dim3 grid((unsigned)(g.n_win_blocks + (sum_n + tail_rows + ROWS_PER_WG - 1) / ROWS_PER_WG), (unsigned)(3 * g.segs));
+  const WinArgs wn = win ? *win : WinArgs{};
+  const size_t lds = win ? win_lds : 0;
+#define LK_ROWS(TT)                                                                       \
+  do {                                                                                    \
+    if (u <= 1) launch_rows_u<TT, 1>(mode, stream_out, grid, lds, stream, g, wn);         \
+    else if (u <= 2) launch_rows_u<TT, 2>(mode, stream_out, grid, lds, stream, g, wn);    \
+    else if (u <= 4) launch_rows_u<TT, 4>(mode, stream_out, grid, lds, stream, g, wn);    \
+    else if (u <= 5) launch_rows_u<TT, 5>(mode, stream_out, grid, lds, stream, g, wn);    \
+    else launch_rows_u<TT, 8>(mode, stream_out, grid, lds, stream, g, wn);                \
   } while (0)
   if (dtype == 1) LK_ROWS(bf16_t);
   else LK_ROWS(float);

@@ -1,7 +1,8 @@
 // The hierarchical schedule (paper Sec. 3.2.2) as one call: every stage's windows, scores, selection and merge are
-// enqueued through the library's own entry points, arranged over the caller's stream and two helper streams so that
-//   - xi (needs only Q and the stage's K rows) runs next to the feature-divergence chain and the selection,
-//   - the next stage's windows (need only pos and the selection) are built next to the merge of the rows.
+// enqueued through the library's own entry points, arranged so that
+//   - xi (needs only Q and the stage's K rows) runs next to the feature-divergence chain and the selection: in the same
+//     launches where lightkv_score_select can do that, on a helper stream otherwise,
+//   - the next stage's windows (need only pos and the selection) are built by workgroups of the merge's launch.
 // Nothing here launches a kernel itself or allocates device memory.  lightkv_compress_schedule never synchronises;
 // lightkv_compress_schedule_ratio (token counts that depend on the data) waits for the stream once per stage, to read
 // the sequence offsets the stage left.
@@ -16,11 +17,24 @@
 
 namespace {
 
-// Helper streams and events of one call: stream[0] runs xi, stream[1] builds the next stage's windows; event[0..3] =
-// fork_xi, join_xi, fork_win, join_win.  Sets come from a per-device pool (lk_helpers.h), distinct from the one
-// lightkv_score uses for its own fork.
-using Helpers = lk::HelperSet<2, 4>;
-enum { EV_FORK_XI = 0, EV_JOIN_XI = 1, EV_FORK_WIN = 2, EV_JOIN_WIN = 3 };
+// The helper stream (it runs xi) and the fork and join events of one call.  Sets come from a per-device pool
+// (lk_helpers.h), distinct from the one lightkv_score uses for its own fork.
+using Helpers = lk::HelperSet<1, 2, 1>;
+enum { EV_FORK_XI = 0, EV_JOIN_XI = 1 };
+
+// a stage's windows, with the counts that go with them in a schedule
+lk::WinSpec windows_of(const lightkv_stage &st, int32_t tiles, int32_t grid_h, int32_t grid_w, int count_mode, double rho) {
+  lk::WinSpec s{};
+  s.tiles = tiles; s.grid_h = grid_h; s.grid_w = grid_w; s.w = st.w;
+  s.win_offsets = st.win_offsets; s.win_tokens = st.win_tokens;
+  s.count_mode = count_mode; s.rho = rho; s.dir = st.problem.direction; s.n_windows = st.problem.n_windows;
+  s.cu_target = st.cu_vis_target; s.win_remove = st.win_remove; s.status = count_mode == LIGHTKV_COUNT_TARGET ? st.status : nullptr;
+  return s;
+}
+
+int count_mode_of(const lightkv_stage &st) {
+  return st.problem.match == LIGHTKV_MATCH_EDGE_TOPK ? LIGHTKV_COUNT_EDGES : LIGHTKV_COUNT_RATIO;
+}
 
 // `to` waits for everything enqueued on `from` so far
 bool order_after(hipStream_t to, hipStream_t from, hipEvent_t ev) {
@@ -57,45 +71,35 @@ extern "C" lightkv_status lightkv_compress_schedule(const lightkv_stage *stages,
   }
   hipStream_t main = static_cast<hipStream_t>(stream);
   std::unique_lock<std::mutex> guard;
-  Helpers *h = lk::acquire_helpers<2, 4>(main, guard);
+  Helpers *h = nullptr;               // taken by the first stage that forks
 
   const int d = stages[0].problem.d, head_dim = stages[0].problem.head_dim;
   const void *Xi = X, *Ki = K, *Vi = V;
   int64_t ldxi = ldx, ldki = ldk, ldvi = ldv;
   const int32_t *posi = pos;
   const float *sq = nullptr;          // squared norms of Xi, once a stage has produced them
-  bool windows_pending = false;       // this stage's windows are being built on the window stream
+  bool windows_ready = false;         // this stage's windows were built beside the previous stage's merge
   lightkv_status rc = LIGHTKV_OK;
-  bool xi_forked = false, win_forked = false;
   for (int s = 0; s < n_stages && rc == LIGHTKV_OK; ++s) {
     const lightkv_stage &st = stages[s];
     const lightkv_problem *p = &st.problem;
-    const int sum_n = p->h_cu_vis[p->batch];
-    const bool one_stream = p->max_window_tokens > 0 && p->max_window_tokens <= 64 &&
-                            sum_n <= LIGHTKV_ONE_STREAM_MAX_TOKENS;
-    // ---- xi on its helper stream (or, if there is none, first on the caller's)
-    xi_forked = false;
+    const bool one_stream = lk::score_select_one_stream(p);
+    // ---- xi on the helper stream (or, if there is none, first on the caller's)
+    bool xi_forked = false;
     if (!one_stream) {
       hipStream_t xs = main;
+      if (!h) h = lk::acquire_helpers<1, 2, 1>(main, guard);
       if (h && order_after(h->stream[0], main, h->event[EV_FORK_XI])) { xs = h->stream[0]; xi_forked = true; }
       else if (h) (void)hipGetLastError();
       rc = lightkv_score(p, nullptr, 0, nullptr, Q, q_tok_stride, q_head_stride, Ki, ldki, head_dim, LIGHTKV_XI_TEXT_QUERY,
                          nullptr, softmax_scale, st.xi, nullptr, nullptr, nullptr, 0, ws, ws_bytes, xs);
       if (xi_forked && hipEventRecord(h->event[EV_JOIN_XI], h->stream[0]) != hipSuccess) rc = rc == LIGHTKV_OK ? LIGHTKV_ERR_LAUNCH : rc;
     }
-    // ---- windows: built by the previous stage's tail, or here
-    if (windows_pending) {
-      if (win_forked && hipStreamWaitEvent(main, h->event[EV_JOIN_WIN], 0) != hipSuccess) rc = rc == LIGHTKV_OK ? LIGHTKV_ERR_LAUNCH : rc;
-    } else if (rc == LIGHTKV_OK) {
-      if (st.cu_vis_target)   // windows and their counts (one launch where the partition kernel allows it)
-        rc = (lightkv_status)lk::build_windows_with_counts(p->batch, p->h_cu_vis, p->cu_vis, posi, nullptr, nullptr, tiles,
-                                                           grid_h, grid_w, st.w, st.win_offsets, st.win_tokens, p->n_windows,
-                                                           p->direction, st.cu_vis_target, st.win_remove, st.status, main);
-      else
-        rc = lightkv_build_windows(p->batch, p->h_cu_vis, p->cu_vis, posi, tiles, grid_h, grid_w, st.w, st.win_offsets,
-                                   st.win_tokens, main);
-    }
-    windows_pending = false;
+    // ---- windows (and their counts from the stage's token budget), unless the previous stage's merge built them
+    if (!windows_ready && rc == LIGHTKV_OK)
+      rc = (lightkv_status)lk::build_windows_with_counts(
+          p->batch, p->h_cu_vis, p->cu_vis, posi,
+          windows_of(st, tiles, grid_h, grid_w, st.cu_vis_target ? LIGHTKV_COUNT_TARGET : -1, 0.0), main);
     // ---- feature divergence + selection
     if (rc == LIGHTKV_OK) {
       if (one_stream)
@@ -107,40 +111,25 @@ extern "C" lightkv_status lightkv_compress_schedule(const lightkv_stage *stages,
                                   st.xi, st.best_fd, st.best_dst, st.dst, st.new_index, st.grp_offsets, st.grp_src,
                                   st.cu_vis_out, ws, ws_bytes, main);
     }
-    // ---- the next stage's windows, next to the merge
-    win_forked = false;
-    if (rc == LIGHTKV_OK && s + 1 < n_stages) {
-      const lightkv_stage &nx = stages[s + 1];
-      hipStream_t wsx = main;
-      if (h && order_after(h->stream[1], main, h->event[EV_FORK_WIN])) { wsx = h->stream[1]; win_forked = true; }
-      else if (h) (void)hipGetLastError();
-      // ... with their counts: the next stage's budget over the windows as they now are (cu_vis_out of this stage is
-      // the next stage's cu_vis)
-      if (nx.cu_vis_target)
-        rc = (lightkv_status)lk::build_windows_with_counts(p->batch, p->h_cu_vis, p->cu_vis, posi, st.new_index, st.cu_vis_out,
-                                                           tiles, grid_h, grid_w, nx.w, nx.win_offsets, nx.win_tokens,
-                                                           nx.problem.n_windows, nx.problem.direction, nx.cu_vis_target,
-                                                           nx.win_remove, nx.status, wsx);
-      else
-        rc = lightkv_build_windows_next(p->batch, p->h_cu_vis, p->cu_vis, posi, st.new_index, st.cu_vis_out, tiles, grid_h,
-                                        grid_w, nx.w, nx.win_offsets, nx.win_tokens, wsx);
-      if (win_forked && hipEventRecord(h->event[EV_JOIN_WIN], h->stream[1]) != hipSuccess) rc = rc == LIGHTKV_OK ? LIGHTKV_ERR_LAUNCH : rc;
-      windows_pending = true;
-    }
-    // ---- join xi, merge and compact
+    // ---- join xi (whatever happened: nothing stays forked), then merge and compact; the next stage's windows follow from
+    // pos and the selection alone and are built by workgroups of the same launch (cu_vis_out of this stage is the next
+    // stage's cu_vis)
     if (xi_forked && hipStreamWaitEvent(main, h->event[EV_JOIN_XI], 0) != hipSuccess) rc = rc == LIGHTKV_OK ? LIGHTKV_ERR_LAUNCH : rc;
-    xi_forked = false;
-    if (rc == LIGHTKV_OK)
-      rc = lightkv_aggregate_compact(p, st.new_index, st.grp_offsets, st.grp_src, st.xi, Xi, ldxi, Ki, ldki, Vi, ldvi,
-                                     posi, st.X_out, st.K_out, st.V_out, st.pos_out, st.x_sqnorm_out, st.out_rows, 0, nullptr, main);
+    if (rc == LIGHTKV_OK) {
+      lk::WinSpec next{};
+      if (s + 1 < n_stages)
+        next = windows_of(stages[s + 1], tiles, grid_h, grid_w, stages[s + 1].cu_vis_target ? LIGHTKV_COUNT_TARGET : -1, 0.0);
+      rc = (lightkv_status)lk::aggregate_compact_with_windows(p, st.new_index, st.grp_offsets, st.grp_src, st.xi, Xi, ldxi, Ki,
+                                                              ldki, Vi, ldvi, posi, st.X_out, st.K_out, st.V_out, st.pos_out,
+                                                              st.x_sqnorm_out, st.out_rows, st.cu_vis_out,
+                                                              s + 1 < n_stages ? &next : nullptr, main);
+    }
+    windows_ready = true;
     Xi = st.X_out; Ki = st.K_out; Vi = st.V_out;
     ldxi = ldki = ldvi = d;
     posi = st.pos_out;
     sq = st.x_sqnorm_out;
   }
-  // whatever happened, nothing stays forked: the helper streams rejoin the caller's
-  if (xi_forked) (void)hipStreamWaitEvent(main, h->event[EV_JOIN_XI], 0);
-  if (win_forked) (void)hipStreamWaitEvent(main, h->event[EV_JOIN_WIN], 0);
   return rc;
 }
 
@@ -181,8 +170,6 @@ extern "C" lightkv_status lightkv_compress_schedule_ratio(const lightkv_stage *s
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(main, &cs) != hipSuccess) { (void)hipGetLastError(); return LIGHTKV_ERR_LAUNCH; }
   if (cs != hipStreamCaptureStatusNone) return LIGHTKV_ERR_UNSUPPORTED;   // the call waits for the stream: not capturable
-  std::unique_lock<std::mutex> guard;
-  Helpers *h = lk::acquire_helpers<2, 4>(main, guard);
 
   const int d = stages[0].problem.d, head_dim = stages[0].problem.head_dim;
   const void *Xi = X, *Ki = K, *Vi = V;
@@ -191,7 +178,7 @@ extern "C" lightkv_status lightkv_compress_schedule_ratio(const lightkv_stage *s
   const float *sq = nullptr;
   const int32_t *h_cu = stages[0].problem.h_cu_vis;   // offsets of the stage's input: on the host ...
   const int32_t *d_cu = stages[0].problem.cu_vis;     // ... and on the device
-  bool windows_pending = false, win_forked = false;
+  bool windows_ready = false;
   lightkv_status rc = LIGHTKV_OK;
   for (int s = 0; s < n_stages && rc == LIGHTKV_OK; ++s) {
     const lightkv_stage &st = stages[s];
@@ -211,42 +198,25 @@ extern "C" lightkv_status lightkv_compress_schedule_ratio(const lightkv_stage *s
       rc = lightkv_workspace_size(&q, &need);
     }
     if (rc == LIGHTKV_OK && (!ws || ws_bytes < need)) rc = LIGHTKV_ERR_WORKSPACE;
-    const int count_mode = q.match == LIGHTKV_MATCH_EDGE_TOPK ? LIGHTKV_COUNT_EDGES : LIGHTKV_COUNT_RATIO;
-    // ---- windows and their counts: built next to the previous stage's merge, or here
-    if (windows_pending) {
-      if (win_forked && hipStreamWaitEvent(main, h->event[EV_JOIN_WIN], 0) != hipSuccess) rc = rc == LIGHTKV_OK ? LIGHTKV_ERR_LAUNCH : rc;
-      win_forked = false;
-    } else if (rc == LIGHTKV_OK) {
-      rc = lightkv_build_windows(batch, h_cu, d_cu, posi, tiles, grid_h, grid_w, st.w, st.win_offsets, st.win_tokens, main);
-      if (rc == LIGHTKV_OK)
-        rc = lightkv_window_counts(batch, q.n_windows, st.win_offsets, count_mode, q.direction, rho[s], nullptr, nullptr,
-                                   st.win_remove, nullptr, main);
-    }
-    windows_pending = false;
+    // ---- windows and their counts, unless the previous stage's merge built them
+    if (!windows_ready && rc == LIGHTKV_OK)
+      rc = (lightkv_status)lk::build_windows_with_counts(batch, h_cu, d_cu, posi,
+                                                         windows_of(st, tiles, grid_h, grid_w, count_mode_of(st), rho[s]), main);
     // ---- scores (xi and feature divergence) and selection
     if (rc == LIGHTKV_OK)
       rc = lightkv_score_select(&q, Xi, ldxi, sq, Q, q_tok_stride, q_head_stride, Ki, ldki, head_dim, LIGHTKV_XI_TEXT_QUERY,
                                 nullptr, softmax_scale, st.xi, st.best_fd, st.best_dst, st.dst, st.new_index, st.grp_offsets,
                                 st.grp_src, st.cu_vis_out, ws, ws_bytes, main);
-    // ---- the next stage's windows and counts follow from the selection alone: next to the merge
-    if (rc == LIGHTKV_OK && s + 1 < n_stages) {
-      const lightkv_stage &nx = stages[s + 1];
-      const int nx_mode = nx.problem.match == LIGHTKV_MATCH_EDGE_TOPK ? LIGHTKV_COUNT_EDGES : LIGHTKV_COUNT_RATIO;
-      hipStream_t wsx = main;
-      if (h && order_after(h->stream[1], main, h->event[EV_FORK_WIN])) { wsx = h->stream[1]; win_forked = true; }
-      else if (h) (void)hipGetLastError();
-      rc = lightkv_build_windows_next(batch, h_cu, d_cu, posi, st.new_index, st.cu_vis_out, tiles, grid_h, grid_w, nx.w,
-                                      nx.win_offsets, nx.win_tokens, wsx);
-      if (rc == LIGHTKV_OK)
-        rc = lightkv_window_counts(batch, nx.problem.n_windows, nx.win_offsets, nx_mode, nx.problem.direction, rho[s + 1],
-                                   nullptr, nullptr, nx.win_remove, nullptr, wsx);
-      if (win_forked && hipEventRecord(h->event[EV_JOIN_WIN], h->stream[1]) != hipSuccess) rc = rc == LIGHTKV_OK ? LIGHTKV_ERR_LAUNCH : rc;
-      windows_pending = true;
+    // ---- merge and compact, the next stage's windows and counts beside it (they follow from the selection alone)
+    if (rc == LIGHTKV_OK) {
+      lk::WinSpec next{};
+      if (s + 1 < n_stages) next = windows_of(stages[s + 1], tiles, grid_h, grid_w, count_mode_of(stages[s + 1]), rho[s + 1]);
+      rc = (lightkv_status)lk::aggregate_compact_with_windows(&q, st.new_index, st.grp_offsets, st.grp_src, st.xi, Xi, ldxi, Ki,
+                                                              ldki, Vi, ldvi, posi, st.X_out, st.K_out, st.V_out, st.pos_out,
+                                                              st.x_sqnorm_out, st.out_rows, st.cu_vis_out,
+                                                              s + 1 < n_stages ? &next : nullptr, main);
     }
-    // ---- merge and compact
-    if (rc == LIGHTKV_OK)
-      rc = lightkv_aggregate_compact(&q, st.new_index, st.grp_offsets, st.grp_src, st.xi, Xi, ldxi, Ki, ldki, Vi, ldvi, posi,
-                                     st.X_out, st.K_out, st.V_out, st.pos_out, st.x_sqnorm_out, st.out_rows, 0, nullptr, main);
+    windows_ready = true;
     // ---- the offsets the stage left: the next stage's descriptor
     int32_t *h_out = h_cu_vis_out + (size_t)s * (batch + 1);
     if (rc == LIGHTKV_OK &&
@@ -271,6 +241,5 @@ extern "C" lightkv_status lightkv_compress_schedule_ratio(const lightkv_stage *s
     h_cu = h_out;
     d_cu = st.cu_vis_out;
   }
-  if (win_forked) (void)hipStreamWaitEvent(main, h->event[EV_JOIN_WIN], 0);   // nothing stays forked
   return rc;
 }

@@ -487,6 +487,12 @@ static hipError_t allow_scan_lds() {
   return hipSuccess;
 }
 
+// one workgroup per sequence once a batch is large enough for the single workgroup's serial passes to show, as long
+// as all of them fit the chip at once (one workgroup of this kernel fills a CU)
+static int scan_per_sequence(int batch, int sum_n) {
+  return (batch > 1 && batch <= SCAN_PER_SEQ_MAX_BATCH && sum_n >= SCAN_PER_SEQ_MIN_TOKENS) ? 1 : 0;
+}
+
 hipError_t launch_select_scan(int batch, int sum_n, const int32_t *cu_vis, const int32_t *dst, int32_t *new_index,
                               int32_t *grp_offsets, int32_t *grp_src, int32_t *cu_vis_out, const int32_t *cnt,
                               const int32_t *src_rank, hipStream_t stream) {
@@ -494,9 +500,7 @@ hipError_t launch_select_scan(int batch, int sum_n, const int32_t *cu_vis, const
   g.batch = batch; g.sum_n = sum_n; g.cu_vis = cu_vis;
   g.dst = const_cast<int32_t *>(dst); g.new_index = new_index; g.grp_offsets = grp_offsets; g.grp_src = grp_src;
   g.cu_vis_out = cu_vis_out; g.cnt = const_cast<int32_t *>(cnt); g.src_rank = const_cast<int32_t *>(src_rank);
-  // one workgroup per sequence once a batch is large enough for the single workgroup's serial passes to show, as long
-  // as all of them fit the chip at once (one workgroup of this kernel fills a CU)
-  g.per_seq = (batch > 1 && batch <= SCAN_PER_SEQ_MAX_BATCH && sum_n >= SCAN_PER_SEQ_MIN_TOKENS) ? 1 : 0;
+  g.per_seq = scan_per_sequence(batch, sum_n);
   hipError_t e = allow_scan_lds();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(select_scan_kernel<false>, dim3(g.per_seq ? (unsigned)batch : 1u), dim3(SCAN_THREADS), SCAN_LDS_BYTES,
@@ -511,11 +515,41 @@ hipError_t launch_select_scan_heads(int batch, int sum_n, const int32_t *cu_vis,
   g.batch = batch; g.sum_n = sum_n; g.cu_vis = cu_vis;
   g.dst = const_cast<int32_t *>(dst); g.new_index = new_index; g.grp_offsets = grp_offsets; g.grp_src = grp_src;
   g.cu_vis_out = cu_vis_out; g.cnt = const_cast<int32_t *>(cnt); g.src_rank = const_cast<int32_t *>(src_rank);
+  g.per_seq = scan_per_sequence(batch, sum_n);
   const int n_head_blocks = (sum_n + SCAN_THREADS - 1) / SCAN_THREADS;
   hipError_t e = allow_scan_lds();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(select_scan_kernel<true>, dim3((unsigned)(n_head_blocks + 1)), dim3(SCAN_THREADS), SCAN_LDS_BYTES,
+  hipLaunchKernelGGL(select_scan_kernel<true>, dim3((unsigned)(n_head_blocks + (g.per_seq ? batch : 1))), dim3(SCAN_THREADS), SCAN_LDS_BYTES,
                      stream, g, x, n_head_blocks);
+  return hipGetLastError();
+}
+
+hipError_t launch_select_windows(int n_windows, int max_window_tokens, int sum_n, const int32_t *win_offsets,
+                                 const int32_t *win_tokens, const int32_t *win_remove, const unsigned long long *keys,
+                                 int key_mt, int key_nt, float *best_fd, int32_t *best_dst, int32_t *dst, int32_t *cnt,
+                                 int32_t *src_rank, int dir, hipStream_t stream) {
+  if (n_windows <= 0) return hipSuccess;
+  SelArgs g{};
+  g.best_key = keys; g.key_mt = key_mt; g.key_nt = key_nt; g.dir = dir;
+  g.n_windows = n_windows; g.sum_n = sum_n;
+  g.win_offsets = win_offsets; g.win_tokens = win_tokens; g.win_remove = win_remove;
+  g.best_fd = best_fd; g.best_dst = best_dst;
+  g.dst = dst; g.cnt = cnt; g.src_rank = src_rank;
+  const int maxA = (max_window_tokens + 1) / 2;   // (dir 1: the caller hands in an even bound, so this covers both sides)
+  g.cap = maxA > 1 ? maxA : 1;
+  if (g.cap <= COUNT_MAX_A) {
+    if (g.cap > 96) hipLaunchKernelGGL(select_window_kernel<4>, dim3(n_windows), dim3(COUNT_MAX_A * 4), 0, stream, g);
+    else hipLaunchKernelGGL(select_window_kernel<1>, dim3(n_windows), dim3(COUNT_MAX_A), 0, stream, g);
+    return hipGetLastError();
+  }
+  // counting selection; a window beyond the library's limit keeps its surplus A nodes, as everywhere else
+  g.cap = maxA < RANK_MAX_A ? maxA : RANK_MAX_A;
+  const int bpw = (g.cap + RANK_ROWS - 1) / RANK_ROWS;
+  const dim3 grid((unsigned)(n_windows * bpw)), block(RANK_ROWS * RANK_SEGS);
+  hipLaunchKernelGGL(select_rank_kernel<0>, grid, block, 0, stream, g, bpw);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(select_rank_kernel<1>, grid, block, 0, stream, g, bpw);
   return hipGetLastError();
 }
 
@@ -524,34 +558,9 @@ hipError_t launch_select(int n_windows, int max_window_tokens, int batch, int su
                          const unsigned long long *keys, int key_mt, int key_nt, float *best_fd, int32_t *best_dst,
                          int32_t *dst, int32_t *new_index, int32_t *grp_offsets, int32_t *grp_src, int32_t *cu_vis_out,
                          int32_t *cnt, int32_t *src_rank, int dir, hipStream_t stream) {
-  SelArgs g{};
-  g.best_key = keys; g.key_mt = key_mt; g.key_nt = key_nt; g.dir = dir;
-  g.n_windows = n_windows; g.batch = batch; g.sum_n = sum_n;
-  g.cu_vis = cu_vis; g.win_offsets = win_offsets; g.win_tokens = win_tokens; g.win_remove = win_remove;
-  g.best_fd = best_fd; g.best_dst = best_dst;
-  g.dst = dst; g.new_index = new_index; g.grp_offsets = grp_offsets; g.grp_src = grp_src;
-  g.cu_vis_out = cu_vis_out; g.cnt = cnt; g.src_rank = src_rank;
-  const int maxA = (max_window_tokens + 1) / 2;   // (dir 1: the caller hands in an even bound, so this covers both sides)
-  g.cap = maxA > 1 ? maxA : 1;
-  if (n_windows > 0) {
-    hipError_t e;
-    if (g.cap <= COUNT_MAX_A) {
-      if (g.cap > 96) hipLaunchKernelGGL(select_window_kernel<4>, dim3(n_windows), dim3(COUNT_MAX_A * 4), 0, stream, g);
-      else hipLaunchKernelGGL(select_window_kernel<1>, dim3(n_windows), dim3(COUNT_MAX_A), 0, stream, g);
-      e = hipGetLastError();
-    } else {
-      // counting selection; a window beyond the library's limit keeps its surplus A nodes, as everywhere else
-      g.cap = maxA < RANK_MAX_A ? maxA : RANK_MAX_A;
-      const int bpw = (g.cap + RANK_ROWS - 1) / RANK_ROWS;
-      const dim3 grid((unsigned)(n_windows * bpw)), block(RANK_ROWS * RANK_SEGS);
-      hipLaunchKernelGGL(select_rank_kernel<0>, grid, block, 0, stream, g, bpw);
-      e = hipGetLastError();
-      if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(select_rank_kernel<1>, grid, block, 0, stream, g, bpw);
-      e = hipGetLastError();
-    }
-    if (e != hipSuccess) return e;
-  }
+  const hipError_t e = launch_select_windows(n_windows, max_window_tokens, sum_n, win_offsets, win_tokens, win_remove, keys,
+                                             key_mt, key_nt, best_fd, best_dst, dst, cnt, src_rank, dir, stream);
+  if (e != hipSuccess) return e;
   return launch_select_scan(batch, sum_n, cu_vis, dst, new_index, grp_offsets, grp_src, cu_vis_out, cnt, src_rank, stream);
 }
 

@@ -95,29 +95,38 @@ hipError_t launch_window_counts(int batch, int win_per_seq, const int32_t *win_o
   return hipGetLastError();
 }
 
-hipError_t launch_build_windows(const int32_t *cu_vis, const int32_t *pos, const int32_t *new_index,
-                                const int32_t *cu_out, int batch, int max_seq, int tiles,
-                                int grid_h, int grid_w, int w, int32_t *win_offsets, int32_t *win_tokens,
-                                const int32_t *cu_target, int32_t *win_remove, int32_t *status, int dir, bool *counts_done,
-                                hipStream_t stream) {
-  if (counts_done) *counts_done = false;
+static WinArgs win_args(const WinSpec &spec, const int32_t *cu_vis, const int32_t *pos, const int32_t *new_index,
+                        const int32_t *cu_out, int batch) {
   WinArgs g{};
-  g.cu_vis = cu_vis; g.pos = pos; g.new_index = new_index; g.cu_out = cu_out; g.batch = batch; g.tiles = tiles; g.grid_h = grid_h; g.grid_w = grid_w; g.w = w;
-  g.win_per_seq = (w == 0) ? 1 : tiles * w * w;
-  g.win_offsets = win_offsets; g.win_tokens = win_tokens;
-  g.count_mode = WIN_NO_COUNTS;
+  g.cu_vis = cu_vis; g.pos = pos; g.new_index = new_index; g.cu_out = cu_out; g.batch = batch;
+  g.tiles = spec.tiles; g.grid_h = spec.grid_h; g.grid_w = spec.grid_w; g.w = spec.w;
+  g.win_per_seq = (spec.w == 0) ? 1 : spec.tiles * spec.w * spec.w;
+  g.win_offsets = spec.win_offsets; g.win_tokens = spec.win_tokens;
+  g.count_mode = spec.count_mode; g.rho = spec.rho; g.cu_target = spec.cu_target; g.win_remove = spec.win_remove;
+  g.status = spec.status; g.dir = spec.dir;
+  return g;
+}
+
+hipError_t launch_build_windows(const WinSpec &spec, const int32_t *cu_vis, const int32_t *pos, const int32_t *new_index,
+                                const int32_t *cu_out, int batch, int max_seq, bool *counts_done, hipStream_t stream) {
+  WinArgs g = win_args(spec, cu_vis, pos, new_index, cu_out, batch);
   const size_t lds = win_table_bytes(max_seq, g.win_per_seq);
   if (lds <= WIN_TABLE_LDS_MAX) {
-    if (cu_target && win_remove && counts_done) {   // the counts ride along (the sort fallback leaves them to the caller)
-      g.count_mode = 2; g.cu_target = cu_target; g.win_remove = win_remove; g.status = status; g.dir = dir;
-      *counts_done = true;
-    }
+    *counts_done = spec.count_mode >= 0;
     hipLaunchKernelGGL(build_windows_table_kernel, dim3(batch), dim3(WIN_THREADS), lds, stream, g);
   } else {
+    *counts_done = false;   // the sort leaves the counts to the caller
     const int p2 = next_pow2(max_seq > 1 ? max_seq : 1);
     hipLaunchKernelGGL(build_windows_sort_kernel, dim3(batch), dim3(WIN_THREADS), p2 * sizeof(uint32_t), stream, g);
   }
   return hipGetLastError();
+}
+
+size_t make_win_args(const WinSpec &spec, const int32_t *cu_vis, const int32_t *pos, const int32_t *new_index,
+                     const int32_t *cu_out, int batch, int max_seq, WinArgs *out) {
+  *out = win_args(spec, cu_vis, pos, new_index, cu_out, batch);
+  const size_t lds = win_table_bytes(max_seq, out->win_per_seq);
+  return lds <= ROWS_WIN_LDS_MAX ? lds : 0;
 }
 
 }  // namespace lk

@@ -41,3 +41,59 @@ def test_one_window_around_the_column_tiles_of_the_epilogue(gh, gw, dtype, d):
     wl = make_custom(name="window_%d" % n, seed=n, dtype=dtype, batch=2, grid_h=gh, grid_w=gw, text_lens=(5, 33), d=d,
                      heads=d // 32, head_dim=32, n_c=12, structure="iid", windows_per_axis=(0,), targets=(n - max(1, n // 5),))
     check_workload(wl)
+
+
+@pytest.mark.parametrize("dtype,d,n,tail", [
+    ("bf16", 32, 70, 0), ("bf16", 512, 70, 3), ("bf16", 544, 71, 2), ("bf16", 2048, 33, 5), ("bf16", 2560, 33, 1),
+    ("bf16", 4096, 65, 9), ("bf16", 4160, 30, 2), ("bf16", 5120, 37, 6), ("bf16", 8192, 20, 1), ("bf16", 8704, 20, 3),
+    ("f32", 128, 40, 2), ("f32", 1280, 40, 2), ("f32", 5120, 21, 4),
+    ("bf16", 4096, 6000, 40),          # beyond 128 MB: whole rows per wave, nontemporal stores
+])
+def test_merge_over_the_row_segments(dtype, d, n, tail):
+    """One to five segments per row, whole and partial, with and without rows behind the vision span and squared norms;
+    groups of one, two, three and more than 64 sources.  Reference: the merge in float64.  The kernel rounds once on
+    store (bf16 keeps 8 significant bits: half a unit in the last place is at most 2^-8 of a value) after fp32 arithmetic with at most 80 terms (80 x 2^-24 = 5e-6 of the
+    largest row); squared norms are those of the rows as stored, summed in fp32 over d terms."""
+    import paper_2605_00789_amd as L
+    g = torch.Generator(device="cuda").manual_seed(d + n)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    X, K, V = (torch.randn(n + tail, d, generator=g, device="cuda").to(tdt) for _ in range(3))
+    rng = np.random.default_rng(d)
+    dst = np.full(n, -1)
+    leave = rng.permutation(n)[:n // 3]
+    dst[leave] = -2
+    stay = np.flatnonzero(dst == -1)
+    for k, a in enumerate(leave):
+        dst[a] = stay[0] if k < 70 and n > 300 else stay[k // 3 % len(stay)]
+    gone = dst >= 0
+    order = np.argsort(dst[gone], kind="stable")
+    src = np.flatnonzero(gone)[order].astype(np.int32)
+    new_index = np.where(gone, -1, np.cumsum(~gone) - 1).astype(np.int32)
+    offsets = np.concatenate([[0], np.cumsum(np.bincount(dst[gone], minlength=n))]).astype(np.int32)
+    xi = (rng.gamma(2.0, 1.0, n) + 1e-3).astype(np.float32)
+    out = int((~gone).sum())
+    h_cu = np.array([0, n], dtype=np.int32)
+    cu = torch.from_numpy(h_cu).cuda()
+    prob = L.Problem(batch=1, d=d, heads=d // 32, head_dim=32, dtype=dtype, h_cu_vis=h_cu, cu_vis=cu)
+    outs = [torch.full((out + tail, d), 7.0, dtype=tdt, device="cuda") for _ in range(3)]
+    sq = torch.empty(out, device="cuda")
+    pos = torch.arange(n + tail, dtype=torch.int32, device="cuda")
+    pos_out = torch.empty(out + tail, dtype=torch.int32, device="cuda")
+    L.lightkv_aggregate_compact(prob, torch.from_numpy(new_index).cuda(), torch.from_numpy(offsets).cuda(),
+                                torch.from_numpy(src).cuda(), torch.from_numpy(xi).cuda(), X, K, V, pos, *outs, pos_out,
+                                x_sqnorm_out=sq, tail_rows=tail, cu_vis_out=torch.tensor([0, out], dtype=torch.int32, device="cuda"))
+    w = torch.from_numpy(xi).cuda().double()
+    a, b = torch.from_numpy(np.flatnonzero(gone)).cuda(), torch.from_numpy(dst[gone]).cuda()
+    keep = torch.from_numpy(~gone).cuda()
+    for y, o in zip((X, K, V), outs):
+        y64 = y.double()
+        num, den = w[:, None] * y64[:n], w.clone()
+        num.index_add_(0, b, w[a][:, None] * y64[a])
+        den.index_add_(0, b, w[a])
+        want = torch.cat([(num / den[:, None])[keep], y64[n:]])
+        err = (o.double() - want).abs()
+        bound = (2.0 ** -8 if dtype == "bf16" else 0.0) * want.abs() + 6e-6 * want.abs().max()
+        assert bool((err <= bound).all()), float((err - bound).max())
+    want_sq = outs[0][:out].double().square().sum(1)
+    assert bool(((sq.double() - want_sq).abs() <= 1e-6 * want_sq).all())
+    assert torch.equal(pos_out, torch.cat([pos[:n][keep], pos[n:]]))
