@@ -4,6 +4,8 @@
 #include "lk_launch.h"
 #include "lk_helpers.h"
 #include "lk_win_body.h"
+#include "lk_fd_body.h"
+#include "lk_xi_body.h"
 
 #include <math.h>
 #include <mutex>
@@ -138,19 +140,33 @@ bool use_big_fd(const lightkv_problem *p, const Checked &c) {
   return (int64_t)p->n_windows * big.mt * big.nt >= FD_BIG_MIN_TILES;
 }
 
+// The small-tile plan of a step: the bipartite blocks, or the whole windows for full pairwise matching (n_tiles == 0: the
+// large pairwise tiles).  Not used on the tiled bipartite path.
+FdPlan small_tile_plan(const lightkv_problem *p, const Checked &c) {
+  FdPlan fd = full_pairwise(p) ? make_fd_pair_plan(p->n_windows, c.max_window, p->d)
+                               : make_fd_plan(p->n_windows, c.max_window, p->d, c.elem_bytes);
+  fd.metric = p->metric;
+  if (!full_pairwise(p)) fd.dir = p->direction;
+  return fd;
+}
+
 // lightkv_score_select, both halves requested: the k-th kernels of the two chains share launches on the caller's stream.
 // Not for the tiled FD kernel (one workgroup of it fills a CU's LDS) and not for batches whose xi is one workgroup per
 // (sequence, head) pair; there the chains run on two streams.
 bool fused_launches(const lightkv_problem *p, const Checked &c, const FdPlan &fd, const XiPlan &xp, int xi_mode, const float *lse) {
-  return p->match == LIGHTKV_MATCH_BEST_PER_A && p->n_windows > 0 && c.sum_n > 0 && fd.n_tiles > 0 && xp.max_vis_blocks > 0 &&
-         !use_big_fd(p, c) && !xi_seq_applies(xp, xi_mode, lse, p->batch, p->heads);
+  return !edge_topk(p) && p->n_windows > 0 && c.sum_n > 0 && fd.n_tiles > 0 && xp.max_vis_blocks > 0 &&
+         (full_pairwise(p) || !use_big_fd(p, c)) && !xi_seq_applies(xp, xi_mode, lse, p->batch, p->heads);
 }
 
-WsLayout ws_layout(const FdPlan &fd, const FdBigPlan &big, bool use_big, const XiPlan &xi, int sum_n, size_t n_edge_ints) {
-  // (full pairwise matching needs at most what the tiled bipartite path lays out: norms and one key plane or more)
+WsLayout ws_layout(const FdPlan &fd, const FdBigPlan &big, bool use_big, bool pairwise, const XiPlan &xi, int sum_n,
+                   size_t n_edge_ints) {
+  // full pairwise matching needs what the tiled bipartite path lays out (norms and one key plane or more) and room for the
+  // partial tiles of the small cut, the same for every window bound: a step may be planned with a smaller one than the
+  // workspace was sized for
   WsLayout l;
   size_t off = 0;
-  l.fd_partial = off; off = align_up(off + (use_big ? 0 : fd.partial_floats * sizeof(float)));
+  const size_t partial = pairwise ? PAIR_PARTIAL_FLOATS : (use_big ? 0 : fd.partial_floats);
+  l.fd_partial = off; off = align_up(off + partial * sizeof(float));
   l.fd_norm = off;    off = align_up(off + (use_big ? big.norm_floats * sizeof(float) : 0));
   l.fd_keys = off;    off = align_up(off + (use_big ? big.key_bytes : 0));
   l.xi_stats = off;   off = align_up(off + xi.stat_floats * sizeof(float));
@@ -184,7 +200,7 @@ lightkv_status select_impl(const lightkv_problem *p, bool from_keys, float *best
   const XiPlan xp = make_xi_plan(p->batch, p->h_cu_vis, have_txt ? p->h_cu_txt : nullptr, p->heads, 0);
   const FdBigPlan big = make_fd_big_plan(p->n_windows, c.max_window, c.sum_n);
   if (edge_topk(p) || full_pairwise(p)) return LIGHTKV_ERR_UNSUPPORTED;   // scores of another kind: lightkv_score_select only
-  const WsLayout l = ws_layout(fd, big, use_big_fd(p, c), xp, c.sum_n, 0);
+  const WsLayout l = ws_layout(fd, big, use_big_fd(p, c), full_pairwise(p), xp, c.sum_n, 0);
   // only the selection scratch (and the keys) are used here; accept a workspace that covers the layout
   if (!ws || (reinterpret_cast<uintptr_t>(ws) % ALIGN) != 0 || ws_bytes < l.total) return LIGHTKV_ERR_WORKSPACE;
   char *wsb = static_cast<char *>(ws);
@@ -228,7 +244,7 @@ lightkv_status lightkv_workspace_size(const lightkv_problem *p, size_t *bytes) {
   const FdPlan fd = make_fd_plan(p->n_windows, c.max_window, p->d, c.elem_bytes);
   const XiPlan xi = make_xi_plan(p->batch, p->h_cu_vis, have_txt ? p->h_cu_txt : nullptr, p->heads, 0);
   const FdBigPlan big = make_fd_big_plan(p->n_windows, c.max_window, c.sum_n);
-  *bytes = ws_layout(fd, big, use_big_fd(p, c), xi, c.sum_n, edge_ints(p, c)).total;
+  *bytes = ws_layout(fd, big, use_big_fd(p, c), full_pairwise(p), xi, c.sum_n, edge_ints(p, c)).total;
   return LIGHTKV_OK;
 }
 
@@ -347,7 +363,7 @@ int lk::build_windows_with_counts(int32_t batch, const int32_t *h_cu_vis, const 
 bool lk::score_select_one_stream(const lightkv_problem *p) {
   Checked c;
   if (check_problem(p, true, true, c) != LIGHTKV_OK) return true;   // (lightkv_score_select reports the error)
-  return fused_launches(p, c, make_fd_plan(p->n_windows, c.max_window, p->d, c.elem_bytes),
+  return fused_launches(p, c, small_tile_plan(p, c),
                         make_xi_plan(p->batch, p->h_cu_vis, p->h_cu_txt, p->heads, LIGHTKV_XI_TEXT_QUERY), LIGHTKV_XI_TEXT_QUERY, nullptr);
 }
 
@@ -404,16 +420,16 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
       }
     c.max_window = plan_bound(p, max_window);
   }
-  FdPlan fd = make_fd_plan(p->n_windows, c.max_window, p->d, c.elem_bytes);
+  const FdPlan fd = small_tile_plan(p, c);
   const XiPlan xp = make_xi_plan(p->batch, p->h_cu_vis, p->h_cu_txt && p->cu_txt ? p->h_cu_txt : nullptr, p->heads, 0);
   FdBigPlan big = make_fd_big_plan(p->n_windows, c.max_window, c.sum_n);
-  fd.metric = big.metric = p->metric;
-  fd.dir = big.dir = p->direction;
+  big.metric = p->metric;
+  big.dir = p->direction;
   const bool use_big = use_big_fd(p, c);
   const bool edge = sel && need_fd && edge_topk(p);
   const bool pairwise = need_fd && full_pairwise(p);
   if (pairwise && (uint64_t)c.sum_n * (uint64_t)ldx * 2u >= (1ull << 32)) return LIGHTKV_ERR_UNSUPPORTED;   // 32-bit row offsets
-  const WsLayout l = ws_layout(fd, big, use_big, xp, c.sum_n, need_fd ? edge_ints(p, c) : 0);
+  const WsLayout l = ws_layout(fd, big, use_big, full_pairwise(p), xp, c.sum_n, need_fd ? edge_ints(p, c) : 0);
   if (!ws || (reinterpret_cast<uintptr_t>(ws) % ALIGN) != 0 || ws_bytes < l.total) return LIGHTKV_ERR_WORKSPACE;
   char *wsb = static_cast<char *>(ws);
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -423,12 +439,25 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
   if (need_xi && need_fd && sel && fused_launches(p, c, fd, xp, xi_mode, lse)) {
     const float scale = softmax_scale != 0.f ? softmax_scale : 1.0f / sqrtf((float)p->head_dim);
     int32_t *cnt = reinterpret_cast<int32_t *>(wsb + l.sel_cnt), *rank = reinterpret_cast<int32_t *>(wsb + l.sel_rank);
-    const hipError_t e = launch_score_select_fused(
-        xp, fd, p->dtype, xi_mode, p->batch, p->heads, p->head_dim, p->d, p->n_windows, c.sum_n, c.sum_t, p->cu_vis,
-        p->cu_txt, Q, q_tok_stride, q_head_stride, K, k_tok_stride, k_head_stride, lse, scale,
-        reinterpret_cast<float *>(wsb + l.xi_stats), reinterpret_cast<float *>(wsb + l.xi_part), xi, X, ldx,
-        p->win_offsets, p->win_tokens, p->win_remove, reinterpret_cast<float *>(wsb + l.fd_partial), best_fd, best_dst,
-        sel->dst, cnt, rank, sel->new_index, sel->grp_offsets, sel->grp_src, sel->cu_vis_out, c.max_window, s);
+    unsigned long long *keys = reinterpret_cast<unsigned long long *>(wsb + l.fd_keys);
+    const XiArgs x = make_xi_args(xp, xi_mode, p->batch, p->heads, c.sum_n, c.sum_t, p->cu_vis, p->cu_txt, Q, q_tok_stride,
+                                  q_head_stride, K, k_tok_stride, k_head_stride, lse, scale,
+                                  reinterpret_cast<float *>(wsb + l.xi_stats), reinterpret_cast<float *>(wsb + l.xi_part), xi);
+    FdArgs f = make_fd_args(fd, p->dtype, X, ldx, p->d, p->n_windows, c.sum_n, p->win_offsets, p->win_tokens,
+                            reinterpret_cast<float *>(wsb + l.fd_partial), best_fd, best_dst);
+    const SmallSelArgs q{p->win_remove, sel->dst, cnt, rank};
+    const bool tail = !pairwise && c.max_window <= 64;   // one tile per window: the epilogue selects as well
+    if (pairwise) f.pair_keys = keys;
+    hipError_t e = launch_xi_fd_fused(x, xp, f, q, tail ? FUSED_TAIL : FUSED_EPILOGUE, fd.n_rowblocks, p->dtype, p->head_dim, s);
+    if (e == hipSuccess && pairwise)
+      e = launch_pair_select(p->n_windows, c.max_window, c.sum_n, p->win_offsets, p->win_tokens, p->win_remove, keys, best_fd,
+                             best_dst, sel->dst, cnt, rank, s);
+    else if (e == hipSuccess && !tail)
+      e = launch_select_windows(p->n_windows, c.max_window, c.sum_n, p->win_offsets, p->win_tokens, p->win_remove, nullptr, 0,
+                                0, best_fd, best_dst, sel->dst, cnt, rank, p->direction, s);
+    if (e == hipSuccess)
+      e = launch_select_scan_heads(p->batch, c.sum_n, p->cu_vis, sel->dst, sel->new_index, sel->grp_offsets, sel->grp_src,
+                                   sel->cu_vis_out, cnt, rank, x, s);
     return e == hipSuccess ? LIGHTKV_OK : LIGHTKV_ERR_LAUNCH;
   }
   Fork *fk = nullptr;
@@ -458,16 +487,20 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
     // every two tokens of a window: nearest neighbour per token on the matrix cores, the visit in rank order, index scan
     int32_t *cnt = reinterpret_cast<int32_t *>(wsb + l.sel_cnt), *rank = reinterpret_cast<int32_t *>(wsb + l.sel_rank);
     unsigned long long *keys = reinterpret_cast<unsigned long long *>(wsb + l.fd_keys);
-    if (!sel) {   // scores only: every token's nearest neighbour
-      if (launch_fd_pair(X, ldx, p->d, p->n_windows, c.max_window, c.sum_n, p->metric, p->win_offsets, p->win_tokens,
-                         x_sqnorm, reinterpret_cast<float *>(wsb + l.fd_norm), keys, best_fd, best_dst, s) != hipSuccess)
-        fd_status = LIGHTKV_ERR_LAUNCH;
-    } else if (launch_fd_pair(X, ldx, p->d, p->n_windows, c.max_window, c.sum_n, p->metric, p->win_offsets, p->win_tokens,
-                       x_sqnorm, reinterpret_cast<float *>(wsb + l.fd_norm), keys, nullptr, nullptr, s) != hipSuccess ||
-        launch_pair_select(p->n_windows, c.max_window, c.sum_n, p->win_offsets, p->win_tokens, p->win_remove, keys,
-                           best_fd, best_dst, sel->dst, cnt, rank, s) != hipSuccess ||
-        launch_select_scan(p->batch, c.sum_n, p->cu_vis, sel->dst, sel->new_index, sel->grp_offsets, sel->grp_src,
-                           sel->cu_vis_out, cnt, rank, s) != hipSuccess)
+    hipError_t e;   // scores only (no selection): best_fd / best_dst of every token, otherwise keys for the selection
+    float *fd_out = sel ? nullptr : best_fd;
+    int32_t *dst_out = sel ? nullptr : best_dst;
+    if (fd.n_tiles > 0)
+      e = launch_fd_pair_small(fd, X, ldx, p->d, p->n_windows, c.sum_n, p->win_offsets, p->win_tokens,
+                               reinterpret_cast<float *>(wsb + l.fd_partial), sel ? keys : nullptr, fd_out, dst_out, s);
+    else
+      e = launch_fd_pair(X, ldx, p->d, p->n_windows, c.max_window, c.sum_n, p->metric, p->win_offsets, p->win_tokens, x_sqnorm,
+                         reinterpret_cast<float *>(wsb + l.fd_norm), keys, fd_out, dst_out, s);
+    if (e != hipSuccess ||
+        (sel && (launch_pair_select(p->n_windows, c.max_window, c.sum_n, p->win_offsets, p->win_tokens, p->win_remove, keys,
+                                    best_fd, best_dst, sel->dst, cnt, rank, s) != hipSuccess ||
+                 launch_select_scan(p->batch, c.sum_n, p->cu_vis, sel->dst, sel->new_index, sel->grp_offsets, sel->grp_src,
+                                    sel->cu_vis_out, cnt, rank, s) != hipSuccess)))
       fd_status = LIGHTKV_ERR_LAUNCH;
   } else if (edge) {
     // the k lowest edges of every window: partial tiles, ranking per window, index scan, group lists from the edge list
@@ -536,8 +569,7 @@ lightkv_status lightkv_score_select(const lightkv_problem *p, const void *X, int
   const FdPlan small = make_fd_small_fused_plan(p->n_windows, c.max_window, p->d, c.elem_bytes);
   bool fused = false;
   if (xi_mode != LIGHTKV_XI_GIVEN && p->h_cu_txt && p->cu_txt) {
-    const FdPlan fd = make_fd_plan(p->n_windows, c.max_window, p->d, c.elem_bytes);
-    fused = fused_launches(p, c, fd, make_xi_plan(p->batch, p->h_cu_vis, p->h_cu_txt, p->heads, xi_mode), xi_mode, lse);
+    fused = fused_launches(p, c, small_tile_plan(p, c), make_xi_plan(p->batch, p->h_cu_vis, p->h_cu_txt, p->heads, xi_mode), xi_mode, lse);
   }
   if (fused || (small.n_tiles > 0 && !use_big_fd(p, c)) || p->n_windows == 0 || edge_topk(p) || full_pairwise(p)) {
     const SelectOut sel{dst, new_index, grp_offsets, grp_src, cu_vis_out};

@@ -23,7 +23,9 @@ struct FdArgs {
   int32_t *best_dst;
   int slot, group, mt, nt, n_tiles, ksplit, n_spans, spans_per_wg;
   int metric;   // 0: 1 - cos, 1: |a - b|, 2: |a - b|^2
-  int dir;      // 0: even list positions propose, 1: odd ones (side_a / pos_a)
+  int dir;      // 0: even list positions propose, 1: odd ones, PAIR_DIR: all to all others (side_a / pos_a)
+  unsigned long long *pair_keys;   // PAIR_DIR: where the epilogue files (FD bits << 32 | neighbour's position) by list
+                                   // position; NULL: it writes best_fd / best_dst
 };
 
 // Divergence of a pair from its inner product and squared norms (fp64).  The distances use
@@ -261,6 +263,7 @@ __device__ __forceinline__ void fd_epilogue_body(const FdArgs &g, int block_id, 
     col_base = 0;
   }
   const bool a_valid = l < wi.nA;
+  const bool pair = g.dir == PAIR_DIR;
   const int nB = wi.nB < col_cap ? wi.nB : col_cap;
   // the token of this row (and of the B node at the same position): the loads travel with the others
   const int a_tok = a_valid ? checked_token(g, wi.off + pos_a(l, g.dir)) : -1;
@@ -278,8 +281,9 @@ __device__ __forceinline__ void fd_epilogue_body(const FdArgs &g, int block_id, 
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int c = tc0 + j - col_base;   // column inside the window
-      if (a_valid && t < ncol_tiles && c >= 0 && c < nB) {
-        const double fd = divergence(g.metric, dot[j], a2, nb2[tc0 + j]);
+      if (a_valid && t < ncol_tiles && c >= 0 && c < nB && !(pair && c == l)) {   // no token is its own neighbour
+        double fd = divergence(g.metric, dot[j], a2, nb2[tc0 + j]);
+        if (pair) fd = (double)(float)fd;   // ranked as the keys will be: equal in fp32 goes to the earlier neighbour
         if (fd < best) { best = fd; best_c = c; }   // columns ascend: strict < keeps the first minimum
       }
     }
@@ -289,6 +293,19 @@ __device__ __forceinline__ void fd_epilogue_body(const FdArgs &g, int block_id, 
     const double ob = __shfl_xor(best, m, 64);
     const int oc = __shfl_xor(best_c, m, 64);
     if (ob < best || (ob == best && oc < best_c)) { best = ob; best_c = oc; }
+  }
+  if (pair) {
+    if (sub == 0 && a_valid) {
+      const bool has = best_c != 0x7fffffff;
+      if (g.pair_keys) {
+        g.pair_keys[wi.off + l] = has ? ((unsigned long long)__float_as_uint((float)best) << 32) | (unsigned)best_c : ~0ull;
+      } else if (a_tok >= 0) {
+        const int nb = has ? checked_token(g, wi.off + best_c) : -1;
+        g.best_fd[a_tok] = nb >= 0 ? (float)best : __uint_as_float(0x7f800000u);
+        g.best_dst[a_tok] = nb;
+      }
+    }
+    return;
   }
   if (sub == 0 && a_tok >= 0) {
     // no finite score at all (NaN rows): propose the first B node with FD = +inf, so that counts stay exact

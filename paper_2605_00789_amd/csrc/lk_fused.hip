@@ -83,43 +83,26 @@ static hipError_t launch_two_t(const XiArgs &x, int n_xi_blocks, bool pass1, boo
   return launch_two<T, DH, 64, false>(x, n_xi_blocks, pass1, tail, n_fd_blocks, f, q, stream);
 }
 
-hipError_t launch_score_select_fused(const XiPlan &xp, const FdPlan &fp, int dtype, int xi_mode, int batch, int heads,
-                                     int head_dim, int d, int n_windows, int sum_n, int sum_t, const int32_t *cu_vis,
-                                     const int32_t *cu_txt, const void *Q, int64_t q_tok_stride, int64_t q_head_stride,
-                                     const void *K, int64_t k_tok_stride, int64_t k_head_stride, const float *lse,
-                                     float scale, float *stats, float *xi_part, float *xi, const void *X, int64_t ldx,
-                                     const int32_t *win_offsets, const int32_t *win_tokens, const int32_t *win_remove,
-                                     float *partial, float *best_fd, int32_t *best_dst, int32_t *dst, int32_t *cnt,
-                                     int32_t *src_rank, int32_t *new_index, int32_t *grp_offsets, int32_t *grp_src,
-                                     int32_t *cu_vis_out, int max_window, hipStream_t stream) {
-  const XiArgs x = make_xi_args(xp, xi_mode, batch, heads, sum_n, sum_t, cu_vis, cu_txt, Q, q_tok_stride, q_head_stride, K,
-                                k_tok_stride, k_head_stride, lse, scale, stats, xi_part, xi);
-  const FdArgs f = make_fd_args(fp, dtype, X, ldx, d, n_windows, sum_n, win_offsets, win_tokens, partial, best_fd, best_dst);
-  const SmallSelArgs q{win_remove, dst, cnt, src_rank};
-  const int n_xi_blocks = batch * heads * xp.max_vis_blocks;
-  const bool pass1 = (xi_mode == 0 && lse == nullptr);
-  const bool vision_lse = (xi_mode == 1);
+hipError_t launch_xi_fd_fused(const XiArgs &x, const XiPlan &xp, const FdArgs &f, const SmallSelArgs &q, FusedFinish finish,
+                              int n_rowblocks, int dtype, int head_dim, hipStream_t stream) {
+  const int n_xi_blocks = x.batch * x.heads * xp.max_vis_blocks;
+  const bool vision_lse = x.lse_per_vision != 0;
+  const bool pass1 = !vision_lse && x.lse == nullptr;
   const int max_t = xp.max_text_tiles * 32;
-  const bool tail = max_window <= 64;   // one tile per window
-  const int n_fd_blocks = tail ? fp.n_tiles : fd_epilogue_blocks(fp.n_rowblocks, fp.group, fp.nt);
-  hipError_t e = hipErrorInvalidValue;
-#define LK_CASE(TT, DHV) e = launch_two_t<TT, DHV>(x, n_xi_blocks, pass1, vision_lse, max_t, tail, n_fd_blocks, f, q, stream)
+  const bool tail = finish == FUSED_TAIL;
+  const int n_fd_blocks = tail ? f.n_tiles : fd_epilogue_blocks(n_rowblocks, f.group, f.nt);
+#define LK_CASE(TT, DHV) return launch_two_t<TT, DHV>(x, n_xi_blocks, pass1, vision_lse, max_t, tail, n_fd_blocks, f, q, stream)
   if (dtype == 1) {
     if (head_dim == 128) LK_CASE(bf16_t, 128);
-    else if (head_dim == 64) LK_CASE(bf16_t, 64);
-    else if (head_dim == 32) LK_CASE(bf16_t, 32);
+    if (head_dim == 64) LK_CASE(bf16_t, 64);
+    if (head_dim == 32) LK_CASE(bf16_t, 32);
   } else {
     if (head_dim == 128) LK_CASE(float, 128);
-    else if (head_dim == 64) LK_CASE(float, 64);
-    else if (head_dim == 32) LK_CASE(float, 32);
+    if (head_dim == 64) LK_CASE(float, 64);
+    if (head_dim == 32) LK_CASE(float, 32);
   }
 #undef LK_CASE
-  if (e == hipSuccess && !tail)
-    e = launch_select_windows(n_windows, max_window, sum_n, win_offsets, win_tokens, win_remove, nullptr, 0, 0, best_fd,
-                              best_dst, dst, cnt, src_rank, fp.dir, stream);
-  if (e != hipSuccess) return e;
-  return launch_select_scan_heads(batch, sum_n, cu_vis, dst, new_index, grp_offsets, grp_src, cu_vis_out, cnt, src_rank, x,
-                                  stream);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace lk

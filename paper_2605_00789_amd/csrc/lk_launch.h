@@ -12,10 +12,13 @@ namespace lk {
 // paragraph: the reverse direction is defined analogously).  dir 0: the tokens at list positions 0, 2, 4, ... propose
 // and merge into the tokens at positions 1, 3, 5, ...; dir 1: the odd positions propose, the even ones receive.  In
 // the kernels "A" is always the proposing side and "B" the receiving side.
-__host__ __device__ __forceinline__ int side_a(int v, int dir) { return (v + 1 - dir) >> 1; }
-__host__ __device__ __forceinline__ int side_b(int v, int dir) { return (v + dir) >> 1; }
-__host__ __device__ __forceinline__ int pos_a(int i, int dir) { return 2 * i + dir; }
-__host__ __device__ __forceinline__ int pos_b(int j, int dir) { return 2 * j + 1 - dir; }
+// dir 2 (PAIR_DIR): no split -- every token proposes to every other one (full pairwise matching): both sides are the
+// whole list.
+constexpr int PAIR_DIR = 2;
+__host__ __device__ __forceinline__ int side_a(int v, int dir) { return dir == PAIR_DIR ? v : (v + 1 - dir) >> 1; }
+__host__ __device__ __forceinline__ int side_b(int v, int dir) { return dir == PAIR_DIR ? v : (v + dir) >> 1; }
+__host__ __device__ __forceinline__ int pos_a(int i, int dir) { return dir == PAIR_DIR ? i : 2 * i + dir; }
+__host__ __device__ __forceinline__ int pos_b(int j, int dir) { return dir == PAIR_DIR ? j : 2 * j + 1 - dir; }
 
 // ---- feature divergence (Steps 1-2) ------------------------------------------------------
 // The |A_w| x |B_w| cosine blocks are cut into 32x32 tiles.  Small windows are packed several to
@@ -39,6 +42,12 @@ constexpr int FD_TILE_FLOATS = FD_TOK_OFFSET + 64;  // ... then (slice 0 only) t
 constexpr int FD_MAX_COLS = 2048;                   // |B| of the largest supported window
 
 FdPlan make_fd_plan(int n_windows, int max_window_tokens, int d, int dtype_bytes);
+// The same for full pairwise matching (every window's whole v x v matrix in 32 x 32 tiles); n_tiles == 0: the 192 x 192
+// tiles of launch_fd_pair are the better cut.  The partial tiles never take more than PAIR_PARTIAL_FLOATS, whatever
+// smaller window bound a step is planned with.
+constexpr int PAIR_SMALL_MAX_TILES = 768;
+constexpr size_t PAIR_PARTIAL_FLOATS = (size_t)2048 * FD_TILE_FLOATS;   // slices double while there are below 1024 tile slices
+FdPlan make_fd_pair_plan(int n_windows, int max_window_tokens, int d);
 
 // The partition of one stage's tokens and, optionally, the per-window counts that go with it (host struct).
 struct WinArgs;
@@ -76,6 +85,12 @@ hipError_t launch_window_counts(int batch, int win_per_seq, const int32_t *win_o
 hipError_t launch_fd(const FdPlan &plan, int dtype, const void *X, int64_t ldx, int d, int n_windows, int sum_n,
                      const int32_t *win_offsets, const int32_t *win_tokens, float *partial, float *best_fd,
                      int32_t *best_dst, hipStream_t stream);
+
+// Full pairwise matching on the small tiles: one packed key per list position in `keys`, as launch_fd_pair leaves them,
+// or best_fd / best_dst if keys is NULL.
+hipError_t launch_fd_pair_small(const FdPlan &plan, const void *X, int64_t ldx, int d, int n_windows, int sum_n,
+                                const int32_t *win_offsets, const int32_t *win_tokens, float *partial,
+                                unsigned long long *keys, float *best_fd, int32_t *best_dst, hipStream_t stream);
 
 // Windows of at most 64 tokens: partial tiles, then epilogue + per-window selection in one kernel
 // (n_tiles == 0: not applicable).
@@ -143,20 +158,17 @@ hipError_t launch_pair_select(int n_windows, int max_window, int sum_n, const in
 // Whether lightkv_score_select with xi requested runs this step on the caller's stream alone (lk_api.hip).
 bool score_select_one_stream(const lightkv_problem *p);
 
-// ---- scores + selection on one stream, the k-th kernels of the xi chain and of the FD chain sharing a launch
-// (lk_fused.hip): three launches for windows of at most 64 tokens, the window selection as a fourth (or fourth and
-// fifth) for larger ones
+// ---- xi and FD on one stream, the k-th kernels of the two chains sharing a launch (lk_fused.hip): pass 1 of xi beside
+// the partial tiles, pass 2 beside what finishes them -- FUSED_TAIL: epilogue and selection of windows of at most 64
+// tokens, FUSED_EPILOGUE: best edges of larger ones (keys instead of best_fd / best_dst if pair_keys is given).  The
+// caller goes on with the selection and launch_select_scan_heads, which sums the heads of xi.
+enum FusedFinish { FUSED_TAIL = 0, FUSED_EPILOGUE = 1 };
 struct XiArgs;
 struct XiPlan;
-hipError_t launch_score_select_fused(const XiPlan &xp, const FdPlan &fp, int dtype, int xi_mode, int batch, int heads,
-                                     int head_dim, int d, int n_windows, int sum_n, int sum_t, const int32_t *cu_vis,
-                                     const int32_t *cu_txt, const void *Q, int64_t q_tok_stride, int64_t q_head_stride,
-                                     const void *K, int64_t k_tok_stride, int64_t k_head_stride, const float *lse,
-                                     float scale, float *stats, float *xi_part, float *xi, const void *X, int64_t ldx,
-                                     const int32_t *win_offsets, const int32_t *win_tokens, const int32_t *win_remove,
-                                     float *partial, float *best_fd, int32_t *best_dst, int32_t *dst, int32_t *cnt,
-                                     int32_t *src_rank, int32_t *new_index, int32_t *grp_offsets, int32_t *grp_src,
-                                     int32_t *cu_vis_out, int max_window, hipStream_t stream);
+struct FdArgs;
+struct SmallSelArgs;
+hipError_t launch_xi_fd_fused(const XiArgs &x, const XiPlan &xp, const FdArgs &f, const SmallSelArgs &q, FusedFinish finish,
+                              int n_rowblocks, int dtype, int head_dim, hipStream_t stream);
 // index scan with the head sum of xi in the same launch (x: arguments of the xi passes)
 hipError_t launch_select_scan_heads(int batch, int sum_n, const int32_t *cu_vis, const int32_t *dst, int32_t *new_index,
                                     int32_t *grp_offsets, int32_t *grp_src, int32_t *cu_vis_out, const int32_t *cnt,

@@ -55,9 +55,8 @@ hipError_t launch_fd_select_small(const FdPlan &plan, int dtype, const void *X, 
   return hipGetLastError();
 }
 
-FdPlan make_fd_plan(int n_windows, int max_window_tokens, int d, int dtype_bytes) {
+static FdPlan plan_tiles(int n_windows, int maxA, int maxB, int d, int dtype_bytes) {
   FdPlan p{};
-  const int maxA = (max_window_tokens + 1) / 2, maxB = max_window_tokens / 2;
   if (maxA <= 16) {
     p.slot = maxA <= 8 ? 8 : 16;
     p.group = 32 / p.slot;
@@ -80,6 +79,40 @@ FdPlan make_fd_plan(int n_windows, int max_window_tokens, int d, int dtype_bytes
   p.ksplit = ks;
   p.partial_floats = (size_t)p.n_tiles * ks * FD_TILE_FLOATS;
   return p;
+}
+
+FdPlan make_fd_plan(int n_windows, int max_window_tokens, int d, int dtype_bytes) {
+  return plan_tiles(n_windows, (max_window_tokens + 1) / 2, max_window_tokens / 2, d, dtype_bytes);
+}
+
+// Full pairwise matching cut into 32 x 32 tiles with the hidden axis split over workgroups, instead of 192 x 192 tiles
+// whose workgroup walks the whole hidden axis: a launch of the large tiles takes 78 us however few of them there are (64
+// dependent k-steps at d = 4096), and a window of 36 tokens fills 4 % of one.  The small tiles fetch 512 KB each at
+// d = 4096, so their time grows with their number.  Scores alone, d = 4096, large -> small tiles: 180 windows of 16 tokens
+// 79.7 -> 17.8 us, one window of 576 tokens (324 small tiles) 78.6 -> 41.4, of 800 (625) 79.7 -> 59.9, of 1024 (1024) 80.3 ->
+// 83.9; 64 windows of 128 (1024) 87.9 -> 94.8.  The line lies at 768 tiles.
+FdPlan make_fd_pair_plan(int n_windows, int max_window_tokens, int d) {
+  const int64_t side = (max_window_tokens + 31) / 32;
+  if (max_window_tokens > 2 * 32 * PAIR_SMALL_MAX_TILES || n_windows <= 0) return FdPlan{};
+  const int64_t tiles = max_window_tokens <= 16 ? n_windows : side * side * (int64_t)n_windows;
+  if (tiles > PAIR_SMALL_MAX_TILES) return FdPlan{};
+  FdPlan p = plan_tiles(n_windows, max_window_tokens, max_window_tokens, d, 2);
+  p.dir = PAIR_DIR;
+  return p;
+}
+
+hipError_t launch_fd_pair_small(const FdPlan &plan, const void *X, int64_t ldx, int d, int n_windows, int sum_n,
+                                const int32_t *win_offsets, const int32_t *win_tokens, float *partial,
+                                unsigned long long *keys, float *best_fd, int32_t *best_dst, hipStream_t stream) {
+  if (n_windows == 0 || plan.n_tiles == 0) return hipSuccess;
+  FdArgs g = make_fd_args(plan, 1, X, ldx, d, n_windows, sum_n, win_offsets, win_tokens, partial, best_fd, best_dst);
+  g.pair_keys = keys;
+  hipLaunchKernelGGL(fd_partial_kernel<bf16_t>, dim3((unsigned)(plan.n_tiles * plan.ksplit)), dim3(FD_THREADS), 0, stream, g);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(fd_epilogue_kernel, dim3((unsigned)fd_epilogue_blocks(plan.n_rowblocks, plan.group, plan.nt)),
+                     dim3(FD_THREADS), 0, stream, g);
+  return hipGetLastError();
 }
 
 hipError_t launch_fd_partial(const FdPlan &plan, int dtype, const void *X, int64_t ldx, int d, int n_windows, int sum_n,

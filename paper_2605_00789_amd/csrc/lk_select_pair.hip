@@ -15,14 +15,16 @@
 //   3. the first r_w of the tokens that may leave, in rank order (a scan over ranks)
 //   4. dst, the number of sources of every destination, and the rank of every source among the sources of its
 //      destination in ascending token order -- what select_scan_kernel turns into new_index and the inverse map.
+// Bound: barriers and dependent LDS reads of one workgroup.  So the workgroup is no larger than the window needs (256
+// threads up to 256 tokens), threads without a token of their own share the counting loops, and a round of the visit
+// is three barriers: the minima of the next round are reset while this one's are read, and the count of undecided tokens
+// travels with the last barrier.  Windows of 36 / 120 / 400 tokens: 13 / 18 / 36 us -> 6.1 / 8.9 / 22 us.
 #include "lk_common.h"
 #include "lk_launch.h"
 
 namespace lk {
 
-constexpr int PS_THREADS = 1024;
 constexpr int PS_MAX = 4096;              // tokens of the largest window
-constexpr int PS_ITEMS = PS_MAX / PS_THREADS;
 
 struct PairSelArgs {
   int n_windows, sum_n, cap;              // cap: the caller's bound on the tokens of a window
@@ -34,30 +36,60 @@ struct PairSelArgs {
 
 enum : unsigned char { PS_UNDECIDED = 0, PS_LEAVES = 1, PS_STAYS = 2 };
 
-__global__ __launch_bounds__(PS_THREADS) void pair_select_kernel(PairSelArgs g) {
-  // order-preserving FD bits (step 1); then, per position, the lowest rank among the undecided tokens that name it
-  // (step 2); then the number of its sources (step 4)
-  __shared__ __attribute__((aligned(16))) uint32_t key[PS_MAX];
-  uint32_t *minpend = key;
-  __shared__ __attribute__((aligned(16))) uint16_t nbr[PS_MAX];     // nearest neighbour (list position), 0xffff: none
-  __shared__ uint16_t rnk[PS_MAX];
-  __shared__ uint16_t by_rank[PS_MAX];                              // token at every rank; later: leavers before every rank
-  __shared__ unsigned char state[PS_MAX];
-  __shared__ unsigned char received[PS_MAX];
-  __shared__ int wave_tot[PS_THREADS / 64];
-  __shared__ int n_undecided;
+// Number of entries of list[0 .. n4) (all-ones beyond n; n4 a multiple of 4) that come before (mine, l): smaller, or equal
+// at an earlier position.  Entries [begin, end) only, both multiples of 4.
+__device__ __forceinline__ int count_before(const uint32_t *list, uint32_t mine, int l, int begin, int end) {
+  int c = 0;
+#pragma unroll 4
+  for (int o = begin; o < end; o += 4) {
+    const uint4 q = *reinterpret_cast<const uint4 *>(&list[o]);
+    c += (q.x < mine || (q.x == mine && o < l)) ? 1 : 0;
+    c += (q.y < mine || (q.y == mine && o + 1 < l)) ? 1 : 0;
+    c += (q.z < mine || (q.z == mine && o + 2 < l)) ? 1 : 0;
+    c += (q.w < mine || (q.w == mine && o + 3 < l)) ? 1 : 0;
+  }
+  return c;
+}
+// Entries equal to `mine` before position l, in the same range.
+__device__ __forceinline__ int count_equal_before(const uint32_t *list, uint32_t mine, int l, int begin, int end) {
+  int c = 0;
+#pragma unroll 4
+  for (int o = begin; o < end; o += 4) {
+    const uint4 q = *reinterpret_cast<const uint4 *>(&list[o]);
+    c += (q.x == mine && o < l) ? 1 : 0;
+    c += (q.y == mine && o + 1 < l) ? 1 : 0;
+    c += (q.z == mine && o + 2 < l) ? 1 : 0;
+    c += (q.w == mine && o + 3 < l) ? 1 : 0;
+  }
+  return c;
+}
+
+// NT threads, windows of at most CAP tokens (the launcher's bound).
+template <int NT, int CAP>
+__global__ __launch_bounds__(NT) void pair_select_kernel(PairSelArgs g) {
+  constexpr int ITEMS = CAP / NT;
+  // order-preserving FD bits (step 1); then the neighbour of every token that leaves (step 4)
+  __shared__ __attribute__((aligned(16))) uint32_t key[CAP + 4];
+  __shared__ uint32_t minpend[2][CAP];      // per position, the lowest rank among the undecided tokens that name it
+  __shared__ int count[CAP];                // ranks (step 1), then sources of every position (step 4)
+  __shared__ uint16_t nbr[CAP];             // nearest neighbour (list position), 0xffff: none
+  __shared__ uint16_t rnk[CAP];
+  __shared__ uint16_t by_rank[CAP];         // token at every rank
+  __shared__ unsigned char state[CAP];
+  __shared__ unsigned char received[CAP];
+  __shared__ int wave_tot[NT / 64];
   const int w = blockIdx.x;
   const int off = g.win_offsets[w];
   int v = g.win_offsets[w + 1] - off;
   const int v_all = v;
   v = v < g.cap ? v : g.cap;
-  v = v < PS_MAX ? v : PS_MAX;
+  v = v < CAP ? v : CAP;
   int r = g.win_remove[w];
   r = r < 0 ? 0 : r;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
   // tokens of a window beyond the bound are neither scored nor merged
-  for (int l = v + tid; l < v_all; l += PS_THREADS) {
+  for (int l = v + tid; l < v_all; l += NT) {
     const int t = g.win_tokens[off + l];
     if ((unsigned)t < (unsigned)g.sum_n) {
       g.dst[t] = -1; g.cnt[t] = 0; g.src_rank[t] = 0;
@@ -65,143 +97,147 @@ __global__ __launch_bounds__(PS_THREADS) void pair_select_kernel(PairSelArgs g) 
     }
   }
   // ---- 0. keys -> LDS, best_fd / best_dst
-  int tok[PS_ITEMS];
+  const int v4 = (v + 3) & ~3;
+  int tok[ITEMS];
 #pragma unroll
-  for (int k = 0; k < PS_ITEMS; ++k) {
-    const int l = k * PS_THREADS + tid;
+  for (int k = 0; k < ITEMS; ++k) {
+    const int l = k * NT + tid;
     tok[k] = -1;
-    if (l < PS_MAX) { key[l] = 0xffffffffu; nbr[l] = 0xffffu; state[l] = PS_STAYS; received[l] = 0; }
+    if (k * NT >= v4) continue;   // uniform
+    if (l < v4) { key[l] = 0xffffffffu; nbr[l] = 0xffffu; }
     if (l < v) {
+      state[l] = PS_STAYS; received[l] = 0; minpend[0][l] = 0xffffffffu; count[l] = 0;
       const int t = g.win_tokens[off + l];
       const unsigned long long kk = g.keys[off + l];
       const bool okt = (unsigned)t < (unsigned)g.sum_n;
       const unsigned nb = (unsigned)(kk & 0xffffffffu);
       const float fd = __uint_as_float((unsigned)(kk >> 32));
-      const bool has = okt && kk != ~0ull && nb < (unsigned)v && fd >= 0.f;   // NaN or negative never competes
+      const bool scored = okt && kk != ~0ull && nb < (unsigned)v && fd >= 0.f;   // NaN or negative never competes
+      const int nt = g.win_tokens[off + (scored ? (int)nb : 0)];
+      const bool has = scored && (unsigned)nt < (unsigned)g.sum_n;
       tok[k] = okt ? t : -1;
-      key[l] = has ? f32_order_key(fd) : 0xffffffffu;
-      nbr[l] = has ? (uint16_t)nb : (uint16_t)0xffffu;
-      state[l] = has ? PS_UNDECIDED : PS_STAYS;
+      if (has) { key[l] = f32_order_key(fd); nbr[l] = (uint16_t)nb; state[l] = PS_UNDECIDED; }
       if (okt) {
-        const int nt = has ? g.win_tokens[off + (int)nb] : -1;
-        g.best_fd[t] = has ? fd : __uint_as_float(0x7f800000u);
-        g.best_dst[t] = ((unsigned)nt < (unsigned)g.sum_n) ? nt : -1;
-        if (has && (unsigned)nt >= (unsigned)g.sum_n) { nbr[l] = 0xffffu; state[l] = PS_STAYS; key[l] = 0xffffffffu; }
+        g.best_fd[t] = scored ? fd : __uint_as_float(0x7f800000u);
+        g.best_dst[t] = has ? nt : -1;
       }
     }
   }
   __syncthreads();
-  // ---- 1. ranks by counting (keys beyond v are all-ones: never smaller)
-  const int v4 = (v + 3) & ~3;
+  // ---- 1. ranks by counting (keys beyond v are all-ones: never smaller).  In a window of at most half the workgroup's
+  // threads, `segs` threads share a position and split the list.
+  int span = 64;                       // positions the threads are laid over: a power of two of at least v
+  while (span < v && span < NT) span <<= 1;
+  const int segs = ITEMS == 1 ? NT / span : 1;
+  const int seg_len = ((v4 / 4 + segs - 1) / segs) * 4;
+  const int my_l = ITEMS == 1 ? (tid & (span - 1)) : tid, my_begin = ITEMS == 1 ? (tid / span) * seg_len : 0;
+  const int my_end = min(v4, my_begin + seg_len);
+  if (ITEMS == 1) {
+    if (my_l < v && my_begin < my_end) {
+      const int c = count_before(key, key[my_l], my_l, my_begin, my_end);
+      if (c) atomicAdd(&count[my_l], c);
+    }
+    __syncthreads();
+  }
 #pragma unroll
-  for (int k = 0; k < PS_ITEMS; ++k) {
-    const int l = k * PS_THREADS + tid;
-    if (k * PS_THREADS < v) {   // uniform
-      const uint32_t mine = l < v ? key[l] : 0xffffffffu;
-      int c = 0;
-      for (int o = 0; o < v4; o += 4) {
-        const uint4 q = *reinterpret_cast<const uint4 *>(&key[o]);
-        c += (q.x < mine || (q.x == mine && o < l)) ? 1 : 0;
-        c += (q.y < mine || (q.y == mine && o + 1 < l)) ? 1 : 0;
-        c += (q.z < mine || (q.z == mine && o + 2 < l)) ? 1 : 0;
-        c += (q.w < mine || (q.w == mine && o + 3 < l)) ? 1 : 0;
-      }
-      if (l < v) { rnk[l] = (uint16_t)c; by_rank[c] = (uint16_t)l; }
+  for (int k = 0; k < ITEMS; ++k) {
+    const int l = k * NT + tid;
+    if (l < v) {
+      const int c = ITEMS == 1 ? count[l] : count_before(key, key[l], l, 0, v4);
+      rnk[l] = (uint16_t)c;
+      by_rank[c] = (uint16_t)l;
+      count[l] = 0;
     }
   }
   __syncthreads();
   // ---- 2. the visit as a fixed point
   for (int round = 0; round <= v; ++round) {   // bounded: every round decides at least one token
-    if (tid == 0) n_undecided = 0;
-    for (int l = tid; l < v; l += PS_THREADS) minpend[l] = 0xffffffffu;
+    uint32_t *pend = minpend[round & 1], *next = minpend[(round & 1) ^ 1];
+    for (int l = tid; l < v; l += NT)
+      if (state[l] == PS_UNDECIDED) atomicMin(&pend[nbr[l]], (uint32_t)rnk[l]);
     __syncthreads();
-    for (int l = tid; l < v; l += PS_THREADS)
-      if (state[l] == PS_UNDECIDED) atomicMin(&minpend[nbr[l]], (uint32_t)rnk[l]);
-    __syncthreads();
-    unsigned char decided[PS_ITEMS];
+    unsigned char decided[ITEMS];
     int left = 0;
 #pragma unroll
-    for (int k = 0; k < PS_ITEMS; ++k) {
-      const int l = k * PS_THREADS + tid;
+    for (int k = 0; k < ITEMS; ++k) {
+      const int l = k * NT + tid;
       decided[k] = PS_UNDECIDED;
-      if (l < v && state[l] == PS_UNDECIDED) {
-        const int b = nbr[l];
-        const uint32_t my_rank = rnk[l];
-        const unsigned char sb = state[b];
-        const bool ready = minpend[l] >= my_rank && (sb != PS_UNDECIDED || rnk[b] > my_rank);
-        if (ready) decided[k] = (received[l] || sb == PS_LEAVES) ? PS_STAYS : PS_LEAVES;
-        else ++left;
+      if (l < v) {
+        next[l] = 0xffffffffu;
+        if (state[l] == PS_UNDECIDED) {
+          const int b = nbr[l];
+          const uint32_t my_rank = rnk[l];
+          const unsigned char sb = state[b];
+          const bool ready = pend[l] >= my_rank && (sb != PS_UNDECIDED || rnk[b] > my_rank);
+          if (ready) decided[k] = (received[l] || sb == PS_LEAVES) ? PS_STAYS : PS_LEAVES;
+          else left = 1;
+        }
       }
     }
     __syncthreads();   // every thread has read the states of this round before any is changed
 #pragma unroll
-    for (int k = 0; k < PS_ITEMS; ++k) {
-      const int l = k * PS_THREADS + tid;
+    for (int k = 0; k < ITEMS; ++k) {
+      const int l = k * NT + tid;
       if (decided[k] != PS_UNDECIDED) {
         state[l] = decided[k];
         if (decided[k] == PS_LEAVES) received[nbr[l]] = 1;
       }
     }
-    if (left) atomicAdd(&n_undecided, left);
-    __syncthreads();
-    if (n_undecided == 0) break;   // uniform
-    __syncthreads();               // n_undecided is reset at the top of the next round
+    if (!__syncthreads_or(left)) break;   // uniform
   }
   // ---- 3. the first r leavers in rank order: by_rank[q] -> leavers before rank q (exclusive scan over ranks)
   {
     int carry = 0;
-    for (int q0 = 0; q0 < v; q0 += PS_THREADS) {   // uniform
+    for (int q0 = 0; q0 < v; q0 += NT) {   // uniform
       const int q = q0 + tid;
       const int flag = (q < v && state[by_rank[q]] == PS_LEAVES) ? 1 : 0;
       int inc = flag;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) { const int t = __shfl_up(inc, o, 64); if (lane >= o) inc += t; }
-      __syncthreads();
+      if (q0 > 0) __syncthreads();   // wave_tot may still be read from the pass before
       if (lane == 63) wave_tot[wave] = inc;
       __syncthreads();
       int before = carry;
       for (int k = 0; k < wave; ++k) before += wave_tot[k];
       if (q < v && flag && before + inc - flag >= r) state[by_rank[q]] = PS_STAYS;   // beyond the r-th merge: stays after all
       int total = 0;
-      for (int k = 0; k < PS_THREADS / 64; ++k) total += wave_tot[k];
+      for (int k = 0; k < NT / 64; ++k) total += wave_tot[k];
       carry += total;
     }
   }
   __syncthreads();
-  // ---- 4. destinations, source counts, source ranks.  key[] now counts the sources of every position; nbr of a token
-  // that stays is set to "none" so that the rank loop only compares neighbours.
-  for (int l = tid; l < v4; l += PS_THREADS) {
-    key[l] = 0;
-    if (l >= v || state[l] != PS_LEAVES) nbr[l] = 0xffffu;
+  // ---- 4. destinations, source counts, source ranks.  key[] now holds the neighbour of every token that leaves
+  // (all-ones: stays), count[] the sources of every position.
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const int l = k * NT + tid;
+    if (l < v4) {
+      const bool leaves = l < v && state[l] == PS_LEAVES;
+      key[l] = leaves ? (uint32_t)nbr[l] : 0xffffffffu;
+      if (leaves) atomicAdd(&count[nbr[l]], 1);
+    }
   }
+  int *src_rank = reinterpret_cast<int *>(minpend[0]);   // free now
+  if (ITEMS == 1) for (int l = tid; l < v; l += NT) src_rank[l] = 0;
   __syncthreads();
-  for (int l = tid; l < v; l += PS_THREADS)
-    if (nbr[l] != 0xffffu) atomicAdd(&key[nbr[l]], 1u);
-  __syncthreads();
+  if (ITEMS == 1) {
+    if (my_l < v && key[my_l] != 0xffffffffu && my_begin < my_end) {
+      const int c = count_equal_before(key, key[my_l], my_l, my_begin, my_end);
+      if (c) atomicAdd(&src_rank[my_l], c);
+    }
+    __syncthreads();
+  }
 #pragma unroll
-  for (int k = 0; k < PS_ITEMS; ++k) {
-    const int l = k * PS_THREADS + tid;
-    if (k * PS_THREADS < v) {   // uniform
-      const uint16_t mine = l < v ? nbr[l] : (uint16_t)0xffffu;
+  for (int k = 0; k < ITEMS; ++k) {
+    const int l = k * NT + tid;
+    if (l < v && tok[k] >= 0) {
+      const uint32_t mine = key[l];
+      const bool leaves = mine != 0xffffffffu;
       int c = 0;
-      if (__any(mine != 0xffffu)) {   // waves without a leaver skip the loop
-        for (int o = 0; o < v4; o += 8) {
-          const uint4 q = *reinterpret_cast<const uint4 *>(&nbr[o]);
-          const uint32_t ww[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            c += ((ww[e] & 0xffffu) == mine && o + 2 * e < l) ? 1 : 0;
-            c += ((ww[e] >> 16) == mine && o + 2 * e + 1 < l) ? 1 : 0;
-          }
-        }
-      }
-      if (l < v && tok[k] >= 0) {
-        const bool leaves = mine != 0xffffu;
-        const int bt = leaves ? g.win_tokens[off + mine] : -1;
-        g.dst[tok[k]] = leaves ? bt : -1;
-        g.src_rank[tok[k]] = leaves ? c : 0;
-        g.cnt[tok[k]] = (int)key[l];
-      }
+      if (leaves) c = ITEMS == 1 ? src_rank[l] : count_equal_before(key, mine, l, 0, v4);
+      g.dst[tok[k]] = leaves ? g.win_tokens[off + (int)mine] : -1;
+      g.src_rank[tok[k]] = c;
+      g.cnt[tok[k]] = count[l];
     }
   }
 }
@@ -215,7 +251,10 @@ hipError_t launch_pair_select(int n_windows, int max_window, int sum_n, const in
   g.n_windows = n_windows; g.sum_n = sum_n; g.cap = max_window;
   g.win_offsets = win_offsets; g.win_tokens = win_tokens; g.win_remove = win_remove; g.keys = keys;
   g.best_fd = best_fd; g.best_dst = best_dst; g.dst = dst; g.cnt = cnt; g.src_rank = src_rank;
-  hipLaunchKernelGGL(pair_select_kernel, dim3((unsigned)n_windows), dim3(PS_THREADS), 0, stream, g);
+  const dim3 grid((unsigned)n_windows);
+  if (max_window <= 256) hipLaunchKernelGGL((pair_select_kernel<256, 256>), grid, dim3(256), 0, stream, g);
+  else if (max_window <= 1024) hipLaunchKernelGGL((pair_select_kernel<1024, 1024>), grid, dim3(1024), 0, stream, g);
+  else hipLaunchKernelGGL((pair_select_kernel<1024, PS_MAX>), grid, dim3(1024), 0, stream, g);
   return hipGetLastError();
 }
 

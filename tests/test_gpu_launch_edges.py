@@ -97,3 +97,61 @@ def test_merge_over_the_row_segments(dtype, d, n, tail):
     want_sq = outs[0][:out].double().square().sum(1)
     assert bool(((sq.double() - want_sq).abs() <= 1e-6 * want_sq).all())
     assert torch.equal(pos_out, torch.cat([pos[:n][keep], pos[n:]]))
+
+
+@pytest.mark.parametrize("batch,gh,gw,w,d", [
+    (1, 4, 4, 2, 128), (2, 8, 8, 2, 64), (1, 16, 16, 4, 1088),     # windows of 4, 16 (packed tiles) and 16 tokens
+    (1, 8, 8, 0, 128), (1, 5, 13, 0, 128), (1, 12, 16, 0, 192),    # 64, 65 and 192 tokens: two, three and six tiles a side
+    (3, 16, 16, 1, 128), (1, 16, 17, 0, 128), (1, 27, 27, 0, 64),  # 256, 272 and 729 tokens: both selection sizes
+    (1, 32, 32, 0, 64), (16, 16, 16, 2, 64),                       # 1024 tiles of 32: beyond the small tiles
+])
+def test_full_pairwise_around_the_small_tiles(batch, gh, gw, w, d):
+    """Every token's nearest neighbour against float64 (ties and near-ties within 1e-5 of the best, the protocol's bound
+    for bf16), and the selection exactly against the visit applied to the scores the library reported."""
+    import paper_2605_00789_amd as L
+    from paper_2605_00789_amd import binding as B
+    from oracle import lightkv_oracle as O
+    n = gh * gw
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    X = torch.randn(16, d, generator=g, device="cuda")[torch.randint(0, 16, (batch * n,), generator=g, device="cuda")]
+    X = (X + torch.rand(batch * n, 1, generator=g, device="cuda") * torch.randn(batch * n, d, generator=g, device="cuda")).bfloat16()
+    X[3] = X[1]                                       # an exact copy: divergence zero
+    per = 1 if w == 0 else w * w
+    h = (np.arange(batch + 1) * n).astype(np.int32)
+    cu = torch.from_numpy(h).cuda()
+    pos = torch.arange(n, dtype=torch.int32).repeat(batch).cuda()
+    i32 = dict(dtype=torch.int32, device="cuda")
+    wo, wt, rem = torch.empty(batch * per + 1, **i32), torch.empty(batch * n, **i32), torch.empty(batch * per, **i32)
+    L.lightkv_build_windows(batch, h, cu, pos, 1, gh, gw, w, wo, wt)
+    L.lightkv_window_counts(batch, batch * per, wo, B.COUNT_RATIO, rem, rho=0.3)
+    p = L.Problem(batch=batch, d=d, heads=d // 32, head_dim=32, dtype="bf16", h_cu_vis=h, cu_vis=cu, n_windows=batch * per,
+                  max_window_tokens=min(n, L.lightkv_max_window_cells(1, gh, gw, w)), win_offsets=wo, win_tokens=wt,
+                  win_remove=rem, match=B.MATCH_FULL_PAIRWISE)
+    ws = torch.empty(L.lightkv_workspace_size(p), dtype=torch.uint8, device="cuda")
+    N = batch * n
+    xi, fd, dst, best = torch.ones(N, device="cuda"), torch.empty(N, device="cuda"), torch.empty(N, **i32), torch.empty(N, **i32)
+    new, off, src, cu_out = torch.empty(N, **i32), torch.empty(N + 1, **i32), torch.empty(N, **i32), torch.empty(batch + 1, **i32)
+    L.lightkv_score_select(p, X, None, None, xi, fd, best, dst, new, off, src, cu_out, ws, xi_mode=B.XI_GIVEN)
+    fd2, best2 = torch.empty(N, device="cuda"), torch.empty(N, **i32)
+    L.lightkv_score(p, X, None, None, xi, fd2, best2, ws, xi_mode=B.XI_GIVEN)
+    assert torch.equal(fd, fd2) and torch.equal(best, best2)
+    h_wo, h_wt, h_fd, h_best, h_dst = (t.cpu().numpy() for t in (wo, wt, fd, best, dst))
+    x64 = X.double()
+    x64 = x64 / x64.norm(dim=1, keepdim=True)
+    for k in range(batch * per):
+        toks = h_wt[h_wo[k]:h_wo[k + 1]]
+        t = torch.from_numpy(toks.astype(np.int64)).cuda()
+        m = (1.0 - x64[t] @ x64[t].T.contiguous()).clamp_min(0).cpu().numpy()
+        np.fill_diagonal(m, np.inf)
+        local = {int(a): i for i, a in enumerate(toks)}
+        nb = np.array([local[int(b)] for b in h_best[toks]])
+        assert np.all(np.abs(h_fd[toks] - m[np.arange(len(toks)), nb]) <= 1e-5)
+        assert np.all(h_fd[toks] <= m.min(1) + 1e-5)
+        r, gone, kept, want = int(0.3 * len(toks) + 1e-9), set(), set(), np.full(len(toks), -1)
+        for i in np.argsort(h_fd[toks], kind="stable"):
+            if len(gone) < min(r, (len(toks) + 1) // 2) and i not in kept and nb[i] not in gone:
+                gone.add(i)
+                kept.add(nb[i])
+                want[i] = toks[nb[i]]
+        np.testing.assert_array_equal(h_dst[toks], want)
+    np.testing.assert_array_equal(new.cpu().numpy(), O.kept_index(h_dst))
