@@ -4,7 +4,7 @@
 #include "lk_launch.h"
 #include "lk_helpers.h"
 #include "lk_win_body.h"
-#include "lk_fd_body.h"
+#include "lk_edge_body.h"
 #include "lk_xi_body.h"
 
 #include <math.h>
@@ -154,7 +154,7 @@ FdPlan small_tile_plan(const lightkv_problem *p, const Checked &c) {
 // Not for the tiled FD kernel (one workgroup of it fills a CU's LDS) and not for batches whose xi is one workgroup per
 // (sequence, head) pair; there the chains run on two streams.
 bool fused_launches(const lightkv_problem *p, const Checked &c, const FdPlan &fd, const XiPlan &xp, int xi_mode, const float *lse) {
-  return !edge_topk(p) && p->n_windows > 0 && c.sum_n > 0 && fd.n_tiles > 0 && xp.max_vis_blocks > 0 &&
+  return p->n_windows > 0 && c.sum_n > 0 && fd.n_tiles > 0 && xp.max_vis_blocks > 0 &&
          (full_pairwise(p) || !use_big_fd(p, c)) && !xi_seq_applies(xp, xi_mode, lse, p->batch, p->heads);
 }
 
@@ -435,6 +435,16 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
   hipStream_t s = static_cast<hipStream_t>(stream);
 
   if (use_big && (uint64_t)c.sum_n * (uint64_t)ldx * 2u >= (1ull << 32)) return LIGHTKV_ERR_UNSUPPORTED;   // 32-bit row offsets
+  EdgeArgs edge_args{};
+  EdgeList edge_list{};
+  if (edge) {
+    int32_t *edges = reinterpret_cast<int32_t *>(wsb + l.edges);
+    const int sum_k = (int)c.sum_remove;
+    edge_args = make_edge_args(c.max_window, sum_k, p->win_remove, sel->dst, reinterpret_cast<int32_t *>(wsb + l.sel_cnt),
+                               reinterpret_cast<int32_t *>(wsb + l.sel_rank), edges, c.edge_device_counts,
+                               reinterpret_cast<uint32_t *>(edges + (size_t)3 * (size_t)sum_k));
+    edge_list = EdgeList{edges, sum_k};
+  }
   // both halves and the selection: the two chains side by side in the same launches, on the caller's stream
   if (need_xi && need_fd && sel && fused_launches(p, c, fd, xp, xi_mode, lse)) {
     const float scale = softmax_scale != 0.f ? softmax_scale : 1.0f / sqrtf((float)p->head_dim);
@@ -446,10 +456,13 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
     FdArgs f = make_fd_args(fd, p->dtype, X, ldx, p->d, p->n_windows, c.sum_n, p->win_offsets, p->win_tokens,
                             reinterpret_cast<float *>(wsb + l.fd_partial), best_fd, best_dst);
     const SmallSelArgs q{p->win_remove, sel->dst, cnt, rank};
-    const bool tail = !pairwise && c.max_window <= 64;   // one tile per window: the epilogue selects as well
+    const bool tail = !pairwise && !edge && c.max_window <= 64;   // one tile per window: the epilogue selects as well
     if (pairwise) f.pair_keys = keys;
-    hipError_t e = launch_xi_fd_fused(x, xp, f, q, tail ? FUSED_TAIL : FUSED_EPILOGUE, fd.n_rowblocks, p->dtype, p->head_dim, s);
-    if (e == hipSuccess && pairwise)
+    hipError_t e = launch_xi_fd_fused(x, xp, f, q, edge ? &edge_args : nullptr, edge ? FUSED_EDGES : tail ? FUSED_TAIL : FUSED_EPILOGUE,
+                                      fd.n_rowblocks, p->dtype, p->head_dim, s);
+    if (e == hipSuccess && edge) {
+      if (edge_args.max_a > EDGE_MAX_SIDE) e = launch_edge_select_big(f, edge_args, s);
+    } else if (e == hipSuccess && pairwise)
       e = launch_pair_select(p->n_windows, c.max_window, c.sum_n, p->win_offsets, p->win_tokens, p->win_remove, keys, best_fd,
                              best_dst, sel->dst, cnt, rank, s);
     else if (e == hipSuccess && !tail)
@@ -457,7 +470,7 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
                                 0, best_fd, best_dst, sel->dst, cnt, rank, p->direction, s);
     if (e == hipSuccess)
       e = launch_select_scan_heads(p->batch, c.sum_n, p->cu_vis, sel->dst, sel->new_index, sel->grp_offsets, sel->grp_src,
-                                   sel->cu_vis_out, cnt, rank, x, s);
+                                   sel->cu_vis_out, cnt, rank, edge ? &edge_list : nullptr, x, s);
     return e == hipSuccess ? LIGHTKV_OK : LIGHTKV_ERR_LAUNCH;
   }
   Fork *fk = nullptr;
@@ -500,20 +513,16 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
         (sel && (launch_pair_select(p->n_windows, c.max_window, c.sum_n, p->win_offsets, p->win_tokens, p->win_remove, keys,
                                     best_fd, best_dst, sel->dst, cnt, rank, s) != hipSuccess ||
                  launch_select_scan(p->batch, c.sum_n, p->cu_vis, sel->dst, sel->new_index, sel->grp_offsets, sel->grp_src,
-                                    sel->cu_vis_out, cnt, rank, s) != hipSuccess)))
+                                    sel->cu_vis_out, cnt, rank, nullptr, s) != hipSuccess)))
       fd_status = LIGHTKV_ERR_LAUNCH;
   } else if (edge) {
     // the k lowest edges of every window: partial tiles, ranking per window, index scan, group lists from the edge list
     int32_t *cnt = reinterpret_cast<int32_t *>(wsb + l.sel_cnt), *rank = reinterpret_cast<int32_t *>(wsb + l.sel_rank);
-    int32_t *edges = reinterpret_cast<int32_t *>(wsb + l.edges);
-    const int sum_k = (int)c.sum_remove;
-    if (launch_edge_select(fd, p->dtype, X, ldx, p->d, p->n_windows, c.max_window, c.sum_n, sum_k, p->win_offsets,
-                           p->win_tokens, p->win_remove, reinterpret_cast<float *>(wsb + l.fd_partial), best_fd,
-                           best_dst, sel->dst, cnt, rank, edges, c.edge_device_counts,
-                           reinterpret_cast<uint32_t *>(edges + (size_t)3 * (size_t)sum_k), s) != hipSuccess ||
+    const FdArgs f = make_fd_args(fd, p->dtype, X, ldx, p->d, p->n_windows, c.sum_n, p->win_offsets, p->win_tokens,
+                                  reinterpret_cast<float *>(wsb + l.fd_partial), best_fd, best_dst);
+    if (launch_edge_select(f, edge_args, p->dtype, s) != hipSuccess ||
         launch_select_scan(p->batch, c.sum_n, p->cu_vis, sel->dst, sel->new_index, sel->grp_offsets, sel->grp_src,
-                           sel->cu_vis_out, cnt, rank, s) != hipSuccess ||
-        launch_edge_fill(sum_k, c.sum_n, edges, sel->grp_offsets, sel->grp_src, s) != hipSuccess)
+                           sel->cu_vis_out, cnt, rank, &edge_list, s) != hipSuccess)
       fd_status = LIGHTKV_ERR_LAUNCH;
   } else if (sel) {
     int32_t *cnt = reinterpret_cast<int32_t *>(wsb + l.sel_cnt), *rank = reinterpret_cast<int32_t *>(wsb + l.sel_rank);
@@ -521,7 +530,7 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
                                p->win_remove, reinterpret_cast<float *>(wsb + l.fd_partial), best_fd, best_dst,
                                sel->dst, cnt, rank, s) != hipSuccess ||
         launch_select_scan(p->batch, c.sum_n, p->cu_vis, sel->dst, sel->new_index, sel->grp_offsets, sel->grp_src,
-                           sel->cu_vis_out, cnt, rank, s) != hipSuccess)
+                           sel->cu_vis_out, cnt, rank, nullptr, s) != hipSuccess)
       fd_status = LIGHTKV_ERR_LAUNCH;
   } else if (use_big) {
     if (launch_fd_big(big, X, ldx, p->d, p->n_windows, c.sum_n, p->win_offsets, p->win_tokens,
@@ -598,7 +607,7 @@ static lightkv_status rows_call(int mode, const lightkv_problem *p, const int32_
                                 const void *X, int64_t ldx, const void *K, int64_t ldk, const void *V, int64_t ldv,
                                 const int32_t *pos, void *Xo, void *Ko, void *Vo, int32_t *pos_out,
                                 float *x_sqnorm_out, int64_t out_rows, int64_t tail_rows, const int32_t *cu_vis_out,
-                                const WinSpec *next, void *stream) {
+                                const WinSpec *next, unsigned long long *publish, unsigned publish_tag, void *stream) {
   Checked c;
   lightkv_status st = check_problem(p, false, false, c);
   if (st != LIGHTKV_OK) return st;
@@ -646,7 +655,8 @@ static lightkv_status rows_call(int mode, const lightkv_problem *p, const int32_
     }
   }
   if (launch_rows(mode, p->dtype, p->d, c.sum_n, p->batch, t, new_index, grp_offsets, grp_src, xi, pos, pos_out, x_sqnorm_out,
-                  out_rows, tail_rows, cu_vis_out, win_lds ? &win : nullptr, win_lds, static_cast<hipStream_t>(stream)) != hipSuccess)
+                  out_rows, tail_rows, cu_vis_out, win_lds ? &win : nullptr, win_lds, publish, publish_tag,
+                  static_cast<hipStream_t>(stream)) != hipSuccess)
     return LIGHTKV_ERR_LAUNCH;
   return LIGHTKV_OK;
 }
@@ -655,7 +665,7 @@ lightkv_status lightkv_aggregate(const lightkv_problem *p, const int32_t *grp_of
                                  const float *xi, void *X, int64_t ldx, void *K, int64_t ldk,
                                  void *V, int64_t ldv, void *stream) {
   return rows_call(0, p, nullptr, grp_offsets, grp_src, xi, X, ldx, K, ldk, V, ldv, nullptr, nullptr, nullptr,
-                   nullptr, nullptr, nullptr, 0, 0, nullptr, nullptr, stream);
+                   nullptr, nullptr, nullptr, 0, 0, nullptr, nullptr, nullptr, 0, stream);
 }
 
 lightkv_status lightkv_compact(const lightkv_problem *p, const int32_t *new_index,
@@ -664,7 +674,7 @@ lightkv_status lightkv_compact(const lightkv_problem *p, const int32_t *new_inde
                                void *X_out, void *K_out, void *V_out, int32_t *pos_out, float *x_sqnorm_out,
                                int64_t out_rows, int64_t tail_rows, const int32_t *cu_vis_out, void *stream) {
   return rows_call(1, p, new_index, nullptr, nullptr, nullptr, X, ldx, K, ldk, V, ldv, pos, X_out, K_out, V_out,
-                   pos_out, x_sqnorm_out, out_rows, tail_rows, cu_vis_out, nullptr, stream);
+                   pos_out, x_sqnorm_out, out_rows, tail_rows, cu_vis_out, nullptr, nullptr, 0, stream);
 }
 
 lightkv_status lightkv_aggregate_compact(const lightkv_problem *p, const int32_t *new_index,
@@ -675,7 +685,7 @@ lightkv_status lightkv_aggregate_compact(const lightkv_problem *p, const int32_t
                                          float *x_sqnorm_out, int64_t out_rows, int64_t tail_rows,
                                          const int32_t *cu_vis_out, void *stream) {
   return rows_call(2, p, new_index, grp_offsets, grp_src, xi, X, ldx, K, ldk, V, ldv, pos, X_out, K_out, V_out,
-                   pos_out, x_sqnorm_out, out_rows, tail_rows, cu_vis_out, nullptr, stream);
+                   pos_out, x_sqnorm_out, out_rows, tail_rows, cu_vis_out, nullptr, nullptr, 0, stream);
 }
 
 }  // extern "C"
@@ -684,9 +694,10 @@ int lk::aggregate_compact_with_windows(const lightkv_problem *p, const int32_t *
                                        const int32_t *grp_src, const float *xi, const void *X, int64_t ldx, const void *K,
                                        int64_t ldk, const void *V, int64_t ldv, const int32_t *pos, void *X_out, void *K_out,
                                        void *V_out, int32_t *pos_out, float *x_sqnorm_out, int64_t out_rows,
-                                       const int32_t *cu_vis_out, const WinSpec *next, void *stream) {
+                                       const int32_t *cu_vis_out, const WinSpec *next, unsigned long long *publish,
+                                       unsigned publish_tag, void *stream) {
   return rows_call(2, p, new_index, grp_offsets, grp_src, xi, X, ldx, K, ldk, V, ldv, pos, X_out, K_out, V_out, pos_out,
-                   x_sqnorm_out, out_rows, 0, cu_vis_out, next, stream);
+                   x_sqnorm_out, out_rows, 0, cu_vis_out, next, publish, publish_tag, stream);
 }
 
 // ---- lightkv_select without a workspace argument ---------------------------------------------------------------

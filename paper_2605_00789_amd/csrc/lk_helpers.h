@@ -77,4 +77,38 @@ HelperSet<N_STREAMS, N_EVENTS, TAG> *acquire_helpers(hipStream_t main, std::uniq
   return nullptr;
 }
 
+// A small block of pinned host memory that a kernel of one call writes to while the host of that call waits: per device a
+// pool of MAILBOXES_PER_DEVICE, each allocated on first need and kept for the life of the process (8 KB).  A call holds
+// one for itself; with none free (more calls at once than there are) or none to be had the caller copies instead.
+constexpr int MAILBOXES_PER_DEVICE = 4;
+constexpr int MAILBOX_WORDS = 1024;
+struct Mailbox {
+  unsigned long long *words = nullptr;
+  unsigned tag = 0;      // the last tag handed out; words start as zero, no tag is zero
+  std::mutex in_use;
+  unsigned next_tag() { return tag = tag + 1 ? tag + 1 : 1; }
+};
+inline Mailbox *acquire_mailbox(int n_words, std::unique_lock<std::mutex> &guard) {
+  static Mailbox pool[HELPER_MAX_DEVICES][MAILBOXES_PER_DEVICE];
+  int dev = 0;
+  if (n_words > MAILBOX_WORDS || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= HELPER_MAX_DEVICES) return nullptr;
+  for (int k = 0; k < MAILBOXES_PER_DEVICE; ++k) {
+    Mailbox &m = pool[dev][k];
+    std::unique_lock<std::mutex> g(m.in_use, std::try_to_lock);
+    if (!g.owns_lock()) continue;
+    if (!m.words) {
+      void *p = nullptr;
+      if (hipHostMalloc(&p, sizeof(unsigned long long) * MAILBOX_WORDS, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess || !p) {
+        (void)hipGetLastError();
+        return nullptr;
+      }
+      m.words = static_cast<unsigned long long *>(p);
+      for (int i = 0; i < MAILBOX_WORDS; ++i) m.words[i] = 0;
+    }
+    guard = std::move(g);
+    return &m;
+  }
+  return nullptr;
+}
+
 }  // namespace lk

@@ -75,7 +75,8 @@ int aggregate_compact_with_windows(const lightkv_problem *p, const int32_t *new_
                                    const int32_t *grp_src, const float *xi, const void *X, int64_t ldx, const void *K,
                                    int64_t ldk, const void *V, int64_t ldv, const int32_t *pos, void *X_out, void *K_out,
                                    void *V_out, int32_t *pos_out, float *x_sqnorm_out, int64_t out_rows,
-                                   const int32_t *cu_vis_out, const WinSpec *next, void *stream);
+                                   const int32_t *cu_vis_out, const WinSpec *next, unsigned long long *publish,
+                                   unsigned publish_tag, void *stream);
 
 // per-window counts from a ratio (mode 0: tokens, 1: edges) or from per-sequence target lengths (mode 2)
 hipError_t launch_window_counts(int batch, int win_per_seq, const int32_t *win_offsets, int mode, int dir, double rho,
@@ -105,17 +106,18 @@ hipError_t launch_fd_select_small(const FdPlan &plan, int dtype, const void *X, 
 // `edges` is scratch of 3 * sum_k ints (sum_k = the k of all windows, or a bound on it with device_counts, where a
 // window's k is also bounded by its tokens).
 constexpr int EDGE_MAX_SIDE = 128;
-hipError_t launch_fd_partial(const FdPlan &plan, int dtype, const void *X, int64_t ldx, int d, int n_windows, int sum_n,
-                             const int32_t *win_offsets, const int32_t *win_tokens, float *partial, hipStream_t stream);
-hipError_t launch_edge_select(const FdPlan &plan, int dtype, const void *X, int64_t ldx, int d, int n_windows,
-                              int max_window, int sum_n, int sum_k, const int32_t *win_offsets,
-                              const int32_t *win_tokens, const int32_t *win_remove, float *partial, float *best_fd,
-                              int32_t *best_dst, int32_t *dst, int32_t *cnt, int32_t *src_rank, int32_t *edges,
-                              bool device_counts, uint32_t *big_keys, hipStream_t stream);
+struct FdArgs;
+struct EdgeArgs;
+EdgeArgs make_edge_args(int max_window, int sum_k, const int32_t *win_remove, int32_t *dst, int32_t *cnt, int32_t *src_rank,
+                        int32_t *edges, bool device_counts, uint32_t *big_keys);
+hipError_t launch_fd_partial(const FdArgs &g, int dtype, hipStream_t stream);
+hipError_t launch_edge_select(const FdArgs &g, const EdgeArgs &q, int dtype, hipStream_t stream);
+hipError_t launch_edge_select_big(const FdArgs &g, const EdgeArgs &q, hipStream_t stream);   // behind the keys of every pair
 // the FD keys of every pair of every window, for windows beyond the one-kernel path: 32-bit keys (0 if not needed)
 size_t edge_big_key_count(int n_windows, int max_window);
-hipError_t launch_edge_fill(int sum_k, int sum_n, const int32_t *edges, const int32_t *grp_offsets, int32_t *grp_src,
-                            hipStream_t stream);
+// The edge list as the index scan takes it: [3][sum_k] (A token, B token, position); slots beyond the edges there are
+// (grp_offsets[sum_n]) are not read.
+struct EdgeList { const int32_t *edges; int sum_k; };
 
 // Debug dump of the FD of every pair (lk_fd_dump.hip); at most 65535 windows.
 hipError_t launch_fd_dump(int dtype, const void *X, int64_t ldx, int d, int n_windows, int max_window, int sum_n,
@@ -162,17 +164,19 @@ bool score_select_one_stream(const lightkv_problem *p);
 // the partial tiles, pass 2 beside what finishes them -- FUSED_TAIL: epilogue and selection of windows of at most 64
 // tokens, FUSED_EPILOGUE: best edges of larger ones (keys instead of best_fd / best_dst if pair_keys is given).  The
 // caller goes on with the selection and launch_select_scan_heads, which sums the heads of xi.
-enum FusedFinish { FUSED_TAIL = 0, FUSED_EPILOGUE = 1 };
+// FUSED_EDGES: the k lowest edges of every window (of at most 2 * EDGE_MAX_SIDE tokens), or the keys of every pair of larger
+// ones (launch_edge_select_big goes on).
+enum FusedFinish { FUSED_TAIL = 0, FUSED_EPILOGUE = 1, FUSED_EDGES = 2 };
 struct XiArgs;
 struct XiPlan;
 struct FdArgs;
 struct SmallSelArgs;
-hipError_t launch_xi_fd_fused(const XiArgs &x, const XiPlan &xp, const FdArgs &f, const SmallSelArgs &q, FusedFinish finish,
-                              int n_rowblocks, int dtype, int head_dim, hipStream_t stream);
+hipError_t launch_xi_fd_fused(const XiArgs &x, const XiPlan &xp, const FdArgs &f, const SmallSelArgs &q, const EdgeArgs *edges,
+                              FusedFinish finish, int n_rowblocks, int dtype, int head_dim, hipStream_t stream);
 // index scan with the head sum of xi in the same launch (x: arguments of the xi passes)
 hipError_t launch_select_scan_heads(int batch, int sum_n, const int32_t *cu_vis, const int32_t *dst, int32_t *new_index,
                                     int32_t *grp_offsets, int32_t *grp_src, int32_t *cu_vis_out, const int32_t *cnt,
-                                    const int32_t *src_rank, const XiArgs &x, hipStream_t stream);
+                                    const int32_t *src_rank, const EdgeList *edges, const XiArgs &x, hipStream_t stream);
 
 // ---- prompt-guidance weight xi (Step 3) ----------------------------------------------------
 struct XiPlan {
@@ -210,10 +214,10 @@ hipError_t launch_select_windows(int n_windows, int max_window_tokens, int sum_n
                                  int key_mt, int key_nt, float *best_fd, int32_t *best_dst, int32_t *dst, int32_t *cnt,
                                  int32_t *src_rank, int dir, hipStream_t stream);
 
-// the scan half of lightkv_select alone (dst, cnt, src_rank already written)
+// the scan half of lightkv_select alone (dst, cnt, src_rank already written); edges: the sources come from an edge list
 hipError_t launch_select_scan(int batch, int sum_n, const int32_t *cu_vis, const int32_t *dst, int32_t *new_index,
                               int32_t *grp_offsets, int32_t *grp_src, int32_t *cu_vis_out, const int32_t *cnt,
-                              const int32_t *src_rank, hipStream_t stream);
+                              const int32_t *src_rank, const EdgeList *edges, hipStream_t stream);
 
 // ---- message passing + compaction (Steps 3-5) ---------------------------------------------------
 struct RowTensors {
@@ -228,10 +232,12 @@ struct RowTensors {
 // tail_rows (modes 1 and 2): rows behind the vision span, input row sum_n + j -> output row cu_vis_out[batch] + j
 // win (mode 2, optional): the next stage's windows, built by `batch` workgroups of the same launch with win_lds bytes of
 // LDS each (at most ROWS_WIN_LDS_MAX: the row workgroups of the launch reserve them too)
+// publish (mode 2, optional): host memory of batch + 1 words that receive (publish_tag << 32 | cu_vis_out[i])
 constexpr size_t ROWS_WIN_LDS_MAX = 32 * 1024;
 hipError_t launch_rows(int mode, int dtype, int d, int sum_n, int batch, const RowTensors &t, const int32_t *new_index,
                        const int32_t *grp_offsets, const int32_t *grp_src, const float *xi, const int32_t *pos,
                        int32_t *pos_out, float *x_sqnorm_out, int64_t out_rows, int64_t tail_rows,
-                       const int32_t *cu_vis_out, const WinArgs *win, size_t win_lds, hipStream_t stream);
+                       const int32_t *cu_vis_out, const WinArgs *win, size_t win_lds, unsigned long long *publish,
+                       unsigned publish_tag, hipStream_t stream);
 
 }  // namespace lk

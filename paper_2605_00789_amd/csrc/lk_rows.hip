@@ -21,6 +21,9 @@ struct RowArgs {
   int64_t out_rows;   // capacity of the compacted outputs; rows beyond it are dropped
   int64_t tail_rows;  // rows behind the vision span (modes 1 and 2)
   const int32_t *cu_vis_out;   // with tail_rows: cu_vis_out[batch] vision rows stay
+  unsigned long long *publish;   // host memory, or NULL: (publish_tag << 32 | cu_vis_out[i]) for i = 0 .. batch
+  unsigned publish_tag;
+  int n_guest_blocks; // workgroups in front of the row workgroups: the windows', then the publishing one
   int n_win_blocks;   // workgroups in front of the row workgroups that build the next stage's windows
   int segs;           // segments per row
 };
@@ -74,10 +77,12 @@ constexpr int ROWS_WIN_KEEP = 12;   // passes of 256 tokens the window partition
 //   round 3  xi of the sources and the rows of the first two sources, together
 // A row without sources is stored after round 1.  Third and later sources of a group (rare) are fetched one by one.
 //
-// Two guests share the launch, because a launch or a stream fork of their own costs as much as they do:
+// Guests share the launch, because a launch or a stream fork of their own costs as much as they do:
 //   rows behind the vision span (the prompt's text, Steps 4-5): rows sum_n .. sum_n + tail_rows of the inputs move to
 //   output row n' + j, n' = cu_vis_out[batch] being read from the device;
-//   the next stage's windows: the first n_win_blocks workgroups build them (they need pos and new_index only).
+//   the next stage's windows: the first n_win_blocks workgroups build them (they need pos and new_index only);
+//   the sequence offsets the step leaves, for a host that has to lay the next stage out: one workgroup writes them to
+//   host memory at the start of the launch, so the host works while the rows move.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 template <bool STREAM>
@@ -105,9 +110,17 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
       build_windows_body<ROW_THREADS, ROWS_WIN_KEEP>(wn, blockIdx.x, win_lds);
       return;
     }
+    if ((int)blockIdx.x < g.n_guest_blocks) {
+      if (blockIdx.y > 0) return;
+      // every word carries the tag, so the host needs no order between them
+      for (int i = threadIdx.x; i <= g.batch; i += ROW_THREADS)
+        __hip_atomic_store(&g.publish[i], ((unsigned long long)g.publish_tag << 32) | (unsigned)g.cu_vis_out[i],
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      return;
+    }
   }
   const int lane = threadIdx.x & 63;
-  const int64_t b = (int64_t)((int)blockIdx.x - g.n_win_blocks) * ROWS_PER_WG + (threadIdx.x >> 6);
+  const int64_t b = (int64_t)((int)blockIdx.x - g.n_guest_blocks) * ROWS_PER_WG + (threadIdx.x >> 6);
   const int which = blockIdx.y / g.segs;                   // grid y: tensor and segment
   int seg = blockIdx.y - which * g.segs;
   if (b >= g.sum_n + g.tail_rows) return;
@@ -301,15 +314,18 @@ static void launch_rows_u(int mode, bool stream_out, const dim3 &grid, size_t ld
 hipError_t launch_rows(int mode, int dtype, int d, int sum_n, int batch, const RowTensors &t, const int32_t *new_index,
                        const int32_t *grp_offsets, const int32_t *grp_src, const float *xi, const int32_t *pos,
                        int32_t *pos_out, float *x_sqnorm_out, int64_t out_rows, int64_t tail_rows,
-                       const int32_t *cu_vis_out, const WinArgs *win, size_t win_lds, hipStream_t stream) {
+                       const int32_t *cu_vis_out, const WinArgs *win, size_t win_lds, unsigned long long *publish,
+                       unsigned publish_tag, hipStream_t stream) {
   if (mode == 0) tail_rows = 0;
-  if (sum_n + tail_rows == 0 && !win) return hipSuccess;
+  if (sum_n + tail_rows == 0 && !win && !publish) return hipSuccess;
   RowArgs g{};
   g.x_sqnorm_out = x_sqnorm_out;
   g.t = t; g.new_index = new_index; g.grp_offsets = grp_offsets; g.grp_src = grp_src; g.pos = pos;
   g.pos_out = pos_out; g.xi = xi; g.d = d; g.sum_n = sum_n; g.out_rows = out_rows;
   g.tail_rows = tail_rows; g.cu_vis_out = cu_vis_out; g.batch = batch;
   g.n_win_blocks = win ? batch : 0;
+  g.publish = publish; g.publish_tag = publish_tag;
+  g.n_guest_blocks = g.n_win_blocks + (publish ? 1 : 0);
   int n_tensors = 0;
   for (int i = 0; i < 3; ++i) n_tensors += t.in[i] != nullptr;
   // nontemporal output stores once the tensors are far beyond what stays cached until the next stage reads them
@@ -319,7 +335,7 @@ hipError_t launch_rows(int mode, int dtype, int d, int sum_n, int batch, const R
   const int max_u = stream_out ? ROW_MAX_U_STREAM : ROW_MAX_U;
   g.segs = (per_lane + max_u - 1) / max_u;
   const int u = (per_lane + g.segs - 1) / g.segs;
-  const dim3 grid((unsigned)(g.n_win_blocks + (sum_n + tail_rows + ROWS_PER_WG - 1) / ROWS_PER_WG), (unsigned)(3 * g.segs));
+  const dim3 grid((unsigned)(g.n_guest_blocks + (sum_n + tail_rows + ROWS_PER_WG - 1) / ROWS_PER_WG), (unsigned)(3 * g.segs));
   const WinArgs wn = win ? *win : WinArgs{};
   const size_t lds = win ? win_lds : 0;
 #define LK_ROWS(TT)                                                                       \

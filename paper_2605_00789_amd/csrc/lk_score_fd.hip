@@ -115,11 +115,9 @@ hipError_t launch_fd_pair_small(const FdPlan &plan, const void *X, int64_t ldx, 
   return hipGetLastError();
 }
 
-hipError_t launch_fd_partial(const FdPlan &plan, int dtype, const void *X, int64_t ldx, int d, int n_windows, int sum_n,
-                             const int32_t *win_offsets, const int32_t *win_tokens, float *partial, hipStream_t stream) {
-  if (n_windows == 0 || plan.n_tiles == 0) return hipSuccess;
-  const FdArgs g = make_fd_args(plan, dtype, X, ldx, d, n_windows, sum_n, win_offsets, win_tokens, partial, nullptr, nullptr);
-  const dim3 grid((unsigned)(plan.n_tiles * plan.ksplit));
+hipError_t launch_fd_partial(const FdArgs &g, int dtype, hipStream_t stream) {
+  if (g.n_windows == 0 || g.n_tiles == 0) return hipSuccess;
+  const dim3 grid((unsigned)(g.n_tiles * g.ksplit));
   if (dtype == 1) hipLaunchKernelGGL(fd_partial_kernel<bf16_t>, grid, dim3(FD_THREADS), 0, stream, g);
   else hipLaunchKernelGGL(fd_partial_kernel<float>, grid, dim3(FD_THREADS), 0, stream, g);
   return hipGetLastError();

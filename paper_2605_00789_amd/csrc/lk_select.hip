@@ -28,6 +28,7 @@ struct SelArgs {
   int cap;   // power of two >= the larger side of the largest window
   int dir;   // 0: even list positions propose, 1: odd ones (side_a / pos_a)
   int per_seq;   // scan: one workgroup per sequence (0: one workgroup for the whole batch)
+  EdgeList edges;   // scan<..., true>: the sources of every token come from this list, not from dst
 };
 
 
@@ -308,7 +309,9 @@ constexpr size_t SCAN_LDS_BYTES = (size_t)2 * SCAN_THREADS * SCAN_ITEMS * sizeof
 // partials (last pass of the xi computation, lk_xi_body.h), which is independent of the scan and as short; the scan
 // is the last workgroup.  (The scan stays written out in the kernel: as an inlined function it costs eight more
 // registers at the 128-register limit of a 1024-thread workgroup and spills.)
-template <bool WITH_HEADS>
+// EDGES: the inverse map comes from an edge list (an A token may be a source of several B tokens).  The list is in window
+// order, and a caller's windows may come in any order, so a workgroup looks at all edges and takes its sequence's.
+template <bool WITH_HEADS, bool EDGES>
 __global__ __launch_bounds__(SCAN_THREADS) void select_scan_kernel(SelArgs g, XiArgs x, int n_head_blocks) {
   if (WITH_HEADS && (int)blockIdx.x < n_head_blocks) {
     xi_heads_body(x, blockIdx.x * SCAN_THREADS + threadIdx.x);
@@ -437,6 +440,29 @@ __global__ __launch_bounds__(SCAN_THREADS) void select_scan_kernel(SelArgs g, Xi
   // pass the group starts of all tokens are in LDS (written before the barrier above); otherwise they are read back
   // from global memory after the barrier below.
   // (a target outside [t0, t1) cannot come from the selection kernels; it is dropped rather than followed)
+  if (EDGES) {
+    if (!one_pass) __syncthreads();   // the group starts are read back from global memory
+    int n_edges = cnt_base;
+    if (g.per_seq) {   // ... and those of the sequences behind this one
+      int after = 0;
+      for (int i = t1 + tid; i < g.sum_n; i += SCAN_THREADS) after += g.cnt[i];
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) after += __shfl_xor(after, o, 64);
+      __syncthreads();
+      if (lane == 0) wsum[wave].x = after;
+      __syncthreads();
+#pragma unroll
+      for (int w2 = 0; w2 < SCAN_THREADS / 64; ++w2) n_edges += wsum[w2].x;
+    }
+    n_edges = n_edges < g.edges.sum_k ? n_edges : g.edges.sum_k;
+    for (int i = tid; i < n_edges; i += SCAN_THREADS) {
+      const int a = g.edges.edges[i], b = g.edges.edges[g.edges.sum_k + i], pos = g.edges.edges[2 * g.edges.sum_k + i];
+      if (a < t0 || a >= t1 || b < t0 || b >= t1) continue;
+      const int slot = (one_pass ? gb[b - t0] : g.grp_offsets[b]) + pos;
+      if (slot >= 0 && slot < g.edges.sum_k) g.grp_src[slot] = a;
+    }
+    return;
+  }
   if (one_pass) {
     const int i0 = t0 + tid * per;
 #pragma unroll
@@ -477,12 +503,13 @@ static hipError_t allow_scan_lds() {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (done[dev].load(std::memory_order_acquire)) return hipSuccess;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(select_scan_kernel<false>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)SCAN_LDS_BYTES);
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute(reinterpret_cast<const void *>(select_scan_kernel<true>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)SCAN_LDS_BYTES);
-  if (e != hipSuccess) return e;
+  const void *kernels[4] = {
+      reinterpret_cast<const void *>(select_scan_kernel<false, false>), reinterpret_cast<const void *>(select_scan_kernel<true, false>),
+      reinterpret_cast<const void *>(select_scan_kernel<false, true>), reinterpret_cast<const void *>(select_scan_kernel<true, true>)};
+  for (const void *k : kernels) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SCAN_LDS_BYTES);
+    if (e != hipSuccess) return e;
+  }
   done[dev].store(true, std::memory_order_release);
   return hipSuccess;
 }
@@ -493,35 +520,37 @@ static int scan_per_sequence(int batch, int sum_n) {
   return (batch > 1 && batch <= SCAN_PER_SEQ_MAX_BATCH && sum_n >= SCAN_PER_SEQ_MIN_TOKENS) ? 1 : 0;
 }
 
-hipError_t launch_select_scan(int batch, int sum_n, const int32_t *cu_vis, const int32_t *dst, int32_t *new_index,
+static hipError_t launch_scan(int batch, int sum_n, const int32_t *cu_vis, const int32_t *dst, int32_t *new_index,
                               int32_t *grp_offsets, int32_t *grp_src, int32_t *cu_vis_out, const int32_t *cnt,
-                              const int32_t *src_rank, hipStream_t stream) {
+                              const int32_t *src_rank, const EdgeList *edges, const XiArgs *x, hipStream_t stream) {
   SelArgs g{};
   g.batch = batch; g.sum_n = sum_n; g.cu_vis = cu_vis;
   g.dst = const_cast<int32_t *>(dst); g.new_index = new_index; g.grp_offsets = grp_offsets; g.grp_src = grp_src;
   g.cu_vis_out = cu_vis_out; g.cnt = const_cast<int32_t *>(cnt); g.src_rank = const_cast<int32_t *>(src_rank);
   g.per_seq = scan_per_sequence(batch, sum_n);
-  hipError_t e = allow_scan_lds();
+  if (edges) g.edges = *edges;
+  const hipError_t e = allow_scan_lds();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(select_scan_kernel<false>, dim3(g.per_seq ? (unsigned)batch : 1u), dim3(SCAN_THREADS), SCAN_LDS_BYTES,
-                     stream, g, XiArgs{}, 0);
+  const int n_head_blocks = x ? (sum_n + SCAN_THREADS - 1) / SCAN_THREADS : 0;
+  const dim3 grid((unsigned)(n_head_blocks + (g.per_seq ? batch : 1))), block(SCAN_THREADS);
+  const XiArgs xa = x ? *x : XiArgs{};
+  if (x && edges) hipLaunchKernelGGL((select_scan_kernel<true, true>), grid, block, SCAN_LDS_BYTES, stream, g, xa, n_head_blocks);
+  else if (x) hipLaunchKernelGGL((select_scan_kernel<true, false>), grid, block, SCAN_LDS_BYTES, stream, g, xa, n_head_blocks);
+  else if (edges) hipLaunchKernelGGL((select_scan_kernel<false, true>), grid, block, SCAN_LDS_BYTES, stream, g, xa, 0);
+  else hipLaunchKernelGGL((select_scan_kernel<false, false>), grid, block, SCAN_LDS_BYTES, stream, g, xa, 0);
   return hipGetLastError();
+}
+
+hipError_t launch_select_scan(int batch, int sum_n, const int32_t *cu_vis, const int32_t *dst, int32_t *new_index,
+                              int32_t *grp_offsets, int32_t *grp_src, int32_t *cu_vis_out, const int32_t *cnt,
+                              const int32_t *src_rank, const EdgeList *edges, hipStream_t stream) {
+  return launch_scan(batch, sum_n, cu_vis, dst, new_index, grp_offsets, grp_src, cu_vis_out, cnt, src_rank, edges, nullptr, stream);
 }
 
 hipError_t launch_select_scan_heads(int batch, int sum_n, const int32_t *cu_vis, const int32_t *dst, int32_t *new_index,
                                     int32_t *grp_offsets, int32_t *grp_src, int32_t *cu_vis_out, const int32_t *cnt,
-                                    const int32_t *src_rank, const XiArgs &x, hipStream_t stream) {
-  SelArgs g{};
-  g.batch = batch; g.sum_n = sum_n; g.cu_vis = cu_vis;
-  g.dst = const_cast<int32_t *>(dst); g.new_index = new_index; g.grp_offsets = grp_offsets; g.grp_src = grp_src;
-  g.cu_vis_out = cu_vis_out; g.cnt = const_cast<int32_t *>(cnt); g.src_rank = const_cast<int32_t *>(src_rank);
-  g.per_seq = scan_per_sequence(batch, sum_n);
-  const int n_head_blocks = (sum_n + SCAN_THREADS - 1) / SCAN_THREADS;
-  hipError_t e = allow_scan_lds();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(select_scan_kernel<true>, dim3((unsigned)(n_head_blocks + (g.per_seq ? batch : 1))), dim3(SCAN_THREADS), SCAN_LDS_BYTES,
-                     stream, g, x, n_head_blocks);
-  return hipGetLastError();
+                                    const int32_t *src_rank, const EdgeList *edges, const XiArgs &x, hipStream_t stream) {
+  return launch_scan(batch, sum_n, cu_vis, dst, new_index, grp_offsets, grp_src, cu_vis_out, cnt, src_rank, edges, &x, stream);
 }
 
 hipError_t launch_select_windows(int n_windows, int max_window_tokens, int sum_n, const int32_t *win_offsets,
@@ -561,7 +590,7 @@ hipError_t launch_select(int n_windows, int max_window_tokens, int batch, int su
   const hipError_t e = launch_select_windows(n_windows, max_window_tokens, sum_n, win_offsets, win_tokens, win_remove, keys,
                                              key_mt, key_nt, best_fd, best_dst, dst, cnt, src_rank, dir, stream);
   if (e != hipSuccess) return e;
-  return launch_select_scan(batch, sum_n, cu_vis, dst, new_index, grp_offsets, grp_src, cu_vis_out, cnt, src_rank, stream);
+  return launch_select_scan(batch, sum_n, cu_vis, dst, new_index, grp_offsets, grp_src, cu_vis_out, cnt, src_rank, nullptr, stream);
 }
 
 }  // namespace lk

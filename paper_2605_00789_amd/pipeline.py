@@ -408,15 +408,19 @@ class EdgeTopKSchedule:
             c = self._call = self._call_buffers(h_cu_vis)
         h_out = B.lightkv_compress_schedule_ratio(c["stages"], self.rho, self.tiles, self.grid_h, self.grid_w, X, K, V,
                                                   pos, Q, self._ws)
-        out, n_in = [], int(h_cu_vis[-1])
+        out, n_in, cap = [], int(h_cu_vis[-1]), self.capacity
         for s, b in enumerate(c["bufs"]):
             X_out, K_out, V_out, pos_out = self._out[s % 2]
             n_out = int(h_out[s, -1])
-            n_windows = self.batch * windows_per_sequence(self.tiles, self.windows_per_axis[s])
-            out.append(EdgeStepResult(h_out[s], X_out[:n_out], K_out[:n_out], V_out[:n_out], pos_out[:n_out],
-                                      b["xi"][:n_in], b["best_fd"][:max(n_in, 1)], b["best_dst"][:max(n_in, 1)],
-                                      b["dst"][:max(n_in, 1)], b["new_index"][:max(n_in, 1)], b["grp_offsets"][:n_in + 1],
-                                      b["grp_src"], b["win_offsets"], b["win_tokens"], b["win_remove"][:n_windows],
+            # a view costs more than a microsecond and nothing on the device runs meanwhile: whole buffers go out as they are
+            per_token = (b["xi"], b["best_fd"], b["best_dst"], b["dst"], b["new_index"])
+            offsets = b["grp_offsets"]
+            if n_in < cap:
+                n1 = max(n_in, 1)
+                per_token = (b["xi"][:n_in], b["best_fd"][:n1], b["best_dst"][:n1], b["dst"][:n1], b["new_index"][:n1])
+                offsets = offsets[:n_in + 1]
+            out.append(EdgeStepResult(h_out[s], X_out[:n_out], K_out[:n_out], V_out[:n_out], pos_out[:n_out], *per_token,
+                                      offsets, b["grp_src"], b["win_offsets"], b["win_tokens"], b["win_remove"],
                                       b["cu_vis_out"]))
             n_in = n_out
         return out

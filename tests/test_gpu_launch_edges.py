@@ -155,3 +155,83 @@ def test_full_pairwise_around_the_small_tiles(batch, gh, gw, w, d):
                 want[i] = toks[nb[i]]
         np.testing.assert_array_equal(h_dst[toks], want)
     np.testing.assert_array_equal(new.cpu().numpy(), O.kept_index(h_dst))
+
+
+@pytest.mark.parametrize("dtype,batch,gh,gw,w,d,ties", [
+    ("bf16", 1, 4, 4, 2, 64, False), ("bf16", 2, 12, 12, 3, 256, False), ("f32", 1, 14, 14, 2, 128, False),   # 4, 16, 49 tokens
+    ("bf16", 1, 14, 14, 1, 96, False), ("bf16", 1, 16, 16, 1, 256, True),                    # 196 and 256: the largest in LDS
+    ("bf16", 1, 17, 16, 1, 128, False), ("bf16", 2, 17, 31, 1, 64, True),                    # 272 and 527: the key matrix
+    ("bf16", 9, 16, 16, 4, 64, False), ("f32", 3, 28, 28, 2, 32, True),                      # an index scan per sequence
+])
+@pytest.mark.parametrize("with_xi", [False, True])
+def test_edge_selection_in_any_window_order(dtype, batch, gh, gw, w, d, ties, with_xi):
+    """The k lowest edges of every window against the rule applied in float64 to the scores the library reports for its
+    own order (exact), with windows listed in order and shuffled over the batch: the same edges either way.  `ties`:
+    tokens are copies of a few rows, so that nearly every divergence is shared by many pairs."""
+    import paper_2605_00789_amd as L
+    from paper_2605_00789_amd import binding as B
+    n, N = gh * gw, batch * gh * gw
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rows = torch.randn(5 if ties else 24, d, generator=g, device="cuda")
+    X = rows[torch.randint(0, rows.shape[0], (N,), generator=g, device="cuda")]
+    if not ties:
+        X = X + (0.2 + torch.rand(N, 1, generator=g, device="cuda")) * torch.randn(N, d, generator=g, device="cuda")
+    X = X.to(tdt)
+    K, Q = torch.randn(N, d, generator=g, device="cuda").to(tdt), torch.randn(7 * batch, d, generator=g, device="cuda").to(tdt)
+    per = w * w
+    h, ht = (np.arange(batch + 1) * n).astype(np.int32), (np.arange(batch + 1) * 7).astype(np.int32)
+    cu, cut = torch.from_numpy(h).cuda(), torch.from_numpy(ht).cuda()
+    i32 = dict(dtype=torch.int32, device="cuda")
+    wo, wt = torch.empty(batch * per + 1, **i32), torch.empty(N, **i32)
+    L.lightkv_build_windows(batch, h, cu, torch.arange(n, dtype=torch.int32).repeat(batch).cuda(), 1, gh, gw, w, wo, wt)
+    wo, wt = wo.cpu().numpy(), wt.cpu().numpy()
+    lists = [wt[wo[i]:wo[i + 1]] for i in range(batch * per)]
+    got = []
+    for order in (np.arange(batch * per), np.random.default_rng(3).permutation(batch * per)):
+        ls = [lists[i] for i in order]
+        owo = torch.from_numpy(np.concatenate([[0], np.cumsum([len(l) for l in ls])]).astype(np.int32)).cuda()
+        owt = torch.from_numpy(np.concatenate(ls)).cuda()
+        rem = torch.from_numpy(np.array([min(int(0.18 * len(l)), (len(l) + 1) // 2 * (len(l) // 2)) for l in ls], dtype=np.int32)).cuda()
+        p = L.Problem(batch=batch, d=d, heads=d // 32, head_dim=32, dtype=dtype, h_cu_vis=h, cu_vis=cu, h_cu_txt=ht, cu_txt=cut,
+                      n_windows=batch * per, max_window_tokens=max(len(l) for l in ls), win_offsets=owo, win_tokens=owt,
+                      win_remove=rem, match=B.MATCH_EDGE_TOPK)
+        ws = torch.full((L.lightkv_workspace_size(p),), 0x5a, dtype=torch.uint8, device="cuda")
+        xi, fd = torch.ones(N, device="cuda"), torch.empty(N, device="cuda")
+        best, dst, new, src = (torch.full((N,), -9, **i32) for _ in range(4))
+        off, cu_out = torch.empty(N + 1, **i32), torch.empty(batch + 1, **i32)
+        L.lightkv_score_select(p, X, Q if with_xi else None, K if with_xi else None, xi, fd, best, dst, new, off, src, cu_out, ws,
+                               xi_mode=B.XI_TEXT_QUERY if with_xi else B.XI_GIVEN)
+        total = int(off[-1])
+        got.append([t.cpu().numpy() for t in (fd, best, dst, new, off, cu_out)] + [src[:total].cpu().numpy()])
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+    fd, best, dst, new, off, cu_out, src = got[0]
+    x64 = X.double()
+    x64 = x64 / x64.norm(dim=1, keepdim=True)
+    for l in lists:
+        a, b = l[0::2], l[1::2]
+        k = min(int(0.18 * len(l)), len(a) * len(b))
+        edges = [(s, int(t)) for t in b for s in src[off[t]:off[t + 1]]]
+        assert len(edges) == k and len(set(edges)) == k
+        if not len(b):
+            continue
+        ta, tb = (torch.from_numpy(v.astype(np.int64)).cuda() for v in (a, b))
+        m = (1.0 - x64[ta] @ x64[tb].T.contiguous()).clamp_min(0).cpu().numpy()
+        ia, ib = {int(v): i for i, v in enumerate(a)}, {int(v): i for i, v in enumerate(b)}
+        mine = np.zeros(m.shape, dtype=bool)
+        for s, t in edges:
+            mine[ia[int(s)], ib[t]] = True
+        # nothing left out is lower than anything taken by more than fp32 scores resolve (1e-5 bf16 protocol, 1e-6 fp32)
+        tol = 1e-5 if dtype == "bf16" else 1e-6
+        if 0 < k < m.size:
+            assert m[mine].max() <= m[~mine].min() + tol
+        for t in b:
+            assert list(src[off[t]:off[t + 1]]) == sorted(src[off[t]:off[t + 1]])
+        assert set(np.flatnonzero(mine.any(1))) == {i for i, v in enumerate(a) if dst[v] >= 0}
+        if ties and k:   # copies: exact zeros, taken in (A position, B position) order
+            zero = m <= tol
+            if zero.sum() >= k:
+                want = np.zeros(m.size, dtype=bool)
+                want[np.flatnonzero(zero.reshape(-1))[:k]] = True
+                np.testing.assert_array_equal(mine.reshape(-1), want)
