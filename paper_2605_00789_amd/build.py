@@ -15,6 +15,10 @@ SOURCES = ["lk_api.hip", "lk_windows.hip", "lk_score_fd.hip", "lk_score_fd_big.h
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed-fp32 instruction forms are kept out of the generated code on purpose
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# matrix-core results that vector instructions go on with at once: left alone the compiler puts them into accumulation
+# registers and copies every one of them out (16 copies per 32 x 32 tile)
+FILE_FLAGS = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+              for src in ("lk_score_xi.hip", "lk_fused.hip")}
 
 
 def _hipcc() -> str:
@@ -31,7 +35,7 @@ def build(verbose: bool = True, jobs: int = 6) -> str:
 
     def compile_one(src):
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
-        cmd = [hipcc, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc, *FLAGS, *FILE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
         if r.returncode != 0:

@@ -43,7 +43,13 @@ __device__ __forceinline__ double divergence(int metric, double dot, double a2, 
   return metric == 1 ? sqrt(d2 < 0.0 ? 0.0 : d2) : (d2 < 0.0 ? 0.0 : d2);
 }
 
-constexpr int FD_PARTIAL_LDS = FD_WAVES * (32 * 32 + 2 * 32) * (int)sizeof(float);   // bytes of LDS fd_partial_body needs
+// LDS of fd_partial_body: a staged piece of the tile's 64 rows (one 128-byte span per wave and row; the rows padded by 16
+// bytes, so that the sixteen lanes of a quarter wave read their 16-byte fragments from 64 different banks), and afterwards
+// the four waves' sums.
+constexpr int FD_STAGE_BYTES = FD_WAVES * 128;
+constexpr int FD_STAGE_PITCH = FD_STAGE_BYTES + 16;
+constexpr int FD_RED_LDS = FD_WAVES * (32 * 32 + 2 * 32) * (int)sizeof(float);
+constexpr int FD_PARTIAL_LDS = 64 * FD_STAGE_PITCH > FD_RED_LDS ? 64 * FD_STAGE_PITCH : FD_RED_LDS;
 
 struct WinInfo { int off, nA, nB; };
 
@@ -66,9 +72,7 @@ __device__ __forceinline__ int checked_token(const FdArgs &g, int idx) {
 template <typename T>
 __device__ __forceinline__ void fd_partial_body(const FdArgs &g, int block_id, char *lds) {
   using E = Elem<T>;
-  constexpr int EPC = E::PER_CHUNK;
-  constexpr int LANE_ELEMS = FD_CHUNKS * EPC;   // contiguous elements of one lane in a span
-  constexpr int SPAN = 2 * LANE_ELEMS;          // elements of a row covered by one span
+  constexpr int SPAN = 2 * FD_CHUNKS * E::PER_CHUNK;   // elements of a row covered by one span: 64 bytes per half wave
 
   float (*red)[32 * 32] = reinterpret_cast<float (*)[32 * 32]>(lds);                                  // [FD_WAVES][32 * 32]
   float (*rnorm)[2][32] = reinterpret_cast<float (*)[2][32]>(lds + FD_WAVES * 32 * 32 * sizeof(float));   // [FD_WAVES][2][32]
@@ -103,46 +107,57 @@ __device__ __forceinline__ void fd_partial_body(const FdArgs &g, int block_id, c
   // a tile without A rows or without B rows is never read by the epilogue
   if (__ballot(a_tok >= 0) == 0ull || __ballot(b_tok >= 0) == 0ull) return;
 
-  // padding rows of the tile read token 0: their products land in rows/columns nobody reads
-  const char *pa = static_cast<const char *>(g.X) + (int64_t)(a_tok < 0 ? 0 : a_tok) * g.ldx * E::BYTES;
-  const char *pb = static_cast<const char *>(g.X) + (int64_t)(b_tok < 0 ? 0 : b_tok) * g.ldx * E::BYTES;
+  // The slice travels through LDS in pieces of four spans (one per wave): a wave instruction fetches 512 contiguous bytes
+  // of two rows.  Fetched straight into MFMA operands, every lane's 16 bytes lie on a line of their own and the lines of
+  // the waves in flight are many times the CU's L1, which costs twice the trips: 2880 tokens in
+  // 180 windows 10.6 -> 8.9 us cold, 8.1 -> 6.9 us with X in the caches.
+  // Padding rows of the tile read token 0: their products land in rows/columns nobody reads.
+  constexpr int ROW_PASSES = 64 / (FD_THREADS / 32);      // 32 threads a row, eight rows per pass
+  const int srow = threadIdx.x >> 5, schunk = threadIdx.x & 31;
+  const char *rows[ROW_PASSES];
+#pragma unroll
+  for (int p = 0; p < ROW_PASSES; ++p) {
+    const int q = p * (FD_THREADS / 32) + srow;            // rows 0..31: A nodes, 32..63: B nodes
+    const int t = __shfl(p < ROW_PASSES / 2 ? a_tok : b_tok, q & 31, 64);
+    rows[p] = static_cast<const char *>(g.X) + (int64_t)(t < 0 ? 0 : t) * g.ldx * E::BYTES;
+  }
+  const int64_t row_bytes = (int64_t)g.d * E::BYTES;
+  uint4 st[ROW_PASSES];
+  auto load_piece = [&](int s) {   // spans s .. s + 3
+    const int64_t o = (int64_t)s * 128 + schunk * 16;
+    const bool ok = o + 16 <= row_bytes;
+#pragma unroll
+    for (int p = 0; p < ROW_PASSES; ++p) {
+      const uint4 t = ld16(rows[p] + (ok ? o : row_bytes - 16));   // unconditional load from a clamped address, zeroed
+      st[p] = ok ? t : make_uint4(0, 0, 0, 0);
+    }
+  };
+  static_assert(SPAN * E::BYTES == 128, "a span is one 128-byte line of a row");
 
   f32x16 acc = {0}, na = {0}, nb = {0};
   const int s_begin = ks * g.spans_per_wg;
   const int s_end = min(s_begin + g.spans_per_wg, g.n_spans);
-
-  uint4 ca[FD_CHUNKS], cb[FD_CHUNKS];
-  auto load_span = [&](int s, uint4 *va, uint4 *vb) {
-    const int e0 = s * SPAN + half * LANE_ELEMS;
+  const char *frag = lds + r * FD_STAGE_PITCH + wave * 128 + half * 64;
+  if (s_begin < s_end) load_piece(s_begin);
+  for (int s = s_begin; s < s_end; s += FD_WAVES) {   // uniform
+    if (s > s_begin) __syncthreads();   // the piece before has been consumed
 #pragma unroll
-    for (int c = 0; c < FD_CHUNKS; ++c) {
-      const int e = e0 + c * EPC;
-      const bool ok = (e + EPC <= g.d);
-      const int ec = ok ? e : g.d - EPC;   // unconditional load from a clamped address, zeroed below
-      const uint4 ta = ld16(pa + (int64_t)ec * E::BYTES), tb = ld16(pb + (int64_t)ec * E::BYTES);
-      va[c] = ok ? ta : make_uint4(0, 0, 0, 0);
-      vb[c] = ok ? tb : make_uint4(0, 0, 0, 0);
-    }
-  };
-
-  int s = s_begin + wave;
-  if (s < s_end) load_span(s, ca, cb);
-  while (s < s_end) {
-    uint4 na_next[FD_CHUNKS], nb_next[FD_CHUNKS];
-    const int sn = s + FD_WAVES;
-    if (sn < s_end) load_span(sn, na_next, nb_next);
+    for (int p = 0; p < ROW_PASSES; ++p)
+      *reinterpret_cast<uint4 *>(lds + (p * (FD_THREADS / 32) + srow) * FD_STAGE_PITCH + schunk * 16) = st[p];
+    __syncthreads();
+    if (s + FD_WAVES < s_end) load_piece(s + FD_WAVES);
+    if (s + wave < s_end) {
 #pragma unroll
-    for (int c = 0; c < FD_CHUNKS; ++c) {
-      E::mma32(ca[c], cb[c], acc);
-      if (need_na) E::mma32(ca[c], ca[c], na);
-      if (need_nb) E::mma32(cb[c], cb[c], nb);
+      for (int c = 0; c < FD_CHUNKS; ++c) {
+        const uint4 ca = *reinterpret_cast<const uint4 *>(frag + c * 16);
+        const uint4 cb = *reinterpret_cast<const uint4 *>(frag + 32 * FD_STAGE_PITCH + c * 16);
+        E::mma32(ca, cb, acc);
+        if (need_na) E::mma32(ca, ca, na);
+        if (need_nb) E::mma32(cb, cb, nb);
+      }
     }
-    if (sn < s_end) {
-#pragma unroll
-      for (int c = 0; c < FD_CHUNKS; ++c) { ca[c] = na_next[c]; cb[c] = nb_next[c]; }
-    }
-    s = sn;
   }
+  __syncthreads();   // the stage becomes the reduction buffer
 
   // cross-wave sum through LDS
 #pragma unroll

@@ -6,10 +6,9 @@
 // (a tile times itself: the diagonal is |x|^2), so a token identical to another one gets cos == 1 exactly.
 // The FD matrix is never written: an epilogue reduces each A row to (min FD, arg min) directly.
 //
-//   fd_partial_kernel : one workgroup = one 32x32 tile x one slice of the hidden axis; the four waves of
-//                       the workgroup take interleaved 128-byte runs of that slice straight from global
-//                       memory into MFMA operands (no LDS staging: nothing is reused across waves), are
-//                       summed through LDS and stored as a partial tile.
+//   fd_partial_kernel : one workgroup = one 32x32 tile x one slice of the hidden axis; the tile's rows are staged through
+//                       LDS in coalesced pieces, the four waves of the workgroup take interleaved 128-byte runs of
+//                       them as MFMA operands, are summed through LDS and stored as a partial tile.
 //   fd_epilogue_kernel: sums the partial tiles over the slices in a fixed order (fp64), forms
 //                       cos = dot / sqrt(|a|^2 |b|^2), FD = max(1 - cos, 0) and keeps the first minimum per row.
 #include "lk_fd_body.h"

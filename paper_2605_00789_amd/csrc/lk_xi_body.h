@@ -2,6 +2,7 @@
 // index and a block of LDS as arguments so that a launch can run them next to the bodies of another step
 // (lk_fused.hip) as well as on their own (lk_score_xi.hip, where the algorithm is described).
 #pragma once
+#include <type_traits>
 #include "lk_common.h"
 #include "lk_launch.h"
 
@@ -16,6 +17,13 @@ constexpr float LOG2E = 1.4426950408889634f;
 // results; a probability below 2^-126 is zero for every purpose here, and the wrapper is five more instructions on each
 // of the H*T*N exponentials.
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// The larger (NEG: the smaller) of two raw products.  med3 against an infinity is one instruction; fmaxf on a matrix-core
+// result is two, because its operand has to be quietened first.  Like fmaxf it drops a NaN beside a number.
+template <bool NEG>
+__device__ __forceinline__ float extreme(float a, float b) {
+  return __builtin_amdgcn_fmed3f(a, b, __uint_as_float(NEG ? 0xff800000u : 0x7f800000u));
+}
 
 struct XiArgs {
   const void *vis, *txt;                 // vision-side and prompt-side tensors of the contraction
@@ -62,37 +70,25 @@ template <typename T, int DH, int RW> struct XiStage {
   static constexpr int LDS_COLSUM = ROWS * PITCH + ROWS * 8;        // pass 2
 };
 
-// Copies prompt rows [j0, j0 + ROWS) of head h into LDS (rows past nT repeat the last one).
-template <typename T, int DH, int RW>
-__device__ __forceinline__ void stage_prompt_rows(const XiArgs &g, char *q_lds, int t0, int nT, int j0, int64_t txt_ho) {
-  using S = XiStage<T, DH, RW>;
-  constexpr int BYTES = Elem<T>::BYTES;
-  constexpr int PER_PASS = XI_THREADS / S::CPR;             // rows covered by one pass of the workgroup
-  const int c = threadIdx.x % S::CPR, r0 = threadIdx.x / S::CPR;
-#pragma unroll
-  for (int p = 0; p < S::ROWS / PER_PASS; ++p) {
-    const int r = p * PER_PASS + r0;
-    const int j = j0 + r;
-    const int tok = t0 + (j < nT ? j : nT - 1);
-    const uint4 v = ld16(static_cast<const char *>(g.txt) + ((int64_t)tok * g.txt_ts + txt_ho) * BYTES + c * 16);
-    *reinterpret_cast<uint4 *>(q_lds + r * S::PITCH + c * 16) = v;
-  }
-}
-
-// The same copy in two halves, so that other loads can be issued between the global loads and the LDS stores that wait
-// for them.
+// Copies prompt rows [j0, j0 + ROWS) of head h into LDS (rows past nT repeat the last one), in two halves, so that other
+// loads can be issued between the global loads and the LDS stores that wait for them.  A thread's rows are equally spaced:
+// one multiplication for the first address, additions for the others (a 64-bit multiplication per row was a quarter of
+// the vector instructions of a short kernel).
 template <typename T, int DH, int RW>
 __device__ __forceinline__ void load_prompt_rows(const XiArgs &g, int t0, int nT, int j0, int64_t txt_ho,
                                                  uint4 (&v)[XiStage<T, DH, RW>::ROWS / (XI_THREADS / XiStage<T, DH, RW>::CPR)]) {
   using S = XiStage<T, DH, RW>;
   constexpr int BYTES = Elem<T>::BYTES;
-  constexpr int PER_PASS = XI_THREADS / S::CPR;
+  constexpr int PER_PASS = XI_THREADS / S::CPR;             // rows covered by one pass of the workgroup
   const int c = threadIdx.x % S::CPR, r0 = threadIdx.x / S::CPR;
+  const char *base = static_cast<const char *>(g.txt) + ((int64_t)t0 * g.txt_ts + txt_ho) * BYTES + c * 16;
+  const char *last = base + (int64_t)(nT - 1) * g.txt_ts * BYTES;
+  const int64_t step = (int64_t)PER_PASS * g.txt_ts * BYTES;   // uniform
+  const char *at = base + (int64_t)j0 * g.txt_ts * BYTES + (int64_t)r0 * g.txt_ts * BYTES;
 #pragma unroll
   for (int p = 0; p < S::ROWS / PER_PASS; ++p) {
-    const int j = j0 + p * PER_PASS + r0;
-    const int tok = t0 + (j < nT ? j : nT - 1);
-    v[p] = ld16(static_cast<const char *>(g.txt) + ((int64_t)tok * g.txt_ts + txt_ho) * BYTES + c * 16);
+    v[p] = ld16(j0 + p * PER_PASS + r0 < nT ? at : last);
+    at += step;
   }
 }
 template <typename T, int DH, int RW>
@@ -141,43 +137,58 @@ __device__ __forceinline__ void xi_rowstat_body(const XiArgs &g, int block_id, c
 
   uint4 k[NCH];
   load_half_row<T, DH>(g.vis, v0, vt * 32 + r, nV, g.vis_ts, vis_ho, half, k);
-  bool row_ok[16];
-#pragma unroll
-  for (int x = 0; x < 16; ++x) row_ok[x] = (vt * 32 + acc_row(x, lane)) < nV;
+  const int row0 = vt * 32;
   const bool partial_block = blk * 128 + 128 > nV;          // uniform: only the last block of a sequence masks rows
   const bool neg_scale = g.scale_log2 < 0.f;
   const float pad = neg_scale ? __uint_as_float(0x7f800000u) : NEG_INF;   // product whose logit is -inf
 
   for (int j0 = 0; j0 < nT; j0 += S::ROWS) {
     __syncthreads();   // the previous chunk has been consumed
-    stage_prompt_rows<T, DH, RW>(g, q_lds, t0, nT, j0, txt_ho);
+    {
+      uint4 staged[S::ROWS / (XI_THREADS / S::CPR)];
+      load_prompt_rows<T, DH, RW>(g, t0, nT, j0, txt_ho, staged);
+      store_prompt_rows<T, DH, RW>(q_lds, staged);
+    }
     __syncthreads();
     const int n_tt = min(S::TILES, (nT - j0 + 31) >> 5);
-    for (int tt = 0; tt < n_tt; ++tt) {
+    // Bound: vector instructions (per 32 x 32 tile 16 extremes, 16 x (fma, exp, add), the exponentials at a quarter of the
+    // rate), if the waits are out of the way: a tile's fragments are requested right behind the products of the tile
+    // before, and arrive under its exponentials.
+    auto tiles = [&](auto neg_tag, auto mask_tag) {
+      constexpr bool NEG = decltype(neg_tag)::value;   // a negative scale: the largest logit is the smallest product
+      constexpr bool MASK = decltype(mask_tag)::value;
       uint4 q[NCH];
-      read_prompt_frag<T, DH>(q_lds, tt * 32 + r, half, q);
-      f32x16 acc = {0};
+      read_prompt_frag<T, DH>(q_lds, r, half, q);
+      for (int tt = 0; tt < n_tt; ++tt) {
+        f32x16 acc = {0};
 #pragma unroll
-      for (int c = 0; c < NCH; ++c) E::mma32(k[c], q[c], acc);   // rows: vision tokens, cols: prompt rows
-      // logits are acc * scale_log2; the extreme is taken on the raw products (maximum for a positive scale, minimum
-      // for a negative one), the scale goes into the exponent's multiply-add
-      if (partial_block) {
+        for (int c = 0; c < NCH; ++c) E::mma32(k[c], q[c], acc);   // rows: vision tokens, cols: prompt rows
+        __builtin_amdgcn_sched_barrier(0);
+        read_prompt_frag<T, DH>(q_lds, (tt + 1 < n_tt ? tt + 1 : tt) * 32 + r, half, q);
+        __builtin_amdgcn_sched_barrier(0);
+        // logits are acc * scale_log2; the extreme is taken on the raw products, the scale goes into the exponent's
+        // multiply-add
+        if (MASK) {
 #pragma unroll
-        for (int x = 0; x < 16; ++x) acc[x] = row_ok[x] ? acc[x] : pad;
+          for (int x = 0; x < 16; ++x) acc[x] = (row0 + acc_row(x, lane) < nV) ? acc[x] : pad;
+        }
+        float e0 = extreme<NEG>(acc[0], acc[1]), e1 = extreme<NEG>(acc[2], acc[3]);
+#pragma unroll
+        for (int x = 4; x < 16; x += 2) { e0 = extreme<NEG>(e0, acc[x]); e1 = extreme<NEG>(e1, acc[x + 1]); }
+        float e = extreme<NEG>(e0, e1);
+        e = extreme<NEG>(e, __shfl_xor(e, 32, 64));   // both half-waves hold rows of the same column
+        const float m = e * g.scale_log2;
+        float s = 0.f;
+#pragma unroll
+        for (int x = 0; x < 16; ++x) s += fast_exp2(fmaf(acc[x], g.scale_log2, -m));   // padded rows: exp2(-inf) = 0
+        s = (m > NEG_INF) ? s : 0.f;              // a tile of padded rows only: (-inf, 0), as the merge expects
+        s += __shfl_xor(s, 32, 64);
+        if (half == 0) part[wave][tt * 32 + r] = make_float2(m, s);
       }
-      float e = acc[0];
-#pragma unroll
-      for (int x = 1; x < 16; ++x) e = neg_scale ? fminf(e, acc[x]) : fmaxf(e, acc[x]);
-      const float eo = __shfl_xor(e, 32, 64);   // both half-waves hold rows of the same column
-      e = neg_scale ? fminf(e, eo) : fmaxf(e, eo);
-      const float m = e * g.scale_log2;
-      float s = 0.f;
-#pragma unroll
-      for (int x = 0; x < 16; ++x) s += fast_exp2(fmaf(acc[x], g.scale_log2, -m));   // padded rows: exp2(-inf) = 0
-      s = (m > NEG_INF) ? s : 0.f;              // a tile of padded rows only: (-inf, 0), as the merge expects
-      s += __shfl_xor(s, 32, 64);
-      if (half == 0) part[wave][tt * 32 + r] = make_float2(m, s);
-    }
+    };
+    if (neg_scale) tiles(std::true_type{}, std::true_type{});   // (rare: always masked)
+    else if (partial_block) tiles(std::false_type{}, std::true_type{});
+    else tiles(std::false_type{}, std::false_type{});
     __syncthreads();
     for (int idx = threadIdx.x; idx < n_tt * 32; idx += XI_THREADS) {
       const int j = j0 + idx;
@@ -188,7 +199,7 @@ __device__ __forceinline__ void xi_rowstat_body(const XiArgs &g, int block_id, c
         float s = 0.f;
         if (m > NEG_INF) {
 #pragma unroll
-          for (int w = 0; w < 4; ++w) s += part[w][idx].y * exp2f(part[w][idx].x - m);
+          for (int w = 0; w < 4; ++w) s += part[w][idx].y * fast_exp2(part[w][idx].x - m);
         }
         reinterpret_cast<float2 *>(g.stats)[((int64_t)h * g.sum_t + t0 + j) * g.max_vis_blocks + blk] = make_float2(m, s);
       }
@@ -205,7 +216,9 @@ __device__ __forceinline__ void xi_colsum_body(const XiArgs &g, int block_id, ch
   using S = XiStage<T, DH, RW>;
   constexpr int NCH = XiShape<T, DH>::NCH;
   char *q_lds = lds;                                                     // [ROWS * PITCH]
-  float2 *rowstat = reinterpret_cast<float2 *>(lds + S::ROWS * S::PITCH);   // [ROWS] (max in exp2 domain, 1/sum)
+  // of every prompt row of the chunk: maximum in the exp2 domain, 1 / sum (two arrays: the four rows of a group of
+  // accumulator registers are one 16-byte read each)
+  float *row_max = reinterpret_cast<float *>(lds + S::ROWS * S::PITCH), *row_inv = row_max + S::ROWS;
 
   int id = block_id;
   const int blk = id % g.max_vis_blocks; id /= g.max_vis_blocks;
@@ -254,24 +267,21 @@ __device__ __forceinline__ void xi_colsum_body(const XiArgs &g, int block_id, ch
         const float2 *p = reinterpret_cast<const float2 *>(g.stats) +
                           ((int64_t)h * g.sum_t + t0 + (j < nT ? j : nT - 1)) * g.max_vis_blocks;
         float pm = NEG_INF, psum = 0.f;
-        for (int s0 = 0; s0 < nblk; s0 += 8 * TPR) {   // eight pairs per thread in flight; merged in index order
+        for (int s0 = part; s0 < nblk + part; s0 += 8 * TPR) {   // uniform; eight pairs per thread in flight, in index order
           float2 a[8];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int sb = s0 + TPR * u + part;
-            a[u] = p[sb < nblk ? sb : nblk - 1];
-            if (sb >= nblk) a[u] = make_float2(NEG_INF, 0.f);
-          }
+          for (int u = 0; u < 8; ++u) a[u] = p[s0 + TPR * u < nblk ? s0 + TPR * u : nblk - 1];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) a[u].x = s0 + TPR * u < nblk ? a[u].x : NEG_INF;   // a surplus pair adds y * 0
           float mn = pm;
 #pragma unroll
           for (int u = 0; u < 8; ++u) mn = fmaxf(mn, a[u].x);
-          if (mn > NEG_INF) {
-            float acc = psum * exp2f(pm - mn);
+          const float ref = mn > NEG_INF ? mn : 0.f;   // (nothing but masked blocks so far: every term is exp2(-inf) = 0)
+          float acc = psum * fast_exp2(pm - ref);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc += a[u].y * exp2f(a[u].x - mn);   // a pair of (-inf, 0) adds 0
-            psum = acc;
-            pm = mn;
-          }
+          for (int u = 0; u < 8; ++u) acc += a[u].y * fast_exp2(a[u].x - ref);
+          psum = acc;
+          pm = mn;
         }
 #pragma unroll
         for (int o = 1; o < TPR; o <<= 1) {   // the threads of a row are neighbouring lanes
@@ -280,30 +290,40 @@ __device__ __forceinline__ void xi_colsum_body(const XiArgs &g, int block_id, ch
           // lower lane's pair first, so that both lanes of a pair compute the same bits
           const float lo_m = (threadIdx.x & o) ? om : pm, lo_s = (threadIdx.x & o) ? os : psum;
           const float hi_m = (threadIdx.x & o) ? pm : om, hi_s = (threadIdx.x & o) ? psum : os;
-          psum = (mn > NEG_INF) ? lo_s * exp2f(lo_m - mn) + hi_s * exp2f(hi_m - mn) : 0.f;
+          psum = (mn > NEG_INF) ? lo_s * fast_exp2(lo_m - mn) + hi_s * fast_exp2(hi_m - mn) : 0.f;
           pm = mn;
         }
         if (j < nT) { m = pm; inv = 1.f / psum; }
       }
       store_prompt_rows<T, DH, RW>(q_lds, staged);
-      if (part == 0) rowstat[idx] = make_float2(m, inv);   // rows past nT get weight 0
+      if (part == 0) { row_max[idx] = m; row_inv[idx] = inv; }   // rows past nT get weight 0
     }
     __syncthreads();
     const int n_tt = min(S::TILES, (nT - j0 + 31) >> 5);
+    uint4 q[NCH];
+    read_prompt_frag<T, DH>(q_lds, r, half, q);
     for (int tt = 0; tt < n_tt; ++tt) {
-      uint4 q[NCH];
-      read_prompt_frag<T, DH>(q_lds, tt * 32 + r, half, q);
       f32x16 acc = {0};
 #pragma unroll
       for (int c = 0; c < NCH; ++c) E::mma32(q[c], k[c], acc);   // rows: prompt tokens, cols: vision tokens
+      __builtin_amdgcn_sched_barrier(0);
+      f32x4 rm[4], ri[4];
+      if (!VISION_LSE) {
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {   // accumulator registers 4 gq .. 4 gq + 3: rows 8 gq + 4 half + 0 .. 3
+          rm[gq] = *reinterpret_cast<const f32x4 *>(row_max + tt * 32 + 8 * gq + 4 * half);
+          ri[gq] = *reinterpret_cast<const f32x4 *>(row_inv + tt * 32 + 8 * gq + 4 * half);
+        }
+      }
+      read_prompt_frag<T, DH>(q_lds, (tt + 1 < n_tt ? tt + 1 : tt) * 32 + r, half, q);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int x = 0; x < 16; ++x) {
-        const int row = tt * 32 + acc_row(x, lane);
         if (VISION_LSE) {
+          const int row = tt * 32 + acc_row(x, lane);
           colsum += (j0 + row < nT) ? fast_exp2(fmaf(acc[x], g.scale_log2, -col_m)) : 0.f;
         } else {
-          const float2 st = rowstat[row];
-          colsum = fmaf(fast_exp2(fmaf(acc[x], g.scale_log2, -st.x)), st.y, colsum);
+          colsum = fmaf(fast_exp2(fmaf(acc[x], g.scale_log2, -rm[x >> 2][x & 3])), ri[x >> 2][x & 3], colsum);
         }
       }
     }
