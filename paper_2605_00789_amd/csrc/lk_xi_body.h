@@ -41,6 +41,10 @@ struct XiArgs {
 template <typename T, int DH> struct XiShape {
   using E = Elem<T>;
   static constexpr int NCH = DH / 2 / E::PER_CHUNK;   // 16-byte chunks per lane: half a head row
+  // Fragments of the next tile are requested while this one's exponentials run, unless they are as large as the vision
+  // rows' (fp32 heads of 128: 64 registers each): there the products take four times as long anyway, and the registers
+  // are worth more as waves (with them the fused kernel spilled; 6 x 1300 fp32 tokens 295 -> 363 us)
+  static constexpr bool AHEAD = NCH <= 8;
 };
 
 // Loads half a head row of token (first + min(idx, count - 1)): always a valid address, never a branch, so
@@ -158,14 +162,17 @@ __device__ __forceinline__ void xi_rowstat_body(const XiArgs &g, int block_id, c
       constexpr bool NEG = decltype(neg_tag)::value;   // a negative scale: the largest logit is the smallest product
       constexpr bool MASK = decltype(mask_tag)::value;
       uint4 q[NCH];
-      read_prompt_frag<T, DH>(q_lds, r, half, q);
+      if (XiShape<T, DH>::AHEAD) read_prompt_frag<T, DH>(q_lds, r, half, q);
       for (int tt = 0; tt < n_tt; ++tt) {
         f32x16 acc = {0};
+        if (!XiShape<T, DH>::AHEAD) read_prompt_frag<T, DH>(q_lds, tt * 32 + r, half, q);
 #pragma unroll
         for (int c = 0; c < NCH; ++c) E::mma32(k[c], q[c], acc);   // rows: vision tokens, cols: prompt rows
-        __builtin_amdgcn_sched_barrier(0);
-        read_prompt_frag<T, DH>(q_lds, (tt + 1 < n_tt ? tt + 1 : tt) * 32 + r, half, q);
-        __builtin_amdgcn_sched_barrier(0);
+        if (XiShape<T, DH>::AHEAD) {
+          __builtin_amdgcn_sched_barrier(0);
+          read_prompt_frag<T, DH>(q_lds, (tt + 1 < n_tt ? tt + 1 : tt) * 32 + r, half, q);
+          __builtin_amdgcn_sched_barrier(0);
+        }
         // logits are acc * scale_log2; the extreme is taken on the raw products, the scale goes into the exponent's
         // multiply-add
         if (MASK) {
@@ -215,6 +222,9 @@ __device__ __forceinline__ void xi_colsum_body(const XiArgs &g, int block_id, ch
   using E = Elem<T>;
   using S = XiStage<T, DH, RW>;
   constexpr int NCH = XiShape<T, DH>::NCH;
+  // Column sums against an lse per vision token have no row statistics to read behind the products: with the next
+  // tile's fragments in registers 576 x 512 tokens, 32 heads of 128 took 39.9 us, without 38.3.
+  constexpr bool AHEAD = XiShape<T, DH>::AHEAD && !VISION_LSE;
   char *q_lds = lds;                                                     // [ROWS * PITCH]
   // of every prompt row of the chunk: maximum in the exp2 domain, 1 / sum (two arrays: the four rows of a group of
   // accumulator registers are one 16-byte read each)
@@ -301,12 +311,13 @@ __device__ __forceinline__ void xi_colsum_body(const XiArgs &g, int block_id, ch
     __syncthreads();
     const int n_tt = min(S::TILES, (nT - j0 + 31) >> 5);
     uint4 q[NCH];
-    read_prompt_frag<T, DH>(q_lds, r, half, q);
+    if (AHEAD) read_prompt_frag<T, DH>(q_lds, r, half, q);
     for (int tt = 0; tt < n_tt; ++tt) {
       f32x16 acc = {0};
+      if (!AHEAD) read_prompt_frag<T, DH>(q_lds, tt * 32 + r, half, q);
 #pragma unroll
       for (int c = 0; c < NCH; ++c) E::mma32(q[c], k[c], acc);   // rows: prompt tokens, cols: vision tokens
-      __builtin_amdgcn_sched_barrier(0);
+      if (AHEAD) __builtin_amdgcn_sched_barrier(0);
       f32x4 rm[4], ri[4];
       if (!VISION_LSE) {
 #pragma unroll
@@ -315,15 +326,19 @@ __device__ __forceinline__ void xi_colsum_body(const XiArgs &g, int block_id, ch
           ri[gq] = *reinterpret_cast<const f32x4 *>(row_inv + tt * 32 + 8 * gq + 4 * half);
         }
       }
-      read_prompt_frag<T, DH>(q_lds, (tt + 1 < n_tt ? tt + 1 : tt) * 32 + r, half, q);
-      __builtin_amdgcn_sched_barrier(0);
+      if (AHEAD) {
+        read_prompt_frag<T, DH>(q_lds, (tt + 1 < n_tt ? tt + 1 : tt) * 32 + r, half, q);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (VISION_LSE && j0 + tt * 32 + 32 > nT) {   // uniform: the last tile of the prompt masks rows
 #pragma unroll
-      for (int x = 0; x < 16; ++x) {
-        if (VISION_LSE) {
-          const int row = tt * 32 + acc_row(x, lane);
-          colsum += (j0 + row < nT) ? fast_exp2(fmaf(acc[x], g.scale_log2, -col_m)) : 0.f;
-        } else {
-          colsum = fmaf(fast_exp2(fmaf(acc[x], g.scale_log2, -rm[x >> 2][x & 3])), ri[x >> 2][x & 3], colsum);
+        for (int x = 0; x < 16; ++x)
+          colsum += (j0 + tt * 32 + acc_row(x, lane) < nT) ? fast_exp2(fmaf(acc[x], g.scale_log2, -col_m)) : 0.f;
+      } else {
+#pragma unroll
+        for (int x = 0; x < 16; ++x) {
+          if (VISION_LSE) colsum += fast_exp2(fmaf(acc[x], g.scale_log2, -col_m));
+          else colsum = fmaf(fast_exp2(fmaf(acc[x], g.scale_log2, -rm[x >> 2][x & 3])), ri[x >> 2][x & 3], colsum);
         }
       }
     }
