@@ -223,7 +223,7 @@ __device__ __forceinline__ void xi_colsum_body(const XiArgs &g, int block_id, ch
   using S = XiStage<T, DH, RW>;
   constexpr int NCH = XiShape<T, DH>::NCH;
   // Column sums against an lse per vision token have no row statistics to read behind the products: with the next
-  // tile's fragments in registers 576 x 512 tokens, 32 heads of 128 took 39.9 us, without 38.3.
+  // tile's fragments in registers four sequences of 2880 x 150..700 tokens took 39.9 us, without 38.3.
   constexpr bool AHEAD = XiShape<T, DH>::AHEAD && !VISION_LSE;
   char *q_lds = lds;                                                     // [ROWS * PITCH]
   // of every prompt row of the chunk: maximum in the exp2 domain, 1 / sum (two arrays: the four rows of a group of
