@@ -270,9 +270,10 @@ lightkv_status lightkv_window_counts(int32_t batch, int32_t n_windows, const int
  *     bit for bit.  At most 65535 windows; needs X.
  *   The two halves are independent and may be enqueued by two calls, e.g. on two streams with the same workspace:
  *   X == NULL computes xi only (windows, best_fd, best_dst are not touched), xi_mode GIVEN computes the FD half only.
- *   When both halves are requested in one call the library runs them concurrently (xi on an internal helper stream
- *   that forks from and joins `stream`; the only object the library ever creates, one per device, on the first such
- *   call outside stream capture; host threads that make such calls on one device take turns enqueueing).
+ *   When both halves are requested in one call they share launches on `stream`; on the tiled path of large windows, for
+ *   batches with one workgroup per (sequence, head) pair and with fd_dump, xi runs on an internal helper stream that
+ *   forks from and joins `stream` (created per device on the first such call outside stream capture; host threads that
+ *   make such calls on one device take turns enqueueing).
  */
 lightkv_status lightkv_score(const lightkv_problem *p, const void *X, int64_t ldx, const float *x_sqnorm,
                              const void *Q, int64_t q_tok_stride, int64_t q_head_stride,

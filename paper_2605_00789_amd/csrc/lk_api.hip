@@ -445,8 +445,9 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
                                reinterpret_cast<uint32_t *>(edges + (size_t)3 * (size_t)sum_k));
     edge_list = EdgeList{edges, sum_k};
   }
-  // both halves and the selection: the two chains side by side in the same launches, on the caller's stream
-  if (need_xi && need_fd && sel && fused_launches(p, c, fd, xp, xi_mode, lse)) {
+  // both halves: the two chains side by side in the same launches, on the caller's stream, with the selection or without
+  // (a fork and a join cost the host as much as three launches, and the device 9-15 us each: scores of 560 tokens, vision-side lse, 53 -> 16.5 us a call)
+  if (need_xi && need_fd && (sel || !fd_dump) && fused_launches(p, c, fd, xp, xi_mode, lse)) {
     const float scale = softmax_scale != 0.f ? softmax_scale : 1.0f / sqrtf((float)p->head_dim);
     int32_t *cnt = reinterpret_cast<int32_t *>(wsb + l.sel_cnt), *rank = reinterpret_cast<int32_t *>(wsb + l.sel_rank);
     unsigned long long *keys = reinterpret_cast<unsigned long long *>(wsb + l.fd_keys);
@@ -455,11 +456,15 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
                                   reinterpret_cast<float *>(wsb + l.xi_stats), reinterpret_cast<float *>(wsb + l.xi_part), xi);
     FdArgs f = make_fd_args(fd, p->dtype, X, ldx, p->d, p->n_windows, c.sum_n, p->win_offsets, p->win_tokens,
                             reinterpret_cast<float *>(wsb + l.fd_partial), best_fd, best_dst);
-    const SmallSelArgs q{p->win_remove, sel->dst, cnt, rank};
-    const bool tail = !pairwise && !edge && c.max_window <= 64;   // one tile per window: the epilogue selects as well
-    if (pairwise) f.pair_keys = keys;
+    const SmallSelArgs q{p->win_remove, sel ? sel->dst : nullptr, cnt, rank};
+    const bool tail = sel && !pairwise && !edge && c.max_window <= 64;   // one tile per window: the epilogue selects as well
+    if (pairwise && sel) f.pair_keys = keys;
     hipError_t e = launch_xi_fd_fused(x, xp, f, q, edge ? &edge_args : nullptr, edge ? FUSED_EDGES : tail ? FUSED_TAIL : FUSED_EPILOGUE,
                                       fd.n_rowblocks, p->dtype, p->head_dim, s);
+    if (!sel) {
+      if (e == hipSuccess) e = launch_xi_heads(x, s);
+      return e == hipSuccess ? LIGHTKV_OK : LIGHTKV_ERR_LAUNCH;
+    }
     if (e == hipSuccess && edge) {
       if (edge_args.max_a > EDGE_MAX_SIDE) e = launch_edge_select_big(f, edge_args, s);
     } else if (e == hipSuccess && pairwise)

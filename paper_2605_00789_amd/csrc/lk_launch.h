@@ -163,7 +163,7 @@ bool score_select_one_stream(const lightkv_problem *p);
 // ---- xi and FD on one stream, the k-th kernels of the two chains sharing a launch (lk_fused.hip): pass 1 of xi beside
 // the partial tiles, pass 2 beside what finishes them -- FUSED_TAIL: epilogue and selection of windows of at most 64
 // tokens, FUSED_EPILOGUE: best edges of larger ones (keys instead of best_fd / best_dst if pair_keys is given).  The
-// caller goes on with the selection and launch_select_scan_heads, which sums the heads of xi.
+// caller goes on with the selection and launch_select_scan_heads, which sums the heads of xi, or launch_xi_heads.
 // FUSED_EDGES: the k lowest edges of every window (of at most 2 * EDGE_MAX_SIDE tokens), or the keys of every pair of larger
 // ones (launch_edge_select_big goes on).
 enum FusedFinish { FUSED_TAIL = 0, FUSED_EPILOGUE = 1, FUSED_EDGES = 2 };
@@ -173,6 +173,7 @@ struct FdArgs;
 struct SmallSelArgs;
 hipError_t launch_xi_fd_fused(const XiArgs &x, const XiPlan &xp, const FdArgs &f, const SmallSelArgs &q, const EdgeArgs *edges,
                               FusedFinish finish, int n_rowblocks, int dtype, int head_dim, hipStream_t stream);
+hipError_t launch_xi_heads(const XiArgs &x, hipStream_t stream);   // the head sum alone (scores without a selection)
 // index scan with the head sum of xi in the same launch (x: arguments of the xi passes)
 hipError_t launch_select_scan_heads(int batch, int sum_n, const int32_t *cu_vis, const int32_t *dst, int32_t *new_index,
                                     int32_t *grp_offsets, int32_t *grp_src, int32_t *cu_vis_out, const int32_t *cnt,

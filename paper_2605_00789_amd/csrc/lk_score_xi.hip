@@ -32,6 +32,11 @@ __global__ __launch_bounds__(XI_THREADS) void xi_colsum_kernel(XiArgs g) {
 
 __global__ __launch_bounds__(64) void xi_heads_kernel(XiArgs g) { xi_heads_body(g, blockIdx.x * 64 + threadIdx.x); }
 
+hipError_t launch_xi_heads(const XiArgs &g, hipStream_t stream) {
+  if (g.sum_n) hipLaunchKernelGGL(xi_heads_kernel, dim3((unsigned)((g.sum_n + 63) / 64)), dim3(64), 0, stream, g);
+  return hipGetLastError();
+}
+
 XiPlan make_xi_plan(int batch, const int32_t *h_cu_vis, const int32_t *h_cu_txt, int heads, int xi_mode) {
   XiPlan p{};
   if (xi_mode == 2 || !h_cu_txt) return p;
@@ -64,8 +69,7 @@ static hipError_t launch_xi_rw(const XiPlan &plan, const XiArgs &g, int xi_mode,
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (g.sum_n) hipLaunchKernelGGL(xi_heads_kernel, dim3((unsigned)((g.sum_n + 63) / 64)), dim3(64), 0, stream, g);
-  return hipGetLastError();
+  return launch_xi_heads(g, stream);
 }
 
 template <typename T, int DH>
@@ -86,8 +90,7 @@ hipError_t launch_xi(const XiPlan &plan, int dtype, int xi_mode, int batch, int 
   if (xi_seq_applies(plan, xi_mode, lse, batch, heads)) {
     const hipError_t e = launch_xi_seq(g, dtype, head_dim, stream);
     if (e != hipSuccess) return e;
-    if (g.sum_n) hipLaunchKernelGGL(xi_heads_kernel, dim3((unsigned)((g.sum_n + 63) / 64)), dim3(64), 0, stream, g);
-    return hipGetLastError();
+    return launch_xi_heads(g, stream);
   }
 #define LK_XI_CASE(TT, DHV) return launch_xi_t<TT, DHV>(plan, g, xi_mode, max_t, stream)
   if (dtype == 1) {

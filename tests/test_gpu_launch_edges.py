@@ -235,3 +235,49 @@ def test_edge_selection_in_any_window_order(dtype, batch, gh, gw, w, d, ties, wi
                 want = np.zeros(m.size, dtype=bool)
                 want[np.flatnonzero(zero.reshape(-1))[:k]] = True
                 np.testing.assert_array_equal(mine.reshape(-1), want)
+
+
+@pytest.mark.parametrize("dtype,heads,hd,batch,gh,gw,w,match,direction", [
+    ("bf16", 2, 64, 3, 9, 7, 2, "best", 0), ("f32", 3, 128, 2, 12, 11, 1, "best", 0), ("bf16", 3, 32, 2, 13, 16, 1, "best", 1),
+    ("f32", 2, 32, 1, 3, 3, 3, "best", 0), ("bf16", 2, 64, 2, 11, 12, 2, "pair", 0), ("bf16", 2, 128, 1, 20, 20, 1, "pair", 0),
+    ("bf16", 4, 128, 2, 24, 24, 1, "best", 0),      # the tiled path: two streams
+])
+@pytest.mark.parametrize("mode", ["text", "text_lse", "vision"])
+def test_scores_of_both_halves_are_those_of_each_half(dtype, heads, hd, batch, gh, gw, w, match, direction, mode):
+    """lightkv_score with both halves in shared launches against one call per half: the same bits, also when a sequence has
+    no prompt and into buffers that held something else."""
+    import paper_2605_00789_amd as L
+    from paper_2605_00789_amd import binding as B
+    n, d = gh * gw, heads * hd
+    N, texts = batch * n, [0 if b and mode != "text_lse" else 5 + 90 * b for b in range(batch)]
+    T = sum(texts)
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    X, V = (torch.randn(N, d, generator=g, device="cuda").to(tdt) for _ in range(2))
+    P = torch.randn(T, d, generator=g, device="cuda").to(tdt)
+    Q, K = (V, P) if mode == "vision" else (P, V)
+    lse = None if mode == "text" else 3.0 + torch.randn(heads, N if mode == "vision" else T, generator=g, device="cuda")
+    h, ht = (np.arange(batch + 1) * n).astype(np.int32), np.concatenate([[0], np.cumsum(texts)]).astype(np.int32)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    wo, wt = torch.empty(batch * w * w + 1, **i32), torch.empty(N, **i32)
+    cu = torch.from_numpy(h).cuda()
+    L.lightkv_build_windows(batch, h, cu, torch.arange(n, **i32).repeat(batch), 1, gh, gw, w, wo, wt)
+    p = L.Problem(batch=batch, d=d, heads=heads, head_dim=hd, dtype=dtype, h_cu_vis=h, cu_vis=cu, h_cu_txt=ht,
+                  cu_txt=torch.from_numpy(ht).cuda(), n_windows=batch * w * w, max_window_tokens=-(-gh // w) * -(-gw // w),
+                  win_offsets=wo, win_tokens=wt, win_remove=torch.zeros(batch * w * w, **i32), direction=direction,
+                  match=B.MATCH_BEST_PER_A if match == "best" else B.MATCH_FULL_PAIRWISE)
+    ws = torch.empty(L.lightkv_workspace_size(p), dtype=torch.uint8, device="cuda")
+    kw = dict(xi_mode=B.XI_VISION_QUERY if mode == "vision" else B.XI_TEXT_QUERY, lse=lse)
+
+    def fresh():
+        return torch.full((N,), -3.0, device="cuda"), torch.full((N,), -3.0, device="cuda"), torch.full((N,), -3, **i32)
+    one, two = fresh(), fresh()
+    for rep in range(2):
+        ws.fill_(0x5a + rep)
+        L.lightkv_score(p, X, Q, K, *one, ws, **kw)
+    ws.fill_(0x33)
+    L.lightkv_score(p, None, Q, K, two[0], None, None, ws, **kw)
+    L.lightkv_score(p, X, None, None, two[0], two[1], two[2], ws, xi_mode=B.XI_GIVEN)
+    for a, b in zip(one, two):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    assert (one[0] != -3.0).all()
