@@ -446,7 +446,8 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
     edge_list = EdgeList{edges, sum_k};
   }
   // both halves: the two chains side by side in the same launches, on the caller's stream, with the selection or without
-  // (a fork and a join cost the host as much as three launches, and the device 9-15 us each: scores of 560 tokens, vision-side lse, 53 -> 16.5 us a call)
+  // (a fork and a join cost the host as much as three launches, and the device 9-15 us each: scores of 560 tokens with a
+  // vision-side lse 53 -> 16.5 us a call)
   if (need_xi && need_fd && (sel || !fd_dump) && fused_launches(p, c, fd, xp, xi_mode, lse)) {
     const float scale = softmax_scale != 0.f ? softmax_scale : 1.0f / sqrtf((float)p->head_dim);
     int32_t *cnt = reinterpret_cast<int32_t *>(wsb + l.sel_cnt), *rank = reinterpret_cast<int32_t *>(wsb + l.sel_rank);
