@@ -180,7 +180,8 @@ const char *lightkv_status_string(int status);
 /* Library version, major*10000 + minor*100 + patch. */
 int lightkv_version(void);
 
-/* Bytes of workspace that any call for this problem needs (upper bound over the four steps). */
+/* Bytes of workspace that any call for this problem needs (upper bound over the four steps).  LIGHTKV_MATCH_FULL_PAIRWISE:
+   with less (down to the squared norms, keys and selection scratch) the calls still run, small windows then slower. */
 lightkv_status lightkv_workspace_size(const lightkv_problem *p, size_t *bytes);
 
 /*

@@ -117,7 +117,10 @@ using Fork = HelperSet<1, 2>;   // stream[0]: xi; event[0]: fork, event[1]: join
 
 struct WsLayout {
   size_t fd_partial = 0, fd_norm = 0, fd_keys = 0, xi_stats = 0, xi_part = 0, sel_cnt = 0,
-         sel_rank = 0, edges = 0, total = 0;
+         sel_rank = 0, edges = 0;
+  // what a call must have, and what lightkv_workspace_size says.  They differ for full pairwise matching only, where the
+  // partial tiles of the small cut lie behind everything else: without room for them the large tiles, which need none, run
+  size_t least = 0, total = 0;
 };
 
 bool edge_topk(const lightkv_problem *p) { return p->match == LIGHTKV_MATCH_EDGE_TOPK; }
@@ -140,6 +143,10 @@ bool use_big_fd(const lightkv_problem *p, const Checked &c) {
   return (int64_t)p->n_windows * big.mt * big.nt >= FD_BIG_MIN_TILES;
 }
 
+size_t pair_partial(const lightkv_problem *p, const Checked &c) {
+  return full_pairwise(p) ? pair_partial_floats(p->n_windows, c.max_window, p->d) : 0;
+}
+
 // The small-tile plan of a step: the bipartite blocks, or the whole windows for full pairwise matching (n_tiles == 0: the
 // large pairwise tiles).  Not used on the tiled bipartite path.
 FdPlan small_tile_plan(const lightkv_problem *p, const Checked &c) {
@@ -158,15 +165,12 @@ bool fused_launches(const lightkv_problem *p, const Checked &c, const FdPlan &fd
          (full_pairwise(p) || !use_big_fd(p, c)) && !xi_seq_applies(xp, xi_mode, lse, p->batch, p->heads);
 }
 
-WsLayout ws_layout(const FdPlan &fd, const FdBigPlan &big, bool use_big, bool pairwise, const XiPlan &xi, int sum_n,
+// pair_partial: full pairwise matching, the floats its small tiles take (pair_partial_floats)
+WsLayout ws_layout(const FdPlan &fd, const FdBigPlan &big, bool use_big, size_t pair_partial, const XiPlan &xi, int sum_n,
                    size_t n_edge_ints) {
-  // full pairwise matching needs what the tiled bipartite path lays out (norms and one key plane or more) and room for the
-  // partial tiles of the small cut, the same for every window bound: a step may be planned with a smaller one than the
-  // workspace was sized for
   WsLayout l;
   size_t off = 0;
-  const size_t partial = pairwise ? PAIR_PARTIAL_FLOATS : (use_big ? 0 : fd.partial_floats);
-  l.fd_partial = off; off = align_up(off + partial * sizeof(float));
+  l.fd_partial = off; off = align_up(off + (use_big ? 0 : fd.partial_floats * sizeof(float)));
   l.fd_norm = off;    off = align_up(off + (use_big ? big.norm_floats * sizeof(float) : 0));
   l.fd_keys = off;    off = align_up(off + (use_big ? big.key_bytes : 0));
   l.xi_stats = off;   off = align_up(off + xi.stat_floats * sizeof(float));
@@ -174,6 +178,8 @@ WsLayout ws_layout(const FdPlan &fd, const FdBigPlan &big, bool use_big, bool pa
   l.sel_cnt = off;    off = align_up(off + (size_t)sum_n * sizeof(int32_t));
   l.sel_rank = off;   off = align_up(off + (size_t)sum_n * sizeof(int32_t));
   l.edges = off;      off = align_up(off + n_edge_ints * sizeof(int32_t));
+  l.least = off + ALIGN;
+  if (pair_partial) { l.fd_partial = off; off = align_up(off + pair_partial * sizeof(float)); }
   l.total = off + ALIGN;
   return l;
 }
@@ -200,7 +206,7 @@ lightkv_status select_impl(const lightkv_problem *p, bool from_keys, float *best
   const XiPlan xp = make_xi_plan(p->batch, p->h_cu_vis, have_txt ? p->h_cu_txt : nullptr, p->heads, 0);
   const FdBigPlan big = make_fd_big_plan(p->n_windows, c.max_window, c.sum_n);
   if (edge_topk(p) || full_pairwise(p)) return LIGHTKV_ERR_UNSUPPORTED;   // scores of another kind: lightkv_score_select only
-  const WsLayout l = ws_layout(fd, big, use_big_fd(p, c), full_pairwise(p), xp, c.sum_n, 0);
+  const WsLayout l = ws_layout(fd, big, use_big_fd(p, c), 0, xp, c.sum_n, 0);
   // only the selection scratch (and the keys) are used here; accept a workspace that covers the layout
   if (!ws || (reinterpret_cast<uintptr_t>(ws) % ALIGN) != 0 || ws_bytes < l.total) return LIGHTKV_ERR_WORKSPACE;
   char *wsb = static_cast<char *>(ws);
@@ -234,8 +240,8 @@ int lightkv_version(void) { return 320; }   // 0.3.2: lightkv_compress_schedule_
                                             // direction argument of lightkv_window_counts, edge lists for windows of
                                             // up to 4096 tokens)
 
-lightkv_status lightkv_workspace_size(const lightkv_problem *p, size_t *bytes) {
-  if (!bytes) return LIGHTKV_ERR_NULL;
+// Sizes of the workspace for a problem (lk_launch.h).
+static lightkv_status workspace_sizes(const lightkv_problem *p, size_t *least, size_t *total) {
   Checked c;
   // prompt offsets are optional here: without them the xi scratch is not counted (XI_GIVEN callers)
   const bool have_txt = p && p->h_cu_txt && p->cu_txt;
@@ -244,8 +250,18 @@ lightkv_status lightkv_workspace_size(const lightkv_problem *p, size_t *bytes) {
   const FdPlan fd = make_fd_plan(p->n_windows, c.max_window, p->d, c.elem_bytes);
   const XiPlan xi = make_xi_plan(p->batch, p->h_cu_vis, have_txt ? p->h_cu_txt : nullptr, p->heads, 0);
   const FdBigPlan big = make_fd_big_plan(p->n_windows, c.max_window, c.sum_n);
-  *bytes = ws_layout(fd, big, use_big_fd(p, c), full_pairwise(p), xi, c.sum_n, edge_ints(p, c)).total;
+  const WsLayout l = ws_layout(fd, big, use_big_fd(p, c), pair_partial(p, c), xi, c.sum_n, edge_ints(p, c));
+  *least = l.least;
+  *total = l.total;
   return LIGHTKV_OK;
+}
+
+lightkv_status lightkv_workspace_size(const lightkv_problem *p, size_t *bytes) {
+  if (!bytes) return LIGHTKV_ERR_NULL;
+  size_t least = 0, total = 0;
+  const lightkv_status st = workspace_sizes(p, &least, &total);
+  if (st == LIGHTKV_OK) *bytes = total;
+  return st;
 }
 
 // Largest sequence of the batch; validates what every form of the partition needs.
@@ -360,6 +376,11 @@ int lk::build_windows_with_counts(int32_t batch, const int32_t *h_cu_vis, const 
   return build_windows_impl(batch, h_cu_vis, cu_vis, pos, nullptr, nullptr, spec, stream);
 }
 
+int lk::least_workspace(const lightkv_problem *p, size_t *bytes) {
+  size_t total = 0;
+  return workspace_sizes(p, bytes, &total);
+}
+
 bool lk::score_select_one_stream(const lightkv_problem *p) {
   Checked c;
   if (check_problem(p, true, true, c) != LIGHTKV_OK) return true;   // (lightkv_score_select reports the error)
@@ -420,7 +441,7 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
       }
     c.max_window = plan_bound(p, max_window);
   }
-  const FdPlan fd = small_tile_plan(p, c);
+  FdPlan fd = small_tile_plan(p, c);
   const XiPlan xp = make_xi_plan(p->batch, p->h_cu_vis, p->h_cu_txt && p->cu_txt ? p->h_cu_txt : nullptr, p->heads, 0);
   FdBigPlan big = make_fd_big_plan(p->n_windows, c.max_window, c.sum_n);
   big.metric = p->metric;
@@ -429,8 +450,9 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
   const bool edge = sel && need_fd && edge_topk(p);
   const bool pairwise = need_fd && full_pairwise(p);
   if (pairwise && (uint64_t)c.sum_n * (uint64_t)ldx * 2u >= (1ull << 32)) return LIGHTKV_ERR_UNSUPPORTED;   // 32-bit row offsets
-  const WsLayout l = ws_layout(fd, big, use_big, full_pairwise(p), xp, c.sum_n, need_fd ? edge_ints(p, c) : 0);
-  if (!ws || (reinterpret_cast<uintptr_t>(ws) % ALIGN) != 0 || ws_bytes < l.total) return LIGHTKV_ERR_WORKSPACE;
+  const WsLayout l = ws_layout(fd, big, use_big, pair_partial(p, c), xp, c.sum_n, need_fd ? edge_ints(p, c) : 0);
+  if (!ws || (reinterpret_cast<uintptr_t>(ws) % ALIGN) != 0 || ws_bytes < l.least) return LIGHTKV_ERR_WORKSPACE;
+  if (full_pairwise(p) && ws_bytes < l.total) fd = FdPlan{};   // no room for the small tiles: the large ones
   char *wsb = static_cast<char *>(ws);
   hipStream_t s = static_cast<hipStream_t>(stream);
 

@@ -43,11 +43,12 @@ constexpr int FD_MAX_COLS = 2048;                   // |B| of the largest suppor
 
 FdPlan make_fd_plan(int n_windows, int max_window_tokens, int d, int dtype_bytes);
 // The same for full pairwise matching (every window's whole v x v matrix in 32 x 32 tiles); n_tiles == 0: the 192 x 192
-// tiles of launch_fd_pair are the better cut.  The partial tiles never take more than PAIR_PARTIAL_FLOATS, whatever
-// smaller window bound a step is planned with.
+// tiles of launch_fd_pair are the better cut.
 constexpr int PAIR_SMALL_MAX_TILES = 768;
-constexpr size_t PAIR_PARTIAL_FLOATS = (size_t)2048 * FD_TILE_FLOATS;   // slices double while there are below 1024 tile slices
 FdPlan make_fd_pair_plan(int n_windows, int max_window_tokens, int d);
+// The most floats the partial tiles take under this window bound or a smaller one: a step may be planned with a smaller
+// bound than its workspace was sized for, and the plans are not monotone in it.
+size_t pair_partial_floats(int n_windows, int max_window_tokens, int d);
 
 // The partition of one stage's tokens and, optionally, the per-window counts that go with it (host struct).
 struct WinArgs;
@@ -156,6 +157,9 @@ hipError_t launch_pair_select(int n_windows, int max_window, int sum_n, const in
                               const int32_t *win_tokens, const int32_t *win_remove, const unsigned long long *keys,
                               float *best_fd, int32_t *best_dst, int32_t *dst, int32_t *cnt, int32_t *src_rank,
                               hipStream_t stream);
+
+// The smallest workspace the calls take for a problem (lightkv_workspace_size may ask for more: lk_api.hip); a lightkv_status.
+int least_workspace(const lightkv_problem *p, size_t *bytes);
 
 // Whether lightkv_score_select with xi requested runs this step on the caller's stream alone (lk_api.hip).
 bool score_select_one_stream(const lightkv_problem *p);

@@ -217,10 +217,10 @@ extern "C" lightkv_status lightkv_compress_schedule_ratio(const lightkv_stage *s
     const int bound = st.problem.max_window_tokens;
     q.max_window_tokens = std::max(1, std::min(bound, max_seq));
     size_t need = 0;
-    rc = lightkv_workspace_size(&q, &need);
+    rc = (lightkv_status)lk::least_workspace(&q, &need);
     if (rc == LIGHTKV_OK && (!ws || ws_bytes < need) && q.max_window_tokens != bound) {
       q.max_window_tokens = bound;
-      rc = lightkv_workspace_size(&q, &need);
+      rc = (lightkv_status)lk::least_workspace(&q, &need);
     }
     if (rc == LIGHTKV_OK && (!ws || ws_bytes < need)) rc = LIGHTKV_ERR_WORKSPACE;
     // ---- windows and their counts, unless the previous stage's merge built them

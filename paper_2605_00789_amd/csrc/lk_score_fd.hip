@@ -100,6 +100,17 @@ FdPlan make_fd_pair_plan(int n_windows, int max_window_tokens, int d) {
   return p;
 }
 
+size_t pair_partial_floats(int n_windows, int max_window_tokens, int d) {
+  size_t most = 0;
+  // a plan changes with the bound only where a tile side does (8, 16, then every 32 tokens), and its tiles only grow in number
+  for (int side = 8;; side = side < 32 ? 2 * side : side + 32) {
+    const FdPlan p = make_fd_pair_plan(n_windows, side < max_window_tokens ? side : max_window_tokens, d);
+    most = p.partial_floats > most ? p.partial_floats : most;
+    if (side >= max_window_tokens || p.n_tiles == 0) break;
+  }
+  return most;
+}
+
 hipError_t launch_fd_pair_small(const FdPlan &plan, const void *X, int64_t ldx, int d, int n_windows, int sum_n,
                                 const int32_t *win_offsets, const int32_t *win_tokens, float *partial,
                                 unsigned long long *keys, float *best_fd, int32_t *best_dst, hipStream_t stream) {

@@ -281,3 +281,54 @@ def test_scores_of_both_halves_are_those_of_each_half(dtype, heads, hd, batch, g
     for a, b in zip(one, two):
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
     assert (one[0] != -3.0).all()
+
+
+@pytest.mark.parametrize("gh,gw,w", [(24, 24, 1), (24, 24, 4), (5, 13, 0)])
+def test_full_pairwise_without_room_for_the_small_tiles(gh, gw, w):
+    """A workspace that holds the squared norms, one to four key planes, xi and the selection scratch alone is enough: the
+    large tiles need no partial sums.  Scores agree with those of the full workspace to the 1e-5 that two fp32 summation
+    orders of bf16 products may differ by; the call alone, both halves in one call, and a ratio-driven schedule."""
+    import paper_2605_00789_amd as L
+    from paper_2605_00789_amd import binding as B
+    n, d, heads, t = gh * gw, 256, 4, 33
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X, K = (torch.randn(n, d, generator=g, device="cuda").bfloat16() for _ in range(2))
+    Q = torch.randn(t, d, generator=g, device="cuda").bfloat16()
+    per, i32 = max(w * w, 1), dict(dtype=torch.int32, device="cuda")
+    h, ht = np.array([0, n], dtype=np.int32), np.array([0, t], dtype=np.int32)
+    cu, cut, pos = torch.from_numpy(h).cuda(), torch.from_numpy(ht).cuda(), torch.arange(n, **i32)
+    wo, wt, rem = torch.empty(per + 1, **i32), torch.empty(n, **i32), torch.empty(per, **i32)
+    L.lightkv_build_windows(1, h, cu, pos, 1, gh, gw, w, wo, wt)
+    L.lightkv_window_counts(1, per, wo, B.COUNT_RATIO, rem, rho=0.3)
+    bound = min(n, L.lightkv_max_window_cells(1, gh, gw, w))
+    p = L.Problem(batch=1, d=d, heads=heads, head_dim=d // heads, dtype="bf16", h_cu_vis=h, cu_vis=cu, h_cu_txt=ht, cu_txt=cut,
+                  n_windows=per, max_window_tokens=bound, win_offsets=wo, win_tokens=wt, win_remove=rem, match=B.MATCH_FULL_PAIRWISE)
+
+    def least(planes):
+        parts = [4 * n, 8 * n * planes, 4 * heads * t * -(-n // 128) * 2, 4 * heads * n, 4 * n, 4 * n]
+        return sum(-(-b // 256) * 256 for b in parts) + 256
+    planes = max(1, -(-(bound // 2) // 96))
+    planes = planes if planes <= 4 else 1
+    small, full = least(planes), L.lightkv_workspace_size(p)
+    assert small < full
+    got = {}
+    for name, size in (("small", small), ("full", full)):
+        ws = torch.full((size + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+        xi, fd, best = torch.empty(n, device="cuda"), torch.empty(n, device="cuda"), torch.empty(n, **i32)
+        L.lightkv_score(p, X, Q, K, xi, fd, best, ws[:size])
+        dst, new, src, fd2, best2 = (torch.empty(n, **i32) for _ in range(5))
+        fd2, off, cu_out = torch.empty(n, device="cuda"), torch.empty(n + 1, **i32), torch.empty(2, **i32)
+        L.lightkv_score_select(p, X, Q, K, xi, fd2, best2, dst, new, off, src, cu_out, ws[:size])
+        assert torch.equal(fd, fd2) and torch.equal(best, best2)
+        assert bool((ws[size:] == 0x5a).all())
+        got[name] = (xi, fd, int(cu_out[1]))
+    assert torch.equal(got["small"][0], got["full"][0])
+    assert float((got["small"][1] - got["full"][1]).abs().max()) <= 1e-5
+    assert got["small"][2] < n and got["full"][2] < n
+    with pytest.raises(L.LightKVError, match="workspace"):
+        L.lightkv_score(p, X, Q, K, xi, fd, best, torch.empty(small - 512, dtype=torch.uint8, device="cuda"))
+    s = L.EdgeTopKSchedule(dtype="bf16", batch=1, d=d, heads=heads, head_dim=d // heads, tiles=1, grid_h=gh, grid_w=gw, cu_txt=ht,
+                           windows_per_axis=[w, w], rho=[0.3, 0.3], match="full_pairwise")
+    s._ws = torch.empty(small, dtype=torch.uint8, device="cuda")
+    out = s.run(h, X, K, K, Q, pos)
+    assert len(out) == 2 and 0 < int(out[-1].h_cu_vis_out[1]) < int(out[0].h_cu_vis_out[1]) < n
