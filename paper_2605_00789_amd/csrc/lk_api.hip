@@ -465,7 +465,7 @@ lightkv_status score_impl(const lightkv_problem *p, const void *X, int64_t ldx, 
     edge_args = make_edge_args(c.max_window, sum_k, p->win_remove, sel->dst, reinterpret_cast<int32_t *>(wsb + l.sel_cnt),
                                reinterpret_cast<int32_t *>(wsb + l.sel_rank), edges, c.edge_device_counts,
                                reinterpret_cast<uint32_t *>(edges + (size_t)3 * (size_t)sum_k));
-    edge_list = EdgeList{edges, sum_k};
+    edge_list = EdgeList{edges, sum_k, c.edge_device_counts ? EDGE_SCAN_MAX_BOUND : EDGE_SCAN_MAX_KNOWN};
   }
   // both halves: the two chains side by side in the same launches, on the caller's stream, with the selection or without
   // (a fork and a join cost the host as much as three launches, and the device 9-15 us each: scores of 560 tokens with a

@@ -117,8 +117,14 @@ hipError_t launch_edge_select_big(const FdArgs &g, const EdgeArgs &q, hipStream_
 // the FD keys of every pair of every window, for windows beyond the one-kernel path: 32-bit keys (0 if not needed)
 size_t edge_big_key_count(int n_windows, int max_window);
 // The edge list as the index scan takes it: [3][sum_k] (A token, B token, position); slots beyond the edges there are
-// (grp_offsets[sum_n]) are not read.
-struct EdgeList { const int32_t *edges; int sum_k; };
+// (grp_offsets[sum_n]) are not read.  A list of more than scan_max slots gets a launch of its own behind the scan.
+struct EdgeList { const int32_t *edges; int sum_k, scan_max; };
+// The line: one workgroup of the scan takes 1024 edges a trip, a launch costs 1-2 us.  Score-select calls at d = 512, list in
+// the scan -> of its own, us: 1024 edges 21.7 -> 23.3, 3104 24.6 -> 24.4, 5184 24.2 -> 22.5, 663552 303 -> 75 (d = 1024).  Where
+// only a bound is known (one slot per token): 2880 tokens 20.5 -> 21.6, 16384 with 1536 edges 51.0 -> 51.5, with 8192 56.7 ->
+// 53.4, 65536 tokens with 6144 edges 97.7 -> 90.4.
+constexpr int EDGE_SCAN_MAX_KNOWN = 2048;    // slots where the host knows the counts
+constexpr int EDGE_SCAN_MAX_BOUND = 16384;   // ... where it knows a bound
 
 // Debug dump of the FD of every pair (lk_fd_dump.hip); at most 65535 windows.
 hipError_t launch_fd_dump(int dtype, const void *X, int64_t ldx, int d, int n_windows, int max_window, int sum_n,

@@ -441,6 +441,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void select_scan_kernel(SelArgs g, Xi
   // from global memory after the barrier below.
   // (a target outside [t0, t1) cannot come from the selection kernels; it is dropped rather than followed)
   if (EDGES) {
+    if (g.edges.sum_k == 0) return;   // uniform: a long list, edge_fill_kernel places it
     if (!one_pass) __syncthreads();   // the group starts are read back from global memory
     int n_edges = cnt_base;
     if (g.per_seq) {   // ... and those of the sequences behind this one
@@ -496,6 +497,16 @@ __global__ __launch_bounds__(SCAN_THREADS) void select_scan_kernel(SelArgs g, Xi
 
 
 
+// Long edge lists: one thread per edge, behind the scan.  Only the slots of edges there are read (grp_offsets[sum_n] of them).
+__global__ __launch_bounds__(256) void edge_fill_kernel(EdgeList e, const int32_t *grp_offsets, int32_t *grp_src, int sum_n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= e.sum_k || i >= grp_offsets[sum_n]) return;
+  const int a = e.edges[i], b = e.edges[e.sum_k + i], pos = e.edges[2 * e.sum_k + i];
+  if ((unsigned)a >= (unsigned)sum_n || (unsigned)b >= (unsigned)sum_n) return;
+  const int slot = grp_offsets[b] + pos;
+  if (slot >= 0 && slot < e.sum_k) grp_src[slot] = a;
+}
+
 // The scan kernels take more dynamic LDS than the default limit: a property of a kernel as loaded on a device, set once
 // per device (setting it twice is harmless: the flag only has to be free of data races).
 static hipError_t allow_scan_lds() {
@@ -528,7 +539,8 @@ static hipError_t launch_scan(int batch, int sum_n, const int32_t *cu_vis, const
   g.dst = const_cast<int32_t *>(dst); g.new_index = new_index; g.grp_offsets = grp_offsets; g.grp_src = grp_src;
   g.cu_vis_out = cu_vis_out; g.cnt = const_cast<int32_t *>(cnt); g.src_rank = const_cast<int32_t *>(src_rank);
   g.per_seq = scan_per_sequence(batch, sum_n);
-  if (edges) g.edges = *edges;
+  const bool long_list = edges && edges->sum_k > edges->scan_max;
+  if (edges && !long_list) g.edges = *edges;
   const hipError_t e = allow_scan_lds();
   if (e != hipSuccess) return e;
   const int n_head_blocks = x ? (sum_n + SCAN_THREADS - 1) / SCAN_THREADS : 0;
@@ -538,6 +550,9 @@ static hipError_t launch_scan(int batch, int sum_n, const int32_t *cu_vis, const
   else if (x) hipLaunchKernelGGL((select_scan_kernel<true, false>), grid, block, SCAN_LDS_BYTES, stream, g, xa, n_head_blocks);
   else if (edges) hipLaunchKernelGGL((select_scan_kernel<false, true>), grid, block, SCAN_LDS_BYTES, stream, g, xa, 0);
   else hipLaunchKernelGGL((select_scan_kernel<false, false>), grid, block, SCAN_LDS_BYTES, stream, g, xa, 0);
+  if (long_list)
+    hipLaunchKernelGGL(edge_fill_kernel, dim3((unsigned)((edges->sum_k + 255) / 256)), dim3(256), 0, stream, *edges, grp_offsets,
+                       grp_src, sum_n);
   return hipGetLastError();
 }
 

@@ -15,7 +15,7 @@
 //                        plus the window's edge list (a, b, position of a among b's sources) at a fixed offset
 //                        (the k of the windows before it); every window writes all of its slots.
 //   select_scan_kernel : new_index from dst, grp_offsets from cnt, grp_src[grp_offsets[b] + position] = a for every edge
-//                        of the list (lk_select.hip).
+//                        of the list (lk_select.hip; long lists: edge_fill_kernel behind it).
 // With xi requested the same bodies run beside the second xi pass (lk_fused.hip).
 //
 // Windows of more than 2 * EDGE_MAX_SIDE tokens (up to the library's 4096) do not fit that kernel's LDS; for them

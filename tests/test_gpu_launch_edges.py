@@ -332,3 +332,46 @@ def test_full_pairwise_without_room_for_the_small_tiles(gh, gw, w):
     s._ws = torch.empty(small, dtype=torch.uint8, device="cuda")
     out = s.run(h, X, K, K, Q, pos)
     assert len(out) == 2 and 0 < int(out[-1].h_cu_vis_out[1]) < int(out[0].h_cu_vis_out[1]) < n
+
+
+@pytest.mark.parametrize("batch,n,v,k", [(1, 576, 36, 17), (8, 576, 36, 16), (8, 576, 36, 17), (29, 565, 37, 4), (29, 566, 37, 4)])
+@pytest.mark.parametrize("with_xi", [False, True])
+def test_edge_lists_placed_by_the_scan_and_by_a_launch_of_their_own(batch, n, v, k, with_xi):
+    """Counts known to the host (the list gets a launch of its own beyond 2048 edges) and to the device alone (beyond 16384
+    tokens): lists of 272, 2048, 2176 edges and of 16385 and 16414 tokens.  The same bits either way, and the sources of
+    every token are the edges that the tokens' own columns say."""
+    import paper_2605_00789_amd as L
+    from paper_2605_00789_amd import binding as B
+    N, d = batch * n, 64
+    g = torch.Generator(device="cuda").manual_seed(N)
+    X, K = (torch.randn(N, d, generator=g, device="cuda").bfloat16() for _ in range(2))
+    Q = torch.randn(3 * batch, d, generator=g, device="cuda").bfloat16()
+    h, ht = (np.arange(batch + 1) * n).astype(np.int32), (np.arange(batch + 1) * 3).astype(np.int32)
+    wo = np.unique(np.concatenate([np.append(np.arange(b * n, (b + 1) * n, v), (b + 1) * n) for b in range(batch)])).astype(np.int32)
+    sizes = np.diff(wo)
+    rem = np.minimum(k, (sizes + 1) // 2 * (sizes // 2)).astype(np.int32)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    cu, cut, d_wo, d_rem = (torch.from_numpy(a).cuda() for a in (h, ht, wo, rem))
+    wt = torch.arange(N, **i32)
+    got = []
+    for host in (True, False):
+        p = L.Problem(batch=batch, d=d, heads=2, head_dim=32, dtype="bf16", h_cu_vis=h, cu_vis=cu, h_cu_txt=ht, cu_txt=cut,
+                      n_windows=len(sizes), max_window_tokens=v, win_offsets=d_wo, win_tokens=wt, win_remove=d_rem,
+                      match=B.MATCH_EDGE_TOPK, h_win_offsets=wo if host else None, h_win_remove=rem if host else None)
+        ws = torch.full((L.lightkv_workspace_size(p),), 0x21, dtype=torch.uint8, device="cuda")   # a stale list of valid tokens
+        xi, fd = torch.ones(N, device="cuda"), torch.empty(N, device="cuda")
+        best, dst, new, src = (torch.full((N,), -9, **i32) for _ in range(4))
+        off, cu_out = torch.empty(N + 1, **i32), torch.empty(batch + 1, **i32)
+        L.lightkv_score_select(p, X, Q if with_xi else None, K if with_xi else None, xi, fd, best, dst, new, off, src, cu_out, ws,
+                               xi_mode=B.XI_TEXT_QUERY if with_xi else B.XI_GIVEN)
+        got.append([t.cpu().numpy() for t in (fd, best, dst, new, off, cu_out, src, xi)])
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+    fd, best, dst, new, off, cu_out, src, xi = got[0]
+    assert off[-1] == rem.sum()
+    assert (src[off[-1]:] == -9).all()
+    win = np.repeat(np.arange(len(sizes)), sizes)
+    owner = np.repeat(np.arange(N), np.diff(off))
+    assert (win[src[:off[-1]]] == win[owner]).all() and ((owner - wo[win[owner]]) % 2 == 1).all()
+    assert set(src[:off[-1]]) == set(np.flatnonzero(dst >= 0))
+    np.testing.assert_array_equal(np.bincount(win[owner], minlength=len(sizes)), rem)
