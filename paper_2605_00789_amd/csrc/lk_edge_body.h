@@ -48,7 +48,7 @@ struct EdgeLds {
   int hist[EDGE_BINS];
   int tok[2 * EDGE_MAX_SIDE];   // the window's tokens (checked), in list order: a token lookup inside a loop must not be a
                                 // trip to global memory
-  uint2 cand[EDGE_THREADS];     // (key, pair index) of the keys around the threshold
+  uint2 cand[64];               // (key, pair index) of the keys around the threshold
   int wsum[EDGE_WAVES];
   uint32_t wlo[EDGE_WAVES], whi[EDGE_WAVES];
   int pick[3];
@@ -63,8 +63,9 @@ __host__ __device__ __forceinline__ size_t edge_lds_bytes(int max_a, int max_b) 
 // flight together with the norms'.  (2) The threshold: one histogram of 2048 bins over the range the keys really span
 // leaves a handful of keys in the bin that holds the k-th; these are gathered and ranked by counting with their pair
 // index, which settles ties as well.  (Four passes of 8 bits over the raw keys -- the first of them useless, as FD lies
-// in [0, 2] -- took 10 of the 25 us of a 55 x 55 window.)  Only when more keys than threads share the bin is it
-// narrowed by another histogram.  With this and the launch shared with the second xi pass, three stages of
+// in [0, 2] -- took 10 of the 25 us of a 55 x 55 window.)  A bin of more than 64 keys is first narrowed by another
+// histogram (keys are dense around the median of unrelated tokens: 5184 pairs a window, half of them wanted, counting among up
+// to 256 keys in LDS 64 us a call, among up to 64 in registers 46).  With this and the launch shared with the second xi pass, three stages of
 // 2880 tokens take 316 us instead of 350.
 __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs &q, int w, char *lds) {
   EdgeLds &L = *reinterpret_cast<EdgeLds *>(lds);
@@ -225,7 +226,7 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
       ordered_ties = remaining < in_bin;
       break;
     }
-    if (in_bin <= EDGE_THREADS) {   // rank the keys of the bin by (key, pair index)
+    if (in_bin <= 64) {   // rank the keys of the bin by (key, pair index), in the registers of the first wave
 #pragma unroll
       for (int it = 0; it < EDGE_ITEMS; ++it) {
         if (it * EDGE_THREADS >= E) break;
@@ -234,14 +235,14 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
           L.cand[atomicAdd(&L.n_cand, 1)] = make_uint2(key, (uint32_t)(it * EDGE_THREADS + tid));
       }
       __syncthreads();
-      if (tid < in_bin) {
-        const uint2 me = L.cand[tid];
+      if (wave == 0) {
+        const uint2 me = L.cand[lane < in_bin ? lane : 0];
         int rank = 0;
-        for (int i = 0; i < in_bin; ++i) {
-          const uint2 o = L.cand[i];
-          rank += (o.x < me.x || (o.x == me.x && o.y < me.y)) ? 1 : 0;
+        for (int i = 0; i < in_bin; ++i) {   // uniform
+          const uint32_t ox = (uint32_t)__builtin_amdgcn_readlane((int)me.x, i), oy = (uint32_t)__builtin_amdgcn_readlane((int)me.y, i);
+          rank += (ox < me.x || (ox == me.x && oy < me.y)) ? 1 : 0;
         }
-        if (rank == remaining - 1) { L.pick[0] = (int)me.x; L.pick[1] = (int)me.y; }   // the order is strict: exactly one
+        if (lane < in_bin && rank == remaining - 1) { L.pick[0] = (int)me.x; L.pick[1] = (int)me.y; }   // the order is strict: exactly one
       }
       __syncthreads();
       threshold = (uint32_t)L.pick[0];
@@ -291,27 +292,39 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
   __syncthreads();
 
   // ---- lower half of the workgroup, per B node: its selected edges in ascending A position.  The slots of the list are
-  // handed out by an LDS counter: what the index scan makes of the list does not depend on their order.
+  // handed out by an LDS counter, once per node (once per edge is a serial chain of as many LDS trips as A nodes); what the
+  // index scan makes of the list does not depend on their order.
   if (tid < nB) {
     const int b_tok = L.tok[2 * tid + 1];
+    unsigned long long taken[EDGE_MAX_SIDE / 64] = {};   // the A positions of this node's edges
     int pos = 0;
     if (any) {
-      for (int la8 = 0; la8 < nA; la8 += 8) {
-        uint32_t key[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) key[i] = keys[(la8 + i < nA ? la8 + i : nA - 1) * pitch + tid];
+      for (int half = 0; half < EDGE_MAX_SIDE / 64; ++half) {
+        const int end = nA < 64 * half + 64 ? nA : 64 * half + 64;
+        for (int la8 = 64 * half; la8 < end; la8 += 8) {
+          uint32_t key[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int la = la8 + i;
-          if (la < nA && key[i] <= threshold) {
-            const int slot = edge_base + atomicAdd(&L.n_slots, 1);
-            if (slot < q.sum_k) {
-              q.edges[slot] = L.tok[2 * la];
-              q.edges[q.sum_k + slot] = b_tok;
-              q.edges[2 * q.sum_k + slot] = pos;
-            }
-            ++pos;
+          for (int i = 0; i < 8; ++i) key[i] = keys[(la8 + i < nA ? la8 + i : nA - 1) * pitch + tid];
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            taken[half] |= (unsigned long long)(la8 + i < nA && key[i] <= threshold ? 1 : 0) << ((la8 & 63) + i);
+        }
+      }
+      int n = 0;
+#pragma unroll
+      for (int half = 0; half < EDGE_MAX_SIDE / 64; ++half) n += __popcll(taken[half]);
+      const int slot0 = edge_base + (n ? atomicAdd(&L.n_slots, n) : 0);
+#pragma unroll
+      for (int half = 0; half < EDGE_MAX_SIDE / 64; ++half) {
+        for (unsigned long long m = taken[half]; m; m &= m - 1) {
+          const int la = 64 * half + __ffsll((long long)m) - 1, slot = slot0 + pos;
+          if (slot < q.sum_k) {
+            q.edges[slot] = L.tok[2 * la];
+            q.edges[q.sum_k + slot] = b_tok;
+            q.edges[2 * q.sum_k + slot] = pos;
           }
+          ++pos;
         }
       }
     }

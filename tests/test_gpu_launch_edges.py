@@ -375,3 +375,50 @@ def test_edge_lists_placed_by_the_scan_and_by_a_launch_of_their_own(batch, n, v,
     assert (win[src[:off[-1]]] == win[owner]).all() and ((owner - wo[win[owner]]) % 2 == 1).all()
     assert set(src[:off[-1]]) == set(np.flatnonzero(dst >= 0))
     np.testing.assert_array_equal(np.bincount(win[owner], minlength=len(sizes)), rem)
+
+
+@pytest.mark.parametrize("n,d,share", [(36, 256, 0.5), (144, 1024, 0.02), (144, 1024, 0.3), (144, 1024, 0.5), (144, 1024, 0.9),
+                                       (255, 512, 0.5), (256, 512, 1.0)])
+def test_edge_selection_of_many_pairs(n, d, share):
+    """Unrelated tokens: the divergences crowd around one, and the threshold lies where hundreds of them share its first
+    bin.  The pairs taken against their divergence in float64 (bf16 protocol: nothing left out is lower by more than 1e-5), four
+    windows with another order each."""
+    import paper_2605_00789_amd as L
+    from paper_2605_00789_amd import binding as B
+    W, N = 4, 4 * n
+    g = torch.Generator(device="cuda").manual_seed(n + int(100 * share))
+    X = torch.randn(N, d, generator=g, device="cuda").bfloat16()
+    lists = [np.sort(p) for p in np.split(np.random.default_rng(n).permutation(N).astype(np.int32), W)]
+    wo, h = (np.arange(W + 1) * n).astype(np.int32), np.array([0, N], dtype=np.int32)
+    na, nb = (n + 1) // 2, n // 2
+    k = int(share * na * nb)
+    rem = np.full(W, k, dtype=np.int32)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    p = L.Problem(batch=1, d=d, heads=d // 32, head_dim=32, dtype="bf16", h_cu_vis=h, cu_vis=torch.from_numpy(h).cuda(), n_windows=W,
+                  max_window_tokens=n, win_offsets=torch.from_numpy(wo).cuda(), win_tokens=torch.from_numpy(np.concatenate(lists)).cuda(),
+                  win_remove=torch.from_numpy(rem).cuda(), match=B.MATCH_EDGE_TOPK, h_win_offsets=wo, h_win_remove=rem)
+    ws = torch.full((L.lightkv_workspace_size(p),), 0x5a, dtype=torch.uint8, device="cuda")
+    xi, fd = torch.ones(N, device="cuda"), torch.empty(N, device="cuda")
+    best, dst, new = (torch.empty(N, **i32) for _ in range(3))
+    off, cu_out, src = torch.empty(N + 1, **i32), torch.empty(2, **i32), torch.full((W * k,), -9, **i32)
+    L.lightkv_score_select(p, X, None, None, xi, fd, best, dst, new, off, src, cu_out, ws, xi_mode=B.XI_GIVEN)
+    off, src, dst = off.cpu().numpy(), src.cpu().numpy(), dst.cpu().numpy()
+    x64 = X.double()
+    x64 = x64 / x64.norm(dim=1, keepdim=True)
+    for l in lists:
+        a, b = l[0::2], l[1::2]
+        ta, tb = (torch.from_numpy(v.astype(np.int64)).cuda() for v in (a, b))
+        m = (1.0 - x64[ta] @ x64[tb].T.contiguous()).clamp_min(0).cpu().numpy()
+        ia, mine = {int(v): i for i, v in enumerate(a)}, np.zeros(m.shape, dtype=bool)
+        for j, t in enumerate(b):
+            s = src[off[t]:off[t + 1]]
+            assert list(s) == sorted(s)
+            mine[[ia[int(v)] for v in s], j] = True
+        assert mine.sum() == k
+        if k < m.size:
+            assert m[mine].max() <= m[~mine].min() + 1e-5
+        np.testing.assert_array_equal(dst[a] >= 0, mine.any(1))
+        low = np.where(mine, m, np.inf)
+        hit = np.flatnonzero(mine.any(1))
+        to = np.array([int(np.flatnonzero(b == dst[a[i]])[0]) for i in hit], dtype=int)
+        assert mine[hit, to].all() and (low[hit, to] <= low[hit].min(1) + 1e-5).all()
