@@ -384,9 +384,19 @@ __device__ __forceinline__ void edge_keys_body(const FdArgs &g, const EdgeArgs &
   if (row0 >= wi.nA || col0 >= wi.nB || wi.nA > q.max_a || wi.nB > q.max_b) return;   // uniform
   const int64_t ks_stride = (int64_t)g.n_tiles * FD_TILE_FLOATS;
   const float *base = g.partial + (int64_t)tile * FD_TILE_FLOATS;
-  const int r = tid >> 3, c0 = (tid & 7) * 4;   // four neighbouring columns per thread
+  // Four pairs per thread: neighbouring columns of a row where the slices are what takes time (one 16-byte load each).  With a
+  // single slice (any problem of 1024 tiles or more) every eighth row of one column, one load a pair, so that a wave writes
+  // whole runs of the matrix: 64 windows of 576 tokens at d = 256 33 -> 21 us (sixteen copies of each load before).
+  const bool one = g.ksplit == 1;   // uniform
+  const int r0 = one ? tid >> 5 : tid >> 3, c0 = one ? tid & 31 : (tid & 7) * 4;
+  const int dr = one ? 8 : 0, dc = one ? 0 : 1;
   f32x4 v[FD_MAX_KSPLIT];
-  load_slices4(base + r * 32 + c0, ks_stride, g.ksplit, v);
+  if (one) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[0][j] = base[(r0 + 8 * j) * 32 + c0];
+  } else {
+    load_slices4(base + r0 * 32 + c0, ks_stride, g.ksplit, v);
+  }
   if (tid < 64) {
     // |a|^2 was accumulated by the first tile of this row of tiles, |b|^2 by the first tile of this column of tiles
     const int i = tid & 31;
@@ -395,13 +405,18 @@ __device__ __forceinline__ void edge_keys_body(const FdArgs &g, const EdgeArgs &
     L.rtok[tid] = reinterpret_cast<const int32_t *>(base + FD_TOK_OFFSET)[tid];   // tokens of the 32 rows, then of the 32 columns
   }
   double dot[4];
-  sum_slices4(v, g.ksplit, dot);
+  if (one) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) dot[j] = (double)v[0][j];
+  } else {
+    sum_slices4(v, g.ksplit, dot);
+  }
   __syncthreads();
   uint32_t *M = q.big_keys + (size_t)w * q.big_stride;
-  const int pitch = wi.nB, la = row0 + r;
+  const int pitch = wi.nB;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int c = c0 + j, lb = col0 + c;
+    const int r = r0 + dr * j, c = c0 + dc * j, la = row0 + r, lb = col0 + c;
     float f = (float)divergence(g.metric, dot[j], L.na2[r], L.nb2[c]);
     if (!(f >= 0.f) || L.rtok[r] < 0 || L.rtok[32 + c] < 0) f = __uint_as_float(0x7f800000u);   // NaN ranks last, like +inf
     if (la < wi.nA && lb < wi.nB) M[(size_t)la * pitch + lb] = f32_order_key(f);
