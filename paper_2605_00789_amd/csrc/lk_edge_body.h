@@ -8,7 +8,8 @@ namespace lk {
 
 constexpr int EDGE_THREADS = 256;
 constexpr int EDGE_WAVES = EDGE_THREADS / 64;
-constexpr int EDGE_ITEMS = EDGE_MAX_SIDE * EDGE_MAX_SIDE / EDGE_THREADS;   // keys per thread, at most
+constexpr int EDGE_ITEMS = EDGE_MAX_SIDE * EDGE_MAX_SIDE / EDGE_THREADS;   // keys per thread, at most ...
+constexpr int EDGE_ITEMS_SMALL = 4;                                        // ... and in windows of up to 64 tokens
 constexpr int EDGE_BINS = 2048;
 
 struct EdgeArgs {
@@ -67,6 +68,9 @@ __host__ __device__ __forceinline__ size_t edge_lds_bytes(int max_a, int max_b) 
 // histogram (keys are dense around the median of unrelated tokens: 5184 pairs a window, half of them wanted, counting among up
 // to 256 keys in LDS 64 us a call, among up to 64 in registers 46).  With this and the launch shared with the second xi pass, three stages of
 // 2880 tokens take 316 us instead of 350.
+// ONE: the hidden axis is not split (one slice); its sixteen copies are half of the registers otherwise, and 1024 windows of
+// 36 tokens at d = 1024 beside xi take 26 us instead of 21.  ITEMS: keys per thread, the launcher's bound.
+template <bool ONE, int ITEMS>
 __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs &q, int w, char *lds) {
   EdgeLds &L = *reinterpret_cast<EdgeLds *>(lds);
   uint32_t *keys = reinterpret_cast<uint32_t *>(lds + sizeof(EdgeLds));   // [nA][pitch]
@@ -75,7 +79,7 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
   const int nA = wi.nA, nB = wi.nB;
   // the host refuses such windows, and sizes the LDS from its own bound on the window: a device-side list that breaks
   // either is left alone
-  if (nA > EDGE_MAX_SIDE || nB > EDGE_MAX_SIDE || nA * (nB | 1) > q.key_capacity) return;
+  if (nA > EDGE_MAX_SIDE || nB > EDGE_MAX_SIDE || nA * nB > ITEMS * EDGE_THREADS || nA * (nB | 1) > q.key_capacity) return;
   const int E = nA * nB;
   const int k = edge_count(q.win_remove[w], nA, nB, q.clamp_v);
 
@@ -107,11 +111,16 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
     const int la = u / n4, lb = (u - la * n4) * 4;
     return g.partial + (int64_t)tile_of(la, lb) * FD_TILE_FLOATS + in_tile(la) * 32 + in_tile(lb);
   };
-  f32x4 v[FD_MAX_KSPLIT];
-  load_slices4(unit_ptr(tid), ks_stride, g.ksplit, v);
+  f32x4 v[ONE ? 1 : FD_MAX_KSPLIT];
+  auto load_unit = [&](int u) {
+    if constexpr (ONE) v[0] = *reinterpret_cast<const f32x4 *>(unit_ptr(u));
+    else load_slices4(unit_ptr(u), ks_stride, g.ksplit, v);
+  };
+  auto sum1 = [&](const float *p) { if constexpr (ONE) return (double)*p; else return sum_slices(p, ks_stride, g.ksplit); };
+  load_unit(tid);
   for (int i = tid; i < nA + nB; i += EDGE_THREADS) {
-    if (i < nA) L.na2[i] = sum_slices(g.partial + (int64_t)tile_of(i, 0) * FD_TILE_FLOATS + 32 * 32 + in_tile(i), ks_stride, g.ksplit);
-    else L.nb2[i - nA] = sum_slices(g.partial + (int64_t)tile_of(0, i - nA) * FD_TILE_FLOATS + 32 * 32 + 32 + in_tile(i - nA), ks_stride, g.ksplit);
+    if (i < nA) L.na2[i] = sum1(g.partial + (int64_t)tile_of(i, 0) * FD_TILE_FLOATS + 32 * 32 + in_tile(i));
+    else L.nb2[i - nA] = sum1(g.partial + (int64_t)tile_of(0, i - nA) * FD_TILE_FLOATS + 32 * 32 + 32 + in_tile(i - nA));
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
@@ -128,8 +137,13 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
   for (int u0 = 0; u0 < units; u0 += EDGE_THREADS) {   // uniform
     const int u = u0 + tid;
     double dot[4];
-    sum_slices4(v, g.ksplit, dot);
-    if (u0 + EDGE_THREADS < units) load_slices4(unit_ptr(u + EDGE_THREADS), ks_stride, g.ksplit, v);
+    if constexpr (ONE) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) dot[j] = (double)v[0][j];
+    } else {
+      sum_slices4(v, g.ksplit, dot);
+    }
+    if (u0 + EDGE_THREADS < units) load_unit(u + EDGE_THREADS);
     if (u < units) {
       const int la = u / n4, lb0 = (u - la * n4) * 4;
       const double a2 = L.na2[la];
@@ -163,11 +177,11 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
   // EDGE_THREADS pairs moves the position by (step_a, step_b) with at most one carry
   const int step_a = EDGE_THREADS / nB, step_b = EDGE_THREADS - step_a * nB;
   const int la0 = tid / nB, lb0 = tid - la0 * nB;   // this thread's first pair
-  uint32_t kreg[EDGE_ITEMS];
+  uint32_t kreg[ITEMS];
   {
     int la = la0, lb = lb0;
 #pragma unroll
-    for (int it = 0; it < EDGE_ITEMS; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
       if (it * EDGE_THREADS >= E) break;   // uniform over the workgroup
       kreg[it] = (it * EDGE_THREADS + tid < E) ? keys[la * pitch + lb] : 0u;
       lb += step_b; la += step_a;
@@ -187,7 +201,7 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
     for (int i = 0; i < EDGE_BINS / EDGE_THREADS / 4; ++i) reinterpret_cast<uint4 *>(L.hist)[i * EDGE_THREADS + tid] = make_uint4(0, 0, 0, 0);
     __syncthreads();
 #pragma unroll
-    for (int it = 0; it < EDGE_ITEMS; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
       if (it * EDGE_THREADS >= E) break;
       const uint32_t key = kreg[it];
       if (it * EDGE_THREADS + tid < E && key >= lo && key <= hi) atomicAdd(&L.hist[(key - lo) >> shift], 1);
@@ -228,7 +242,7 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
     }
     if (in_bin <= 64) {   // rank the keys of the bin by (key, pair index), in the registers of the first wave
 #pragma unroll
-      for (int it = 0; it < EDGE_ITEMS; ++it) {
+      for (int it = 0; it < ITEMS; ++it) {
         if (it * EDGE_THREADS >= E) break;
         const uint32_t key = kreg[it];
         if (it * EDGE_THREADS + tid < E && key >= lo && key <= hi)
@@ -259,7 +273,7 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
     int base = 0;
     int la = la0, lb = lb0;
 #pragma unroll
-    for (int it = 0; it < EDGE_ITEMS; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
       if (it * EDGE_THREADS >= E) break;
       const bool eq = it * EDGE_THREADS + tid < E && kreg[it] == threshold;
       const unsigned long long bal = __ballot(eq);
@@ -281,7 +295,7 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
   } else if (any) {
     int la = la0, lb = lb0;
 #pragma unroll
-    for (int it = 0; it < EDGE_ITEMS; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
       if (it * EDGE_THREADS >= E) break;
       const uint32_t e = (uint32_t)(it * EDGE_THREADS + tid);
       if (e < (uint32_t)E && kreg[it] == threshold && e > tie_e) keys[la * pitch + lb] = 0xffffffffu;

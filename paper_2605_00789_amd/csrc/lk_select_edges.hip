@@ -36,9 +36,10 @@
 
 namespace lk {
 
-__global__ __launch_bounds__(EDGE_THREADS) void edge_select_kernel(FdArgs g, EdgeArgs q) {
+template <bool ONE, int ITEMS>
+__global__ __launch_bounds__(EDGE_THREADS, ITEMS == EDGE_ITEMS ? 2 : 3) void edge_select_kernel(FdArgs g, EdgeArgs q) {
   extern __shared__ __attribute__((aligned(16))) char edge_lds[];
-  edge_select_body(g, q, blockIdx.x, edge_lds);
+  edge_select_body<ONE, ITEMS>(g, q, blockIdx.x, edge_lds);
 }
 __global__ __launch_bounds__(EDGE_THREADS) void edge_keys_kernel(FdArgs g, EdgeArgs q) {
   __shared__ __attribute__((aligned(16))) char lds[sizeof(EdgeKeysLds)];
@@ -269,15 +270,21 @@ hipError_t launch_edge_select(const FdArgs &g, const EdgeArgs &q, int dtype, hip
     return e != hipSuccess ? e : launch_edge_select_big(g, q, stream);
   }
   static std::atomic<bool> allowed[64];   // more dynamic LDS than the 64 KB default, set once per device
+  using Kernel = void (*)(FdArgs, EdgeArgs);
+  static const Kernel kernels[2][2] = {{edge_select_kernel<false, EDGE_ITEMS_SMALL>, edge_select_kernel<false, EDGE_ITEMS>},
+                                       {edge_select_kernel<true, EDGE_ITEMS_SMALL>, edge_select_kernel<true, EDGE_ITEMS>}};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (!allowed[dev].load(std::memory_order_acquire)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(edge_select_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)edge_lds_bytes(EDGE_MAX_SIDE, EDGE_MAX_SIDE));
-    if (e != hipSuccess) return e;
+    for (int i = 0; i < 4; ++i) {
+      e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernels[i >> 1][i & 1]), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)edge_lds_bytes(EDGE_MAX_SIDE, EDGE_MAX_SIDE));
+      if (e != hipSuccess) return e;
+    }
     allowed[dev].store(true, std::memory_order_release);
   }
-  hipLaunchKernelGGL(edge_select_kernel, dim3((unsigned)g.n_windows), dim3(EDGE_THREADS), edge_lds_bytes(q.max_a, q.max_b), stream, g, q);
+  const Kernel k = kernels[g.ksplit == 1][q.max_a * q.max_b > EDGE_ITEMS_SMALL * EDGE_THREADS];
+  hipLaunchKernelGGL(k, dim3((unsigned)g.n_windows), dim3(EDGE_THREADS), edge_lds_bytes(q.max_a, q.max_b), stream, g, q);
   return hipGetLastError();
 }
 

@@ -334,11 +334,11 @@ def test_full_pairwise_without_room_for_the_small_tiles(gh, gw, w):
     assert len(out) == 2 and 0 < int(out[-1].h_cu_vis_out[1]) < int(out[0].h_cu_vis_out[1]) < n
 
 
-@pytest.mark.parametrize("batch,n,v,k", [(1, 576, 36, 17), (8, 576, 36, 16), (8, 576, 36, 17), (29, 565, 37, 4), (29, 566, 37, 4)])
+@pytest.mark.parametrize("batch,n,v,k", [(1, 576, 36, 17), (8, 576, 36, 16), (8, 576, 36, 17), (29, 565, 37, 4), (29, 566, 37, 4), (29, 565, 16, 3)])
 @pytest.mark.parametrize("with_xi", [False, True])
 def test_edge_lists_placed_by_the_scan_and_by_a_launch_of_their_own(batch, n, v, k, with_xi):
     """Counts known to the host (the list gets a launch of its own beyond 2048 edges) and to the device alone (beyond 16384
-    tokens): lists of 272, 2048, 2176 edges and of 16385 and 16414 tokens.  The same bits either way, and the sources of
+    tokens): lists of 272, 2048, 2176 edges and of 16385 and 16414 tokens; 1044 windows, where xi has a stream of its own.  The same bits either way, and the sources of
     every token are the edges that the tokens' own columns say."""
     import paper_2605_00789_amd as L
     from paper_2605_00789_amd import binding as B
@@ -377,7 +377,7 @@ def test_edge_lists_placed_by_the_scan_and_by_a_launch_of_their_own(batch, n, v,
     np.testing.assert_array_equal(np.bincount(win[owner], minlength=len(sizes)), rem)
 
 
-@pytest.mark.parametrize("n,d,share", [(36, 256, 0.5), (144, 1024, 0.02), (144, 1024, 0.3), (144, 1024, 0.5), (144, 1024, 0.9),
+@pytest.mark.parametrize("n,d,share", [(36, 256, 0.5), (64, 512, 0.4), (65, 512, 0.4), (144, 1024, 0.02), (144, 1024, 0.3), (144, 1024, 0.5), (144, 1024, 0.9),
                                        (255, 512, 0.5), (256, 512, 1.0)])
 def test_edge_selection_of_many_pairs(n, d, share):
     """Unrelated tokens: the divergences crowd around one, and the threshold lies where hundreds of them share its first
