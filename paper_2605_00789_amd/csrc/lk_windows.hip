@@ -67,6 +67,7 @@ struct CountArgs {
 
 __global__ __launch_bounds__(CNT_THREADS) void window_counts_kernel(CountArgs g) {
   __shared__ int size_lds[CNT_CACHE];
+  __shared__ long long scratch[CNT_THREADS / 64];
   const int b = blockIdx.x, W = g.win_per_seq, w0 = b * W;
   const int tid = threadIdx.x;
   auto size_mem = [&](int w) { return g.win_offsets[w0 + w + 1] - g.win_offsets[w0 + w]; };
@@ -80,9 +81,10 @@ __global__ __launch_bounds__(CNT_THREADS) void window_counts_kernel(CountArgs g)
   // one per pass, which is what this small kernel's time consists of); longer lists re-read the rest
   for (int w = tid; w < W && w < CNT_CACHE; w += CNT_THREADS) size_lds[w] = size_mem(w);
   __syncthreads();
-  if (tid < 64)
-    counts_target_wave(W, budget, g.dir, [&](int w) { return w < CNT_CACHE ? size_lds[w] : size_mem(w); }, g.win_remove + w0,
-                       g.status ? g.status + b : nullptr);
+  auto size_of = [&](int w) { return w < CNT_CACHE ? size_lds[w] : size_mem(w); };
+  int32_t *status = g.status ? g.status + b : nullptr;
+  if (W > COUNTS_WAVE_MAX) counts_target<CNT_THREADS / 64>(W, budget, g.dir, size_of, g.win_remove + w0, status, scratch);
+  else if (tid < 64) counts_target<1>(W, budget, g.dir, size_of, g.win_remove + w0, status, nullptr);
 }
 
 hipError_t launch_window_counts(int batch, int win_per_seq, const int32_t *win_offsets, int mode, int dir, double rho,

@@ -422,3 +422,55 @@ def test_edge_selection_of_many_pairs(n, d, share):
         hit = np.flatnonzero(mine.any(1))
         to = np.array([int(np.flatnonzero(b == dst[a[i]])[0]) for i in hit], dtype=int)
         assert mine[hit, to].all() and (low[hit, to] <= low[hit].min(1) + 1e-5).all()
+
+
+@pytest.mark.parametrize("W", [1, 63, 64, 65, 511, 512, 513, 700, 4097, 9000])
+@pytest.mark.parametrize("kind", ["equal", "ragged"])
+def test_token_budgets_over_many_windows(W, kind):
+    """One wave up to 512 windows of a sequence, the workgroup beyond; window sizes in LDS and (beyond 8192) in memory.
+    Budgets of nothing, a third, all but one and all of what the windows can give, and two that cannot be met."""
+    import paper_2605_00789_amd as L
+    from paper_2605_00789_amd import binding as B
+    from oracle import lightkv_oracle as O
+    rng = np.random.default_rng(W)
+    sizes = np.full(W, 5) if kind == "equal" else rng.integers(0, 40, W)
+    caps = np.where(sizes >= 2, (sizes + 1) // 2, 0)
+    n, most = int(sizes.sum()), int(caps.sum())
+    batch = 6
+    leave = [0, most // 3, max(most - 1, 0), most, min(most + 1, n), -3]
+    wo = np.concatenate([[0], np.cumsum(np.tile(sizes, batch))]).astype(np.int32)
+    cu = (np.arange(batch + 1) * n).astype(np.int32)
+    target = np.concatenate([[0], np.cumsum([n - l for l in leave])]).astype(np.int32)
+    out = torch.full((batch * W,), -7, dtype=torch.int32, device="cuda")
+    status = torch.full((batch,), -7, dtype=torch.int32, device="cuda")
+    L.lightkv_window_counts(batch, batch * W, torch.from_numpy(wo).cuda(), B.COUNT_TARGET, out, cu_vis=torch.from_numpy(cu).cuda(),
+                            cu_vis_target=torch.from_numpy(target).cuda(), status=status)
+    got = out.cpu().numpy().reshape(batch, W)
+    for b, l in enumerate(leave):
+        bad = l < 0 or l > most
+        assert int(status[b]) == int(bad)
+        if bad:
+            np.testing.assert_array_equal(got[b], caps if l > most else 0)
+            continue
+        q = max(v for v in range(int(caps.max()) + 2) if np.minimum(caps, v).sum() <= l)   # the rule as the header states it
+        want = np.minimum(caps, q)
+        want[np.flatnonzero(caps > q)[:l - int(want.sum())]] += 1
+        np.testing.assert_array_equal(got[b], want)
+
+
+@pytest.mark.parametrize("tiles,gh,gw,w", [(1, 8, 8, 90), (1, 3, 5, 9), (2, 7, 11, 8), (1, 1, 129, 5), (1, 97, 89, 8), (1, 128, 128, 4)])
+def test_window_partition_with_scattered_cells(tiles, gh, gw, w):
+    """Tokens in any order, cells missing and repeated, more windows than tokens; grids whose sides are no powers of two."""
+    import paper_2605_00789_amd as L
+    from oracle import lightkv_oracle as O
+    n = min(tiles * gh * gw, 9000)
+    rng = np.random.default_rng(n + w)
+    pos = rng.integers(0, tiles * gh * gw, 2 * n).astype(np.int32)
+    h_cu = np.array([0, n, 2 * n], dtype=np.int32)
+    wps = tiles * w * w
+    ro, rt = O.build_windows(pos, h_cu, tiles, gh, gw, w)
+    wo = torch.full((2 * wps + 1,), -7, dtype=torch.int32, device="cuda")
+    wt = torch.full((2 * n,), -7, dtype=torch.int32, device="cuda")
+    L.lightkv_build_windows(2, h_cu, torch.from_numpy(h_cu).cuda(), torch.from_numpy(pos).cuda(), tiles, gh, gw, w, wo, wt)
+    np.testing.assert_array_equal(wo.cpu().numpy(), ro)
+    np.testing.assert_array_equal(wt.cpu().numpy(), rt)
