@@ -103,6 +103,9 @@ static WinArgs win_args(const WinSpec &spec, const int32_t *cu_vis, const int32_
   g.cu_vis = cu_vis; g.pos = pos; g.new_index = new_index; g.cu_out = cu_out; g.batch = batch;
   g.tiles = spec.tiles; g.grid_h = spec.grid_h; g.grid_w = spec.grid_w; g.w = spec.w;
   g.win_per_seq = (spec.w == 0) ? 1 : spec.tiles * spec.w * spec.w;
+  g.by_cells = make_fast_div((uint32_t)(spec.grid_h * spec.grid_w));
+  g.by_grid_h = make_fast_div((uint32_t)spec.grid_h);
+  g.by_grid_w = make_fast_div((uint32_t)spec.grid_w);
   g.win_offsets = spec.win_offsets; g.win_tokens = spec.win_tokens;
   g.count_mode = spec.count_mode; g.rho = spec.rho; g.cu_target = spec.cu_target; g.win_remove = spec.win_remove;
   g.status = spec.status; g.dir = spec.dir;
