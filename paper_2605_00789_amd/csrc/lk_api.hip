@@ -377,8 +377,21 @@ lightkv_status lightkv_window_counts(int32_t batch, int32_t n_windows, const int
 
 // The schedules' form: a spec with counts.
 int lk::build_windows_with_counts(int32_t batch, const int32_t *h_cu_vis, const int32_t *cu_vis, const int32_t *pos,
-                                  const WinSpec &spec, void *stream) {
-  return build_windows_impl(batch, h_cu_vis, cu_vis, pos, nullptr, nullptr, spec, stream);
+                                  const int32_t *new_index, const int32_t *cu_vis_out, const WinSpec &spec, void *stream) {
+  return build_windows_impl(batch, h_cu_vis, cu_vis, pos, new_index, cu_vis_out, spec, stream);
+}
+
+bool lk::windows_ride(const lightkv_problem *p, const WinSpec &next) {
+  int max_seq = 0;
+  WinArgs unused;
+  // (pos and the selection are the caller's to check: any non-null pointer stands for them here)
+  if (check_windows(p->batch, p->h_cu_vis, p->cu_vis, p->cu_vis, next, max_seq) != LIGHTKV_OK) return false;
+  return make_win_args(next, p->cu_vis, nullptr, nullptr, nullptr, p->batch, max_seq, &unused) > 0;
+}
+
+bool lk::tiled_divergence(const lightkv_problem *p) {
+  Checked c;
+  return check_problem(p, true, false, c) == LIGHTKV_OK && !full_pairwise(p) && use_big_fd(p, c);
 }
 
 int lk::least_workspace(const lightkv_problem *p, size_t *bytes) {

@@ -2,7 +2,8 @@
 // enqueued through the library's own entry points, arranged so that
 //   - xi (needs only Q and the stage's K rows) runs next to the feature-divergence chain and the selection: in the same
 //     launches where lightkv_score_select can do that, on a helper stream otherwise,
-//   - the next stage's windows (need only pos and the selection) are built by workgroups of the merge's launch.
+//   - the next stage's windows (need only pos and the selection) are built by workgroups of the merge's launch, or beside
+//     the merge on a second helper stream (RideOrFork below).
 // Nothing here launches a kernel itself or allocates device memory.  lightkv_compress_schedule never synchronises;
 // lightkv_compress_schedule_ratio (token counts that depend on the data) waits once per stage for the sequence offsets the
 // stage leaves, and for the stream before it returns.
@@ -17,10 +18,10 @@
 
 namespace {
 
-// The helper stream (it runs xi) and the fork and join events of one call.  Sets come from a per-device pool
-// (lk_helpers.h), distinct from the one lightkv_score uses for its own fork.
-using Helpers = lk::HelperSet<1, 2, 1>;
-enum { EV_FORK_XI = 0, EV_JOIN_XI = 1 };
+// The helper streams (0 runs xi, 1 builds windows) and the fork and join events of one call.  Sets come from a per-device
+// pool (lk_helpers.h), distinct from the one lightkv_score uses for its own fork.
+using Helpers = lk::HelperSet<2, 4, 1>;
+enum { EV_FORK_XI = 0, EV_JOIN_XI = 1, EV_FORK_WIN = 2, EV_JOIN_WIN = 3 };
 
 // a stage's windows, with the counts that go with them in a schedule
 lk::WinSpec windows_of(const lightkv_stage &st, int32_t tiles, int32_t grid_h, int32_t grid_w, int count_mode, double rho) {
@@ -62,6 +63,41 @@ bool order_after(hipStream_t to, hipStream_t from, hipEvent_t ev) {
   return hipEventRecord(ev, from) == hipSuccess && hipStreamWaitEvent(to, ev, 0) == hipSuccess;
 }
 
+// The helpers of a call, taken when a stage first forks.
+struct CallHelpers {
+  hipStream_t main;
+  std::unique_lock<std::mutex> guard;
+  Helpers *h = nullptr;
+  bool tried = false;
+  explicit CallHelpers(hipStream_t m) : main(m) {}
+  Helpers *get() {
+    if (!tried) { tried = true; h = lk::acquire_helpers<2, 4, 1>(main, guard); }
+    return h;
+  }
+};
+
+// The next stage's windows, once the selection has been enqueued on the caller's stream: guests of the merge's launch
+// (`ride`, the merge then takes the spec), or a launch of their own on the second helper stream.
+struct NextWindows {
+  bool forked = false;
+  // true: the merge has to take them along
+  bool enqueue(CallHelpers &helpers, bool ride, const lightkv_problem *p, const int32_t *pos, const lightkv_stage &st,
+               const lk::WinSpec &spec, lightkv_status &rc) {
+    forked = false;
+    Helpers *h = ride ? nullptr : helpers.get();
+    if (!h) return true;
+    if (!order_after(h->stream[1], helpers.main, h->event[EV_FORK_WIN])) { (void)hipGetLastError(); return true; }
+    forked = true;
+    rc = (lightkv_status)lk::build_windows_with_counts(p->batch, p->h_cu_vis, p->cu_vis, pos, st.new_index, st.cu_vis_out, spec, h->stream[1]);
+    if (hipEventRecord(h->event[EV_JOIN_WIN], h->stream[1]) != hipSuccess && rc == LIGHTKV_OK) rc = LIGHTKV_ERR_LAUNCH;
+    return false;
+  }
+  void join(CallHelpers &helpers, lightkv_status &rc) {
+    if (forked && hipStreamWaitEvent(helpers.main, helpers.h->event[EV_JOIN_WIN], 0) != hipSuccess && rc == LIGHTKV_OK) rc = LIGHTKV_ERR_LAUNCH;
+    forked = false;
+  }
+};
+
 }  // namespace
 
 extern "C" lightkv_status lightkv_compress_schedule(const lightkv_stage *stages, int32_t n_stages,
@@ -91,8 +127,8 @@ extern "C" lightkv_status lightkv_compress_schedule(const lightkv_stage *stages,
     if (!ws || ws_bytes < need) return LIGHTKV_ERR_WORKSPACE;
   }
   hipStream_t main = static_cast<hipStream_t>(stream);
-  std::unique_lock<std::mutex> guard;
-  Helpers *h = nullptr;               // taken by the first stage that forks
+  CallHelpers helpers(main);
+  NextWindows next_windows;
 
   const int d = stages[0].problem.d, head_dim = stages[0].problem.head_dim;
   const void *Xi = X, *Ki = K, *Vi = V;
@@ -109,17 +145,18 @@ extern "C" lightkv_status lightkv_compress_schedule(const lightkv_stage *stages,
     bool xi_forked = false;
     if (!one_stream) {
       hipStream_t xs = main;
-      if (!h) h = lk::acquire_helpers<1, 2, 1>(main, guard);
+      Helpers *h = helpers.get();
       if (h && order_after(h->stream[0], main, h->event[EV_FORK_XI])) { xs = h->stream[0]; xi_forked = true; }
       else if (h) (void)hipGetLastError();
       rc = lightkv_score(p, nullptr, 0, nullptr, Q, q_tok_stride, q_head_stride, Ki, ldki, head_dim, LIGHTKV_XI_TEXT_QUERY,
                          nullptr, softmax_scale, st.xi, nullptr, nullptr, nullptr, 0, ws, ws_bytes, xs);
       if (xi_forked && hipEventRecord(h->event[EV_JOIN_XI], h->stream[0]) != hipSuccess) rc = rc == LIGHTKV_OK ? LIGHTKV_ERR_LAUNCH : rc;
     }
-    // ---- windows (and their counts from the stage's token budget), unless the previous stage's merge built them
+    // ---- windows (and their counts from the stage's token budget), unless they were built beside the previous stage's merge
+    next_windows.join(helpers, rc);
     if (!windows_ready && rc == LIGHTKV_OK)
       rc = (lightkv_status)lk::build_windows_with_counts(
-          p->batch, p->h_cu_vis, p->cu_vis, posi,
+          p->batch, p->h_cu_vis, p->cu_vis, posi, nullptr, nullptr,
           windows_of(st, tiles, grid_h, grid_w, st.cu_vis_target ? LIGHTKV_COUNT_TARGET : -1, 0.0), main);
     // ---- feature divergence + selection
     if (rc == LIGHTKV_OK) {
@@ -132,25 +169,30 @@ extern "C" lightkv_status lightkv_compress_schedule(const lightkv_stage *stages,
                                   st.xi, st.best_fd, st.best_dst, st.dst, st.new_index, st.grp_offsets, st.grp_src,
                                   st.cu_vis_out, ws, ws_bytes, main);
     }
-    // ---- join xi (whatever happened: nothing stays forked), then merge and compact; the next stage's windows follow from
-    // pos and the selection alone and are built by workgroups of the same launch (cu_vis_out of this stage is the next
-    // stage's cu_vis)
-    if (xi_forked && hipStreamWaitEvent(main, h->event[EV_JOIN_XI], 0) != hipSuccess) rc = rc == LIGHTKV_OK ? LIGHTKV_ERR_LAUNCH : rc;
-    if (rc == LIGHTKV_OK) {
-      lk::WinSpec next{};
-      if (s + 1 < n_stages)
-        next = windows_of(stages[s + 1], tiles, grid_h, grid_w, stages[s + 1].cu_vis_target ? LIGHTKV_COUNT_TARGET : -1, 0.0);
+    // ---- the next stage's windows follow from pos and the selection alone (cu_vis_out of this stage is the next stage's
+    // cu_vis).  They ride in the merge's launch if they fit there, unless the next stage forks xi for the tiled FD kernel: a
+    // workgroup of that kernel fills a CU, and xi has to be there before it -- the two forks then start the two chains together
+    // (three eager stages of 8192 tokens, d = 4096: 497 us, riding 556).
+    lk::WinSpec next{};
+    bool ride = false;
+    if (rc == LIGHTKV_OK && s + 1 < n_stages) {
+      next = windows_of(stages[s + 1], tiles, grid_h, grid_w, stages[s + 1].cu_vis_target ? LIGHTKV_COUNT_TARGET : -1, 0.0);
+      ride = next_windows.enqueue(helpers, lk::windows_ride(p, next) && !lk::tiled_divergence(&stages[s + 1].problem), p, posi, st, next, rc);
+    }
+    // ---- join xi (whatever happened: nothing stays forked), merge and compact
+    if (xi_forked && hipStreamWaitEvent(main, helpers.h->event[EV_JOIN_XI], 0) != hipSuccess) rc = rc == LIGHTKV_OK ? LIGHTKV_ERR_LAUNCH : rc;
+    if (rc == LIGHTKV_OK)
       rc = (lightkv_status)lk::aggregate_compact_with_windows(p, st.new_index, st.grp_offsets, st.grp_src, st.xi, Xi, ldxi, Ki,
                                                               ldki, Vi, ldvi, posi, st.X_out, st.K_out, st.V_out, st.pos_out,
                                                               st.x_sqnorm_out, st.out_rows, st.cu_vis_out,
-                                                              s + 1 < n_stages ? &next : nullptr, nullptr, 0, main);
-    }
+                                                              ride ? &next : nullptr, nullptr, 0, main);
     windows_ready = true;
     Xi = st.X_out; Ki = st.K_out; Vi = st.V_out;
     ldxi = ldki = ldvi = d;
     posi = st.pos_out;
     sq = st.x_sqnorm_out;
   }
+  next_windows.join(helpers, rc);   // after an error
   return rc;
 }
 
@@ -202,6 +244,8 @@ extern "C" lightkv_status lightkv_compress_schedule_ratio(const lightkv_stage *s
   const int32_t *h_cu = stages[0].problem.h_cu_vis;   // offsets of the stage's input: on the host ...
   const int32_t *d_cu = stages[0].problem.cu_vis;     // ... and on the device
   bool windows_ready = false;
+  CallHelpers helpers(main);
+  NextWindows next_windows;
   std::unique_lock<std::mutex> box_guard;
   lk::Mailbox *box = lk::acquire_mailbox(batch + 1, box_guard);
   lightkv_status rc = LIGHTKV_OK;
@@ -223,9 +267,10 @@ extern "C" lightkv_status lightkv_compress_schedule_ratio(const lightkv_stage *s
       rc = (lightkv_status)lk::least_workspace(&q, &need);
     }
     if (rc == LIGHTKV_OK && (!ws || ws_bytes < need)) rc = LIGHTKV_ERR_WORKSPACE;
-    // ---- windows and their counts, unless the previous stage's merge built them
+    // ---- windows and their counts, unless they were built beside the previous stage's merge
+    next_windows.join(helpers, rc);
     if (!windows_ready && rc == LIGHTKV_OK)
-      rc = (lightkv_status)lk::build_windows_with_counts(batch, h_cu, d_cu, posi,
+      rc = (lightkv_status)lk::build_windows_with_counts(batch, h_cu, d_cu, posi, nullptr, nullptr,
                                                          windows_of(st, tiles, grid_h, grid_w, count_mode_of(st), rho[s]), main);
     // ---- scores (xi and feature divergence) and selection
     if (rc == LIGHTKV_OK)
@@ -233,15 +278,18 @@ extern "C" lightkv_status lightkv_compress_schedule_ratio(const lightkv_stage *s
                                 nullptr, softmax_scale, st.xi, st.best_fd, st.best_dst, st.dst, st.new_index, st.grp_offsets,
                                 st.grp_src, st.cu_vis_out, ws, ws_bytes, main);
     // ---- merge and compact, the next stage's windows and counts beside it (they follow from the selection alone)
-    if (rc == LIGHTKV_OK) {
-      lk::WinSpec next{};
-      if (s + 1 < n_stages) next = windows_of(stages[s + 1], tiles, grid_h, grid_w, count_mode_of(stages[s + 1]), rho[s + 1]);
+    lk::WinSpec next{};
+    bool ride = false;
+    if (rc == LIGHTKV_OK && s + 1 < n_stages) {
+      next = windows_of(stages[s + 1], tiles, grid_h, grid_w, count_mode_of(stages[s + 1]), rho[s + 1]);
+      ride = next_windows.enqueue(helpers, lk::windows_ride(&q, next), &q, posi, st, next, rc);
+    }
+    if (rc == LIGHTKV_OK)
       rc = (lightkv_status)lk::aggregate_compact_with_windows(&q, st.new_index, st.grp_offsets, st.grp_src, st.xi, Xi, ldxi, Ki,
                                                               ldki, Vi, ldvi, posi, st.X_out, st.K_out, st.V_out, st.pos_out,
                                                               st.x_sqnorm_out, st.out_rows, st.cu_vis_out,
-                                                              s + 1 < n_stages ? &next : nullptr, box ? box->words : nullptr,
+                                                              ride ? &next : nullptr, box ? box->words : nullptr,
                                                               box ? box->next_tag() : 0u, main);
-    }
     windows_ready = true;
     // ---- the offsets the stage left: the next stage's descriptor
     int32_t *h_out = h_cu_vis_out + (size_t)s * (batch + 1);
@@ -276,6 +324,7 @@ extern "C" lightkv_status lightkv_compress_schedule_ratio(const lightkv_stage *s
     h_cu = h_out;
     d_cu = st.cu_vis_out;
   }
+  next_windows.join(helpers, rc);   // after an error
   // what was enqueued has finished when the call returns, whatever it returns
   if (hipStreamSynchronize(main) != hipSuccess) {
     (void)hipGetLastError();

@@ -474,3 +474,80 @@ def test_window_partition_with_scattered_cells(tiles, gh, gw, w):
     L.lightkv_build_windows(2, h_cu, torch.from_numpy(h_cu).cuda(), torch.from_numpy(pos).cuda(), tiles, gh, gw, w, wo, wt)
     np.testing.assert_array_equal(wo.cpu().numpy(), ro)
     np.testing.assert_array_equal(wt.cpu().numpy(), rt)
+
+
+SCHEDULES = [
+    # tokens beyond those whose window and rank the riding partition keeps in registers; a batch with windows of unequal sizes
+    (1, 56, 58, (8, 4, 2), (2700, 2200, 1800), 2, 64), (2, 61, 67, (5, 3, 2), (3500, 3000, 2500), 1, 64),
+    (1, 80, 80, (8, 16, 8), (5500, 4700, 4000), 2, 32),      # 256 windows: the counts do not fit beside the rows
+    (1, 80, 80, (8, 24, 20), (5500, 4700, 4000), 2, 32),     # 576 windows: nor the partition's own LDS (sorted)
+    (1, 64, 64, (4, 2, 1), (3300, 2700, 2200), 8, 32),       # the tiled divergence: windows beside the merge on a stream
+]
+
+
+def _schedule(batch, gh, gw, windows, targets, heads, hd):
+    import paper_2605_00789_amd as L
+    n, d, t = gh * gw, heads * hd, 9
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X, K, V = (torch.randn(batch * n, d, generator=g, device="cuda").bfloat16() for _ in range(3))
+    Q = torch.randn(batch * t, d, generator=g, device="cuda").bfloat16()
+    pos = torch.arange(n, dtype=torch.int32, device="cuda").repeat(batch)
+    kw = dict(dtype="bf16", batch=batch, d=d, heads=heads, head_dim=hd, tiles=1, grid_h=gh, grid_w=gw,
+              cu_txt=(np.arange(batch + 1) * t).astype(np.int32), windows_per_axis=windows)
+    return L, kw, (X, K, V, Q, pos)
+
+
+@pytest.mark.parametrize("shape", SCHEDULES, ids=lambda s: "%dx%dx%d_%s" % (s[0], s[1], s[2], "-".join(map(str, s[3]))))
+def test_schedule_builds_windows_in_every_place(shape):
+    """The next stage's windows ride in the merge's launch or are built beside it: the schedule in one call against the same
+    stages call by call, bit for bit, eagerly and as a replayed graph."""
+    L, kw, (X, K, V, Q, pos) = _schedule(*shape)
+    names = ("win_offsets", "win_tokens", "win_remove", "status", "xi", "best_fd", "dst", "new_index", "grp_offsets", "cu_vis_out",
+             "X_out", "K_out", "V_out", "pos_out")
+    one, steps = (L.CompressionPipeline(targets=shape[4], **kw) for _ in range(2))
+    a, sq = (X, K, V, pos), None
+    for s in range(len(shape[3])):
+        st = steps.run_stage(s, *a[:3], Q, a[3], x_sqnorm=sq)
+        a, sq = (st.X_out, st.K_out, st.V_out, st.pos_out), st.x_sq_out
+
+    def check(what):
+        torch.cuda.synchronize()
+        for s, (x, y) in enumerate(zip(one.stages, steps.stages)):
+            assert int(x.status.sum()) == 0
+            for n in names:
+                assert torch.equal(getattr(x, n), getattr(y, n)), (what, s, n)
+
+    def scribble():
+        for st in one.stages:
+            st.X_out.zero_(); st.win_tokens.fill_(-1); st.win_remove.fill_(-1); st.xi.fill_(float("nan")); st.dst.fill_(-3)
+    for rep in range(2):
+        scribble()
+        one.run(X, K, V, Q, pos)
+        check("eager %d" % rep)
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        one.run(X, K, V, Q, pos)
+    for rep in range(3):
+        scribble()
+        torch.cuda.synchronize()
+        graph.replay()
+        check("replay %d" % rep)
+
+
+@pytest.mark.parametrize("match", ["best_per_a", "edge_topk", "full_pairwise"])
+@pytest.mark.parametrize("shape", SCHEDULES, ids=lambda s: "%dx%dx%d_%s" % (s[0], s[1], s[2], "-".join(map(str, s[3]))))
+def test_ratio_schedule_builds_windows_in_every_place(shape, match):
+    """The same for schedules whose counts depend on the data: one call against the stages call by call."""
+    L, kw, (X, K, V, Q, pos) = _schedule(*shape)
+    h = (np.arange(shape[0] + 1) * (shape[1] * shape[2])).astype(np.int32)
+    res = []
+    for form in ("run", "run_steps"):
+        s = L.EdgeTopKSchedule(rho=[0.2] * len(shape[3]), match=match, **kw)
+        last = [getattr(s, form)(h, X, K, V, Q, pos) for _ in range(2)][-1]
+        torch.cuda.synchronize()
+        res.append([r.h_cu_vis_out for r in last] + [t.cpu() for t in (last[-1].X, last[-1].K, last[-1].V, last[-1].pos)])
+    for x, y in zip(*res):
+        if isinstance(x, np.ndarray):
+            np.testing.assert_array_equal(x, y)
+        else:
+            assert torch.equal(x, y)
