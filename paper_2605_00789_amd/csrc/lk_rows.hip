@@ -57,15 +57,19 @@ template <> struct RowIO<float> {
 };
 
 // One wave = one segment of one row of one tensor (4 rows per workgroup): U chunks of 16 bytes per lane, so that the
-// whole segment is in flight before anything is consumed.  A row of more than 8 chunks per lane (8 KB) is cut into
-// equal segments for as many waves: two passes of one wave over a 10 KB row are two trips to memory in a row (2304 rows
-// of 5120 bf16 and 200 text rows: 52 + 6 us in two launches -> 41 us).  All loads are unconditional (clamped addresses) so that the
-// compiler never has to wait inside a branch.
+// whole segment is in flight before anything is consumed.  A merged row of more than 8 chunks per lane (8 KB; 5 KB in a short
+// launch) is cut into equal segments for as many waves: two passes of one wave over a 10 KB row are two trips to memory in a
+// row (2304 rows of 5120 bf16 and 200 text rows: 52 + 6 us in two launches -> 41 us).  A row that is only moved has nothing to
+// wait for between its passes: one wave takes them in turn (9216 rows of 16 KB 153 us in segments, 146 so).  All loads are
+// unconditional (clamped addresses) so that the compiler never has to wait inside a branch.
 constexpr int ROWS_PER_WG = ROW_THREADS / WAVE;
-// 16-byte chunks per lane and segment, at most.  Streaming sizes (HBM bound) want few long segments: 21312 rows of
-// 8 KB and 5352 behind them 199 us against 204 us with rows cut in two; cache-resident ones want more waves with shorter lives:
-// three stages of 2880 tokens 238 us a step with whole rows, 234 us with rows cut in two.
-constexpr int ROW_MAX_U_STREAM = 8, ROW_MAX_U = 5;
+// 16-byte chunks per lane and segment, at most.  Launches of few rows leave waves idle and want more of them with shorter
+// lives; longer ones pay for them.  us, 8 KB rows in segments of 4 / whole: merge of three tensors 144 rows 4.9 / 6.4, 2000
+// rows 19.8 / 20.6, 4096 rows 35.6 / 34.8; of one tensor 1100 rows 6.9 / 7.5, 2880 rows 13.0 / 12.5, 16384 rows 58.8 / 49.2.
+// With squared norms (one wave per row of the first tensor) three tensors of 2880 rows 25.2 / 26.6, 5400 42.4 / 44.2, 9216
+// 71.2 / 70.7.
+constexpr int ROW_MAX_U = 8, ROW_MAX_U_SHORT = 5;
+constexpr int64_t ROWS_SHORT_MAX = 2048, ROWS_SHORT_MAX_SQ = 6144;
 constexpr int64_t ROWS_STREAM_OUT_BYTES = 128ll << 20;   // inputs beyond this: nontemporal output stores
 constexpr int ROWS_WIN_KEEP = 12;   // passes of 256 tokens the window partition keeps in registers (3072 tokens)
 
@@ -105,13 +109,13 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
   constexpr int HU = U > 4 ? (U + 1) / 2 : U;   // chunks of a merge in flight per source
   if constexpr (MODE == 2) {
     if ((int)blockIdx.x < g.n_win_blocks) {
-      if (blockIdx.y > 0) return;
+      if (blockIdx.y + blockIdx.z > 0) return;
       extern __shared__ __attribute__((aligned(16))) char win_lds[];
       build_windows_body<ROW_THREADS, ROWS_WIN_KEEP>(wn, blockIdx.x, win_lds);
       return;
     }
     if ((int)blockIdx.x < g.n_guest_blocks) {
-      if (blockIdx.y > 0) return;
+      if (blockIdx.y + blockIdx.z > 0) return;
       // every word carries the tag, so the host needs no order between them
       for (int i = threadIdx.x; i <= g.batch; i += ROW_THREADS)
         __hip_atomic_store(&g.publish[i], ((unsigned long long)g.publish_tag << 32) | (unsigned)g.cu_vis_out[i],
@@ -121,8 +125,8 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
   }
   const int lane = threadIdx.x & 63;
   const int64_t b = (int64_t)((int)blockIdx.x - g.n_guest_blocks) * ROWS_PER_WG + (threadIdx.x >> 6);
-  const int which = blockIdx.y / g.segs;                   // grid y: tensor and segment
-  int seg = blockIdx.y - which * g.segs;
+  const int which = blockIdx.z;   // tensor
+  int seg = blockIdx.y;
   if (b >= g.sum_n + g.tail_rows) return;
   const char *in = static_cast<const char *>(g.t.in[which]);
   char *out = static_cast<char *>(g.t.out[which]);
@@ -134,7 +138,7 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
   // segments of such a row in turn.
   const bool want_sq = MODE != 0 && which == 0 && g.x_sqnorm_out != nullptr && b < g.sum_n;
   if (want_sq && seg > 0) return;
-  const int seg_end = want_sq ? g.segs : seg + 1;
+  const int seg_end = want_sq || MODE == 1 ? g.segs : seg + 1;   // (a launch of mode 1 has one workgroup per four rows)
 
   // round 1 (the in-place mode touches few rows: it looks at the group bounds first instead of fetching every row)
   if (MODE == 0 && g.grp_offsets[b + 1] == g.grp_offsets[b]) return;
@@ -161,10 +165,13 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
     if (which == 0 && seg == 0 && lane == 0 && g.pos && g.pos_out) g.pos_out[out_row] = g.pos[b];
     if (in == nullptr) return;
     char *row_out = out + out_row * g.t.ld_out[which] * BYTES;
+    for (int sg = seg; sg < seg_end; ++sg) {
+      if (sg > seg) load_row(row_in, sg, v);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int c = (seg * U + u) * WAVE + lane;
-      if (c < n_chunks) store16<STREAM>(row_out + (int64_t)c * 16, v[u]);
+      for (int u = 0; u < U; ++u) {
+        const int c = (sg * U + u) * WAVE + lane;
+        if (c < n_chunks) store16<STREAM>(row_out + (int64_t)c * 16, v[u]);
+      }
     }
     return;
   }
@@ -330,12 +337,14 @@ hipError_t launch_rows(int mode, int dtype, int d, int sum_n, int batch, const R
   for (int i = 0; i < 3; ++i) n_tensors += t.in[i] != nullptr;
   // nontemporal output stores once the tensors are far beyond what stays cached until the next stage reads them
   const bool stream_out = mode != 0 && (int64_t)sum_n * d * (dtype == 1 ? 2 : 4) * n_tensors > ROWS_STREAM_OUT_BYTES;
-  // chunks per lane of a whole row; rows beyond max_u are cut into equal segments, rounded up to a size there is
+  // chunks per lane of a whole row; rows beyond max_u are taken in equal segments, rounded up to a size there is
   const int per_lane = (d * (dtype == 1 ? 2 : 4) / 16 + WAVE - 1) / WAVE;
-  const int max_u = stream_out ? ROW_MAX_U_STREAM : ROW_MAX_U;
+  const bool is_short = !stream_out && sum_n + tail_rows <= (x_sqnorm_out ? ROWS_SHORT_MAX_SQ : ROWS_SHORT_MAX);
+  const int max_u = mode != 1 && is_short ? ROW_MAX_U_SHORT : ROW_MAX_U;
   g.segs = (per_lane + max_u - 1) / max_u;
   const int u = (per_lane + g.segs - 1) / g.segs;
-  const dim3 grid((unsigned)(g.n_guest_blocks + (sum_n + tail_rows + ROWS_PER_WG - 1) / ROWS_PER_WG), (unsigned)(3 * g.segs));
+  const dim3 grid((unsigned)(g.n_guest_blocks + (sum_n + tail_rows + ROWS_PER_WG - 1) / ROWS_PER_WG),
+                  (unsigned)(mode == 1 ? 1 : g.segs), 3u);
   const WinArgs wn = win ? *win : WinArgs{};
   const size_t lds = win ? win_lds : 0;
 #define LK_ROWS(TT)                                                                       \

@@ -48,6 +48,7 @@ def test_one_window_around_the_column_tiles_of_the_epilogue(gh, gw, dtype, d):
     ("bf16", 4096, 65, 9), ("bf16", 4160, 30, 2), ("bf16", 5120, 37, 6), ("bf16", 8192, 20, 1), ("bf16", 8704, 20, 3),
     ("f32", 128, 40, 2), ("f32", 1280, 40, 2), ("f32", 5120, 21, 4),
     ("bf16", 4096, 6000, 40),          # beyond 128 MB: whole rows per wave, nontemporal stores
+    ("bf16", 2816, 6140, 4), ("bf16", 2816, 6141, 4),   # the last launch of short segments with squared norms, the first without
 ])
 def test_merge_over_the_row_segments(dtype, d, n, tail):
     """One to five segments per row, whole and partial, with and without rows behind the vision span and squared norms;
@@ -97,6 +98,48 @@ def test_merge_over_the_row_segments(dtype, d, n, tail):
     want_sq = outs[0][:out].double().square().sum(1)
     assert bool(((sq.double() - want_sq).abs() <= 1e-6 * want_sq).all())
     assert torch.equal(pos_out, torch.cat([pos[:n][keep], pos[n:]]))
+
+
+@pytest.mark.parametrize("dtype,d,n,tail", [("bf16", 64, 30, 3), ("bf16", 4096, 30, 0), ("bf16", 4160, 31, 2), ("bf16", 8704, 30, 3),
+                                            ("bf16", 4224, 2100, 5), ("f32", 4352, 33, 1)])
+def test_rows_in_one_wave_or_several(dtype, d, n, tail):
+    """lightkv_compact takes a row in one wave's passes and must move its bytes unchanged, rows behind the vision span
+    included; lightkv_aggregate followed by it gives the bits of lightkv_aggregate_compact, whatever segments each launch cuts."""
+    import paper_2605_00789_amd as L
+    g = torch.Generator(device="cuda").manual_seed(d + n)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    X, K, V = (torch.randn(n + tail, d, generator=g, device="cuda").to(tdt) for _ in range(3))
+    rng = np.random.default_rng(n)
+    dst = np.full(n, -1)
+    leave = np.sort(rng.permutation(n)[:n // 4])
+    dst[leave] = -2
+    stay = np.flatnonzero(dst == -1)
+    dst[leave] = rng.choice(stay, len(leave))
+    gone = dst >= 0
+    src = np.flatnonzero(gone)[np.argsort(dst[gone], kind="stable")].astype(np.int32)
+    new_index = np.where(gone, -1, np.cumsum(~gone) - 1).astype(np.int32)
+    off = np.concatenate([[0], np.cumsum(np.bincount(dst[gone], minlength=n))]).astype(np.int32)
+    out, h = int((~gone).sum()), np.array([0, n], dtype=np.int32)
+    p = L.Problem(batch=1, d=d, heads=d // 32, head_dim=32, dtype=dtype, h_cu_vis=h, cu_vis=torch.from_numpy(h).cuda())
+    new_index, off, src = (torch.from_numpy(a).cuda() for a in (new_index, off, src))
+    xi, pos = torch.rand(n, generator=g, device="cuda") + 0.1, torch.arange(n + tail, dtype=torch.int32, device="cuda")
+    cu_out = torch.tensor([0, out], dtype=torch.int32, device="cuda")
+    kw = dict(tail_rows=tail, cu_vis_out=cu_out)
+    rows = torch.cat([torch.from_numpy(np.flatnonzero(~gone)).cuda(), torch.arange(n, n + tail, device="cuda")])
+
+    def fresh():
+        return [torch.full((out + tail, d), 7.0, dtype=tdt, device="cuda") for _ in range(3)] + [torch.empty(out + tail, dtype=torch.int32, device="cuda")]
+    a = fresh()
+    L.lightkv_compact(p, new_index, X, K, V, pos, *a, **kw)
+    for got, y in zip(a, (X, K, V, pos)):
+        assert torch.equal(got, y[rows])
+    b, c = fresh(), fresh()
+    L.lightkv_aggregate_compact(p, new_index, off, src, xi, X, K, V, pos, *b, **kw)
+    m = [t.clone() for t in (X, K, V)]
+    L.lightkv_aggregate(p, off, src, xi, *m)
+    L.lightkv_compact(p, new_index, *m, pos, *c, **kw)
+    for x, y in zip(b, c):
+        assert torch.equal(x, y)
 
 
 @pytest.mark.parametrize("batch,gh,gw,w,d", [
