@@ -389,11 +389,6 @@ bool lk::windows_ride(const lightkv_problem *p, const WinSpec &next) {
   return make_win_args(next, p->cu_vis, nullptr, nullptr, nullptr, p->batch, max_seq, &unused) > 0;
 }
 
-bool lk::tiled_divergence(const lightkv_problem *p) {
-  Checked c;
-  return check_problem(p, true, false, c) == LIGHTKV_OK && !full_pairwise(p) && use_big_fd(p, c);
-}
-
 int lk::least_workspace(const lightkv_problem *p, size_t *bytes) {
   size_t total = 0;
   return workspace_sizes(p, bytes, &total);

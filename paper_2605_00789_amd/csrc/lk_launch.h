@@ -72,10 +72,8 @@ size_t make_win_args(const WinSpec &spec, const int32_t *cu_vis, const int32_t *
 // Windows + their counts (lk_api.hip), and the fused merge with the next stage's windows beside it; a lightkv_status
 int build_windows_with_counts(int32_t batch, const int32_t *h_cu_vis, const int32_t *cu_vis, const int32_t *pos,
                               const int32_t *new_index, const int32_t *cu_vis_out, const WinSpec &spec, void *stream);
-// Whether the windows of the stage behind p fit into the launch of p's merge, and whether a stage's divergence runs on the tiled
-// kernel of large windows (both false for descriptors that the calls refuse).
+// Whether the windows of the stage behind p fit into the launch of p's merge (false for descriptors that the calls refuse).
 bool windows_ride(const lightkv_problem *p, const WinSpec &next);
-bool tiled_divergence(const lightkv_problem *p);
 int aggregate_compact_with_windows(const lightkv_problem *p, const int32_t *new_index, const int32_t *grp_offsets,
                                    const int32_t *grp_src, const float *xi, const void *X, int64_t ldx, const void *K,
                                    int64_t ldk, const void *V, int64_t ldv, const int32_t *pos, void *X_out, void *K_out,

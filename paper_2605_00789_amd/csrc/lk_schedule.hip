@@ -3,7 +3,7 @@
 //   - xi (needs only Q and the stage's K rows) runs next to the feature-divergence chain and the selection: in the same
 //     launches where lightkv_score_select can do that, on a helper stream otherwise,
 //   - the next stage's windows (need only pos and the selection) are built by workgroups of the merge's launch, or beside
-//     the merge on a second helper stream (RideOrFork below).
+//     the merge on a second helper stream (NextWindows below).
 // Nothing here launches a kernel itself or allocates device memory.  lightkv_compress_schedule never synchronises;
 // lightkv_compress_schedule_ratio (token counts that depend on the data) waits once per stage for the sequence offsets the
 // stage leaves, and for the stream before it returns.
@@ -170,14 +170,14 @@ extern "C" lightkv_status lightkv_compress_schedule(const lightkv_stage *stages,
                                   st.cu_vis_out, ws, ws_bytes, main);
     }
     // ---- the next stage's windows follow from pos and the selection alone (cu_vis_out of this stage is the next stage's
-    // cu_vis).  They ride in the merge's launch if they fit there, unless the next stage forks xi for the tiled FD kernel: a
-    // workgroup of that kernel fills a CU, and xi has to be there before it -- the two forks then start the two chains together
-    // (three eager stages of 8192 tokens, d = 4096: 497 us, riding 556).
+    // cu_vis).  They ride in the merge's launch if they fit there: a queue crossing costs more than they add to it (three eager
+    // stages of 2880 tokens, d = 1024, 158 us riding, 182 forked; of 8192, d = 4096, 468 and 494; of 16384, d = 1024, 516 and
+    // 457: the other way round where the partition outlives the rows).
     lk::WinSpec next{};
     bool ride = false;
     if (rc == LIGHTKV_OK && s + 1 < n_stages) {
       next = windows_of(stages[s + 1], tiles, grid_h, grid_w, stages[s + 1].cu_vis_target ? LIGHTKV_COUNT_TARGET : -1, 0.0);
-      ride = next_windows.enqueue(helpers, lk::windows_ride(p, next) && !lk::tiled_divergence(&stages[s + 1].problem), p, posi, st, next, rc);
+      ride = next_windows.enqueue(helpers, lk::windows_ride(p, next), p, posi, st, next, rc);
     }
     // ---- join xi (whatever happened: nothing stays forked), merge and compact
     if (xi_forked && hipStreamWaitEvent(main, helpers.h->event[EV_JOIN_XI], 0) != hipSuccess) rc = rc == LIGHTKV_OK ? LIGHTKV_ERR_LAUNCH : rc;

@@ -6,13 +6,16 @@
 // consecutive tokens counts its tokens per window with ballots; a prefix over the runs and a scan
 // over the windows give each token its slot directly -- no sort, no atomics, order preserved.
 // Fallback: LDS bitonic sort of (window id, local index) keys.
+#include <atomic>
 #include "lk_win_body.h"
 
 namespace lk {
 
 constexpr int WIN_THREADS = 1024;
 constexpr int LOCAL_BITS = 14;             // local token index < 16384
-constexpr size_t WIN_TABLE_LDS_MAX = 56 * 1024;   // bytes of LDS the (run, window) count table may take
+// Bytes of LDS the partition may take: all that a workgroup can have, as sorting 16384 tokens takes 127 us and counting them
+// into 256 windows 35.
+constexpr size_t WIN_TABLE_LDS_MAX = 152 * 1024;
 constexpr int WIN_KEEP = 4;                // passes of 1024 tokens whose window and rank stay in registers between phases
 
 __global__ __launch_bounds__(WIN_THREADS) void build_windows_table_kernel(WinArgs g) {
@@ -112,11 +115,25 @@ static WinArgs win_args(const WinSpec &spec, const int32_t *cu_vis, const int32_
   return g;
 }
 
+// more dynamic LDS than the 64 KB default, set once per device
+static hipError_t allow_table_lds() {
+  static std::atomic<bool> done[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  if (done[dev].load(std::memory_order_acquire)) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(build_windows_table_kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)WIN_TABLE_LDS_MAX);
+  if (e == hipSuccess) done[dev].store(true, std::memory_order_release);
+  return e;
+}
+
 hipError_t launch_build_windows(const WinSpec &spec, const int32_t *cu_vis, const int32_t *pos, const int32_t *new_index,
                                 const int32_t *cu_out, int batch, int max_seq, bool *counts_done, hipStream_t stream) {
   WinArgs g = win_args(spec, cu_vis, pos, new_index, cu_out, batch);
   const size_t lds = win_table_bytes(max_seq, g.win_per_seq);
   if (lds <= WIN_TABLE_LDS_MAX) {
+    const hipError_t e = allow_table_lds();
+    if (e != hipSuccess) return e;
     *counts_done = spec.count_mode >= 0;
     hipLaunchKernelGGL(build_windows_table_kernel, dim3(batch), dim3(WIN_THREADS), lds, stream, g);
   } else {

@@ -501,7 +501,7 @@ def test_token_budgets_over_many_windows(W, kind):
         np.testing.assert_array_equal(got[b], want)
 
 
-@pytest.mark.parametrize("tiles,gh,gw,w", [(1, 8, 8, 90), (1, 3, 5, 9), (2, 7, 11, 8), (1, 1, 129, 5), (1, 97, 89, 8), (1, 128, 128, 4)])
+@pytest.mark.parametrize("tiles,gh,gw,w", [(1, 8, 8, 90), (1, 3, 5, 9), (2, 7, 11, 8), (1, 1, 129, 5), (1, 97, 89, 8), (1, 128, 128, 4), (1, 128, 128, 16)])
 def test_window_partition_with_scattered_cells(tiles, gh, gw, w):
     """Tokens in any order, cells missing and repeated, more windows than tokens; grids whose sides are no powers of two."""
     import paper_2605_00789_amd as L
@@ -523,8 +523,8 @@ SCHEDULES = [
     # tokens beyond those whose window and rank the riding partition keeps in registers; a batch with windows of unequal sizes
     (1, 56, 58, (8, 4, 2), (2700, 2200, 1800), 2, 64), (2, 61, 67, (5, 3, 2), (3500, 3000, 2500), 1, 64),
     (1, 80, 80, (8, 16, 8), (5500, 4700, 4000), 2, 32),      # 256 windows: the counts do not fit beside the rows
-    (1, 80, 80, (8, 24, 20), (5500, 4700, 4000), 2, 32),     # 576 windows: nor the partition's own LDS (sorted)
-    (1, 64, 64, (4, 2, 1), (3300, 2700, 2200), 8, 32),       # the tiled divergence: windows beside the merge on a stream
+    (1, 80, 80, (8, 30, 28), (5500, 4700, 4000), 2, 32),     # 900 windows: nor the partition's own LDS (sorted)
+    (1, 64, 64, (4, 2, 1), (3300, 2700, 2200), 8, 32),       # the tiled divergence, where xi forks as well
 ]
 
 
