@@ -123,7 +123,8 @@ struct WsLayout {
   size_t least = 0, total = 0;
 };
 
-constexpr int EDGE_FUSED_MAX = 1024;   // windows, and 32 x 32 tiles, of a step (see fused_launches)
+constexpr int EDGE_FUSED_MAX = 1024;      // windows, and 32 x 32 tiles, of a step (see fused_launches)
+constexpr int EDGE_FUSED_MAX_XI = 4096;   // tiles of its xi
 bool edge_topk(const lightkv_problem *p) { return p->match == LIGHTKV_MATCH_EDGE_TOPK; }
 bool full_pairwise(const lightkv_problem *p) { return p->match == LIGHTKV_MATCH_FULL_PAIRWISE; }
 // ints of scratch for the edge list (A token, B token, position among the B token's sources)
@@ -160,13 +161,17 @@ FdPlan small_tile_plan(const lightkv_problem *p, const Checked &c) {
 
 // lightkv_score_select, both halves requested: the k-th kernels of the two chains share launches on the caller's stream.
 // Not for the tiled FD kernel (one workgroup of it fills a CU's LDS) and not for batches whose xi is one workgroup per
-// (sequence, head) pair; there the chains run on two streams.  Nor for the k lowest edges of many windows or tiles: the column
-// sums get two waves per SIMD beside that selection, and a step of that size no longer waits for launches.  us a replayed
-// call, eight heads of 128, windows of 36 tokens, shared / forked: 31 x 576 tokens with prompts of 64 57 / 62, 64 x 576 with
-// prompts of 300 157 / 131.
+// (sequence, head) pair; there the chains run on two streams.  Nor for the k lowest edges of many windows or tiles beside a long
+// xi: the column sums get two waves per SIMD in that launch, and a step of that size no longer waits for launches.  us a
+// call, 64 x 576 tokens in windows of 36, shared / forked: eight heads of 128 and prompts of 300 157 / 136, of 64 with an lse
+// 76 / 65; three heads and prompts of 64 66 / 70.  With an lse xi is one pass, and beside windows of more than 128 tokens it
+// stays the shorter half: windows of 144 87 / 99, 7 x 2880 tokens in windows of 240 133 / 147.
 bool fused_launches(const lightkv_problem *p, const Checked &c, const FdPlan &fd, const XiPlan &xp, int xi_mode, const float *lse) {
   if (p->n_windows == 0 || c.sum_n == 0 || fd.n_tiles == 0 || xp.max_vis_blocks == 0) return false;
-  if (edge_topk(p) && (fd.n_tiles >= EDGE_FUSED_MAX || p->n_windows >= EDGE_FUSED_MAX)) return false;
+  if (edge_topk(p) && (fd.n_tiles >= EDGE_FUSED_MAX || p->n_windows >= EDGE_FUSED_MAX) && !(lse && c.max_window > 128)) {
+    const int64_t xi_tiles = (int64_t)p->batch * p->heads * xp.max_vis_blocks * xp.max_text_tiles;   // 128 vision x 32 prompt tokens
+    if (xi_tiles >= EDGE_FUSED_MAX_XI) return false;
+  }
   return (full_pairwise(p) || !use_big_fd(p, c)) && !xi_seq_applies(xp, xi_mode, lse, p->batch, p->heads);
 }
 

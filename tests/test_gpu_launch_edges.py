@@ -377,19 +377,21 @@ def test_full_pairwise_without_room_for_the_small_tiles(gh, gw, w):
     assert len(out) == 2 and 0 < int(out[-1].h_cu_vis_out[1]) < int(out[0].h_cu_vis_out[1]) < n
 
 
-@pytest.mark.parametrize("batch,n,v,k", [(1, 576, 36, 17), (8, 576, 36, 16), (8, 576, 36, 17), (29, 565, 37, 4), (29, 566, 37, 4), (29, 565, 16, 3)])
+@pytest.mark.parametrize("batch,n,v,k,T", [(1, 576, 36, 17, 3), (8, 576, 36, 16, 3), (8, 576, 36, 17, 3), (29, 565, 37, 4, 3),
+                                           (29, 566, 37, 4, 3), (29, 565, 16, 3, 3), (29, 565, 16, 3, 1000)])
 @pytest.mark.parametrize("with_xi", [False, True])
-def test_edge_lists_placed_by_the_scan_and_by_a_launch_of_their_own(batch, n, v, k, with_xi):
+def test_edge_lists_placed_by_the_scan_and_by_a_launch_of_their_own(batch, n, v, k, T, with_xi):
     """Counts known to the host (the list gets a launch of its own beyond 2048 edges) and to the device alone (beyond 16384
-    tokens): lists of 272, 2048, 2176 edges and of 16385 and 16414 tokens; 1044 windows, where xi has a stream of its own.  The same bits either way, and the sources of
+    tokens): lists of 272, 2048, 2176 edges and of 16385 and 16414 tokens; 1044 windows with short prompts and (T) with ones of 1000, where xi
+    has a stream of its own.  The same bits either way, and the sources of
     every token are the edges that the tokens' own columns say."""
     import paper_2605_00789_amd as L
     from paper_2605_00789_amd import binding as B
     N, d = batch * n, 64
     g = torch.Generator(device="cuda").manual_seed(N)
     X, K = (torch.randn(N, d, generator=g, device="cuda").bfloat16() for _ in range(2))
-    Q = torch.randn(3 * batch, d, generator=g, device="cuda").bfloat16()
-    h, ht = (np.arange(batch + 1) * n).astype(np.int32), (np.arange(batch + 1) * 3).astype(np.int32)
+    Q = torch.randn(T * batch, d, generator=g, device="cuda").bfloat16()
+    h, ht = (np.arange(batch + 1) * n).astype(np.int32), (np.arange(batch + 1) * T).astype(np.int32)
     wo = np.unique(np.concatenate([np.append(np.arange(b * n, (b + 1) * n, v), (b + 1) * n) for b in range(batch)])).astype(np.int32)
     sizes = np.diff(wo)
     rem = np.minimum(k, (sizes + 1) // 2 * (sizes // 2)).astype(np.int32)
