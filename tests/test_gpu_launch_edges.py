@@ -596,3 +596,110 @@ def test_ratio_schedule_builds_windows_in_every_place(shape, match):
             np.testing.assert_array_equal(x, y)
         else:
             assert torch.equal(x, y)
+
+
+def _ratio_job(seed, match, batch=1, gh=24, gw=24, windows=(4, 2, 1), d=256, heads=4):
+    import paper_2605_00789_amd as L
+    n, t = gh * gw, 7
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    X, K, V = (torch.randn(batch * n, d, generator=g, device="cuda").bfloat16() for _ in range(3))
+    Q = torch.randn(batch * t, d, generator=g, device="cuda").bfloat16()
+    pos = torch.arange(n, dtype=torch.int32, device="cuda").repeat(batch)
+    h = (np.arange(batch + 1) * n).astype(np.int32)
+
+    def make():
+        return L.EdgeTopKSchedule(dtype="bf16", batch=batch, d=d, heads=heads, head_dim=d // heads, tiles=1, grid_h=gh, grid_w=gw,
+                                  cu_txt=(np.arange(batch + 1) * t).astype(np.int32), windows_per_axis=windows,
+                                  rho=[0.25] * len(windows), match=match)
+    return make, (h, X, K, V, Q, pos)
+
+
+def _ratio_result(out):
+    return [r.h_cu_vis_out.copy() for r in out] + [t.cpu().numpy() if t.dtype == torch.int32 else t.float().cpu().numpy()
+                                                   for t in (out[-1].X, out[-1].K, out[-1].V, out[-1].pos)]
+
+
+def test_ratio_schedules_of_several_threads_at_once():
+    """Six host threads, more than there are mailboxes for the offsets of a stage, run data-dependent schedules of different
+    matchings and sizes on streams and buffers of their own, again and again: the bits of a run alone, every time."""
+    import threading
+    jobs = []
+    for i, match in enumerate(["edge_topk", "best_per_a", "full_pairwise", "edge_topk", "best_per_a", "full_pairwise"]):
+        make, args = _ratio_job(i, match, batch=1 + i % 3, gh=12 + 4 * (i % 4), windows=(4, 2, 1) if i % 2 else (3, 1))
+        s = make()
+        want = _ratio_result(s.run(*args))
+        jobs.append((s, args, want))
+    torch.cuda.synchronize()
+    errors, start = [], threading.Barrier(len(jobs))
+
+    def work(k):
+        try:
+            s, args, want = jobs[k]
+            stream = torch.cuda.Stream()
+            start.wait(timeout=60)
+            with torch.cuda.stream(stream):
+                for it in range(25):
+                    for j, (a, b) in enumerate(zip(_ratio_result(s.run(*args)), want)):
+                        if not np.array_equal(a, b):
+                            errors.append((k, it, j))
+        except Exception as e:   # noqa: BLE001
+            errors.append(repr(e))
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(jobs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(timeout=100)
+    assert not any(t.is_alive() for t in threads)
+    assert not errors, errors[:5]
+
+
+@pytest.mark.parametrize("batch", [1022, 1023, 1024, 1100])
+@pytest.mark.parametrize("match", ["edge_topk", "best_per_a"])
+def test_ratio_schedule_of_more_sequences_than_a_mailbox_holds(batch, match):
+    """Up to 1023 sequences the offsets come through the mailbox, beyond that by a copy: against the stages call by call."""
+    make, args = _ratio_job(batch, match, batch=batch, gh=2, gw=3, windows=(1, 1), d=64, heads=2)
+    want = _ratio_result(make().run_steps(*args))
+    s = make()
+    for _ in range(3):
+        for a, b in zip(_ratio_result(s.run(*args)), want):
+            np.testing.assert_array_equal(a, b)
+
+
+def test_ratio_schedule_beside_an_open_capture():
+    """The first ratio-driven call of a process, which allocates its mailbox, on one thread while another has a capture open: the
+    right result, and the capture ends and replays."""
+    import os
+    import subprocess
+    import sys
+    code = r"""
+import sys, threading
+sys.path.insert(0, '.'); sys.path.insert(0, 'tests')
+import numpy as np, torch
+from test_gpu_launch_edges import _ratio_job, _ratio_result
+make, args = _ratio_job(3, 'edge_topk')
+s, ref = make(), make()
+a, b = torch.ones(1000, device='cuda'), torch.zeros(1000, device='cuda')
+torch.cuda.synchronize()
+got, errors = [], []
+def other():
+    try:
+        with torch.cuda.stream(torch.cuda.Stream()):
+            got.append(_ratio_result(s.run(*args)))
+    except Exception as e:
+        errors.append(repr(e))
+graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+with torch.cuda.graph(graph, stream=stream, capture_error_mode='thread_local'):
+    b.add_(a)
+    t = threading.Thread(target=other); t.start(); t.join(timeout=60)
+    b.add_(a)
+assert not errors and len(got) == 1, errors
+for _ in range(3): graph.replay()
+torch.cuda.synchronize()
+assert float(b.min()) == 6.0 == float(b.max())
+for x, y in zip(got[0], _ratio_result(ref.run_steps(*args))): np.testing.assert_array_equal(x, y)
+print('beside-capture ok', flush=True)
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-u", "-c", code], cwd=root, capture_output=True, text=True, timeout=100)
+    print(r.stdout[-2000:], r.stderr[-3000:], flush=True)
+    assert r.returncode == 0 and "beside-capture ok" in r.stdout

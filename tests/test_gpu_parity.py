@@ -695,20 +695,33 @@ def test_graph_replay_equals_eager_in_the_benchmark_launch_configuration():
             assert junk.item() == junk.item()
 
 
+def _forking_workload(kind):
+    """Steps whose halves cannot share launches, so that the library forks xi onto a helper stream, in lightkv_score with both
+    halves as in the schedule: "global" -- one window of 2880 tokens on the tiled divergence; "pairs" -- 16 sequences x 16 heads
+    = 256 (sequence, head) pairs, one workgroup each."""
+    from workloads import make_custom, make_workload
+    if kind == "global":
+        return make_workload("global")
+    return make_custom(name="pairs", seed=77, dtype="bf16", batch=16, grid_h=12, grid_w=12, text_lens=tuple(range(10, 170, 10)), d=512, heads=16,
+                       head_dim=32, n_c=20, structure="grid", windows_per_axis=(3, 2), n_final=90)
+
+
 def test_first_call_of_a_process_under_stream_capture():
     """A process whose very first library call is captured into a graph: the helper streams cannot be created then, so
-    the schedule is captured in stream order -- it must still replay to the results of an eager run.  Runs in a child
-    process (the helper streams of this one exist already)."""
+    the schedule is captured in stream order -- it must still replay to the results of an eager run, which makes and uses the
+    helper streams for the workloads that fork.  Runs in a child process (the helper streams of this one exist already)."""
     import subprocess
     import sys
     code = r"""
 import sys
 sys.path.insert(0, '.')
 import numpy as np, torch
+sys.path.insert(0, 'tests')
 from workloads import make_workload
+from test_gpu_parity import _forking_workload
 from paper_2605_00789_amd import CompressionPipeline, to_device as to_dev
-for cfg in (2, 3):
-    wl = make_workload(cfg)
+for cfg in sys.argv[1].split(','):
+    wl = _forking_workload(cfg) if cfg in ('pairs', 'global') else make_workload(int(cfg))
     pipe = CompressionPipeline(dtype=wl.dtype, batch=wl.batch, d=wl.d, heads=wl.heads, head_dim=wl.head_dim,
                                tiles=wl.tiles, grid_h=wl.grid_h, grid_w=wl.grid_w, cu_txt=wl.cu_txt,
                                windows_per_axis=wl.windows_per_axis, targets=wl.targets)
@@ -718,7 +731,7 @@ for cfg in (2, 3):
     names = ("X_out", "K_out", "V_out", "pos_out", "xi", "dst", "new_index", "grp_offsets", "cu_vis_out")
     with torch.cuda.stream(stream):
         graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(graph, stream=stream):      # no call of the library before this one (config 2)
+        with torch.cuda.graph(graph, stream=stream):      # no call of the library before the first of these
             pipe.run(X, K, V, Q, pos)
         graph.replay()
         stream.synchronize()
@@ -739,15 +752,17 @@ for cfg in (2, 3):
 """
     import os
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-    r = subprocess.run([sys.executable, "-u", "-c", code], cwd=root, capture_output=True, text=True, timeout=280)
-    print(r.stdout[-2000:], r.stderr[-3000:], flush=True)
-    assert r.returncode == 0 and "capture-first ok 3" in r.stdout
+    for order in ("2,3,pairs,global", "global,pairs"):   # the first call: one that never forks, one that would
+        r = subprocess.run([sys.executable, "-u", "-c", code, order], cwd=root, capture_output=True, text=True, timeout=280)
+        print(r.stdout[-2000:], r.stderr[-3000:], flush=True)
+        assert r.returncode == 0 and "capture-first ok " + order.split(",")[-1] in r.stdout
 
 
 def test_host_threads_share_the_helper_streams():
-    """Two host threads run schedules on their own streams, buffers and workspaces at the same time.  The library's
-    helper streams and events are per device, so the threads take turns enqueueing; each must get the results of a
-    run on its own, bit for bit (lightkv_compress_schedule, and lightkv_score with both halves in one call)."""
+    """Five host threads run schedules on their own streams, buffers and workspaces at the same time.  The library's
+    helper streams and events are per device, so threads whose steps fork ("global", "pairs") take turns enqueueing; each must
+    get the results of a run on its own, bit for bit (lightkv_compress_schedule, and lightkv_score with both halves in one
+    call)."""
     import threading
     from workloads import make_workload
     from parity import to_dev
@@ -755,8 +770,8 @@ def test_host_threads_share_the_helper_streams():
     from paper_2605_00789_amd import binding as B
     names = ("X_out", "K_out", "V_out", "pos_out", "xi", "dst", "new_index", "grp_offsets", "cu_vis_out", "best_fd")
     jobs = []
-    for cfg in (2, "halving", 3):
-        wl = make_workload(cfg)
+    for cfg in (2, "halving", 3, "global", "pairs"):
+        wl = _forking_workload(cfg) if cfg in ("global", "pairs") else make_workload(cfg)
         pipe = CompressionPipeline(dtype=wl.dtype, batch=wl.batch, d=wl.d, heads=wl.heads, head_dim=wl.head_dim,
                                    tiles=wl.tiles, grid_h=wl.grid_h, grid_w=wl.grid_w, cu_txt=wl.cu_txt,
                                    windows_per_axis=wl.windows_per_axis, targets=wl.targets)
@@ -767,7 +782,7 @@ def test_host_threads_share_the_helper_streams():
         want = [[getattr(st, n).clone() for n in names] for st in pipe.stages]
         st0 = pipe.stages[0]
         xi0, fd0, bd0 = (torch.empty_like(t) for t in (st0.xi, st0.best_fd, st0.best_dst))
-        B.lightkv_score(st0.problem, X, Q, K, xi0, fd0, bd0, pipe.ws)     # both halves: the library forks inside
+        B.lightkv_score(st0.problem, X, Q, K, xi0, fd0, bd0, pipe.ws)     # both halves: forks inside for the last two
         torch.cuda.synchronize()
         jobs.append(dict(pipe=pipe, args=(X, K, V, Q, pos), want=want, score=(xi0.clone(), fd0.clone(), bd0.clone())))
     errors = []
@@ -1045,7 +1060,8 @@ def test_uneven_windows_still_hit_the_stage_targets():
     assert [r.n_out for r in reps] == wl.targets
 
 
-def test_an_open_capture_does_not_block_other_callers():
+@pytest.mark.parametrize("pair", [(3, "halving"), ("global", "pairs"), ("pairs", "global")])
+def test_an_open_capture_does_not_block_other_callers(pair):
     """While one host thread has a stream capture open that contains a schedule (helper streams forked into the
     capture), another thread runs a schedule eagerly on its own stream: it must get a helper set of its own and the
     right results, and the capture must end and replay correctly afterwards."""
@@ -1055,8 +1071,8 @@ def test_an_open_capture_does_not_block_other_callers():
     from paper_2605_00789_amd import CompressionPipeline
     names = ("X_out", "K_out", "V_out", "pos_out", "xi", "dst", "new_index", "grp_offsets", "cu_vis_out", "win_remove")
     jobs = []
-    for cfg in (3, "halving"):
-        wl = make_workload(cfg)
+    for cfg in pair:
+        wl = _forking_workload(cfg) if cfg in ("global", "pairs") else make_workload(cfg)
         pipe = CompressionPipeline(dtype=wl.dtype, batch=wl.batch, d=wl.d, heads=wl.heads, head_dim=wl.head_dim,
                                    tiles=wl.tiles, grid_h=wl.grid_h, grid_w=wl.grid_w, cu_txt=wl.cu_txt,
                                    windows_per_axis=wl.windows_per_axis, targets=wl.targets)
