@@ -22,16 +22,18 @@
  *     memory and frees none.  Scratch comes from the caller's workspace `ws` (size
  *     from lightkv_workspace_size, 256-byte aligned); lightkv_select_static uses a
  *     static device array instead.
- *   - state the library keeps between calls (per device, host-side handles only,
- *     created on first use outside stream capture, default priority, never
- *     destroyed): one helper stream with two events for lightkv_score, another such
- *     set for lightkv_compress_schedule, and the "large LDS" attribute of some
- *     kernels.  Calls whose `stream` is being captured never
- *     touch the helper streams: they enqueue everything on `stream` in order, so
- *     a capture only ever contains the caller's stream.
+ *   - state the library keeps between calls (per device, made on first need and
+ *     never destroyed): pools of up to four sets of helper streams and events,
+ *     default priority, made outside stream capture only -- a stream with two events
+ *     for lightkv_score, two streams with four for the schedules --; up to four
+ *     blocks of 8 KB of pinned, device-visible host memory for
+ *     lightkv_compress_schedule_ratio; and the "large LDS" attribute of some kernels.
+ *     A call whose `stream` is being captured forks into the capture where a set is
+ *     there already (the graph then has parallel branches) and otherwise enqueues
+ *     everything on `stream` in order.
  *   - all work is enqueued on `stream` (a hipStream_t passed as void*, NULL = the
  *     default stream) or on helper streams that fork from and rejoin it before the
- *     call returns; no call synchronises or reads device memory on the host, with
+ *     call returns; no call synchronises or reads device results on the host, with
  *     one exception that says so: lightkv_compress_schedule_ratio.
  *   - tensors are token-major: row i holds the `d` contiguous elements of token i;
  *     `ld*` are row strides in elements.  Sequences of a batch are packed one after
@@ -136,9 +138,9 @@ typedef enum {
 #define LIGHTKV_EDGE_MAX_WINDOW_TOKENS 4096 /* tokens in one window with LIGHTKV_MATCH_EDGE_TOPK; windows bounded by more than
                                                256 tokens are ranked through a matrix of all their FD values in the workspace */
 #define LIGHTKV_SELECT_STATIC_MAX_TOKENS 65536  /* vision tokens of a batch in lightkv_select_static */
-/* Steps of at most this many vision tokens whose windows hold at most 64 tokens are three launches on the caller's stream
-   when lightkv_score_select is asked for xi as well.  (The call shares launches between the two chains on larger steps,
-   too; the constant is for callers that arrange the single calls over streams of their own.) */
+/* For callers that arrange the single calls over streams of their own: steps of at most this many vision tokens whose windows
+   hold at most 64 tokens are better left to one lightkv_score_select that computes xi as well.  The library itself does not
+   look at it (see lightkv_score_select for what shares launches). */
 #define LIGHTKV_ONE_STREAM_MAX_TOKENS 1024
 
 /*
@@ -272,7 +274,8 @@ lightkv_status lightkv_window_counts(int32_t batch, int32_t n_windows, const int
  *   The two halves are independent and may be enqueued by two calls, e.g. on two streams with the same workspace:
  *   X == NULL computes xi only (windows, best_fd, best_dst are not touched), xi_mode GIVEN computes the FD half only.
  *   When both halves are requested in one call they share launches on `stream`; on the tiled path of large windows, for
- *   batches with one workgroup per (sequence, head) pair and with fd_dump, xi runs on an internal helper stream that
+ *   batches with one workgroup per (sequence, head) pair, for LIGHTKV_MATCH_EDGE_TOPK on many windows beside a long xi, and
+ *   with fd_dump, xi runs on an internal helper stream that
  *   forks from and joins `stream` (created per device on the first such call outside stream capture; host threads that
  *   make such calls on one device take turns enqueueing).
  */
@@ -315,8 +318,9 @@ lightkv_status lightkv_select_static(const lightkv_problem *p, const float *best
  * lightkv_score followed by lightkv_select in one call: same arguments, same outputs (bit for bit).  When every
  * window holds at most 64 tokens, the row arg-min and the per-window selection run in one kernel (one launch less);
  * if xi is computed as well, the xi passes share the launches of the FD kernels and the whole call runs on `stream`
- * (three launches, or four to five with larger windows; no helper stream), except on the tiled path of large windows and
- * for batches of 256 or more (sequence, head) pairs with prompts of at most 256 tokens.  Otherwise the call
+ * (three launches, or four to five with larger windows; no helper stream), except on the tiled path of large windows,
+ * for batches of 256 or more (sequence, head) pairs with prompts of at most 256 tokens, and for LIGHTKV_MATCH_EDGE_TOPK on
+ * 1024 or more windows (or 32 x 32 tiles of their pairs) beside a long xi.  Otherwise the call
  * is the two calls in sequence.  X must not be NULL; xi_mode GIVEN skips the xi half as in lightkv_score.
  *
  * With p->match == LIGHTKV_MATCH_EDGE_TOPK (this call only; lightkv_select alone returns LIGHTKV_ERR_UNSUPPORTED,
@@ -427,10 +431,11 @@ typedef struct lightkv_stage {
  *   Q[sumT, heads, head_dim] (prompt queries, TEXT_QUERY) is the same for all stages; xi of stage s is computed
  *   against the K rows that stage merges.  softmax_scale as in lightkv_score.
  * Per stage the call enqueues what the single calls would -- lightkv_build_windows (stage 0; later stages' windows are
- * built by workgroups of the previous stage's merge launch), lightkv_score_select with xi, lightkv_aggregate_compact --
- * with the same results, bit for bit.  Stages whose lightkv_score_select would fork (see there) run xi on one internal
- * helper stream beside the feature divergence and the selection; it forks from and joins `stream` (created per device on
- * the first such call outside stream capture, default priority, kept for the life of the process; if it cannot be made, or
+ * built by workgroups of the previous stage's merge launch, or beside it where they do not fit), lightkv_score_select with
+ * xi, lightkv_aggregate_compact -- with the same results, bit for bit.  Stages whose lightkv_score_select would fork (see
+ * there) run xi on an internal helper stream beside the feature divergence and the selection, windows that do not fit the
+ * merge's launch are built on a second one; they fork from and join `stream` (created per device on
+ * the first such call outside stream capture, default priority, kept for the life of the process; if they cannot be made, or
  * the first call on a device comes under capture, everything is enqueued on `stream` in order).
  * One workspace serves all stages: ws_bytes must cover lightkv_workspace_size of every
  * stage.  Host threads calling this on one device take turns enqueueing.  Only LIGHTKV_MATCH_BEST_PER_A (fixed token
@@ -452,9 +457,12 @@ lightkv_status lightkv_compress_schedule(const lightkv_stage *stages, int32_t n_
  * (lightkv_window_counts: LIGHTKV_COUNT_EDGES for EDGE_TOPK, LIGHTKV_COUNT_RATIO otherwise) and consumed there.
  * Per stage the call enqueues lightkv_build_windows + lightkv_window_counts (stage 0; later stages' windows and counts
  * are built beside the previous stage's merge, as in lightkv_compress_schedule), lightkv_score_select (xi from Q and the stage's K rows, TEXT_QUERY) and
- * lightkv_aggregate_compact -- with the same results as those calls, bit for bit -- then copies the stage's cu_vis_out
- * to h_cu_vis_out[s * (batch+1) ...] (host, [n_stages * (batch+1)], out) and WAITS for `stream`: the next stage's launch
- * plans need those offsets.  One synchronisation per stage; the call cannot be captured into a graph (a capturing
+ * lightkv_aggregate_compact -- with the same results as those calls, bit for bit.  The next stage's launch plans need the
+ * sequence offsets the stage leaves: as the merge starts, its launch writes them to pinned host memory, where the calling thread
+ * waits for them (it polls, a core is busy meanwhile), puts them into h_cu_vis_out[s * (batch+1) ...] (host,
+ * [n_stages * (batch+1)], out) and enqueues the next stage while the rows still move.  More than 1023 sequences, or more
+ * calls at once on a device than there are blocks of such memory: a copy and a synchronisation per stage instead.  The call
+ * synchronises `stream` once, at its end, also when it returns an error; it cannot be captured into a graph (a capturing
  * stream -> LIGHTKV_ERR_UNSUPPORTED, nothing enqueued).  When it returns LIGHTKV_OK every stage has finished.
  * Of the descriptors: stages[0].problem carries the input's h_cu_vis / cu_vis; for s > 0 those two fields are ignored
  * (the library uses what stage s-1 left).  problem.max_window_tokens is required for every stage (a bound from the cell

@@ -341,8 +341,8 @@ def lightkv_compress_schedule(stages: StageArray, tiles, grid_h, grid_w, X, K, V
 
 def lightkv_compress_schedule_ratio(stages: StageArray, rho, tiles, grid_h, grid_w, X, K, V, pos, Q, ws, *,
                                     softmax_scale=0.0, stream=None) -> np.ndarray:
-    """All stages of a schedule whose token counts depend on the data, in one call (it waits for the stream once per
-    stage).  rho: one ratio per stage.  Returns the [n_stages, batch + 1] sequence offsets the stages left (host)."""
+    """All stages of a schedule whose token counts depend on the data, in one call (it waits for the offsets every stage
+    leaves, and for the stream at its end).  rho: one ratio per stage.  Returns the [n_stages, batch + 1] sequence offsets the stages left (host)."""
     prob = stages.keep[0]["problem"].c
     if len(rho) != stages.n:
         raise ValueError("one ratio per stage")

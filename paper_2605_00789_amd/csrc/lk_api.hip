@@ -1,5 +1,5 @@
 // C ABI of the LightKV compression step: argument validation, workspace layout, launches.
-// Nothing here allocates, synchronises or reads device memory.
+// Nothing here allocates device memory, synchronises or reads results on the host.
 #include "../../include/lightkv.h"
 #include "lk_launch.h"
 #include "lk_helpers.h"
@@ -109,10 +109,10 @@ lightkv_status check_problem(const lightkv_problem *p, bool need_windows, bool n
   return LIGHTKV_OK;
 }
 
-// The two halves of lightkv_score (xi from Q/K, FD from X) share no data, so they are enqueued as a fork/join:
-// xi on a helper stream, FD on the caller's stream, joined by events before the call returns.  Under stream capture
-// the fork/join becomes two parallel branches of the graph.  Helper sets come from a per-device pool (lk_helpers.h);
-// without one the work runs serially on the caller's stream.
+// The two halves of lightkv_score (xi from Q/K, FD from X) share no data.  Where they cannot share launches (fused_launches
+// below) they are enqueued as a fork/join: xi on a helper stream, FD on the caller's stream, joined by events before the call
+// returns.  Under stream capture the fork/join becomes two parallel branches of the graph.  Helper sets come from a per-device
+// pool (lk_helpers.h); without one the work runs serially on the caller's stream.
 using Fork = HelperSet<1, 2>;   // stream[0]: xi; event[0]: fork, event[1]: join
 
 struct WsLayout {

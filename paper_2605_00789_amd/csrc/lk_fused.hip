@@ -13,7 +13,7 @@
 //                                              |  k lowest edges: the selection of every window, or the keys of
 //                                              |  large windows' pairs
 //   (larger windows: the per-window selection, a launch or two of its own)
-//   last       xi heads summed                 |  index scan                     (select_scan_kernel<true>)
+//   last       xi heads summed                 |  index scan                     (select_scan_kernel<true, ...>)
 //
 // Results are bit-identical to the separate kernels.  On two streams the chains overlap as well, but every crossing
 // between hardware queues costs 9-15 us (eager calls: an event record, a wait and the start behind it), two of them on

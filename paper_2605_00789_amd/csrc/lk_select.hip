@@ -307,7 +307,7 @@ constexpr size_t SCAN_LDS_BYTES = (size_t)2 * SCAN_THREADS * SCAN_ITEMS * sizeof
 
 // WITH_HEADS: the first n_head_blocks workgroups of the launch do something else entirely -- they sum the per-head xi
 // partials (last pass of the xi computation, lk_xi_body.h), which is independent of the scan and as short; the scan
-// is the last workgroup.  (The scan stays written out in the kernel: as an inlined function it costs eight more
+// is the last workgroup, or the last one per sequence.  (The scan stays written out in the kernel: as an inlined function it costs eight more
 // registers at the 128-register limit of a 1024-thread workgroup and spills.)
 // EDGES: the inverse map comes from an edge list (an A token may be a source of several B tokens).  The list is in window
 // order, and a caller's windows may come in any order, so a workgroup looks at all edges and takes its sequence's.

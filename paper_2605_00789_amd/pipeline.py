@@ -142,8 +142,8 @@ class CompressionPipeline:
         p = st.problem
         main = torch.cuda.current_stream() if stream is None else stream
         xi = st.xi
-        # small steps with windows of at most 64 tokens: lightkv_score_select runs the xi passes inside the launches of
-        # the FD chain, all on the caller's stream; otherwise xi gets the helper stream
+        # small steps with windows of at most 64 tokens: one lightkv_score_select computes xi as well, in the launches of
+        # the FD chain on the caller's stream; otherwise this form gives xi the helper stream (run() leaves that to the library)
         one_stream = (self.fused and xi_given is None and 0 < p.c.max_window_tokens <= 64
                       and X.shape[0] <= B.ONE_STREAM_MAX_TOKENS)
         if xi_given is not None:
