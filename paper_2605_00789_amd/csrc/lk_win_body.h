@@ -99,10 +99,11 @@ __device__ __forceinline__ long long group_sum_ll(long long v, long long *scratc
 // The level is found by filling: from level q with `missing` tokens left and `open` windows that can still give, the
 // level rises by missing / open, which can never overshoot; it is final once missing < open.  Equal windows take two
 // rounds.  A round is two sums over the windows in one pass of shuffles, so a single wave needs no barrier at all (a
-// binary search took two workgroup barriers per probe, 5-8 probes).  A wave takes 64 windows a step, though: beyond
-// COUNTS_WAVE_MAX windows the whole workgroup is the faster form (lightkv_window_counts, one wave / four: 180 windows 4.4 /
-// 5.3 us, 1024 9.4 / 6.9, 8192 45.8 / 18.0).
-constexpr int COUNTS_WAVE_MAX = 512;
+// binary search took two workgroup barriers per probe, 5-8 probes).  A wave takes 64 windows a step, though, and with many of
+// them the whole workgroup is the faster form (lightkv_window_counts, one wave / four: 64 windows 3.4 / 4.1 us, 180 4.3 / 4.3,
+// 512 5.9 / 4.6, 1024 9.5 / 6.1, 8192 47.5 / 23.0).  Inside the partition the single wave counts while the others place
+// tokens, so it keeps more of them there.
+constexpr int COUNTS_WAVE_MAX = 192, COUNTS_WAVE_MAX_BESIDE = 512;
 template <int NW, typename SizeFn>
 __device__ __forceinline__ void counts_target(int W, int budget, int dir, SizeFn size_of, int32_t *win_remove,
                                               int32_t *status, long long *scratch) {
@@ -274,7 +275,7 @@ __device__ __forceinline__ void build_windows_body(const WinArgs &g, int b, char
   auto size_of = [&](int w) { return winbase[w + 1] - winbase[w]; };
   if (g.count_mode == 2) {
     int32_t *status = g.status ? g.status + b : nullptr;
-    if (wps > COUNTS_WAVE_MAX) counts_target<NT / 64>(wps, out_n - target_n, g.dir, size_of, g.win_remove + wbase, status, scratch);
+    if (wps > COUNTS_WAVE_MAX_BESIDE) counts_target<NT / 64>(wps, out_n - target_n, g.dir, size_of, g.win_remove + wbase, status, scratch);
     // otherwise the last wave, which has the fewest tokens to place (in a small sequence none at all)
     else if (tid >= NT - 64) counts_target<1>(wps, out_n - target_n, g.dir, size_of, g.win_remove + wbase, status, nullptr);
   } else if (g.count_mode >= 0) {
