@@ -79,7 +79,9 @@ constexpr int ROWS_WIN_KEEP = 12;   // passes of 256 tokens the window partition
 //   round 1  the row itself, xi of the row, new_index and the group bounds (all depend on the row number only)
 //   round 2  the source list of the group
 //   round 3  xi of the sources and the rows of the first two sources, together
-// A row without sources is stored after round 1.  Third and later sources of a group (rare) are fetched one by one.
+// A row without sources is stored after round 1.  Later sources come in pairs: groups of 5 to 11 sources exist in every
+// launch, and the last of their waves is what a short launch waits for (three stages of 576 tokens 123.9 -> 120.2 us, with the
+// arguments fetched at once; one by one before).
 //
 // Guests share the launch, because a launch or a stream fork of their own costs as much as they do:
 //   rows behind the vision span (the prompt's text, Steps 4-5): rows sum_n .. sum_n + tail_rows of the inputs move to
@@ -96,8 +98,13 @@ __device__ __forceinline__ void store16(char *p, const uint4 &v) {
   else *reinterpret_cast<u32x4 *>(p) = t4;
 }
 
-// Registers: 8 chunks a lane fit three waves per SIMD (167; left alone the compiler takes 179 = two waves, merge of 21312
-// rows 230 us against 199), 4 need 140 and spill when held to four waves (2880 tokens 234 against 229 us a step).
+__device__ __forceinline__ float read_lane(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+// Registers: 8 chunks a lane fit three waves per SIMD (157; with vector registers for the row addresses 167, and 179 = two
+// waves left alone, merge of 21312 rows 230 us against 199), 4 need 130 and spill when held to four waves (three eager stages
+// of 2880 tokens 220.4 us against 218.2).
 //
 // STREAM: the output rows are stored nontemporally (a template parameter: as a run-time choice between two stores of
 // the same value the compiler merges them into one plain store)
@@ -107,6 +114,12 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
   constexpr int N = IO::N;
   constexpr int BYTES = Elem<T>::BYTES;
   constexpr int HU = U > 4 ? (U + 1) / 2 : U;   // chunks of a merge in flight per source
+  const int which = blockIdx.z;   // tensor
+  const char *in = static_cast<const char *>(g.t.in[which]);
+  char *out = static_cast<char *>(g.t.out[which]);
+  const int64_t ld_in = g.t.ld_in[which] * BYTES, ld_out = g.t.ld_out[which] * BYTES;
+  fetch_now(in, out, ld_in, ld_out, g.new_index, g.grp_offsets, g.grp_src, g.xi, g.d, g.sum_n, g.out_rows, g.tail_rows,
+            g.x_sqnorm_out, g.pos, g.pos_out, g.n_guest_blocks, g.n_win_blocks, g.segs);
   if constexpr (MODE == 2) {
     if ((int)blockIdx.x < g.n_win_blocks) {
       if (blockIdx.y + blockIdx.z > 0) return;
@@ -124,13 +137,10 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
     }
   }
   const int lane = threadIdx.x & 63;
-  const int64_t b = (int64_t)((int)blockIdx.x - g.n_guest_blocks) * ROWS_PER_WG + (threadIdx.x >> 6);
-  const int which = blockIdx.z;   // tensor
+  // (the row is the same for all lanes, and the compiler is told: row addresses then live in scalar registers)
+  const int64_t b = (int64_t)((int)blockIdx.x - g.n_guest_blocks) * ROWS_PER_WG + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int seg = blockIdx.y;
   if (b >= g.sum_n + g.tail_rows) return;
-  const char *in = static_cast<const char *>(g.t.in[which]);
-  char *out = static_cast<char *>(g.t.out[which]);
-  const int64_t ld_in = g.t.ld_in[which] * BYTES;
   const int n_chunks = g.d / N;
   const char *row_in = in ? in + b * ld_in : nullptr;
   // |x|^2 of the row as it is stored (tensor 0 only, on request): the next stage's feature divergence wants it, and
@@ -153,7 +163,7 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int c = (sg * U + u) * WAVE + lane;
-      dst[u] = ld16(row + (int64_t)(c < n_chunks ? c : n_chunks - 1) * 16);
+      dst[u] = ld16(row + (uint32_t)((c < n_chunks ? c : n_chunks - 1) * 16));
     }
   };
   if (in != nullptr) load_row(row_in, seg, v);
@@ -164,13 +174,13 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
     if (out_row >= g.out_rows) return;   // no room in the output: dropped, never written out of bounds
     if (which == 0 && seg == 0 && lane == 0 && g.pos && g.pos_out) g.pos_out[out_row] = g.pos[b];
     if (in == nullptr) return;
-    char *row_out = out + out_row * g.t.ld_out[which] * BYTES;
+    char *row_out = out + out_row * ld_out;
     for (int sg = seg; sg < seg_end; ++sg) {
       if (sg > seg) load_row(row_in, sg, v);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int c = (sg * U + u) * WAVE + lane;
-        if (c < n_chunks) store16<STREAM>(row_out + (int64_t)c * 16, v[u]);
+        if (c < n_chunks) store16<STREAM>(row_out + (uint32_t)(c * 16), v[u]);
       }
     }
     return;
@@ -185,7 +195,7 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
   if (MODE == 0 && m == 0) return;                                    // in place: nothing to do for this row
   if (MODE != 0 && which == 0 && seg == 0 && lane == 0 && g.pos && g.pos_out) g.pos_out[out_row] = g.pos[b];
   if (in == nullptr) return;
-  char *row_out = out + (int64_t)out_row * g.t.ld_out[which] * BYTES;
+  char *row_out = out + (int64_t)out_row * ld_out;
 
   // rounds 2 and 3: lane s holds source s and its weight (groups beyond 64 sources take the slow loop)
   int a_l = (int)b;
@@ -194,8 +204,8 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
   if (MODE != 1 && m > 0) {
     const int mm = m < WAVE ? m : WAVE;
     a_l = g.grp_src[s0 + (lane < mm ? lane : mm - 1)];
-    row_a0 = in + (int64_t)__shfl(a_l, 0, 64) * ld_in;
-    row_a1 = in + (int64_t)__shfl(a_l, mm > 1 ? 1 : 0, 64) * ld_in;
+    row_a0 = in + (int64_t)__builtin_amdgcn_readlane(a_l, 0) * ld_in;
+    row_a1 = in + (int64_t)__builtin_amdgcn_readlane(a_l, mm > 1 ? 1 : 0) * ld_in;
   }
 
   float sq = 0.f;
@@ -205,13 +215,33 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
     if (MODE != 1 && m > 0) {
       // first half of the segment: its source chunks go out together with the xi loads below
       uint4 va0[HU], va1[HU];
+      auto load_source = [&](const char *row, int hb, uint4 (&dst)[HU]) {
 #pragma unroll
-      for (int u = 0; u < HU; ++u) {
-        const int c = (seg * U + u) * WAVE + lane;
-        const int64_t o = (int64_t)(c < n_chunks ? c : n_chunks - 1) * 16;
-        va0[u] = ld16(row_a0 + o);
-        va1[u] = ld16(row_a1 + o);
-      }
+        for (int u = 0; u < HU; ++u) {
+          if (hb + u < U) {
+            const int c = (seg * U + hb + u) * WAVE + lane;
+            dst[u] = ld16(row + (uint32_t)((c < n_chunks ? c : n_chunks - 1) * 16));
+          }
+        }
+      };
+      auto source_row = [&](int s) {   // source s of the group (groups of more than 64: from memory)
+        return in + (int64_t)(m <= WAVE ? __builtin_amdgcn_readlane(a_l, s) : g.grp_src[s0 + s]) * ld_in;
+      };
+      auto weight = [&](int s) { return m <= WAVE ? read_lane(w_l, s) : g.xi[g.grp_src[s0 + s]] * read_lane(w_l, 0); };
+      auto add = [&](const uint4 (&src)[HU], float w, int hb, float (&acc)[HU][N]) {
+#pragma unroll
+        for (int u = 0; u < HU; ++u) {
+          if (hb + u < U) {
+            float ya[N], yb[N];
+            IO::unpack(src[u], ya);
+            IO::unpack(v[hb + u], yb);
+#pragma unroll
+            for (int e = 0; e < N; ++e) acc[u][e] = fmaf(w, ya[e] - yb[e], acc[u][e]);
+          }
+        }
+      };
+      load_source(row_a0, 0, va0);
+      load_source(row_a1, 0, va1);
       if (first) {
         const int mm = m < WAVE ? m : WAVE;
         float x_l = g.xi[a_l];
@@ -223,21 +253,14 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
         for (int s = s0 + WAVE; s < s1; ++s) den += g.xi[g.grp_src[s]];
         w_l = x_l / den;
         if (m > WAVE) w_l = 1.f / den;   // slow path keeps 1/den instead
-        w0 = (m <= WAVE) ? __shfl(w_l, 0, 64) : g.xi[__shfl(a_l, 0, 64)] * __shfl(w_l, 0, 64);
-        w1 = (m <= 1) ? 0.f : ((m <= WAVE) ? __shfl(w_l, 1, 64) : g.xi[g.grp_src[s0 + 1]] * __shfl(w_l, 0, 64));
+        w0 = weight(0);
+        w1 = (m <= 1) ? 0.f : weight(1);
       }
 #pragma unroll
       for (int hb = 0; hb < U; hb += HU) {
         if (hb > 0) {
-#pragma unroll
-          for (int u = 0; u < HU; ++u) {
-            if (hb + u < U) {
-              const int c = (seg * U + hb + u) * WAVE + lane;
-              const int64_t o = (int64_t)(c < n_chunks ? c : n_chunks - 1) * 16;
-              va0[u] = ld16(row_a0 + o);
-              va1[u] = ld16(row_a1 + o);
-            }
-          }
+          load_source(row_a0, hb, va0);
+          load_source(row_a1, hb, va1);
         }
         float acc[HU][N];   // y_b stays packed in v[] and is unpacked where it is used
 #pragma unroll
@@ -251,35 +274,11 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
             for (int e = 0; e < N; ++e) acc[u][e] = fmaf(w1, y1[e] - yb[e], fmaf(w0, y0[e] - yb[e], yb[e]));
           }
         }
-        for (int s = 2; s < m; ++s) {   // third and later sources
-          int a;
-          float w;
-          if (m <= WAVE) {
-            a = __shfl(a_l, s, 64);
-            w = __shfl(w_l, s, 64);
-          } else {
-            a = g.grp_src[s0 + s];
-            w = g.xi[a] * __shfl(w_l, 0, 64);
-          }
-          const char *row_a = in + (int64_t)a * ld_in;
-          uint4 va[HU];
-#pragma unroll
-          for (int u = 0; u < HU; ++u) {
-            if (hb + u < U) {
-              const int c = (seg * U + hb + u) * WAVE + lane;
-              va[u] = ld16(row_a + (int64_t)(c < n_chunks ? c : n_chunks - 1) * 16);
-            }
-          }
-#pragma unroll
-          for (int u = 0; u < HU; ++u) {
-            if (hb + u < U) {
-              float ya[N], yb[N];
-              IO::unpack(va[u], ya);
-              IO::unpack(v[hb + u], yb);
-#pragma unroll
-              for (int e = 0; e < N; ++e) acc[u][e] = fmaf(w, ya[e] - yb[e], acc[u][e]);
-            }
-          }
+        for (int s = 2; s < m; s += 2) {   // later sources, two in flight
+          load_source(source_row(s), hb, va0);
+          load_source(source_row(s + 1 < m ? s + 1 : s), hb, va1);
+          add(va0, weight(s), hb, acc);
+          if (s + 1 < m) add(va1, weight(s + 1), hb, acc);
         }
 #pragma unroll
         for (int u = 0; u < HU; ++u)
@@ -289,7 +288,7 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int c = (seg * U + u) * WAVE + lane;
-      if (c < n_chunks) store16<STREAM>(row_out + (int64_t)c * 16, v[u]);
+      if (c < n_chunks) store16<STREAM>(row_out + (uint32_t)(c * 16), v[u]);
     }
     if (want_sq) {
 #pragma unroll

@@ -100,6 +100,49 @@ def test_merge_over_the_row_segments(dtype, d, n, tail):
     assert torch.equal(pos_out, torch.cat([pos[:n][keep], pos[n:]]))
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 2048), ("bf16", 4096), ("bf16", 5120), ("f32", 1024), ("f32", 2560)])
+def test_groups_of_any_number_of_sources(dtype, d):
+    """Groups of 1 to 9 sources (the later ones come in pairs), and of 63 to 66 around the sources whose weights a wave keeps,
+    in place and with the compaction.  Reference and bound as in test_merge_over_the_row_segments."""
+    import paper_2605_00789_amd as L
+    sizes = [1, 2, 3, 4, 5, 6, 7, 8, 9, 63, 64, 65, 66]
+    n = sum(sizes) + len(sizes)
+    rng = np.random.default_rng(d)
+    perm = rng.permutation(n)
+    dst, at = np.full(n, -1), len(sizes)
+    for k, m in enumerate(sizes):
+        dst[perm[at:at + m]] = perm[k]
+        at += m
+    gone = dst >= 0
+    src = np.flatnonzero(gone)[np.argsort(dst[gone], kind="stable")].astype(np.int32)
+    new_index = np.where(gone, -1, np.cumsum(~gone) - 1).astype(np.int32)
+    offsets = np.concatenate([[0], np.cumsum(np.bincount(dst[gone], minlength=n))]).astype(np.int32)
+    xi = (rng.gamma(2.0, 1.0, n) + 1e-3).astype(np.float32)
+    g = torch.Generator(device="cuda").manual_seed(d)
+    X, K, V = (torch.randn(n, d, generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32) for _ in range(3))
+    h_cu = np.array([0, n], dtype=np.int32)
+    prob = L.Problem(batch=1, d=d, heads=d // 32, head_dim=32, dtype=dtype, h_cu_vis=h_cu, cu_vis=torch.from_numpy(h_cu).cuda())
+    off_d, src_d, xi_d = torch.from_numpy(offsets).cuda(), torch.from_numpy(src).cuda(), torch.from_numpy(xi).cuda()
+    keep = torch.from_numpy(~gone).cuda()
+    outs = [torch.full((len(sizes), d), 7.0, dtype=X.dtype, device="cuda") for _ in range(3)]
+    pos = torch.arange(n, dtype=torch.int32, device="cuda")
+    L.lightkv_aggregate_compact(prob, torch.from_numpy(new_index).cuda(), off_d, src_d, xi_d, X, K, V, pos, *outs, pos[:len(sizes)].clone())
+    in_place = [t.clone() for t in (X, K, V)]
+    L.lightkv_aggregate(prob, off_d, src_d, xi_d, *in_place)
+    a, b = torch.from_numpy(np.flatnonzero(gone)).cuda(), torch.from_numpy(dst[gone]).cuda()
+    w = xi_d.double()
+    for y, o, p in zip((X, K, V), outs, in_place):
+        y64 = y.double()
+        num, den = w[:, None] * y64, w.clone()
+        num.index_add_(0, b, w[a][:, None] * y64[a])
+        den.index_add_(0, b, w[a])
+        want = (num / den[:, None])[keep]
+        bound = (2.0 ** -8 if dtype == "bf16" else 0.0) * want.abs() + 6e-6 * want.abs().max()
+        assert bool(((o.double() - want).abs() <= bound).all())
+        assert torch.equal(p[keep], o)
+        assert torch.equal(p[~keep], y[~keep])
+
+
 @pytest.mark.parametrize("dtype,d,n,tail", [("bf16", 64, 30, 3), ("bf16", 4096, 30, 0), ("bf16", 4160, 31, 2), ("bf16", 8704, 30, 3),
                                             ("bf16", 4224, 2100, 5), ("f32", 4352, 33, 1)])
 def test_rows_in_one_wave_or_several(dtype, d, n, tail):
