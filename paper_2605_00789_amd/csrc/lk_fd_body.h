@@ -497,7 +497,8 @@ inline FdArgs make_fd_args(const FdPlan &plan, int dtype, const void *X, int64_t
   g.n_tiles = plan.n_tiles; g.ksplit = plan.ksplit; g.metric = plan.metric; g.dir = plan.dir;
   const int span = (dtype == 1) ? 64 : 32;
   g.n_spans = (d + span - 1) / span;
-  g.spans_per_wg = (g.n_spans + plan.ksplit - 1) / plan.ksplit;
+  const int pieces = (g.n_spans + FD_WAVES - 1) / FD_WAVES;
+  g.spans_per_wg = (pieces + plan.ksplit - 1) / plan.ksplit * FD_WAVES;
   return g;
 }
 

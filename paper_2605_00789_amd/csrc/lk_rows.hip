@@ -118,8 +118,7 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
   const char *in = static_cast<const char *>(g.t.in[which]);
   char *out = static_cast<char *>(g.t.out[which]);
   const int64_t ld_in = g.t.ld_in[which] * BYTES, ld_out = g.t.ld_out[which] * BYTES;
-  fetch_now(in, out, ld_in, ld_out, g.new_index, g.grp_offsets, g.grp_src, g.xi, g.d, g.sum_n, g.out_rows, g.tail_rows,
-            g.x_sqnorm_out, g.pos, g.pos_out, g.n_guest_blocks, g.n_win_blocks, g.segs);
+  fetch_now(in, ld_in, g.new_index, g.grp_offsets, g.xi, g.d, g.sum_n, g.tail_rows, g.n_guest_blocks, g.segs);
   if constexpr (MODE == 2) {
     if ((int)blockIdx.x < g.n_win_blocks) {
       if (blockIdx.y + blockIdx.z > 0) return;
@@ -224,6 +223,17 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
           }
         }
       };
+      auto load_first_two = [&](int hb) {   // chunk by chunk: the sums start with the first of both
+#pragma unroll
+        for (int u = 0; u < HU; ++u) {
+          if (hb + u < U) {
+            const int c = (seg * U + hb + u) * WAVE + lane;
+            const uint32_t o = (uint32_t)((c < n_chunks ? c : n_chunks - 1) * 16);
+            va0[u] = ld16(row_a0 + o);
+            va1[u] = ld16(row_a1 + o);
+          }
+        }
+      };
       auto source_row = [&](int s) {   // source s of the group (groups of more than 64: from memory)
         return in + (int64_t)(m <= WAVE ? __builtin_amdgcn_readlane(a_l, s) : g.grp_src[s0 + s]) * ld_in;
       };
@@ -240,8 +250,7 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
           }
         }
       };
-      load_source(row_a0, 0, va0);
-      load_source(row_a1, 0, va1);
+      load_first_two(0);
       if (first) {
         const int mm = m < WAVE ? m : WAVE;
         float x_l = g.xi[a_l];
@@ -258,10 +267,7 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
       }
 #pragma unroll
       for (int hb = 0; hb < U; hb += HU) {
-        if (hb > 0) {
-          load_source(row_a0, hb, va0);
-          load_source(row_a1, hb, va1);
-        }
+        if (hb > 0) load_first_two(hb);
         float acc[HU][N];   // y_b stays packed in v[] and is unpacked where it is used
 #pragma unroll
         for (int u = 0; u < HU; ++u) {
@@ -276,7 +282,7 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
         }
         for (int s = 2; s < m; s += 2) {   // later sources, two in flight
           load_source(source_row(s), hb, va0);
-          load_source(source_row(s + 1 < m ? s + 1 : s), hb, va1);
+          if (s + 1 < m) load_source(source_row(s + 1), hb, va1);   // uniform
           add(va0, weight(s), hb, acc);
           if (s + 1 < m) add(va1, weight(s + 1), hb, acc);
         }

@@ -54,6 +54,15 @@ hipError_t launch_fd_select_small(const FdPlan &plan, int dtype, const void *X, 
   return hipGetLastError();
 }
 
+// Workgroups of the partial tiles.  The hidden axis is split until there is one for every CU, and on (up to four for every CU)
+// while a slice is longer than eight pieces: beside xi's row statistics (768 workgroups fit the chip at a time, three a CU) each
+// further one waits for a slot, and a slice of several pieces has the next piece in flight while it multiplies.  Always split to
+// four a CU before: three stages of 2880 tokens 218.2 -> 207.4 us, the step of a 13B-shaped layer (3456 x 5120) 110.2 -> 104.8
+// (there also because a slice of 5 spans staged 8).  Slices of any length: full pairwise, 5 x 648 tokens, d = 3712, 320 tiles
+// in two stages 266 -> 281 us, so that line is drawn.  fp32 products take sixteen times as long, a piece of them is 1.3 us of a
+// matrix pipe: split as before (3 x 513 tokens, d = 1024: 85.0 us with slices of one piece, 87.1 of two).
+constexpr int FD_TARGET_WGS = 256, FD_ROOM_WGS = 1024, FD_SLICE_PIECES = 8;
+
 static FdPlan plan_tiles(int n_windows, int maxA, int maxB, int d, int dtype_bytes) {
   FdPlan p{};
   if (maxA <= 16) {
@@ -73,10 +82,20 @@ static FdPlan plan_tiles(int n_windows, int maxA, int maxB, int d, int dtype_byt
   const int span = (dtype_bytes == 2) ? 64 : 32;
   const int n_spans = (d + span - 1) / span;
   const int max_ks = n_spans / FD_WAVES > 0 ? n_spans / FD_WAVES : 1;
-  int ks = 1;
-  while ((int64_t)p.n_tiles * ks < 1024 && ks * 2 <= max_ks && ks * 2 <= 16) ks *= 2;   // 16 = FD_MAX_KSPLIT
-  p.ksplit = ks;
-  p.partial_floats = (size_t)p.n_tiles * ks * FD_TILE_FLOATS;
+  // a workgroup stages FD_WAVES spans at a time: a slice is a whole number of these pieces
+  const int pieces = (n_spans + FD_WAVES - 1) / FD_WAVES;
+  auto split = [&](int target, int longest) {
+    int ks = 1;
+    while (((int64_t)p.n_tiles * ks < target || ((int64_t)p.n_tiles * ks < FD_ROOM_WGS && pieces > longest * ks)) &&
+           ks * 2 <= max_ks && ks * 2 <= FD_MAX_KSPLIT)
+      ks *= 2;
+    return ks;
+  };
+  const int ks = split(dtype_bytes == 2 ? FD_TARGET_WGS : FD_ROOM_WGS, FD_SLICE_PIECES), per = (pieces + ks - 1) / ks;
+  p.ksplit = (pieces + per - 1) / per;
+  // The room for the slices stays that of the finer split: a workspace has to serve plans with a smaller window bound as well,
+  // which can be split further.
+  p.partial_floats = (size_t)p.n_tiles * split(FD_ROOM_WGS, pieces) * FD_TILE_FLOATS;
   return p;
 }
 
