@@ -29,6 +29,7 @@ template <int A, int B> struct MaxOf { static constexpr int value = A > B ? A : 
 
 template <typename T, int DH, int RW>
 __global__ __launch_bounds__(XI_THREADS, 3) void rowstat_partial_kernel(XiArgs x, int n_xi_blocks, FdArgs f) {
+  fetch_args<XiArgs, int, FdArgs>();
   static_assert(XI_THREADS == FD_THREADS, "both bodies are written for 256 threads");
   __shared__ __attribute__((aligned(16))) char lds[MaxOf<XiStage<T, DH, RW>::LDS_ROWSTAT, FD_PARTIAL_LDS>::value];
   // the two kinds of workgroup alternate, so that both chains get the chip from the start of the launch
@@ -46,6 +47,7 @@ __global__ __launch_bounds__(XI_THREADS, 3) void rowstat_partial_kernel(XiArgs x
 // TAIL: tile tails (windows of at most 64 tokens); otherwise the epilogue of larger windows
 template <typename T, int DH, int RW, bool VISION_LSE, bool TAIL>
 __global__ __launch_bounds__(XI_THREADS) void colsum_tail_kernel(XiArgs x, int n_fd_blocks, FdArgs f, SmallSelArgs q) {
+  fetch_args<XiArgs, int, FdArgs, SmallSelArgs>();
   constexpr int FD_LDS = TAIL ? (int)sizeof(SmallTileLds) : FD_EPILOGUE_LDS;
   __shared__ __attribute__((aligned(16))) char lds[MaxOf<XiStage<T, DH, RW>::LDS_COLSUM, FD_LDS>::value];
   // the few FD workgroups go first: they are the longer dependency chain and must not wait for a free slot
@@ -60,6 +62,7 @@ __global__ __launch_bounds__(XI_THREADS) void colsum_tail_kernel(XiArgs x, int n
 // The same beside the edge selection; dynamic LDS, as the keys of a window may need more than the column sums do.
 template <typename T, int DH, int RW, bool VISION_LSE>
 __global__ __launch_bounds__(XI_THREADS) void colsum_edges_kernel(XiArgs x, int n_fd_blocks, FdArgs f, EdgeArgs q) {
+  fetch_args<XiArgs, int, FdArgs, EdgeArgs>();
   extern __shared__ __attribute__((aligned(16))) char dyn_lds[];
   if ((int)blockIdx.x >= n_fd_blocks) xi_colsum_body<T, DH, RW, VISION_LSE>(x, blockIdx.x - n_fd_blocks, dyn_lds);
   else if (q.max_a > EDGE_MAX_SIDE) edge_keys_body(f, q, blockIdx.x, dyn_lds);

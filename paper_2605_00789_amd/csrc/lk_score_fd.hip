@@ -17,16 +17,19 @@ namespace lk {
 
 template <typename T>
 __global__ __launch_bounds__(FD_THREADS, 3) void fd_partial_kernel(FdArgs g) {
+  fetch_args<FdArgs>();
   __shared__ __attribute__((aligned(16))) char lds[FD_PARTIAL_LDS];
   fd_partial_body<T>(g, blockIdx.x, lds);
 }
 
 __global__ __launch_bounds__(FD_THREADS) void fd_tail_select_kernel(FdArgs g, SmallSelArgs q) {
+  fetch_args<FdArgs, SmallSelArgs>();
   __shared__ __attribute__((aligned(16))) char lds[sizeof(SmallTileLds)];
   fd_tail_select_body(g, q, blockIdx.x, lds);
 }
 
 __global__ __launch_bounds__(FD_THREADS) void fd_epilogue_kernel(FdArgs g) {
+  fetch_args<FdArgs>();
   __shared__ __attribute__((aligned(16))) char lds[FD_EPILOGUE_LDS];
   fd_epilogue_body(g, blockIdx.x, lds);
 }

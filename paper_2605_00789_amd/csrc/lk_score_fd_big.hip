@@ -50,6 +50,7 @@ struct BigArgs {
 
 // ---- |x|^2 per token, summed in fp32 ----------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void row_norms_kernel(BigArgs g) {
+  fetch_args<BigArgs>();
   const int lane = threadIdx.x & 63;
   const int tok = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (tok >= g.sum_n) return;
@@ -358,6 +359,7 @@ __global__ __launch_bounds__(BIG_THREADS) void fd_big_kernel(BigArgs g) {
 // key was offered for (B nodes, A nodes of windows without a B node, rows of NaNs, rows beyond the caller's window
 // bound) gets +inf / -1.
 __global__ __launch_bounds__(256) void fd_big_finalize_kernel(BigArgs g, int chunks_per_window) {
+  fetch_args<BigArgs, int>();
   const int w = blockIdx.x / chunks_per_window, c = blockIdx.x - w * chunks_per_window;
   const int off = g.win_offsets[w];
   const int v = g.win_offsets[w + 1] - off;

@@ -20,17 +20,22 @@ namespace lk {
 
 template <typename T, int DH, int RW>
 __global__ __launch_bounds__(XI_THREADS) void xi_rowstat_kernel(XiArgs g) {
+  fetch_args<XiArgs>();
   __shared__ __attribute__((aligned(16))) char lds[XiStage<T, DH, RW>::LDS_ROWSTAT];
   xi_rowstat_body<T, DH, RW>(g, blockIdx.x, lds);
 }
 
 template <typename T, int DH, int RW, bool VISION_LSE>
 __global__ __launch_bounds__(XI_THREADS) void xi_colsum_kernel(XiArgs g) {
+  fetch_args<XiArgs>();
   __shared__ __attribute__((aligned(16))) char lds[XiStage<T, DH, RW>::LDS_COLSUM];
   xi_colsum_body<T, DH, RW, VISION_LSE>(g, blockIdx.x, lds);
 }
 
-__global__ __launch_bounds__(64) void xi_heads_kernel(XiArgs g) { xi_heads_body(g, blockIdx.x * 64 + threadIdx.x); }
+__global__ __launch_bounds__(64) void xi_heads_kernel(XiArgs g) {
+  fetch_args<XiArgs>();
+  xi_heads_body(g, blockIdx.x * 64 + threadIdx.x);
+}
 
 hipError_t launch_xi_heads(const XiArgs &g, hipStream_t stream) {
   if (g.sum_n) hipLaunchKernelGGL(xi_heads_kernel, dim3((unsigned)((g.sum_n + 63) / 64)), dim3(64), 0, stream, g);

@@ -60,6 +60,7 @@ constexpr int COUNT_MAX_A = 256;
 
 template <int SEGS>
 __global__ __launch_bounds__(COUNT_MAX_A * SEGS) void select_window_kernel(SelArgs g) {
+  fetch_args<SelArgs>();
   // order-preserving FD bits of every A node, then the target of every merged A node; all-ones beyond |A| (never
   // smaller than a key, never a valid target), padded to whole groups of four
   __shared__ __attribute__((aligned(16))) uint32_t key[COUNT_MAX_A + 4];
@@ -174,6 +175,7 @@ constexpr int RANK_MAX_A = 2048;   // |A| of the largest window the library acce
 
 template <int MODE>
 __global__ __launch_bounds__(RANK_ROWS * RANK_SEGS) void select_rank_kernel(SelArgs g, int blocks_per_window) {
+  fetch_args<SelArgs, int>();
   // MODE 0: order-preserving FD bits; MODE 1: dst of every A node.  Padded with all-ones up to whole 4-entry groups
   // per segment: an all-ones entry is never smaller than a key and never a valid target.
   __shared__ __attribute__((aligned(16))) uint32_t vals[RANK_MAX_A + 4 * RANK_SEGS];
@@ -313,6 +315,7 @@ constexpr size_t SCAN_LDS_BYTES = (size_t)2 * SCAN_THREADS * SCAN_ITEMS * sizeof
 // order, and a caller's windows may come in any order, so a workgroup looks at all edges and takes its sequence's.
 template <bool WITH_HEADS, bool EDGES>
 __global__ __launch_bounds__(SCAN_THREADS) void select_scan_kernel(SelArgs g, XiArgs x, int n_head_blocks) {
+  fetch_args<SelArgs, XiArgs, int>();
   if (WITH_HEADS && (int)blockIdx.x < n_head_blocks) {
     xi_heads_body(x, blockIdx.x * SCAN_THREADS + threadIdx.x);
     return;

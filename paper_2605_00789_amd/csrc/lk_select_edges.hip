@@ -38,10 +38,12 @@ namespace lk {
 
 template <bool ONE, int ITEMS>
 __global__ __launch_bounds__(EDGE_THREADS, ITEMS == EDGE_ITEMS ? 2 : 3) void edge_select_kernel(FdArgs g, EdgeArgs q) {
+  fetch_args<FdArgs, EdgeArgs>();
   extern __shared__ __attribute__((aligned(16))) char edge_lds[];
   edge_select_body<ONE, ITEMS>(g, q, blockIdx.x, edge_lds);
 }
 __global__ __launch_bounds__(EDGE_THREADS) void edge_keys_kernel(FdArgs g, EdgeArgs q) {
+  fetch_args<FdArgs, EdgeArgs>();
   __shared__ __attribute__((aligned(16))) char lds[sizeof(EdgeKeysLds)];
   edge_keys_body(g, q, blockIdx.x, lds);
 }
@@ -56,6 +58,7 @@ constexpr int EB_BINS = 2048;       // 11-bit digits
 constexpr int EB_LOADS = 16;   // keys a thread keeps in flight per step of the radix and column passes
 constexpr int EB_ROWS = 4;     // rows a wave takes at a time in the row pass
 __global__ __launch_bounds__(EB_THREADS) void edge_select_big_kernel(FdArgs g, EdgeArgs q) {
+  fetch_args<FdArgs, EdgeArgs>();
   __shared__ int hist[EB_BINS];
   __shared__ int tok[2 * EB_MAX_SIDE];
   __shared__ uint16_t selcol[EB_MAX_SIDE];   // lowest selected edge of every A node (0xffff: none)

@@ -67,6 +67,7 @@ __device__ __forceinline__ int count_equal_before(const uint32_t *list, uint32_t
 // NT threads, windows of at most CAP tokens (the launcher's bound).
 template <int NT, int CAP>
 __global__ __launch_bounds__(NT) void pair_select_kernel(PairSelArgs g) {
+  fetch_args<PairSelArgs>();
   constexpr int ITEMS = CAP / NT;
   // order-preserving FD bits (step 1); then the neighbour of every token that leaves (step 4)
   __shared__ __attribute__((aligned(16))) uint32_t key[CAP + 4];

@@ -19,6 +19,7 @@ constexpr size_t WIN_TABLE_LDS_MAX = 152 * 1024;
 constexpr int WIN_KEEP = 4;                // passes of 1024 tokens whose window and rank stay in registers between phases
 
 __global__ __launch_bounds__(WIN_THREADS) void build_windows_table_kernel(WinArgs g) {
+  fetch_args<WinArgs>();
   extern __shared__ __attribute__((aligned(16))) char win_lds[];
   build_windows_body<WIN_THREADS, WIN_KEEP>(g, blockIdx.x, win_lds);
 }
@@ -69,6 +70,7 @@ struct CountArgs {
 };
 
 __global__ __launch_bounds__(CNT_THREADS) void window_counts_kernel(CountArgs g) {
+  fetch_args<CountArgs>();
   __shared__ int size_lds[CNT_CACHE];
   __shared__ long long scratch[CNT_THREADS / 64];
   const int b = blockIdx.x, W = g.win_per_seq, w0 = b * W;
