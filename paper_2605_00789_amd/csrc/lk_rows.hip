@@ -66,7 +66,7 @@ constexpr int ROWS_PER_WG = ROW_THREADS / WAVE;
 // 16-byte chunks per lane and segment, at most.  Launches of few rows leave waves idle and want more of them with shorter
 // lives; longer ones pay for them.  us, 8 KB rows in segments of 4 / whole: merge of three tensors 144 rows 4.9 / 6.4, 2000
 // rows 19.8 / 20.6, 4096 rows 35.6 / 34.8; of one tensor 1100 rows 6.9 / 7.5, 2880 rows 13.0 / 12.5, 16384 rows 58.8 / 49.2.
-// With squared norms (one wave per row of the first tensor) three tensors of 2880 rows 25.2 / 26.6, 5400 42.4 / 44.2, 9216
+// With squared norms (all segments of a row in one wave when this was measured) three tensors of 2880 rows 25.2 / 26.6, 5400 42.4 / 44.2, 9216
 // 71.2 / 70.7.
 constexpr int ROW_MAX_U = 8, ROW_MAX_U_SHORT = 5;
 constexpr int64_t ROWS_SHORT_MAX = 2048, ROWS_SHORT_MAX_SQ = 6144;
@@ -137,17 +137,26 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
   }
   const int lane = threadIdx.x & 63;
   // (the row is the same for all lanes, and the compiler is told: row addresses then live in scalar registers)
-  const int64_t b = (int64_t)((int)blockIdx.x - g.n_guest_blocks) * ROWS_PER_WG + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int64_t b = (int64_t)((int)blockIdx.x - g.n_guest_blocks) * ROWS_PER_WG + wave;
   int seg = blockIdx.y;
+  // |x|^2 needs all segments of a row: they are waves of one workgroup then (ROWS_PER_WG / segs rows each)
+  const bool sq_split = MODE == 2 && which == 0 && g.x_sqnorm_out != nullptr && (g.segs == 2 || g.segs == ROWS_PER_WG);
+  if (sq_split) {
+    const int sh = g.segs == 2 ? 1 : 2;
+    b = (((int64_t)((int)blockIdx.x - g.n_guest_blocks) * g.segs + blockIdx.y) * ROWS_PER_WG + wave) >> sh;
+    seg = wave & (g.segs - 1);
+  }
   if (b >= g.sum_n + g.tail_rows) return;
   const int n_chunks = g.d / N;
   const char *row_in = in ? in + b * ld_in : nullptr;
   // |x|^2 of the row as it is stored (tensor 0 only, on request): the next stage's feature divergence wants it, and
-  // here the row is in registers anyway.  Same order of summation as the stand-alone pass over X, so one wave takes all
-  // segments of such a row in turn.
+  // here the row is in registers anyway.  Same order of summation as the stand-alone pass over X: a lane's sum goes on from
+  // segment to segment, through LDS where they are waves of one workgroup, in one wave that takes them in turn otherwise (in
+  // turn at two segments as well, three stages of 576 tokens took 115.5 us instead of 107.7).
   const bool want_sq = MODE != 0 && which == 0 && g.x_sqnorm_out != nullptr && b < g.sum_n;
-  if (want_sq && seg > 0) return;
-  const int seg_end = want_sq || MODE == 1 ? g.segs : seg + 1;   // (a launch of mode 1 has one workgroup per four rows)
+  if (want_sq && !sq_split && seg > 0) return;
+  const int seg_end = (want_sq && !sq_split) || MODE == 1 ? g.segs : seg + 1;   // (a launch of mode 1 has one workgroup per four rows)
 
   // round 1 (the in-place mode touches few rows: it looks at the group bounds first instead of fetching every row)
   if (MODE == 0 && g.grp_offsets[b + 1] == g.grp_offsets[b]) return;
@@ -297,12 +306,29 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
       if (c < n_chunks) store16<STREAM>(row_out + (uint32_t)(c * 16), v[u]);
     }
     if (want_sq) {
+      float t[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int c = (seg * U + u) * WAVE + lane;
-        const float t = BYTES == 2 ? sumsq_chunk_bf16(v[u]) : sumsq_chunk_f32(v[u]);
-        sq += (c < n_chunks) ? t : 0.f;
+        t[u] = BYTES == 2 ? sumsq_chunk_bf16(v[u]) : sumsq_chunk_f32(v[u]);
+        t[u] = (seg * U + u) * WAVE + lane < n_chunks ? t[u] : 0.f;
       }
+      if constexpr (MODE == 2) {
+        if (sq_split) {   // wait for the sum of the segments before (waves whose rows end early are not waited for)
+          __shared__ float before[ROWS_PER_WG][WAVE];
+          for (int k = 1; k <= seg; ++k) lds_barrier();
+          if (seg > 0) sq = before[wave - 1][lane];
+#pragma unroll
+          for (int u = 0; u < U; ++u) sq += t[u];
+          if (seg + 1 < g.segs) {
+            before[wave][lane] = sq;
+            for (int k = seg + 1; k < g.segs; ++k) lds_barrier();
+            return;
+          }
+          break;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) sq += t[u];
     }
     first = false;
   }

@@ -47,6 +47,7 @@ def test_one_window_around_the_column_tiles_of_the_epilogue(gh, gw, dtype, d):
     ("bf16", 32, 70, 0), ("bf16", 512, 70, 3), ("bf16", 544, 71, 2), ("bf16", 2048, 33, 5), ("bf16", 2560, 33, 1),
     ("bf16", 4096, 65, 9), ("bf16", 4160, 30, 2), ("bf16", 5120, 37, 6), ("bf16", 8192, 20, 1), ("bf16", 8704, 20, 3),
     ("f32", 128, 40, 2), ("f32", 1280, 40, 2), ("f32", 5120, 21, 4),
+    ("bf16", 4096, 31, 1), ("bf16", 6144, 25, 3), ("f32", 2048, 30, 1), ("f32", 3072, 30, 2), ("f32", 4608, 29, 3),   # 2 to 4 segments, squared norms across them
     ("bf16", 4096, 6000, 40),          # beyond 128 MB: whole rows per wave, nontemporal stores
     ("bf16", 2816, 6140, 4), ("bf16", 2816, 6141, 4),   # the last launch of short segments with squared norms, the first without
 ])
