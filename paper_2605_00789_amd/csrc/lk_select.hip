@@ -106,15 +106,7 @@ __global__ __launch_bounds__(COUNT_MAX_A * SEGS) void select_window_kernel(SelAr
   const uint32_t mine = has_a ? f32_order_key(fd) : 0xffffffffu;
   if (seg == 0 && la < n4) key[la] = mine;
   __syncthreads();
-  int c0 = 0;
-#pragma unroll 4
-  for (int o = o_begin; o < o_end; o += 4) {
-    const uint4 k = *reinterpret_cast<const uint4 *>(&key[o]);
-    c0 += (k.x < mine || (k.x == mine && o < la)) ? 1 : 0;
-    c0 += (k.y < mine || (k.y == mine && o + 1 < la)) ? 1 : 0;
-    c0 += (k.z < mine || (k.z == mine && o + 2 < la)) ? 1 : 0;
-    c0 += (k.w < mine || (k.w == mine && o + 3 < la)) ? 1 : 0;
-  }
+  int c0 = count_before(key, mine, la, o_begin, o_end);
   if (SEGS > 1) {
     part[0][seg][la] = c0;
     __syncthreads();
@@ -127,19 +119,8 @@ __global__ __launch_bounds__(COUNT_MAX_A * SEGS) void select_window_kernel(SelAr
   if (seg == 0 && la < n4) tgt[la] = mine_t;
   __syncthreads();
   const uint32_t self = (uint32_t)b_tok;
-  int c1 = 0, c2 = 0;
-#pragma unroll 4
-  for (int o = o_begin; o < o_end; o += 4) {
-    const uint4 d = *reinterpret_cast<const uint4 *>(&tgt[o]);
-    c1 += (d.x == mine_t && o < la) ? 1 : 0;
-    c1 += (d.y == mine_t && o + 1 < la) ? 1 : 0;
-    c1 += (d.z == mine_t && o + 2 < la) ? 1 : 0;
-    c1 += (d.w == mine_t && o + 3 < la) ? 1 : 0;
-    c2 += (d.x == self) ? 1 : 0;
-    c2 += (d.y == self) ? 1 : 0;
-    c2 += (d.z == self) ? 1 : 0;
-    c2 += (d.w == self) ? 1 : 0;
-  }
+  int c1 = merged ? count_equal_before(tgt, mine_t, la, o_begin, o_end) : 0;
+  int c2 = has_b ? count_equal(tgt, self, o_begin, o_end) : 0;
   if (SEGS > 1) {
     part[1][seg][la] = c1;
     part[2][seg][la] = c2;
@@ -245,30 +226,11 @@ __global__ __launch_bounds__(RANK_ROWS * RANK_SEGS) void select_rank_kernel(SelA
   const int o_begin = seg * seg_len;
   int c0 = 0, c1 = 0;
   if (MODE == 0) {
-    const uint32_t mine = vals[has_a ? la : 0];
-#pragma unroll 4
-    for (int o = o_begin; o < o_begin + seg_len; o += 4) {
-      const uint4 k = *reinterpret_cast<const uint4 *>(&vals[o]);
-      c0 += (k.x < mine || (k.x == mine && o < la)) ? 1 : 0;
-      c0 += (k.y < mine || (k.y == mine && o + 1 < la)) ? 1 : 0;
-      c0 += (k.z < mine || (k.z == mine && o + 2 < la)) ? 1 : 0;
-      c0 += (k.w < mine || (k.w == mine && o + 3 < la)) ? 1 : 0;
-    }
+    c0 = count_before(vals, vals[has_a ? la : 0], la, o_begin, o_begin + seg_len);
   } else {
     const uint32_t mine = has_a ? vals[la] : 0xffffffffu;    // target of this A node (all-ones: stays)
-    const uint32_t self = (uint32_t)b_tok;                   // this B node as a target
-#pragma unroll 4
-    for (int o = o_begin; o < o_begin + seg_len; o += 4) {
-      const uint4 d = *reinterpret_cast<const uint4 *>(&vals[o]);
-      c0 += (d.x == mine && o < la) ? 1 : 0;
-      c0 += (d.y == mine && o + 1 < la) ? 1 : 0;
-      c0 += (d.z == mine && o + 2 < la) ? 1 : 0;
-      c0 += (d.w == mine && o + 3 < la) ? 1 : 0;
-      c1 += (d.x == self) ? 1 : 0;
-      c1 += (d.y == self) ? 1 : 0;
-      c1 += (d.z == self) ? 1 : 0;
-      c1 += (d.w == self) ? 1 : 0;
-    }
+    if (mine != 0xffffffffu) c0 = count_equal_before(vals, mine, la, o_begin, o_begin + seg_len);
+    if (has_b) c1 = count_equal(vals, (uint32_t)b_tok, o_begin, o_begin + seg_len);   // this B node as a target
   }
   part[0][seg][row] = c0;
   part[1][seg][row] = c1;

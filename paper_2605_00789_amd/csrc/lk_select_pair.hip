@@ -18,7 +18,7 @@
 // Bound: barriers and dependent LDS reads of one workgroup.  So the workgroup is no larger than the window needs (256
 // threads up to 256 tokens), threads without a token of their own share the counting loops, and a round of the visit
 // is three barriers: the minima of the next round are reset while this one's are read, and the count of undecided tokens
-// travels with the last barrier.  Windows of 36 / 120 / 400 tokens: 13 / 18 / 36 us -> 6.1 / 8.9 / 22 us.
+// travels with the last barrier.  Windows of 36 / 120 / 400 tokens: 13 / 18 / 36 us -> 6.1 / 8.0 / 14.5 us.
 #include "lk_common.h"
 #include "lk_launch.h"
 
@@ -35,34 +35,6 @@ struct PairSelArgs {
 };
 
 enum : unsigned char { PS_UNDECIDED = 0, PS_LEAVES = 1, PS_STAYS = 2 };
-
-// Number of entries of list[0 .. n4) (all-ones beyond n; n4 a multiple of 4) that come before (mine, l): smaller, or equal
-// at an earlier position.  Entries [begin, end) only, both multiples of 4.
-__device__ __forceinline__ int count_before(const uint32_t *list, uint32_t mine, int l, int begin, int end) {
-  int c = 0;
-#pragma unroll 4
-  for (int o = begin; o < end; o += 4) {
-    const uint4 q = *reinterpret_cast<const uint4 *>(&list[o]);
-    c += (q.x < mine || (q.x == mine && o < l)) ? 1 : 0;
-    c += (q.y < mine || (q.y == mine && o + 1 < l)) ? 1 : 0;
-    c += (q.z < mine || (q.z == mine && o + 2 < l)) ? 1 : 0;
-    c += (q.w < mine || (q.w == mine && o + 3 < l)) ? 1 : 0;
-  }
-  return c;
-}
-// Entries equal to `mine` before position l, in the same range.
-__device__ __forceinline__ int count_equal_before(const uint32_t *list, uint32_t mine, int l, int begin, int end) {
-  int c = 0;
-#pragma unroll 4
-  for (int o = begin; o < end; o += 4) {
-    const uint4 q = *reinterpret_cast<const uint4 *>(&list[o]);
-    c += (q.x == mine && o < l) ? 1 : 0;
-    c += (q.y == mine && o + 1 < l) ? 1 : 0;
-    c += (q.z == mine && o + 2 < l) ? 1 : 0;
-    c += (q.w == mine && o + 3 < l) ? 1 : 0;
-  }
-  return c;
-}
 
 // NT threads, windows of at most CAP tokens (the launcher's bound).
 template <int NT, int CAP>
@@ -105,7 +77,7 @@ __global__ __launch_bounds__(NT) void pair_select_kernel(PairSelArgs g) {
     const int l = k * NT + tid;
     tok[k] = -1;
     if (k * NT >= v4) continue;   // uniform
-    if (l < v4) { key[l] = 0xffffffffu; nbr[l] = 0xffffu; }
+    if (l < v4) { key[l] = l < v ? 0xfffffffeu : 0xffffffffu; nbr[l] = 0xffffu; }   // (without a neighbour: behind +inf, in order)
     if (l < v) {
       state[l] = PS_STAYS; received[l] = 0; minpend[0][l] = 0xffffffffu; count[l] = 0;
       const int t = g.win_tokens[off + l];

@@ -747,3 +747,39 @@ print('beside-capture ok', flush=True)
     r = subprocess.run([sys.executable, "-u", "-c", code], cwd=root, capture_output=True, text=True, timeout=100)
     print(r.stdout[-2000:], r.stderr[-3000:], flush=True)
     assert r.returncode == 0 and "beside-capture ok" in r.stdout
+
+
+@pytest.mark.parametrize("v", [2, 3, 7, 8, 9, 16, 17, 63, 190, 191, 193, 194, 400, 511, 512, 513, 514, 801])
+def test_ranks_among_equal_scores(v):
+    """lightkv_select on scores with many ties (three distinct values, +inf among them): an A node's rank counts the earlier
+    nodes with its score, a source's rank the earlier sources of its target.  Windows around the groups of four of the counting
+    loops, the segments of the window kernel and the line to the kernel of large windows; plain Python as reference."""
+    import paper_2605_00789_amd as L
+    rng = np.random.default_rng(v)
+    n_w, nA, nB = 3, (v + 1) // 2, v // 2
+    n = n_w * v
+    fd, prop = np.full(n, np.inf, dtype=np.float32), np.full(n, -1, dtype=np.int32)
+    for w in range(n_w):
+        a, b = np.arange(w * v, (w + 1) * v, 2), np.arange(w * v + 1, (w + 1) * v, 2)
+        fd[a] = rng.choice(np.array([0.0, 0.25, np.inf], dtype=np.float32), nA)
+        prop[a] = rng.choice(b[:max(1, nB // 3)], nA)
+    remove = np.array([nA, max(1, nA // 2), 1], dtype=np.int32)
+    h_cu, wo = np.array([0, n], dtype=np.int32), (np.arange(n_w + 1) * v).astype(np.int32)
+    i32 = lambda t: torch.from_numpy(np.ascontiguousarray(t, dtype=np.int32)).cuda()
+    empty = lambda k: torch.full((k,), -7, dtype=torch.int32, device="cuda")
+    prob = L.Problem(batch=1, d=64, heads=2, head_dim=32, dtype="bf16", h_cu_vis=h_cu, cu_vis=i32(h_cu), n_windows=n_w,
+                     max_window_tokens=v, win_offsets=i32(wo), win_tokens=i32(np.arange(n)), win_remove=i32(remove))
+    ws = torch.empty(L.lightkv_workspace_size(prob), dtype=torch.uint8, device="cuda")
+    dst, new_index, offs, src, cu = empty(n), empty(n), empty(n + 1), empty(n), empty(2)
+    L.lightkv_select(prob, torch.from_numpy(fd).cuda(), i32(prop), dst, new_index, offs, src, cu, ws)
+    want = np.full(n, -1)
+    for w in range(n_w):
+        a = np.arange(w * v, (w + 1) * v, 2)
+        gone = a[np.argsort(fd[a], kind="stable")[:remove[w]]]
+        want[gone] = prop[gone]
+    np.testing.assert_array_equal(dst.cpu().numpy(), want)
+    keep = want < 0
+    np.testing.assert_array_equal(new_index.cpu().numpy(), np.where(keep, np.cumsum(keep) - 1, -1))
+    order = np.flatnonzero(~keep)[np.argsort(want[~keep], kind="stable")]
+    np.testing.assert_array_equal(offs.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(want[~keep], minlength=n))]))
+    np.testing.assert_array_equal(src.cpu().numpy()[:len(order)], order)
