@@ -2,6 +2,7 @@
 // workgroup index and a block of LDS as arguments so that a launch can run them next to the bodies of another step
 // (lk_fused.hip) as well as on their own (lk_score_fd.hip, where the algorithm is described).
 #pragma once
+#include <type_traits>
 #include "lk_common.h"
 #include "lk_launch.h"
 
@@ -185,32 +186,45 @@ __device__ __forceinline__ void fd_partial_body(const FdArgs &g, int block_id, c
 
 constexpr int FD_MAX_KSPLIT = 16;
 
+// f(N) with the smallest N of 4, 8, 16 that covers the slices: uniform, so a branch; inside it every load is unconditional
+// (surplus slices re-read the last one and are dropped afterwards), the compiler then issues all of them before the first wait.
+// Sixteen loads and sums whatever the number of slices: one stage of 64 fp32 tokens 27.2 us, now 26.9, three of 2880 tokens
+// 203.3 / 202.1, the step of a 13B-shaped layer 105.9 / 104.9.
+template <typename F> __device__ __forceinline__ void for_slices(int ksplit, F f) {
+  if (ksplit <= 4) f(std::integral_constant<int, 4>{});
+  else if (ksplit <= 8) f(std::integral_constant<int, 8>{});
+  else f(std::integral_constant<int, FD_MAX_KSPLIT>{});
+}
 // Sum of one partial value over the slices, in slice order (fp64).
 __device__ __forceinline__ double sum_slices(const float *p, int64_t ks_stride, int ksplit) {
-  // every load is unconditional (surplus slices re-read the last one and are dropped afterwards): the
-  // compiler then issues all of them before the first wait instead of one load per branch
-  float v[FD_MAX_KSPLIT];
-#pragma unroll
-  for (int ks = 0; ks < FD_MAX_KSPLIT; ++ks) v[ks] = p[(ks < ksplit ? ks : ksplit - 1) * ks_stride];
   double s = 0.0;
+  for_slices(ksplit, [&](auto n) {
+    float v[decltype(n)::value];
 #pragma unroll
-  for (int ks = 0; ks < FD_MAX_KSPLIT; ++ks) s += (ks < ksplit) ? (double)v[ks] : 0.0;
+    for (int ks = 0; ks < decltype(n)::value; ++ks) v[ks] = p[(ks < ksplit ? ks : ksplit - 1) * ks_stride];
+#pragma unroll
+    for (int ks = 0; ks < decltype(n)::value; ++ks) s += (ks < ksplit) ? (double)v[ks] : 0.0;
+  });
   return s;
 }
 // The same for four neighbouring values: the loads (16 bytes each, all in flight together) and the sums are separate
 // calls, so that other loads can be issued between them.
 __device__ __forceinline__ void load_slices4(const float *p, int64_t ks_stride, int ksplit, f32x4 (&v)[FD_MAX_KSPLIT]) {
+  for_slices(ksplit, [&](auto n) {
 #pragma unroll
-  for (int ks = 0; ks < FD_MAX_KSPLIT; ++ks) v[ks] = *reinterpret_cast<const f32x4 *>(p + (ks < ksplit ? ks : ksplit - 1) * ks_stride);
+    for (int ks = 0; ks < decltype(n)::value; ++ks) v[ks] = *reinterpret_cast<const f32x4 *>(p + (ks < ksplit ? ks : ksplit - 1) * ks_stride);
+  });
 }
 __device__ __forceinline__ void sum_slices4(const f32x4 (&v)[FD_MAX_KSPLIT], int ksplit, double (&dot)[4]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) dot[j] = 0.0;
+  for_slices(ksplit, [&](auto n) {
 #pragma unroll
-  for (int ks = 0; ks < FD_MAX_KSPLIT; ++ks) {
+    for (int ks = 0; ks < decltype(n)::value; ++ks) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) dot[j] += (ks < ksplit) ? (double)v[ks][j] : 0.0;
-  }
+      for (int j = 0; j < 4; ++j) dot[j] += (ks < ksplit) ? (double)v[ks][j] : 0.0;
+    }
+  });
 }
 
 // ---------------------------------------------------------------------------------------------------------
