@@ -5,6 +5,7 @@
 // A token b with sources a_1..a_m becomes  y_b + sum_a w_a (y_a - y_b),  w_a = xi_a / (xi_b + sum xi_a),
 // which equals the xi-weighted mean of the equation and returns y_b bit for bit when all rows are equal.
 // Sources are visited in ascending token order (grp_src), so results are reproducible run to run.
+#include <type_traits>
 #include "lk_win_body.h"
 
 namespace lk {
@@ -66,8 +67,8 @@ constexpr int ROWS_PER_WG = ROW_THREADS / WAVE;
 // 16-byte chunks per lane and segment, at most.  Launches of few rows leave waves idle and want more of them with shorter
 // lives; longer ones pay for them.  us, 8 KB rows in segments of 4 / whole: merge of three tensors 144 rows 4.9 / 6.4, 2000
 // rows 19.8 / 20.6, 4096 rows 35.6 / 34.8; of one tensor 1100 rows 6.9 / 7.5, 2880 rows 13.0 / 12.5, 16384 rows 58.8 / 49.2.
-// With squared norms (all segments of a row in one wave when this was measured) three tensors of 2880 rows 25.2 / 26.6, 5400 42.4 / 44.2, 9216
-// 71.2 / 70.7.
+// With squared norms, whose segments wait for one another, three tensors, inputs from memory: 2880 rows 29.8 / 31.8, 5400 48.6 /
+// 50.8, 6100 53.2 / 53.1, 7000 59.7 / 59.5, 9216 75.7 / 75.6.
 constexpr int ROW_MAX_U = 8, ROW_MAX_U_SHORT = 5;
 constexpr int64_t ROWS_SHORT_MAX = 2048, ROWS_SHORT_MAX_SQ = 6144;
 constexpr int64_t ROWS_STREAM_OUT_BYTES = 128ll << 20;   // inputs beyond this: nontemporal output stores
@@ -81,7 +82,7 @@ constexpr int ROWS_WIN_KEEP = 12;   // passes of 256 tokens the window partition
 //   round 3  xi of the sources and the rows of the first two sources, together
 // A row without sources is stored after round 1.  Later sources come in pairs: groups of 5 to 11 sources exist in every
 // launch, and the last of their waves is what a short launch waits for (three stages of 576 tokens 123.9 -> 120.2 us, with the
-// arguments fetched at once; one by one before).
+// arguments fetched at once; one by one before, and still where addresses are in vector registers, which have no room for two).
 //
 // Guests share the launch, because a launch or a stream fork of their own costs as much as they do:
 //   rows behind the vision span (the prompt's text, Steps 4-5): rows sum_n .. sum_n + tail_rows of the inputs move to
@@ -98,17 +99,22 @@ __device__ __forceinline__ void store16(char *p, const uint4 &v) {
   else *reinterpret_cast<u32x4 *>(p) = t4;
 }
 
-__device__ __forceinline__ float read_lane(float v, int lane) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+// v of a lane that is the same for the whole wave, in a scalar register or in a vector one
+template <bool SCALAR> __device__ __forceinline__ int lane_value(int v, int lane) {
+  return SCALAR ? __builtin_amdgcn_readlane(v, lane) : __shfl(v, lane, 64);
+}
+template <bool SCALAR> __device__ __forceinline__ float lane_value(float v, int lane) {
+  return __int_as_float(lane_value<SCALAR>(__float_as_int(v), lane));
 }
 
-// Registers: 8 chunks a lane fit three waves per SIMD (157; with vector registers for the row addresses 167, and 179 = two
-// waves left alone, merge of 21312 rows 230 us against 199), 4 need 130 and spill when held to four waves (three eager stages
-// of 2880 tokens 220.4 us against 218.2).
+// Registers: 8 chunks a lane fit three waves per SIMD (166; 179 = two waves left alone, merge of 21312 rows 230 us against 199),
+// 4 take 134 with row addresses in vector registers and 128 = four waves with scalar ones, 5 chunks 122 and 112.  Rows that are only
+// moved keep vector addresses: scalar ones took 24 registers more than eight waves have, the last three loads of an 8 KB row were
+// parked in scratch memory (2880 rows and 128 text rows 27.6 -> 35.2 us, 9216 72 -> 86).
 //
 // STREAM: the output rows are stored nontemporally (a template parameter: as a run-time choice between two stores of
 // the same value the compiler merges them into one plain store)
-template <typename T, int MODE, bool STREAM, int U>
+template <typename T, int MODE, bool STREAM, int U, bool SCALAR>
 __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 : 4)) void rows_kernel(RowArgs g, WinArgs wn) {
   using IO = RowIO<T>;
   constexpr int N = IO::N;
@@ -136,15 +142,18 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
     }
   }
   const int lane = threadIdx.x & 63;
-  // (the row is the same for all lanes, and the compiler is told: row addresses then live in scalar registers)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int64_t b = (int64_t)((int)blockIdx.x - g.n_guest_blocks) * ROWS_PER_WG + wave;
+  // SCALAR: the row is the same for all lanes, and the compiler is told: row addresses then live in scalar registers
+  const int row_wave = SCALAR ? wave : (int)(threadIdx.x >> 6);
+  using Offset = std::conditional_t<SCALAR, uint32_t, int64_t>;
+  int64_t b = (int64_t)((int)blockIdx.x - g.n_guest_blocks) * ROWS_PER_WG + row_wave;
   int seg = blockIdx.y;
-  // |x|^2 needs all segments of a row: they are waves of one workgroup then (ROWS_PER_WG / segs rows each)
+  // |x|^2 needs all segments of a row: two or four of them are waves of one workgroup then (ROWS_PER_WG / segs rows each).  Other
+  // numbers (three: bf16 rows of 10 to 15 KB in short launches) don't fill a workgroup and are taken in turn by one wave.
   const bool sq_split = MODE == 2 && which == 0 && g.x_sqnorm_out != nullptr && (g.segs == 2 || g.segs == ROWS_PER_WG);
   if (sq_split) {
     const int sh = g.segs == 2 ? 1 : 2;
-    b = (((int64_t)((int)blockIdx.x - g.n_guest_blocks) * g.segs + blockIdx.y) * ROWS_PER_WG + wave) >> sh;
+    b = (((int64_t)((int)blockIdx.x - g.n_guest_blocks) * g.segs + blockIdx.y) * ROWS_PER_WG + row_wave) >> sh;
     seg = wave & (g.segs - 1);
   }
   if (b >= g.sum_n + g.tail_rows) return;
@@ -171,7 +180,7 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int c = (sg * U + u) * WAVE + lane;
-      dst[u] = ld16(row + (uint32_t)((c < n_chunks ? c : n_chunks - 1) * 16));
+      dst[u] = ld16(row + (Offset)((c < n_chunks ? c : n_chunks - 1) * 16));
     }
   };
   if (in != nullptr) load_row(row_in, seg, v);
@@ -188,7 +197,7 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int c = (sg * U + u) * WAVE + lane;
-        if (c < n_chunks) store16<STREAM>(row_out + (uint32_t)(c * 16), v[u]);
+        if (c < n_chunks) store16<STREAM>(row_out + (Offset)(c * 16), v[u]);
       }
     }
     return;
@@ -212,8 +221,8 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
   if (MODE != 1 && m > 0) {
     const int mm = m < WAVE ? m : WAVE;
     a_l = g.grp_src[s0 + (lane < mm ? lane : mm - 1)];
-    row_a0 = in + (int64_t)__builtin_amdgcn_readlane(a_l, 0) * ld_in;
-    row_a1 = in + (int64_t)__builtin_amdgcn_readlane(a_l, mm > 1 ? 1 : 0) * ld_in;
+    row_a0 = in + (int64_t)lane_value<SCALAR>(a_l, 0) * ld_in;
+    row_a1 = in + (int64_t)lane_value<SCALAR>(a_l, mm > 1 ? 1 : 0) * ld_in;
   }
 
   float sq = 0.f;
@@ -228,7 +237,7 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
         for (int u = 0; u < HU; ++u) {
           if (hb + u < U) {
             const int c = (seg * U + hb + u) * WAVE + lane;
-            dst[u] = ld16(row + (uint32_t)((c < n_chunks ? c : n_chunks - 1) * 16));
+            dst[u] = ld16(row + (Offset)((c < n_chunks ? c : n_chunks - 1) * 16));
           }
         }
       };
@@ -237,16 +246,16 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
         for (int u = 0; u < HU; ++u) {
           if (hb + u < U) {
             const int c = (seg * U + hb + u) * WAVE + lane;
-            const uint32_t o = (uint32_t)((c < n_chunks ? c : n_chunks - 1) * 16);
+            const Offset o = (Offset)((c < n_chunks ? c : n_chunks - 1) * 16);
             va0[u] = ld16(row_a0 + o);
             va1[u] = ld16(row_a1 + o);
           }
         }
       };
       auto source_row = [&](int s) {   // source s of the group (groups of more than 64: from memory)
-        return in + (int64_t)(m <= WAVE ? __builtin_amdgcn_readlane(a_l, s) : g.grp_src[s0 + s]) * ld_in;
+        return in + (int64_t)(m <= WAVE ? lane_value<SCALAR>(a_l, s) : g.grp_src[s0 + s]) * ld_in;
       };
-      auto weight = [&](int s) { return m <= WAVE ? read_lane(w_l, s) : g.xi[g.grp_src[s0 + s]] * read_lane(w_l, 0); };
+      auto weight = [&](int s) { return m <= WAVE ? lane_value<SCALAR>(w_l, s) : g.xi[g.grp_src[s0 + s]] * lane_value<SCALAR>(w_l, 0); };
       auto add = [&](const uint4 (&src)[HU], float w, int hb, float (&acc)[HU][N]) {
 #pragma unroll
         for (int u = 0; u < HU; ++u) {
@@ -289,11 +298,18 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
             for (int e = 0; e < N; ++e) acc[u][e] = fmaf(w1, y1[e] - yb[e], fmaf(w0, y0[e] - yb[e], yb[e]));
           }
         }
-        for (int s = 2; s < m; s += 2) {   // later sources, two in flight
-          load_source(source_row(s), hb, va0);
-          if (s + 1 < m) load_source(source_row(s + 1), hb, va1);   // uniform
-          add(va0, weight(s), hb, acc);
-          if (s + 1 < m) add(va1, weight(s + 1), hb, acc);
+        if constexpr (SCALAR) {
+          for (int s = 2; s < m; s += 2) {   // later sources, two in flight
+            load_source(source_row(s), hb, va0);
+            if (s + 1 < m) load_source(source_row(s + 1), hb, va1);   // uniform
+            add(va0, weight(s), hb, acc);
+            if (s + 1 < m) add(va1, weight(s + 1), hb, acc);
+          }
+        } else {
+          for (int s = 2; s < m; ++s) {   // one by one
+            load_source(source_row(s), hb, va0);
+            add(va0, weight(s), hb, acc);
+          }
         }
 #pragma unroll
         for (int u = 0; u < HU; ++u)
@@ -303,7 +319,7 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int c = (seg * U + u) * WAVE + lane;
-      if (c < n_chunks) store16<STREAM>(row_out + (uint32_t)(c * 16), v[u]);
+      if (c < n_chunks) store16<STREAM>(row_out + (Offset)(c * 16), v[u]);
     }
     if (want_sq) {
       float t[U];
@@ -339,14 +355,21 @@ __global__ __launch_bounds__(ROW_THREADS, MODE == 1 ? 8 : (U > 5 || U == 4 ? 3 :
 }
 
 template <typename T, int U>
-static void launch_rows_u(int mode, bool stream_out, const dim3 &grid, size_t lds, hipStream_t stream, const RowArgs &g,
+static void launch_rows_u(int mode, bool stream_out, bool scalar, const dim3 &grid, size_t lds, hipStream_t stream, const RowArgs &g,
                           const WinArgs &wn) {
   const dim3 block(ROW_THREADS);
-  if (mode == 0) hipLaunchKernelGGL((rows_kernel<T, 0, false, U>), grid, block, lds, stream, g, wn);
-  else if (mode == 1 && stream_out) hipLaunchKernelGGL((rows_kernel<T, 1, true, U>), grid, block, lds, stream, g, wn);
-  else if (mode == 1) hipLaunchKernelGGL((rows_kernel<T, 1, false, U>), grid, block, lds, stream, g, wn);
-  else if (stream_out) hipLaunchKernelGGL((rows_kernel<T, 2, true, U>), grid, block, lds, stream, g, wn);
-  else hipLaunchKernelGGL((rows_kernel<T, 2, false, U>), grid, block, lds, stream, g, wn);
+  if constexpr (U <= ROW_MAX_U_SHORT) {
+    if (scalar && mode == 0) { hipLaunchKernelGGL((rows_kernel<T, 0, false, U, true>), grid, block, lds, stream, g, wn); return; }
+    if constexpr (U == 2 || U == 4) {
+      if (scalar && stream_out) { hipLaunchKernelGGL((rows_kernel<T, 2, true, U, true>), grid, block, lds, stream, g, wn); return; }
+    }
+    if (scalar && mode == 2) { hipLaunchKernelGGL((rows_kernel<T, 2, false, U, true>), grid, block, lds, stream, g, wn); return; }
+  }
+  if (mode == 0) hipLaunchKernelGGL((rows_kernel<T, 0, false, U, false>), grid, block, lds, stream, g, wn);
+  else if (mode == 1 && stream_out) hipLaunchKernelGGL((rows_kernel<T, 1, true, U, false>), grid, block, lds, stream, g, wn);
+  else if (mode == 1) hipLaunchKernelGGL((rows_kernel<T, 1, false, U, false>), grid, block, lds, stream, g, wn);
+  else if (stream_out) hipLaunchKernelGGL((rows_kernel<T, 2, true, U, false>), grid, block, lds, stream, g, wn);
+  else hipLaunchKernelGGL((rows_kernel<T, 2, false, U, false>), grid, block, lds, stream, g, wn);
 }
 
 hipError_t launch_rows(int mode, int dtype, int d, int sum_n, int batch, const RowTensors &t, const int32_t *new_index,
@@ -376,15 +399,21 @@ hipError_t launch_rows(int mode, int dtype, int d, int sum_n, int batch, const R
   const int u = (per_lane + g.segs - 1) / g.segs;
   const dim3 grid((unsigned)(g.n_guest_blocks + (sum_n + tail_rows + ROWS_PER_WG - 1) / ROWS_PER_WG),
                   (unsigned)(mode == 1 ? 1 : g.segs), 3u);
+  // Row addresses in scalar registers and later sources in pairs: the last waves of a short launch are what it waits for.  In a
+  // longer one the bytes are, and vector addresses keep more of them in flight (2772 rows of 8960 bytes and 197 text rows 33.0 us
+  // against 33.4; 16000 of 1 KB 26.8 / 29.3, of 8 KB 121.6 / 122.0; 9216 in place 43.0 / 43.6), except for bf16 rows of two to four
+  // chunks a lane, where they cost a wave per SIMD (6400 rows of 3 KB 30.4 against 27.3, 16000 63.2 / 55.9; of 4 KB 33.4 / 31.4 and
+  // 69.6 / 64.5; 16000 of 2 KB 38.2 / 37.7).
+  const bool scalar = mode != 1 && (is_short || (dtype == 1 && u >= 2 && u <= 4));
   const WinArgs wn = win ? *win : WinArgs{};
   const size_t lds = win ? win_lds : 0;
 #define LK_ROWS(TT)                                                                       \
   do {                                                                                    \
-    if (u <= 1) launch_rows_u<TT, 1>(mode, stream_out, grid, lds, stream, g, wn);         \
-    else if (u <= 2) launch_rows_u<TT, 2>(mode, stream_out, grid, lds, stream, g, wn);    \
-    else if (u <= 4) launch_rows_u<TT, 4>(mode, stream_out, grid, lds, stream, g, wn);    \
-    else if (u <= 5) launch_rows_u<TT, 5>(mode, stream_out, grid, lds, stream, g, wn);    \
-    else launch_rows_u<TT, 8>(mode, stream_out, grid, lds, stream, g, wn);                \
+    if (u <= 1) launch_rows_u<TT, 1>(mode, stream_out, scalar, grid, lds, stream, g, wn);         \
+    else if (u <= 2) launch_rows_u<TT, 2>(mode, stream_out, scalar, grid, lds, stream, g, wn);    \
+    else if (u <= 4) launch_rows_u<TT, 4>(mode, stream_out, scalar, grid, lds, stream, g, wn);    \
+    else if (u <= 5) launch_rows_u<TT, 5>(mode, stream_out, scalar, grid, lds, stream, g, wn);    \
+    else launch_rows_u<TT, 8>(mode, stream_out, scalar, grid, lds, stream, g, wn);                \
   } while (0)
   if (dtype == 1) LK_ROWS(bf16_t);
   else LK_ROWS(float);
