@@ -68,9 +68,9 @@ __host__ __device__ __forceinline__ size_t edge_lds_bytes(int max_a, int max_b) 
 // histogram (keys are dense around the median of unrelated tokens: 5184 pairs a window, half of them wanted, counting among up
 // to 256 keys in LDS 64 us a call, among up to 64 in registers 46).  With this and the launch shared with the second xi pass, three stages of
 // 2880 tokens take 316 us instead of 350.
-// ONE: the hidden axis is not split (one slice); its sixteen copies are half of the registers otherwise, and 1024 windows of
-// 36 tokens at d = 1024 beside xi take 26 us instead of 21.  ITEMS: keys per thread, the launcher's bound.
-template <bool ONE, int ITEMS>
+// RECS: room for the records of a tile, chosen by the launcher (0: here).  Sixteen where one would do are half of the registers,
+// and 1024 windows of 36 tokens at d = 1024 beside xi take 26 us instead of 21.  ITEMS: keys per thread, the launcher's bound.
+template <int RECS, int ITEMS>
 __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs &q, int w, char *lds) {
   EdgeLds &L = *reinterpret_cast<EdgeLds *>(lds);
   uint32_t *keys = reinterpret_cast<uint32_t *>(lds + sizeof(EdgeLds));   // [nA][pitch]
@@ -111,56 +111,54 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
     const int la = u / n4, lb = (u - la * n4) * 4;
     return g.partial + (int64_t)tile_of(la, lb) * FD_TILE_FLOATS + in_tile(la) * 32 + in_tile(lb);
   };
-  f32x4 v[ONE ? 1 : FD_MAX_KSPLIT];
-  auto load_unit = [&](int u) {
-    if constexpr (ONE) v[0] = *reinterpret_cast<const f32x4 *>(unit_ptr(u));
-    else load_slices4(unit_ptr(u), ks_stride, g.ksplit, v);
-  };
-  auto sum1 = [&](const float *p) { if constexpr (ONE) return (double)*p; else return sum_slices(p, ks_stride, g.ksplit); };
-  load_unit(tid);
-  for (int i = tid; i < nA + nB; i += EDGE_THREADS) {
-    if (i < nA) L.na2[i] = sum1(g.partial + (int64_t)tile_of(i, 0) * FD_TILE_FLOATS + 32 * 32 + in_tile(i));
-    else L.nb2[i - nA] = sum1(g.partial + (int64_t)tile_of(0, i - nA) * FD_TILE_FLOATS + 32 * 32 + 32 + in_tile(i - nA));
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
-  if (lane == 0) L.wsum[wave] = before;
-  if (tid == 0) { L.n_cand = 0; L.n_slots = 0; }
-  __syncthreads();
-  int edge_base = 0;
-#pragma unroll
-  for (int i = 0; i < EDGE_WAVES; ++i) edge_base += L.wsum[i];
-
-  // ---- FD of every pair -> order-preserving key in LDS
   const int pitch = nB | 1;   // odd: a thread per row and a thread per column both walk the array without bank conflicts
+  int edge_base = 0;
   uint32_t lo = 0xffffffffu, hi = 0u;   // the range the keys span
-  for (int u0 = 0; u0 < units; u0 += EDGE_THREADS) {   // uniform
-    const int u = u0 + tid;
-    double dot[4];
-    if constexpr (ONE) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) dot[j] = (double)v[0][j];
-    } else {
-      sum_slices4(v, g.ksplit, dot);
+  auto fill_keys = [&](auto n) {
+    constexpr int N = decltype(n)::value;
+    f32x4 v[N];
+    load_records4(unit_ptr(tid), ks_stride, g.ksplit, v);
+    for (int i = tid; i < nA + nB; i += EDGE_THREADS) {
+      const float *p = i < nA ? g.partial + (int64_t)tile_of(i, 0) * FD_TILE_FLOATS + 32 * 32 + in_tile(i)
+                              : g.partial + (int64_t)tile_of(0, i - nA) * FD_TILE_FLOATS + 32 * 32 + 32 + in_tile(i - nA);
+      const double n2 = sum_records<N>(p, ks_stride, g.ksplit);
+      if (i < nA) L.na2[i] = n2;
+      else L.nb2[i - nA] = n2;
     }
-    if (u0 + EDGE_THREADS < units) load_unit(u + EDGE_THREADS);
-    if (u < units) {
-      const int la = u / n4, lb0 = (u - la * n4) * 4;
-      const double a2 = L.na2[la];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int lb = lb0 + j;
-        if (lb < nB) {
-          float f = (float)divergence(g.metric, dot[j], a2, L.nb2[lb]);
-          if (!(f >= 0.f)) f = __uint_as_float(0x7f800000u);   // NaN ranks last, like +inf
-          const uint32_t key = f32_order_key(f);
-          keys[la * pitch + lb] = key;
-          lo = key < lo ? key : lo;
-          hi = key > hi ? key : hi;
+    for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
+    if (lane == 0) L.wsum[wave] = before;
+    if (tid == 0) { L.n_cand = 0; L.n_slots = 0; }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < EDGE_WAVES; ++i) edge_base += L.wsum[i];
+
+    // ---- FD of every pair -> order-preserving key in LDS
+    for (int u0 = 0; u0 < units; u0 += EDGE_THREADS) {   // uniform
+      const int u = u0 + tid;
+      double dot[4];
+      sum_records4(v, g.ksplit, dot);
+      if (u0 + EDGE_THREADS < units) load_records4(unit_ptr(u + EDGE_THREADS), ks_stride, g.ksplit, v);
+      if (u < units) {
+        const int la = u / n4, lb0 = (u - la * n4) * 4;
+        const double a2 = L.na2[la];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int lb = lb0 + j;
+          if (lb < nB) {
+            float f = (float)divergence(g.metric, dot[j], a2, L.nb2[lb]);
+            if (!(f >= 0.f)) f = __uint_as_float(0x7f800000u);   // NaN ranks last, like +inf
+            const uint32_t key = f32_order_key(f);
+            keys[la * pitch + lb] = key;
+            lo = key < lo ? key : lo;
+            hi = key > hi ? key : hi;
+          }
         }
       }
     }
-  }
+  };
+  if constexpr (RECS > 0) fill_keys(std::integral_constant<int, RECS>{});
+  else for_records(g.ksplit, fill_keys);
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
     const uint32_t l2 = __shfl_xor(lo, o, 64), h2 = __shfl_xor(hi, o, 64);
@@ -388,7 +386,8 @@ struct EdgeKeysLds {
   double na2[32], nb2[32];
   int rtok[64];
 };
-__device__ __forceinline__ void edge_keys_body(const FdArgs &g, const EdgeArgs &q, int tile, char *lds) {
+template <int N>
+__device__ __forceinline__ void edge_keys_records(const FdArgs &g, const EdgeArgs &q, int tile, char *lds) {
   EdgeKeysLds &L = *reinterpret_cast<EdgeKeysLds *>(lds);
   const int per = g.mt * g.nt;
   const int tid = threadIdx.x;
@@ -399,32 +398,27 @@ __device__ __forceinline__ void edge_keys_body(const FdArgs &g, const EdgeArgs &
   const int64_t ks_stride = (int64_t)g.n_tiles * FD_TILE_FLOATS;
   const float *base = g.partial + (int64_t)tile * FD_TILE_FLOATS;
   // Four pairs per thread: neighbouring columns of a row where the slices are what takes time (one 16-byte load each).  With a
-  // single slice (any problem of 1024 tiles or more) every eighth row of one column, one load a pair, so that a wave writes
+  // single slice every eighth row of one column, one load a pair, so that a wave writes
   // whole runs of the matrix: 64 windows of 576 tokens at d = 256 33 -> 21 us (sixteen copies of each load before).
-  const bool one = g.ksplit == 1;   // uniform
+  constexpr bool one = N == 1;
   const int r0 = one ? tid >> 5 : tid >> 3, c0 = one ? tid & 31 : (tid & 7) * 4;
   const int dr = one ? 8 : 0, dc = one ? 0 : 1;
-  f32x4 v[FD_MAX_KSPLIT];
-  if (one) {
+  f32x4 v[N];
+  if constexpr (one) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[0][j] = base[(r0 + 8 * j) * 32 + c0];
   } else {
-    load_slices4(base + r0 * 32 + c0, ks_stride, g.ksplit, v);
+    load_records4(base + r0 * 32 + c0, ks_stride, g.ksplit, v);
   }
   if (tid < 64) {
     // |a|^2 was accumulated by the first tile of this row of tiles, |b|^2 by the first tile of this column of tiles
     const int i = tid & 31;
-    if (tid < 32) L.na2[i] = sum_slices(g.partial + (int64_t)(w * per + mt * g.nt) * FD_TILE_FLOATS + 32 * 32 + i, ks_stride, g.ksplit);
-    else L.nb2[i] = sum_slices(g.partial + (int64_t)(w * per + nt) * FD_TILE_FLOATS + 32 * 32 + 32 + i, ks_stride, g.ksplit);
+    if (tid < 32) L.na2[i] = sum_records<N>(g.partial + (int64_t)(w * per + mt * g.nt) * FD_TILE_FLOATS + 32 * 32 + i, ks_stride, g.ksplit);
+    else L.nb2[i] = sum_records<N>(g.partial + (int64_t)(w * per + nt) * FD_TILE_FLOATS + 32 * 32 + 32 + i, ks_stride, g.ksplit);
     L.rtok[tid] = reinterpret_cast<const int32_t *>(base + FD_TOK_OFFSET)[tid];   // tokens of the 32 rows, then of the 32 columns
   }
   double dot[4];
-  if (one) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) dot[j] = (double)v[0][j];
-  } else {
-    sum_slices4(v, g.ksplit, dot);
-  }
+  sum_records4(v, g.ksplit, dot);
   __syncthreads();
   uint32_t *M = q.big_keys + (size_t)w * q.big_stride;
   const int pitch = wi.nB;
@@ -435,6 +429,10 @@ __device__ __forceinline__ void edge_keys_body(const FdArgs &g, const EdgeArgs &
     if (!(f >= 0.f) || L.rtok[r] < 0 || L.rtok[32 + c] < 0) f = __uint_as_float(0x7f800000u);   // NaN ranks last, like +inf
     if (la < wi.nA && lb < wi.nB) M[(size_t)la * pitch + lb] = f32_order_key(f);
   }
+}
+__device__ __forceinline__ void edge_keys_body(const FdArgs &g, const EdgeArgs &q, int tile, char *lds) {
+  if (g.ksplit > 1) for_records(g.ksplit, [&](auto n) { edge_keys_records<decltype(n)::value>(g, q, tile, lds); });   // uniform
+  else edge_keys_records<1>(g, q, tile, lds);
 }
 
 }  // namespace lk

@@ -184,47 +184,41 @@ __device__ __forceinline__ void fd_partial_body(const FdArgs &g, int block_id, c
   }
 }
 
-constexpr int FD_MAX_KSPLIT = 16;
+constexpr int FD_MAX_RECS = 16;   // records of partial sums per tile
 
-// f(N) with the smallest N of 4, 8, 16 that covers the slices: uniform, so a branch; inside it every load is unconditional
-// (surplus slices re-read the last one and are dropped afterwards), the compiler then issues all of them before the first wait.
-// Sixteen loads and sums whatever the number of slices: one stage of 64 fp32 tokens 27.2 us, now 26.9, three of 2880 tokens
-// 203.3 / 202.1, the step of a 13B-shaped layer 105.9 / 104.9.
-template <typename F> __device__ __forceinline__ void for_slices(int ksplit, F f) {
-  if (ksplit <= 4) f(std::integral_constant<int, 4>{});
-  else if (ksplit <= 8) f(std::integral_constant<int, 8>{});
-  else f(std::integral_constant<int, FD_MAX_KSPLIT>{});
+// f(N) with the smallest N of 4, 8, 16 that covers a tile's records: uniform, so a branch, and ONE for a whole body: an array of
+// loads that lives across two such branches ends in scratch memory (80 windows of 30 tokens, d = 4096, 64 prompt rows, scores and
+// selection 26.9 us, so 25.8; 20 of 96 tokens 32.6 / 32.0).  Inside it every load is unconditional (surplus records
+// re-read the last one and are dropped afterwards), the compiler then issues all of them before the first wait.
+template <typename F> __device__ __forceinline__ void for_records(int recs, F f) {
+  if (recs > 8) f(std::integral_constant<int, FD_MAX_RECS>{});   // first: it takes the most registers, and two fewer in this place
+  else if (recs <= 4) f(std::integral_constant<int, 4>{});
+  else f(std::integral_constant<int, 8>{});
 }
-// Sum of one partial value over the slices, in slice order (fp64).
-__device__ __forceinline__ double sum_slices(const float *p, int64_t ks_stride, int ksplit) {
+// Sum of one partial value over the records, in their order (fp64).
+template <int N> __device__ __forceinline__ double sum_records(const float *p, int64_t stride, int recs) {
+  float v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = p[(i < recs ? i : recs - 1) * stride];
   double s = 0.0;
-  for_slices(ksplit, [&](auto n) {
-    float v[decltype(n)::value];
 #pragma unroll
-    for (int ks = 0; ks < decltype(n)::value; ++ks) v[ks] = p[(ks < ksplit ? ks : ksplit - 1) * ks_stride];
-#pragma unroll
-    for (int ks = 0; ks < decltype(n)::value; ++ks) s += (ks < ksplit) ? (double)v[ks] : 0.0;
-  });
+  for (int i = 0; i < N; ++i) s += (i < recs) ? (double)v[i] : 0.0;
   return s;
 }
 // The same for four neighbouring values: the loads (16 bytes each, all in flight together) and the sums are separate
 // calls, so that other loads can be issued between them.
-__device__ __forceinline__ void load_slices4(const float *p, int64_t ks_stride, int ksplit, f32x4 (&v)[FD_MAX_KSPLIT]) {
-  for_slices(ksplit, [&](auto n) {
+template <int N> __device__ __forceinline__ void load_records4(const float *p, int64_t stride, int recs, f32x4 (&v)[N]) {
 #pragma unroll
-    for (int ks = 0; ks < decltype(n)::value; ++ks) v[ks] = *reinterpret_cast<const f32x4 *>(p + (ks < ksplit ? ks : ksplit - 1) * ks_stride);
-  });
+  for (int i = 0; i < N; ++i) v[i] = *reinterpret_cast<const f32x4 *>(p + (i < recs ? i : recs - 1) * stride);
 }
-__device__ __forceinline__ void sum_slices4(const f32x4 (&v)[FD_MAX_KSPLIT], int ksplit, double (&dot)[4]) {
+template <int N> __device__ __forceinline__ void sum_records4(const f32x4 (&v)[N], int recs, double (&dot)[4]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) dot[j] = 0.0;
-  for_slices(ksplit, [&](auto n) {
 #pragma unroll
-    for (int ks = 0; ks < decltype(n)::value; ++ks) {
+  for (int i = 0; i < N; ++i) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) dot[j] += (ks < ksplit) ? (double)v[ks][j] : 0.0;
-    }
-  });
+    for (int j = 0; j < 4; ++j) dot[j] += (i < recs) ? (double)v[i][j] : 0.0;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -241,7 +235,8 @@ __host__ __device__ __forceinline__ int fd_epilogue_blocks(int n_rowblocks, int 
   return n_rowblocks << (fd_epilogue_tpr_shift(group, nt) - 3);
 }
 
-__device__ __forceinline__ void fd_epilogue_body(const FdArgs &g, int block_id, char *lds) {
+template <int N>
+__device__ __forceinline__ void fd_epilogue_records(const FdArgs &g, int block_id, char *lds) {
   double *nb2 = reinterpret_cast<double *>(lds);          // [FD_MAX_COLS]
   double *na2 = nb2 + FD_MAX_COLS;                        // [32]
   const int64_t ks_stride = (int64_t)g.n_tiles * FD_TILE_FLOATS;
@@ -268,14 +263,14 @@ __device__ __forceinline__ void fd_epilogue_body(const FdArgs &g, int block_id, 
   const float *prow = g.partial + (int64_t)tile_row0 * FD_TILE_FLOATS + row_in_block * 32 + (sub & 7) * 4;
   // (a column tile past the window's: clamped, its values are dropped below)
   auto tile_at = [&](int t) { return prow + (int64_t)(t < ncol_tiles ? t : ncol_tiles - 1) * FD_TILE_FLOATS; };
-  f32x4 v[FD_MAX_KSPLIT];
-  load_slices4(tile_at(sub >> 3), ks_stride, g.ksplit, v);
+  f32x4 v[N];
+  load_records4(tile_at(sub >> 3), ks_stride, g.ksplit, v);
   for (int c = threadIdx.x; c < ncol_tiles * 32 + 32; c += FD_THREADS) {
     if (c < ncol_tiles * 32)
-      nb2[c] = sum_slices(g.partial + (int64_t)(tile_col0 + (c >> 5)) * FD_TILE_FLOATS + 32 * 32 + 32 + (c & 31),
+      nb2[c] = sum_records<N>(g.partial + (int64_t)(tile_col0 + (c >> 5)) * FD_TILE_FLOATS + 32 * 32 + 32 + (c & 31),
                           ks_stride, g.ksplit);
     else
-      na2[c - ncol_tiles * 32] = sum_slices(g.partial + (int64_t)tile_row0 * FD_TILE_FLOATS + 32 * 32 + (c - ncol_tiles * 32),
+      na2[c - ncol_tiles * 32] = sum_records<N>(g.partial + (int64_t)tile_row0 * FD_TILE_FLOATS + 32 * 32 + (c - ncol_tiles * 32),
                                             ks_stride, g.ksplit);
   }
   const int col_cap = (g.group > 1) ? g.slot : g.nt * 32;   // columns this launch really tiled
@@ -304,8 +299,8 @@ __device__ __forceinline__ void fd_epilogue_body(const FdArgs &g, int block_id, 
   for (int t0 = 0; t0 < ncol_tiles; t0 += t_step) {   // uniform
     const int t = t0 + (sub >> 3);
     double dot[4];
-    sum_slices4(v, g.ksplit, dot);
-    if (t0 + t_step < ncol_tiles) load_slices4(tile_at(t + t_step), ks_stride, g.ksplit, v);
+    sum_records4(v, g.ksplit, dot);
+    if (t0 + t_step < ncol_tiles) load_records4(tile_at(t + t_step), ks_stride, g.ksplit, v);
     const int tc0 = t * 32 + (sub & 7) * 4;   // first of this thread's columns inside the block's tile row
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -348,6 +343,10 @@ __device__ __forceinline__ void fd_epilogue_body(const FdArgs &g, int block_id, 
   }
 }
 
+__device__ __forceinline__ void fd_epilogue_body(const FdArgs &g, int block_id, char *lds) {
+  for_records(g.ksplit, [&](auto n) { fd_epilogue_records<decltype(n)::value>(g, block_id, lds); });
+}
+
 // ---------------------------------------------------------------------------------------------------------
 // Windows that fit one 32 x 32 tile (at most 64 tokens): the epilogue AND the per-window selection (paper Step 2:
 // the r A nodes with the lowest FD) in one kernel.  fd_partial_kernel leaves the partial tiles; one workgroup per
@@ -374,7 +373,8 @@ struct SmallTileLds {
 // Latency bound: every global load of the kernel is independent of the others (the token lists of the tile come from
 // the record fd_partial_kernel left with slice 0; a thread's four columns are one 16-byte load per slice), so all of
 // them are one trip to memory -- thread-per-value loads were four trips in a row (10 us a launch).
-__device__ __forceinline__ void fd_tail_select_body(const FdArgs &g, const SmallSelArgs &q, int tile, char *lds) {
+template <int N>
+__device__ __forceinline__ void fd_tail_select_records(const FdArgs &g, const SmallSelArgs &q, int tile, char *lds) {
   SmallTileLds &L = *reinterpret_cast<SmallTileLds *>(lds);
   const int tid = threadIdx.x;
   const int64_t ks_stride = (int64_t)g.n_tiles * FD_TILE_FLOATS;
@@ -385,8 +385,8 @@ __device__ __forceinline__ void fd_tail_select_body(const FdArgs &g, const Small
 
   // ---- products (everyone), metadata and squared norms (wave 0)
   // a tile without A rows or without B rows has no sums from fd_partial_kernel: they are not used either
-  f32x4 v[FD_MAX_KSPLIT];
-  load_slices4(base + rr0 * 32 + cl * 4, ks_stride, g.ksplit, v);
+  f32x4 v[N];
+  load_records4(base + rr0 * 32 + cl * 4, ks_stride, g.ksplit, v);
   if (tid < 64) {
     const int m_tok = reinterpret_cast<const int32_t *>(base + FD_TOK_OFFSET)[tid];   // rows 0..31, then columns 0..31
     const int rr = tid & 31;
@@ -394,7 +394,7 @@ __device__ __forceinline__ void fd_tail_select_body(const FdArgs &g, const Small
     const int wc = w < g.n_windows ? w : g.n_windows - 1;
     int m_off = g.win_offsets[wc], m_end = g.win_offsets[wc + 1], m_rem = q.win_remove[wc];
     if (w >= g.n_windows) { m_end = m_off; m_rem = 0; }
-    L.n2[tid >> 5][tid & 31] = sum_slices(base + 32 * 32 + tid, ks_stride, g.ksplit);
+    L.n2[tid >> 5][tid & 31] = sum_records<N>(base + 32 * 32 + tid, ks_stride, g.ksplit);
     if (tid < 32) L.row_tok[tid] = m_tok; else L.col_tok[tid - 32] = m_tok;
     const unsigned long long cm = __ballot(tid >= 32 && m_tok >= 0);
     if (tid == 0) L.col_mask = (uint32_t)(cm >> 32);
@@ -409,7 +409,7 @@ __device__ __forceinline__ void fd_tail_select_body(const FdArgs &g, const Small
     }
   }
   double dots[4];
-  sum_slices4(v, g.ksplit, dots);
+  sum_records4(v, g.ksplit, dots);
   __syncthreads();
 
   // ---- FD and first minimum per row
@@ -497,6 +497,10 @@ __device__ __forceinline__ void fd_tail_select_body(const FdArgs &g, const Small
       }
     }
   }
+}
+
+__device__ __forceinline__ void fd_tail_select_body(const FdArgs &g, const SmallSelArgs &q, int tile, char *lds) {
+  for_records(g.ksplit, [&](auto n) { fd_tail_select_records<decltype(n)::value>(g, q, tile, lds); });
 }
 
 // Arguments of the small-window kernels from a plan and the caller's tensors (host side).

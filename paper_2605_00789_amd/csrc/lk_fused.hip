@@ -66,7 +66,7 @@ __global__ __launch_bounds__(XI_THREADS) void colsum_edges_kernel(XiArgs x, int 
   extern __shared__ __attribute__((aligned(16))) char dyn_lds[];
   if ((int)blockIdx.x >= n_fd_blocks) xi_colsum_body<T, DH, RW, VISION_LSE>(x, blockIdx.x - n_fd_blocks, dyn_lds);
   else if (q.max_a > EDGE_MAX_SIDE) edge_keys_body(f, q, blockIdx.x, dyn_lds);
-  else edge_select_body<false, EDGE_ITEMS>(f, q, blockIdx.x, dyn_lds);
+  else edge_select_body<0, EDGE_ITEMS>(f, q, blockIdx.x, dyn_lds);
 }
 
 template <typename T, int DH, int RW, bool VISION_LSE>

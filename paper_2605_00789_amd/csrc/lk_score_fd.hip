@@ -90,7 +90,7 @@ static FdPlan plan_tiles(int n_windows, int maxA, int maxB, int d, int dtype_byt
   auto split = [&](int target, int longest) {
     int ks = 1;
     while (((int64_t)p.n_tiles * ks < target || ((int64_t)p.n_tiles * ks < FD_ROOM_WGS && pieces > longest * ks)) &&
-           ks * 2 <= max_ks && ks * 2 <= FD_MAX_KSPLIT)
+           ks * 2 <= max_ks && ks * 2 <= FD_MAX_RECS)
       ks *= 2;
     return ks;
   };

@@ -36,11 +36,11 @@
 
 namespace lk {
 
-template <bool ONE, int ITEMS>
+template <int RECS, int ITEMS>
 __global__ __launch_bounds__(EDGE_THREADS, ITEMS == EDGE_ITEMS ? 2 : 3) void edge_select_kernel(FdArgs g, EdgeArgs q) {
   fetch_args<FdArgs, EdgeArgs>();
   extern __shared__ __attribute__((aligned(16))) char edge_lds[];
-  edge_select_body<ONE, ITEMS>(g, q, blockIdx.x, edge_lds);
+  edge_select_body<RECS, ITEMS>(g, q, blockIdx.x, edge_lds);
 }
 __global__ __launch_bounds__(EDGE_THREADS) void edge_keys_kernel(FdArgs g, EdgeArgs q) {
   fetch_args<FdArgs, EdgeArgs>();
@@ -274,19 +274,22 @@ hipError_t launch_edge_select(const FdArgs &g, const EdgeArgs &q, int dtype, hip
   }
   static std::atomic<bool> allowed[64];   // more dynamic LDS than the 64 KB default, set once per device
   using Kernel = void (*)(FdArgs, EdgeArgs);
-  static const Kernel kernels[2][2] = {{edge_select_kernel<false, EDGE_ITEMS_SMALL>, edge_select_kernel<false, EDGE_ITEMS>},
-                                       {edge_select_kernel<true, EDGE_ITEMS_SMALL>, edge_select_kernel<true, EDGE_ITEMS>}};
+  static const Kernel kernels[4][2] = {{edge_select_kernel<1, EDGE_ITEMS_SMALL>, edge_select_kernel<1, EDGE_ITEMS>},
+                                       {edge_select_kernel<4, EDGE_ITEMS_SMALL>, edge_select_kernel<4, EDGE_ITEMS>},
+                                       {edge_select_kernel<8, EDGE_ITEMS_SMALL>, edge_select_kernel<8, EDGE_ITEMS>},
+                                       {edge_select_kernel<16, EDGE_ITEMS_SMALL>, edge_select_kernel<16, EDGE_ITEMS>}};
+  static_assert(FD_MAX_RECS == 16, "the last row serves every number of records");
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (!allowed[dev].load(std::memory_order_acquire)) {
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 8; ++i) {
       e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernels[i >> 1][i & 1]), hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)edge_lds_bytes(EDGE_MAX_SIDE, EDGE_MAX_SIDE));
       if (e != hipSuccess) return e;
     }
     allowed[dev].store(true, std::memory_order_release);
   }
-  const Kernel k = kernels[g.ksplit == 1][q.max_a * q.max_b > EDGE_ITEMS_SMALL * EDGE_THREADS];
+  const Kernel k = kernels[g.ksplit == 1 ? 0 : g.ksplit <= 4 ? 1 : g.ksplit <= 8 ? 2 : 3][q.max_a * q.max_b > EDGE_ITEMS_SMALL * EDGE_THREADS];
   hipLaunchKernelGGL(k, dim3((unsigned)g.n_windows), dim3(EDGE_THREADS), edge_lds_bytes(q.max_a, q.max_b), stream, g, q);
   return hipGetLastError();
 }

@@ -41,3 +41,14 @@ def test_no_row_kernel_keeps_its_loads_in_scratch_memory():
     assert len(rows) >= 50
     scratch = {k: m[".private_segment_fixed_size"] for k, m in rows.items() if m[".private_segment_fixed_size"]}
     assert not scratch, scratch
+
+
+def test_no_finishing_kernel_keeps_its_loads_in_scratch_memory():
+    """The same for the kernels that sum the records of a split hidden axis.  One variant (sixteen records, at most four keys a
+    thread) keeps three words there."""
+    from paper_2605_00789_amd import binding as B
+    names = ("fd_tail_select", "fd_epilogue", "colsum_tail", "colsum_edges", "edge_keys", "edge_select")
+    kernels = {k: m for k, m in _kernels(B.lib_path()).items() if any(n in k for n in names)}
+    assert all(any(n in k for k in kernels) for n in names)
+    scratch = {k: m[".private_segment_fixed_size"] for k, m in kernels.items() if m[".private_segment_fixed_size"]}
+    assert all("edge_select_kernelILi16ELi4E" in k and size <= 12 for k, size in scratch.items()), scratch
