@@ -117,11 +117,11 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
   auto fill_keys = [&](auto n) {
     constexpr int N = decltype(n)::value;
     f32x4 v[N];
-    load_records4(unit_ptr(tid), ks_stride, g.ksplit, v);
+    load_records4(unit_ptr(tid), ks_stride, g.recs, v);
     for (int i = tid; i < nA + nB; i += EDGE_THREADS) {
       const float *p = i < nA ? g.partial + (int64_t)tile_of(i, 0) * FD_TILE_FLOATS + 32 * 32 + in_tile(i)
                               : g.partial + (int64_t)tile_of(0, i - nA) * FD_TILE_FLOATS + 32 * 32 + 32 + in_tile(i - nA);
-      const double n2 = sum_records<N>(p, ks_stride, g.ksplit);
+      const double n2 = sum_records<N>(p, ks_stride, g.recs);
       if (i < nA) L.na2[i] = n2;
       else L.nb2[i - nA] = n2;
     }
@@ -137,8 +137,8 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
     for (int u0 = 0; u0 < units; u0 += EDGE_THREADS) {   // uniform
       const int u = u0 + tid;
       double dot[4];
-      sum_records4(v, g.ksplit, dot);
-      if (u0 + EDGE_THREADS < units) load_records4(unit_ptr(u + EDGE_THREADS), ks_stride, g.ksplit, v);
+      sum_records4(v, g.recs, dot);
+      if (u0 + EDGE_THREADS < units) load_records4(unit_ptr(u + EDGE_THREADS), ks_stride, g.recs, v);
       if (u < units) {
         const int la = u / n4, lb0 = (u - la * n4) * 4;
         const double a2 = L.na2[la];
@@ -158,7 +158,7 @@ __device__ __forceinline__ void edge_select_body(const FdArgs &g, const EdgeArgs
     }
   };
   if constexpr (RECS > 0) fill_keys(std::integral_constant<int, RECS>{});
-  else for_records(g.ksplit, fill_keys);
+  else for_records(g.recs, fill_keys);
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
     const uint32_t l2 = __shfl_xor(lo, o, 64), h2 = __shfl_xor(hi, o, 64);
@@ -408,17 +408,17 @@ __device__ __forceinline__ void edge_keys_records(const FdArgs &g, const EdgeArg
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[0][j] = base[(r0 + 8 * j) * 32 + c0];
   } else {
-    load_records4(base + r0 * 32 + c0, ks_stride, g.ksplit, v);
+    load_records4(base + r0 * 32 + c0, ks_stride, g.recs, v);
   }
   if (tid < 64) {
     // |a|^2 was accumulated by the first tile of this row of tiles, |b|^2 by the first tile of this column of tiles
     const int i = tid & 31;
-    if (tid < 32) L.na2[i] = sum_records<N>(g.partial + (int64_t)(w * per + mt * g.nt) * FD_TILE_FLOATS + 32 * 32 + i, ks_stride, g.ksplit);
-    else L.nb2[i] = sum_records<N>(g.partial + (int64_t)(w * per + nt) * FD_TILE_FLOATS + 32 * 32 + 32 + i, ks_stride, g.ksplit);
+    if (tid < 32) L.na2[i] = sum_records<N>(g.partial + (int64_t)(w * per + mt * g.nt) * FD_TILE_FLOATS + 32 * 32 + i, ks_stride, g.recs);
+    else L.nb2[i] = sum_records<N>(g.partial + (int64_t)(w * per + nt) * FD_TILE_FLOATS + 32 * 32 + 32 + i, ks_stride, g.recs);
     L.rtok[tid] = reinterpret_cast<const int32_t *>(base + FD_TOK_OFFSET)[tid];   // tokens of the 32 rows, then of the 32 columns
   }
   double dot[4];
-  sum_records4(v, g.ksplit, dot);
+  sum_records4(v, g.recs, dot);
   __syncthreads();
   uint32_t *M = q.big_keys + (size_t)w * q.big_stride;
   const int pitch = wi.nB;
@@ -431,7 +431,7 @@ __device__ __forceinline__ void edge_keys_records(const FdArgs &g, const EdgeArg
   }
 }
 __device__ __forceinline__ void edge_keys_body(const FdArgs &g, const EdgeArgs &q, int tile, char *lds) {
-  if (g.ksplit > 1) for_records(g.ksplit, [&](auto n) { edge_keys_records<decltype(n)::value>(g, q, tile, lds); });   // uniform
+  if (g.recs > 1) for_records(g.recs, [&](auto n) { edge_keys_records<decltype(n)::value>(g, q, tile, lds); });   // uniform
   else edge_keys_records<1>(g, q, tile, lds);
 }
 

@@ -22,7 +22,7 @@ struct FdArgs {
   float *partial;
   float *best_fd;
   int32_t *best_dst;
-  int slot, group, mt, nt, n_tiles, ksplit, n_spans, spans_per_wg;
+  int slot, group, mt, nt, n_tiles, ksplit, n_spans, spans_per_wg, chain, recs;
   int metric;   // 0: 1 - cos, 1: |a - b|, 2: |a - b|^2
   int dir;      // 0: even list positions propose, 1: odd ones, PAIR_DIR: all to all others (side_a / pos_a)
   unsigned long long *pair_keys;   // PAIR_DIR: where the epilogue files (FD bits << 32 | neighbour's position) by list
@@ -49,7 +49,7 @@ __device__ __forceinline__ double divergence(int metric, double dot, double a2, 
 // the four waves' sums.
 constexpr int FD_STAGE_BYTES = FD_WAVES * 128;
 constexpr int FD_STAGE_PITCH = FD_STAGE_BYTES + 16;
-constexpr int FD_RED_LDS = FD_WAVES * (32 * 32 + 2 * 32) * (int)sizeof(float);
+constexpr int FD_RED_LDS = FD_WAVES * (32 * 32 + 2 * 32) * (int)sizeof(double);
 constexpr int FD_PARTIAL_LDS = 64 * FD_STAGE_PITCH > FD_RED_LDS ? 64 * FD_STAGE_PITCH : FD_RED_LDS;
 
 struct WinInfo { int off, nA, nB; };
@@ -74,9 +74,6 @@ template <typename T>
 __device__ __forceinline__ void fd_partial_body(const FdArgs &g, int block_id, char *lds) {
   using E = Elem<T>;
   constexpr int SPAN = 2 * FD_CHUNKS * E::PER_CHUNK;   // elements of a row covered by one span: 64 bytes per half wave
-
-  float (*red)[32 * 32] = reinterpret_cast<float (*)[32 * 32]>(lds);                                  // [FD_WAVES][32 * 32]
-  float (*rnorm)[2][32] = reinterpret_cast<float (*)[2][32]>(lds + FD_WAVES * 32 * 32 * sizeof(float));   // [FD_WAVES][2][32]
 
   const int tile = block_id % g.n_tiles;
   const int ks = block_id / g.n_tiles;
@@ -135,7 +132,33 @@ __device__ __forceinline__ void fd_partial_body(const FdArgs &g, int block_id, c
   };
   static_assert(SPAN * E::BYTES == 128, "a span is one 128-byte line of a row");
 
+  // The matrix cores add in fp32.  1 - cos of near-equal rows keeps what those sums lose, so their chains are kept short: in a
+  // slice of several chains (`two`, uniform) each goes into an fp64 sum, and the slice's sums leave as two floats.  Error of
+  // 1 - cos against 64 bits, rows a few percent apart, rms: 80 tiles, d = 4096, 16 slices 1.4e-8, 4 long ones added in fp32
+  // throughout 3.4e-8, so 0.8e-8; 96 tiles, d = 5120, 2.3e-8, 4.3e-8, 1.2e-8.
+  const bool two = g.recs > g.ksplit;
   f32x16 acc = {0}, na = {0}, nb = {0};
+  double sum[16], sum_a = 0.0, sum_b = 0.0;   // (of the norms this lane's diagonal element (r, r), where it holds one)
+#pragma unroll
+  for (int i = 0; i < 16; ++i) sum[i] = 0.0;
+  auto diagonal = [&](float &da, float &db) {
+    const int idx = 4 * (r >> 3) + (r & 3);
+    da = db = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      da = (i == idx) ? na[i] : da;
+      db = (i == idx) ? nb[i] : db;
+    }
+  };
+  auto flush = [&]() {
+    float da, db;
+    diagonal(da, db);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sum[i] += (double)acc[i];
+    sum_a += (double)da;
+    sum_b += (double)db;
+  };
+  int left = g.chain;
   const int s_begin = ks * g.spans_per_wg;
   const int s_end = min(s_begin + g.spans_per_wg, g.n_spans);
   const char *frag = lds + r * FD_STAGE_PITCH + wave * 128 + half * 64;
@@ -147,6 +170,7 @@ __device__ __forceinline__ void fd_partial_body(const FdArgs &g, int block_id, c
       *reinterpret_cast<uint4 *>(lds + (p * (FD_THREADS / 32) + srow) * FD_STAGE_PITCH + schunk * 16) = st[p];
     __syncthreads();
     if (s + FD_WAVES < s_end) load_piece(s + FD_WAVES);
+    if (left == g.chain) { acc = f32x16{0}; na = f32x16{0}; nb = f32x16{0}; }   // uniform: also where the last piece has no span for this wave
     if (s + wave < s_end) {
 #pragma unroll
       for (int c = 0; c < FD_CHUNKS; ++c) {
@@ -157,30 +181,46 @@ __device__ __forceinline__ void fd_partial_body(const FdArgs &g, int block_id, c
         if (need_nb) E::mma32(cb, cb, nb);
       }
     }
+    if (--left == 0 && two) {   // uniform
+      flush();
+      left = g.chain;
+    }
   }
+  if (two && left != g.chain) flush();
   __syncthreads();   // the stage becomes the reduction buffer
 
   // cross-wave sum through LDS
+  float *out = g.partial + ((int64_t)(two ? 2 * ks : ks) * g.n_tiles + tile) * FD_TILE_FLOATS;
+  const bool on_diagonal = ((r >> 2) & 1) == half;   // this lane holds the element (r, r)
+  auto add_waves = [&](auto zero, auto element, auto norm_a, auto norm_b, auto put) {
+    using S = decltype(zero);
+    S (*red)[32 * 32] = reinterpret_cast<S (*)[32 * 32]>(lds);                                  // [FD_WAVES][32 * 32]
+    S (*rnorm)[2][32] = reinterpret_cast<S (*)[2][32]>(lds + FD_WAVES * 32 * 32 * sizeof(S));   // [FD_WAVES][2][32]
 #pragma unroll
-  for (int i = 0; i < 16; ++i) red[wave][acc_row(i, lane) * 32 + r] = acc[i];
-  if (((r >> 2) & 1) == half) {   // this lane holds the diagonal element (r, r)
-    const int idx = 4 * (r >> 3) + (r & 3);
-    float da = 0.f, db = 0.f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      da = (i == idx) ? na[i] : da;
-      db = (i == idx) ? nb[i] : db;
+    for (int i = 0; i < 16; ++i) red[wave][acc_row(i, lane) * 32 + r] = element(i);
+    if (on_diagonal) {
+      rnorm[wave][0][r] = norm_a;
+      rnorm[wave][1][r] = norm_b;
     }
-    rnorm[wave][0][r] = da;
-    rnorm[wave][1][r] = db;
-  }
-  __syncthreads();
-  float *out = g.partial + ((int64_t)ks * g.n_tiles + tile) * FD_TILE_FLOATS;
-  for (int e = threadIdx.x; e < 32 * 32; e += FD_THREADS)
-    out[e] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
-  if (threadIdx.x < 64) {
-    const int which = threadIdx.x >> 5, i = threadIdx.x & 31;
-    out[32 * 32 + threadIdx.x] = (rnorm[0][which][i] + rnorm[1][which][i]) + (rnorm[2][which][i] + rnorm[3][which][i]);
+    __syncthreads();
+    for (int e = threadIdx.x; e < 32 * 32; e += FD_THREADS) put(e, (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]));
+    if (threadIdx.x < 64) {
+      const int which = threadIdx.x >> 5, i = threadIdx.x & 31;
+      put(32 * 32 + threadIdx.x, (rnorm[0][which][i] + rnorm[1][which][i]) + (rnorm[2][which][i] + rnorm[3][which][i]));
+    }
+  };
+  if (two) {
+    float *out_low = out + (int64_t)g.n_tiles * FD_TILE_FLOATS;
+    add_waves(0.0, [&](int i) { return sum[i]; }, sum_a, sum_b, [&](int e, double v) {
+      // (a sum beyond the type's largest value goes on in the second float, infinities and NaN stay what they are)
+      const float high = (float)fmax(fmin(v, 3.4028234663852886e38), -3.4028234663852886e38);
+      out[e] = high;
+      out_low[e] = (float)(v - (double)high);
+    });
+  } else {
+    float da, db;
+    diagonal(da, db);
+    add_waves(0.f, [&](int i) { return acc[i]; }, da, db, [&](int e, float v) { out[e] = v; });
   }
 }
 
@@ -264,14 +304,14 @@ __device__ __forceinline__ void fd_epilogue_records(const FdArgs &g, int block_i
   // (a column tile past the window's: clamped, its values are dropped below)
   auto tile_at = [&](int t) { return prow + (int64_t)(t < ncol_tiles ? t : ncol_tiles - 1) * FD_TILE_FLOATS; };
   f32x4 v[N];
-  load_records4(tile_at(sub >> 3), ks_stride, g.ksplit, v);
+  load_records4(tile_at(sub >> 3), ks_stride, g.recs, v);
   for (int c = threadIdx.x; c < ncol_tiles * 32 + 32; c += FD_THREADS) {
     if (c < ncol_tiles * 32)
       nb2[c] = sum_records<N>(g.partial + (int64_t)(tile_col0 + (c >> 5)) * FD_TILE_FLOATS + 32 * 32 + 32 + (c & 31),
-                          ks_stride, g.ksplit);
+                          ks_stride, g.recs);
     else
       na2[c - ncol_tiles * 32] = sum_records<N>(g.partial + (int64_t)tile_row0 * FD_TILE_FLOATS + 32 * 32 + (c - ncol_tiles * 32),
-                                            ks_stride, g.ksplit);
+                                            ks_stride, g.recs);
   }
   const int col_cap = (g.group > 1) ? g.slot : g.nt * 32;   // columns this launch really tiled
   WinInfo wi;
@@ -299,8 +339,8 @@ __device__ __forceinline__ void fd_epilogue_records(const FdArgs &g, int block_i
   for (int t0 = 0; t0 < ncol_tiles; t0 += t_step) {   // uniform
     const int t = t0 + (sub >> 3);
     double dot[4];
-    sum_records4(v, g.ksplit, dot);
-    if (t0 + t_step < ncol_tiles) load_records4(tile_at(t + t_step), ks_stride, g.ksplit, v);
+    sum_records4(v, g.recs, dot);
+    if (t0 + t_step < ncol_tiles) load_records4(tile_at(t + t_step), ks_stride, g.recs, v);
     const int tc0 = t * 32 + (sub & 7) * 4;   // first of this thread's columns inside the block's tile row
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -344,7 +384,7 @@ __device__ __forceinline__ void fd_epilogue_records(const FdArgs &g, int block_i
 }
 
 __device__ __forceinline__ void fd_epilogue_body(const FdArgs &g, int block_id, char *lds) {
-  for_records(g.ksplit, [&](auto n) { fd_epilogue_records<decltype(n)::value>(g, block_id, lds); });
+  for_records(g.recs, [&](auto n) { fd_epilogue_records<decltype(n)::value>(g, block_id, lds); });
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -386,7 +426,7 @@ __device__ __forceinline__ void fd_tail_select_records(const FdArgs &g, const Sm
   // ---- products (everyone), metadata and squared norms (wave 0)
   // a tile without A rows or without B rows has no sums from fd_partial_kernel: they are not used either
   f32x4 v[N];
-  load_records4(base + rr0 * 32 + cl * 4, ks_stride, g.ksplit, v);
+  load_records4(base + rr0 * 32 + cl * 4, ks_stride, g.recs, v);
   if (tid < 64) {
     const int m_tok = reinterpret_cast<const int32_t *>(base + FD_TOK_OFFSET)[tid];   // rows 0..31, then columns 0..31
     const int rr = tid & 31;
@@ -394,7 +434,7 @@ __device__ __forceinline__ void fd_tail_select_records(const FdArgs &g, const Sm
     const int wc = w < g.n_windows ? w : g.n_windows - 1;
     int m_off = g.win_offsets[wc], m_end = g.win_offsets[wc + 1], m_rem = q.win_remove[wc];
     if (w >= g.n_windows) { m_end = m_off; m_rem = 0; }
-    L.n2[tid >> 5][tid & 31] = sum_records<N>(base + 32 * 32 + tid, ks_stride, g.ksplit);
+    L.n2[tid >> 5][tid & 31] = sum_records<N>(base + 32 * 32 + tid, ks_stride, g.recs);
     if (tid < 32) L.row_tok[tid] = m_tok; else L.col_tok[tid - 32] = m_tok;
     const unsigned long long cm = __ballot(tid >= 32 && m_tok >= 0);
     if (tid == 0) L.col_mask = (uint32_t)(cm >> 32);
@@ -409,7 +449,7 @@ __device__ __forceinline__ void fd_tail_select_records(const FdArgs &g, const Sm
     }
   }
   double dots[4];
-  sum_records4(v, g.ksplit, dots);
+  sum_records4(v, g.recs, dots);
   __syncthreads();
 
   // ---- FD and first minimum per row
@@ -500,7 +540,7 @@ __device__ __forceinline__ void fd_tail_select_records(const FdArgs &g, const Sm
 }
 
 __device__ __forceinline__ void fd_tail_select_body(const FdArgs &g, const SmallSelArgs &q, int tile, char *lds) {
-  for_records(g.ksplit, [&](auto n) { fd_tail_select_records<decltype(n)::value>(g, q, tile, lds); });
+  for_records(g.recs, [&](auto n) { fd_tail_select_records<decltype(n)::value>(g, q, tile, lds); });
 }
 
 // Arguments of the small-window kernels from a plan and the caller's tensors (host side).
@@ -512,11 +552,10 @@ inline FdArgs make_fd_args(const FdPlan &plan, int dtype, const void *X, int64_t
   g.win_offsets = win_offsets; g.win_tokens = win_tokens;
   g.partial = partial; g.best_fd = best_fd; g.best_dst = best_dst;
   g.slot = plan.slot; g.group = plan.group; g.mt = plan.mt; g.nt = plan.nt;
-  g.n_tiles = plan.n_tiles; g.ksplit = plan.ksplit; g.metric = plan.metric; g.dir = plan.dir;
+  g.n_tiles = plan.n_tiles; g.ksplit = plan.ksplit; g.recs = plan.recs; g.metric = plan.metric; g.dir = plan.dir;
   const int span = (dtype == 1) ? 64 : 32;
   g.n_spans = (d + span - 1) / span;
-  const int pieces = (g.n_spans + FD_WAVES - 1) / FD_WAVES;
-  g.spans_per_wg = (pieces + plan.ksplit - 1) / plan.ksplit * FD_WAVES;
+  g.spans_per_wg = plan.spans_per_wg; g.chain = plan.chain;
   return g;
 }
 

@@ -23,8 +23,8 @@ __host__ __device__ __forceinline__ int pos_b(int j, int dir) { return dir == PA
 // ---- feature divergence (Steps 1-2) ------------------------------------------------------
 // The |A_w| x |B_w| cosine blocks are cut into 32x32 tiles.  Small windows are packed several to
 // a tile (block diagonal): `slot` rows/cols per window, `group` windows per tile.  Large windows
-// get mt x nt tiles each.  The d axis is split over `ksplit` workgroups (and the 4 waves of each);
-// partial tiles are summed in a fixed order by the epilogue.
+// get mt x nt tiles each.  The d axis is split over `ksplit` workgroups (and the 4 waves of each) that leave `recs`
+// records of partial sums per tile; these are summed in a fixed order by the epilogue.
 struct FdPlan {
   int slot;         // rows (and cols) reserved per window in a packed tile; 0 when group == 1
   int group;        // windows per tile
@@ -32,7 +32,10 @@ struct FdPlan {
   int n_tiles;      // tile jobs
   int n_rowblocks;  // epilogue jobs (one per 32 A rows)
   int ksplit;
-  size_t partial_floats;   // n_tiles * ksplit * FD_TILE_FLOATS
+  int spans_per_wg;        // spans of the hidden axis per workgroup
+  int chain;               // pieces of FD_WAVES spans that are added in fp32 before the sum goes on in fp64
+  int recs;                // ksplit, or 2 * ksplit: every sum as two floats
+  size_t partial_floats;   // room for the records: n_tiles * FD_TILE_FLOATS for at least recs of them
   int metric;              // 0 cosine FD, 1 Euclidean, 2 squared L2 (set by the caller after planning)
   int dir;                 // 0: even list positions propose, 1: odd ones (set by the caller after planning; a plan for
                            // dir 1 is made with the window bound rounded up to even, so that both sides fit)

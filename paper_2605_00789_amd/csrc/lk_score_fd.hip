@@ -57,14 +57,16 @@ hipError_t launch_fd_select_small(const FdPlan &plan, int dtype, const void *X, 
   return hipGetLastError();
 }
 
-// Workgroups of the partial tiles.  The hidden axis is split until there is one for every CU, and on (up to four for every CU)
-// while a slice is longer than eight pieces: beside xi's row statistics (768 workgroups fit the chip at a time, three a CU) each
-// further one waits for a slot, and a slice of several pieces has the next piece in flight while it multiplies.  Always split to
-// four a CU before: three stages of 2880 tokens 218.2 -> 207.4 us, the step of a 13B-shaped layer (3456 x 5120) 110.2 -> 104.8
-// (there also because a slice of 5 spans staged 8).  Slices of any length: full pairwise, 5 x 648 tokens, d = 3712, 320 tiles
-// in two stages 266 -> 281 us, so that line is drawn.  fp32 products take sixteen times as long, a piece of them is 1.3 us of a
-// matrix pipe: split as before (3 x 513 tokens, d = 1024: 85.0 us with slices of one piece, 87.1 of two).
-constexpr int FD_TARGET_WGS = 256, FD_ROOM_WGS = 1024, FD_SLICE_PIECES = 8;
+// Workgroups of the partial tiles.  The fine split of the hidden axis goes on until there are four workgroups for every CU.  Few
+// tiles of many bf16 pieces are split only until there is one for every CU, and on while a slice is longer than five pieces: beside
+// xi's row statistics (768 workgroups fit the chip at a time, three a CU) each further one waits for a slot, and a slice of several
+// pieces has the next one in flight while it multiplies.  Scores and selection, d = 4096, fine / long slices: 20 windows of 96 tokens
+// (80 tiles) 28.4 / 27.9 us alone, 34.6 / 33.1 with xi of 64 prompt rows; 96 windows of 36, d = 5120 28.6 / 27.5 and 43.5 / 40.0.
+// Not where the two records of a long slice make as many as the fine split has (45 tiles 22.4 / 24.0 alone, 29.5 / 30.8 with xi),
+// nor where there is a tile for every CU anyway (440 tiles, d = 2048: 55.1 / 52.9 alone, but 94.8 / 99.2 with xi; 320: 44.1 / 46.1
+// and 70.4 / 68.8).  fp32 products take sixteen times as long, a piece of them is 1.3 us of a matrix pipe: always fine (3 x 513
+// tokens, d = 1024: 85.0 us with slices of one piece, 87.1 of two).
+constexpr int FD_TARGET_WGS = 256, FD_FINE_WGS = 1024, FD_SLICE_PIECES = 5;
 
 static FdPlan plan_tiles(int n_windows, int maxA, int maxB, int d, int dtype_bytes) {
   FdPlan p{};
@@ -85,20 +87,33 @@ static FdPlan plan_tiles(int n_windows, int maxA, int maxB, int d, int dtype_byt
   const int span = (dtype_bytes == 2) ? 64 : 32;
   const int n_spans = (d + span - 1) / span;
   const int max_ks = n_spans / FD_WAVES > 0 ? n_spans / FD_WAVES : 1;
-  // a workgroup stages FD_WAVES spans at a time: a slice is a whole number of these pieces
   const int pieces = (n_spans + FD_WAVES - 1) / FD_WAVES;
   auto split = [&](int target, int longest) {
     int ks = 1;
-    while (((int64_t)p.n_tiles * ks < target || ((int64_t)p.n_tiles * ks < FD_ROOM_WGS && pieces > longest * ks)) &&
+    while (((int64_t)p.n_tiles * ks < target || ((int64_t)p.n_tiles * ks < FD_FINE_WGS && pieces > longest * ks)) &&
            ks * 2 <= max_ks && ks * 2 <= FD_MAX_RECS)
       ks *= 2;
     return ks;
   };
-  const int ks = split(dtype_bytes == 2 ? FD_TARGET_WGS : FD_ROOM_WGS, FD_SLICE_PIECES), per = (pieces + ks - 1) / ks;
-  p.ksplit = (pieces + per - 1) / per;
-  // The room for the slices stays that of the finer split: a workspace has to serve plans with a smaller window bound as well,
+  const int fine = split(FD_FINE_WGS, pieces);
+  const int ks = dtype_bytes == 2 && p.n_tiles < FD_TARGET_WGS ? split(FD_TARGET_WGS, FD_SLICE_PIECES) : fine;
+  if (2 * ks >= fine) {
+    p.ksplit = p.recs = fine;
+    p.spans_per_wg = (n_spans + fine - 1) / fine;
+    p.chain = pieces;
+  } else {
+    // A slice of several pieces adds no more products in fp32 than one of the finer split would, and hands the rest on as two
+    // floats: two records per workgroup, at most as many as the finer split has (ks <= fine / 2).
+    const int per = (pieces + ks - 1) / ks;   // a workgroup stages FD_WAVES spans at a time: a slice is a whole number of pieces
+    p.ksplit = (pieces + per - 1) / per;
+    p.recs = 2 * p.ksplit;
+    p.spans_per_wg = per * FD_WAVES;
+    const int fine_pieces = (n_spans + fine - 1) / fine / FD_WAVES;   // whole pieces of a slice of the finer split
+    p.chain = fine_pieces > 0 ? fine_pieces : 1;
+  }
+  // The room for the records stays that of the finer split: a workspace has to serve plans with a smaller window bound as well,
   // which can be split further.
-  p.partial_floats = (size_t)p.n_tiles * split(FD_ROOM_WGS, pieces) * FD_TILE_FLOATS;
+  p.partial_floats = (size_t)p.n_tiles * fine * FD_TILE_FLOATS;
   return p;
 }
 

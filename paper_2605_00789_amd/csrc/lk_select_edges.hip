@@ -289,7 +289,7 @@ hipError_t launch_edge_select(const FdArgs &g, const EdgeArgs &q, int dtype, hip
     }
     allowed[dev].store(true, std::memory_order_release);
   }
-  const Kernel k = kernels[g.ksplit == 1 ? 0 : g.ksplit <= 4 ? 1 : g.ksplit <= 8 ? 2 : 3][q.max_a * q.max_b > EDGE_ITEMS_SMALL * EDGE_THREADS];
+  const Kernel k = kernels[g.recs == 1 ? 0 : g.recs <= 4 ? 1 : g.recs <= 8 ? 2 : 3][q.max_a * q.max_b > EDGE_ITEMS_SMALL * EDGE_THREADS];
   hipLaunchKernelGGL(k, dim3((unsigned)g.n_windows), dim3(EDGE_THREADS), edge_lds_bytes(q.max_a, q.max_b), stream, g, q);
   return hipGetLastError();
 }

@@ -783,3 +783,70 @@ def test_ranks_among_equal_scores(v):
     order = np.flatnonzero(~keep)[np.argsort(want[~keep], kind="stable")]
     np.testing.assert_array_equal(offs.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(want[~keep], minlength=n))]))
     np.testing.assert_array_equal(src.cpu().numpy()[:len(order)], order)
+
+
+def _window_scores(X, n_w, v, d, dtype):
+    """best_fd of n_w windows of v tokens each."""
+    import paper_2605_00789_amd as L
+    from paper_2605_00789_amd import binding as B
+    n = n_w * v
+    i32 = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+    h_cu = np.array([0, n], dtype=np.int32)
+    prob = L.Problem(batch=1, d=d, heads=d // 32, head_dim=32, dtype=dtype, h_cu_vis=h_cu, cu_vis=i32(h_cu), n_windows=n_w,
+                     max_window_tokens=v, win_offsets=i32(np.arange(n_w + 1) * v), win_tokens=i32(np.arange(n)),
+                     win_remove=i32(np.zeros(n_w)))
+    ws = torch.empty(L.lightkv_workspace_size(prob), dtype=torch.uint8, device="cuda")
+    fd, dst = torch.empty(n, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda")
+    L.lightkv_score(prob, X, None, None, torch.ones(n, device="cuda"), fd, dst, ws, xi_mode=B.XI_GIVEN)
+    return fd
+
+
+@pytest.mark.parametrize("n_w,v,d,dtype", [
+    (45, 70, 4096, "bf16"), (20, 96, 4096, "bf16"), (96, 36, 5120, "bf16"), (127, 40, 4096, "bf16"),   # long slices
+    (200, 36, 2048, "bf16"), (255, 36, 2048, "bf16"), (140, 36, 1280, "bf16"),
+    (100, 36, 4160, "bf16"), (70, 40, 4192, "bf16"), (80, 36, 4672, "bf16"), (130, 36, 2336, "bf16"),  # ... with pieces no wave or not every wave has a span of
+    (256, 36, 2048, "bf16"), (400, 36, 2048, "bf16"),                                                  # short ones
+    (16, 36, 4096, "bf16"), (180, 16, 4096, "bf16"), (144, 36, 3712, "bf16"), (90, 40, 4096, "f32"),
+])
+def test_error_of_the_divergence_of_near_equal_rows(n_w, v, d, dtype):
+    """1 - cos of rows that differ by a few percent, against 64 bits: what is left of the error of the inner products and the
+    squared norms.  A chain of m fp32 additions of equal shares rounds to u/sqrt(3) * sqrt(m/3) of its sum (rms, u = 2^-24);
+    over C chains that is u/3 * sqrt(m / C) of the whole, and of 1 - cos = 1 - ab / sqrt(aa bb) sqrt(1 + 1/4 + 1/4) times as
+    much.  No chain is longer than 128 elements of bf16 (64 of fp32): m = 16 (32), C = d / 128 (d / 64).  Half as much again is
+    allowed, for the sums that are rounded on their way to memory."""
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    m, chains = (16, d / 128) if dtype == "bf16" else (32, d / 64)
+    bound = 1.5 * 1.5 ** 0.5 * 2.0 ** -24 / 3 * (m / chains) ** 0.5
+    err = []
+    for seed in range(2):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        base = torch.randn(n_w, 1, d, generator=g, device="cuda")
+        X = (base + 0.03 * torch.randn(n_w, v, d, generator=g, device="cuda")).reshape(n_w * v, d).to(dt)
+        fd = _window_scores(X, n_w, v, d, dtype).double().view(n_w, v)[:, 0::2]
+        x = X.double().view(n_w, v, d)
+        a, b = x[:, 0::2], x[:, 1::2]
+        dot = torch.stack([p @ q.T.contiguous() for p, q in zip(a, b)])
+        want = (1.0 - dot / ((a * a).sum(2)[:, :, None] * (b * b).sum(2)[:, None, :]).sqrt()).min(2).values
+        err.append((fd - want).flatten())
+    rms = float(torch.cat(err).square().mean().sqrt())
+    assert rms <= bound, (rms, bound)
+
+
+def test_sums_beyond_the_largest_float():
+    """Rows so large that the squared norm of half a row is beyond the largest fp32 value, but no short slice of it: the
+    divergence is that of the same rows scaled down by a power of two.  Rows with an infinity or a NaN have none."""
+    n_w, v, d = 200, 36, 2048
+    g = torch.Generator(device="cuda").manual_seed(5)
+    X = (1.2 * torch.randn(n_w, 1, d, generator=g, device="cuda").expand(n_w, v, d)
+         + 0.2 * torch.randn(n_w, v, d, generator=g, device="cuda")).reshape(n_w * v, d).to(torch.bfloat16)
+    half = X[:, :d // 2].double().square().sum(1).min()
+    assert float(half) * 4.0 ** 59 > 3.4028234663852886e38
+    small, large = _window_scores(X, n_w, v, d, "bf16"), _window_scores(X * 2.0 ** 59, n_w, v, d, "bf16")
+    assert bool(((small - large).abs() <= 1e-7)[torch.isfinite(small)].all())
+    assert torch.equal(torch.isfinite(small), torch.isfinite(large))
+    X[0, 3], X[2 * v, 5] = float("inf"), float("nan")
+    bad = _window_scores(X, n_w, v, d, "bf16")
+    assert not torch.isfinite(bad[0]) and not torch.isfinite(bad[2 * v])
+    good = torch.isfinite(small)
+    good[0] = good[2 * v] = False
+    assert torch.equal(bad[good], small[good])
