@@ -141,22 +141,18 @@ __device__ __forceinline__ void fd_partial_body(const FdArgs &g, int block_id, c
   double sum[16], sum_a = 0.0, sum_b = 0.0;   // (of the norms this lane's diagonal element (r, r), where it holds one)
 #pragma unroll
   for (int i = 0; i < 16; ++i) sum[i] = 0.0;
-  auto diagonal = [&](float &da, float &db) {
+  auto diagonal = [&](const f32x16 &norms) {
     const int idx = 4 * (r >> 3) + (r & 3);
-    da = db = 0.f;
+    float d = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      da = (i == idx) ? na[i] : da;
-      db = (i == idx) ? nb[i] : db;
-    }
+    for (int i = 0; i < 16; ++i) d = (i == idx) ? norms[i] : d;
+    return d;
   };
   auto flush = [&]() {
-    float da, db;
-    diagonal(da, db);
 #pragma unroll
     for (int i = 0; i < 16; ++i) sum[i] += (double)acc[i];
-    sum_a += (double)da;
-    sum_b += (double)db;
+    if (need_na) sum_a += (double)diagonal(na);
+    if (need_nb) sum_b += (double)diagonal(nb);
   };
   int left = g.chain;
   const int s_begin = ks * g.spans_per_wg;
@@ -170,16 +166,27 @@ __device__ __forceinline__ void fd_partial_body(const FdArgs &g, int block_id, c
       *reinterpret_cast<uint4 *>(lds + (p * (FD_THREADS / 32) + srow) * FD_STAGE_PITCH + schunk * 16) = st[p];
     __syncthreads();
     if (s + FD_WAVES < s_end) load_piece(s + FD_WAVES);
-    if (left == g.chain) { acc = f32x16{0}; na = f32x16{0}; nb = f32x16{0}; }   // uniform: also where the last piece has no span for this wave
+    const bool fresh = left == g.chain;   // uniform
     if (s + wave < s_end) {
 #pragma unroll
       for (int c = 0; c < FD_CHUNKS; ++c) {
         const uint4 ca = *reinterpret_cast<const uint4 *>(frag + c * 16);
         const uint4 cb = *reinterpret_cast<const uint4 *>(frag + 32 * FD_STAGE_PITCH + c * 16);
-        E::mma32(ca, cb, acc);
-        if (need_na) E::mma32(ca, ca, na);
-        if (need_nb) E::mma32(cb, cb, nb);
+        auto multiply = [&](const uint4 &x, const uint4 &y, f32x16 &sum32) {
+          if (c == 0 && fresh) {   // a chain begins: zero as the instruction's constant, not 16 registers set to it
+            f32x16 begin = {0};
+            E::mma32(x, y, begin);
+            sum32 = begin;
+          } else {
+            E::mma32(x, y, sum32);
+          }
+        };
+        multiply(ca, cb, acc);
+        if (need_na) multiply(ca, ca, na);
+        if (need_nb) multiply(cb, cb, nb);
       }
+    } else if (fresh) {   // no span of the last piece for this wave
+      acc = f32x16{0}; na = f32x16{0}; nb = f32x16{0};
     }
     if (--left == 0 && two) {   // uniform
       flush();
@@ -218,9 +225,7 @@ __device__ __forceinline__ void fd_partial_body(const FdArgs &g, int block_id, c
       out_low[e] = (float)(v - (double)high);
     });
   } else {
-    float da, db;
-    diagonal(da, db);
-    add_waves(0.f, [&](int i) { return acc[i]; }, da, db, [&](int e, float v) { out[e] = v; });
+    add_waves(0.f, [&](int i) { return acc[i]; }, diagonal(na), diagonal(nb), [&](int e, float v) { out[e] = v; });
   }
 }
 
