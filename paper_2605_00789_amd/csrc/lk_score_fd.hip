@@ -57,15 +57,15 @@ hipError_t launch_fd_select_small(const FdPlan &plan, int dtype, const void *X, 
   return hipGetLastError();
 }
 
-// Workgroups of the partial tiles.  The fine split of the hidden axis goes on until there are four workgroups for every CU.  Few
-// tiles of many bf16 pieces are split only until there is one for every CU, and on while a slice is longer than five pieces: beside
-// xi's row statistics (768 workgroups fit the chip at a time, three a CU) each further one waits for a slot, and a slice of several
-// pieces has the next one in flight while it multiplies.  Scores and selection, d = 4096, fine / long slices: 20 windows of 96 tokens
-// (80 tiles) 28.4 / 27.9 us alone, 34.6 / 33.1 with xi of 64 prompt rows; 96 windows of 36, d = 5120 28.6 / 27.5 and 43.5 / 40.0.
-// Not where the two records of a long slice make as many as the fine split has (45 tiles 22.4 / 24.0 alone, 29.5 / 30.8 with xi),
-// nor where there is a tile for every CU anyway (440 tiles, d = 2048: 55.1 / 52.9 alone, but 94.8 / 99.2 with xi; 320: 44.1 / 46.1
-// and 70.4 / 68.8).  fp32 products take sixteen times as long, a piece of them is 1.3 us of a matrix pipe: always fine (3 x 513
-// tokens, d = 1024: 85.0 us with slices of one piece, 87.1 of two).
+// Workgroups of the partial tiles.  The fine split of the hidden axis goes on until there are four workgroups for every CU.  Long
+// slices of bf16 rows: split only until there is one for every CU, and on while a slice is longer than five pieces.  Beside xi's row
+// statistics (768 workgroups fit the chip at a time, three a CU) each further one waits for a slot, and a slice of several pieces has
+// the next one in flight while it multiplies.  Scores and selection, fine / long slices, us alone and with xi of 64 prompt rows: 20
+// windows of 96 tokens (80 tiles), d = 4096, 28.3 / 27.8 and 34.0 / 33.8; 96 of 36, d = 5120, 29.4 / 27.5 and 44.2 / 40.0; 300 of
+// 36, d = 1280, 43.0 / 40.2 and 55.7 / 51.3; 200 of 36, d = 2048, 32.3 / 30.3 and 45.6 / 47.4.  Eight pieces: 144 of 36, d = 3712,
+// 29.5 / 30.9 and 46.4 / 46.6.  Not where the two records of a long slice make as many as the fine split has: 180 of 16, d = 4096,
+// 22.2 / 23.5 and 29.4 / 31.0, 80 of 30 20.8 / 21.7 and 27.3 / 26.8.  fp32 products take sixteen times as long, a piece of them is
+// 1.3 us of a matrix pipe: always fine (3 x 513 tokens, d = 1024: 85.0 us with slices of one piece, 87.1 of two).
 constexpr int FD_TARGET_WGS = 256, FD_FINE_WGS = 1024, FD_SLICE_PIECES = 5;
 
 static FdPlan plan_tiles(int n_windows, int maxA, int maxB, int d, int dtype_bytes) {
@@ -96,7 +96,7 @@ static FdPlan plan_tiles(int n_windows, int maxA, int maxB, int d, int dtype_byt
     return ks;
   };
   const int fine = split(FD_FINE_WGS, pieces);
-  const int ks = dtype_bytes == 2 && p.n_tiles < FD_TARGET_WGS ? split(FD_TARGET_WGS, FD_SLICE_PIECES) : fine;
+  const int ks = dtype_bytes == 2 ? split(FD_TARGET_WGS, FD_SLICE_PIECES) : fine;
   if (2 * ks >= fine) {
     p.ksplit = p.recs = fine;
     p.spans_per_wg = (n_spans + fine - 1) / fine;

@@ -803,7 +803,7 @@ def _window_scores(X, n_w, v, d, dtype):
 
 @pytest.mark.parametrize("n_w,v,d,dtype", [
     (45, 70, 4096, "bf16"), (20, 96, 4096, "bf16"), (96, 36, 5120, "bf16"), (127, 40, 4096, "bf16"),   # long slices
-    (200, 36, 2048, "bf16"), (255, 36, 2048, "bf16"), (140, 36, 1280, "bf16"),
+    (200, 36, 2048, "bf16"), (255, 36, 2048, "bf16"), (140, 36, 1280, "bf16"), (300, 40, 1280, "bf16"),
     (100, 36, 4160, "bf16"), (70, 40, 4192, "bf16"), (80, 36, 4672, "bf16"), (130, 36, 2336, "bf16"),  # ... with pieces no wave or not every wave has a span of
     (256, 36, 2048, "bf16"), (400, 36, 2048, "bf16"),                                                  # short ones
     (16, 36, 4096, "bf16"), (180, 16, 4096, "bf16"), (144, 36, 3712, "bf16"), (90, 40, 4096, "f32"),
